@@ -13,14 +13,16 @@ struct RestoreParams {
   const float* meta;      // chunk sections
   int64_t n_tokens;       // tokens held by `frames`
   int32_t n_chunks;
-  int32_t tb;             // tokens per workgroup (0: library default)
+  int32_t tb;             // tokens per workgroup
   int32_t tbc;            // token blocks per chunk
   int32_t tpp;            // tokens per pass of a workgroup = threads / apt
   uint32_t n_units;       // frame call: fm_count * 3 * tbc workgroups with work
   uint32_t units_per_xcd;
   FastDiv dtbc, dL;       // unit -> (token block, chunk), row -> (kind, layer)
-  uint32_t row_units;     // chunk call: token blocks of one (kind, layer) over all chunks
-  FastDiv drpx;           // ... and the share of one XCD
+  // chunk call: rows ((kind, layer) pairs) are taken in bands of band_rows; a band's units (token blocks of its rows,
+  // those that hold tokens) are cut into 8 contiguous parts, one per XCD
+  uint32_t band_rows, band_units;
+  FastDiv drow, dbpx;     // units of a row; units of a band per XCD
   // "rows" body: a wave reads runs of 512 bytes of one plane row, i.e. one row of rows_q = 512 / tw neighbouring
   // tiles; a workgroup (th waves) takes rows_trw rows of tiles, in all F frames (chunk call) or in one (frame call)
   int32_t rows_body, rows_q, rows_lat;  // lat: log2 of the atoms of a tile row

@@ -41,17 +41,19 @@
 
 namespace kvc {
 
-#ifndef KVC_RESTORE_U
-#define KVC_RESTORE_U 8  // tokens in flight per wave
-#endif
-#ifndef KVC_RESTORE_TB
-#define KVC_RESTORE_TB 32  // tokens per workgroup ("waves" body)
-#endif
-#ifndef KVC_RESTORE_TB_LANES
-#define KVC_RESTORE_TB_LANES 128  // tokens per workgroup ("lanes" body)
-#endif
-
 namespace {
+
+// Launch shape of the "waves" and "lanes" bodies.  A workgroup takes kPasses passes of whole tokens, with the loads
+// of all its passes in flight before its first store; a launch that does not reach kFillWorkgroups that way (four on
+// each of the 256 CUs) is cut finer, to 4 and then 2 passes: one frame of (8,128) tiles (192 workgroups instead of
+// 48) 6.0 -> 5.2 us, 200 tokens of 32 layers x 4096 channels 35 us at either count of 1024 or 2048 workgroups.
+constexpr int kPasses = 8;
+constexpr int64_t kFillWorkgroups = 1024;
+// Workgroups have 512 threads where there are many of them (32K tokens x 32 layers: 1.178 ms, 256 threads 1.195 ms)
+// and 256 below this count, where the finer cut evens out the last round (12 frames of (8,128) tiles 14.7 -> 13.1 us,
+// 656 tokens x 60 layers x 512 channels 28.3 -> 26.9 us).  The "lanes" body always takes 256: 12 345 tokens of 80
+// layers x 128 channels 141 -> 136 us, 52 172 tokens of 32 layers 230 -> 221 us.
+constexpr int64_t kManyWorkgroups = 4096;
 
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
@@ -93,10 +95,9 @@ __device__ __forceinline__ void load_channel_pairs(const float* mbase, int64_t f
 
 // ----------------------------------------------------------------- "waves" body
 
-template <int MODE, int DT, bool PAGED>
+template <int MODE, int DT, bool PAGED, int U>
 __device__ __forceinline__ void restore_body_waves(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                    uint32_t tbi, const uint8_t* fsec, uint32_t ff) {
-  constexpr int U = KVC_RESTORE_U;
   const Geo& g = p.g;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t wave = wave_uniform(threadIdx.x >> 6);
@@ -193,10 +194,9 @@ __device__ __forceinline__ uint32_t tile_elem(const Geo& g, uint32_t r, uint32_t
 
 // Unit `tg` is a group of rows_trw rows of tiles of one (chunk, kind, layer), in all F frames (chunk call) or in
 // frame ff alone (frame call: fsec is then that frame's plane and frame_stride 0).
-template <int MODE, int DT, bool PAGED>
+template <int MODE, int DT, bool PAGED, int U>
 __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                   uint32_t tg, const uint8_t* fsec, uint32_t ff) {
-  constexpr int U = KVC_RESTORE_U;
   const Geo& g = p.g;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t r = wave_uniform(threadIdx.x >> 6);       // row of the tiles this wave reads
@@ -278,10 +278,9 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
 
 // ----------------------------------------------------------------- "lanes" body
 
-template <int MODE, int DT, bool PAGED>
+template <int MODE, int DT, bool PAGED, int U>
 __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                    uint32_t tbi, const uint8_t* fsec, uint32_t ff) {
-  constexpr int U = KVC_RESTORE_U;
   const Geo& g = p.g;
   const uint32_t tid = threadIdx.x;
   const uint32_t tsub = fd_div(p.dapt, tid);
@@ -354,14 +353,16 @@ __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint3
 //
 // Chunk call: a "row" is one (kind, layer), i.e. one region [num_blocks][block][H][D] of a paged
 // cache.  The whole chip works on one row at a time; the row's token blocks (over all chunks of the
-// call) are cut into 8 contiguous parts, one per XCD, so the workgroups that share a layer's
-// per-channel pairs and a run of block-table entries also share an L2, and the writes in flight stay
-// inside one region of the cache.
+// call, those that hold tokens) are cut into 8 contiguous parts, one per XCD, so the workgroups that
+// share a layer's per-channel pairs and a run of block-table entries also share an L2, and the writes
+// in flight stay inside one region of the cache.  Rows of fewer than 64 blocks are taken several at a
+// time (a band), or most XCDs would idle: 200 tokens of a 2048-token chunk, 7 blocks a row, all fell
+// to one XCD when the blocks of the whole chunk were cut (32 layers x 4096 channels: 144 -> 35 us).
 //
 // Frame call: units are (frame of the run, plane, block of token slots), each XCD one contiguous range.
 constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2;
 
-template <int DT, bool PAGED, int BODY>
+template <int DT, bool PAGED, int BODY, int U>
 __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
   const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
   uint32_t tbi, l, kind, c, ff = 0;
@@ -392,10 +393,13 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
     if (l >= (uint32_t)p.g.L) return;
     fsec = run + ((int64_t)frel * 3 + pl) * p.g.plane;
   } else {
-    uint32_t row, within;
-    fd_divmod(p.drpx, idx, row, within);
-    const uint32_t u = xcd * p.drpx.d + within;
-    if (u >= p.row_units) return;
+    uint32_t band, within, row, u;
+    fd_divmod(p.dbpx, idx, band, within);
+    const uint32_t w = xcd * p.dbpx.d + within;  // unit of the band
+    if (w >= p.band_units) return;
+    fd_divmod(p.drow, w, row, u);
+    row += band * p.band_rows;
+    if (row >= 2u * (uint32_t)p.g.L) return;  // the last band may hold fewer rows
     fd_divmod(p.dL, row, kind, l);
     fd_divmod(p.dtbc, u, c, tbi);
     const uint32_t lg = l / 3u, pl = l - lg * 3u;
@@ -403,29 +407,32 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
   }
   if (p.g.mode[kind] == KVC_Q_PER_CHANNEL) {
     if (BODY == kBodyRows)
-      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
-      restore_body_waves<KVC_Q_PER_CHANNEL, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_waves<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
-      restore_body_lanes<KVC_Q_PER_CHANNEL, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_lanes<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
   } else {
     if (BODY == kBodyRows)
-      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
-      restore_body_waves<KVC_Q_PER_TOKEN, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_waves<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
-      restore_body_lanes<KVC_Q_PER_TOKEN, DT, PAGED>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_lanes<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
   }
 }
 
 template <int DT, bool PAGED>
-void launch_variant(const RestoreParams& p, int body, dim3 grid, dim3 block, hipStream_t s) {
-  if (body == kBodyRows)
-    hipLaunchKernelGGL((restore_kernel<DT, PAGED, kBodyRows>), grid, block, 0, s, p);
-  else if (body == kBodyWaves)
-    hipLaunchKernelGGL((restore_kernel<DT, PAGED, kBodyWaves>), grid, block, 0, s, p);
-  else
-    hipLaunchKernelGGL((restore_kernel<DT, PAGED, kBodyLanes>), grid, block, 0, s, p);
+void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, hipStream_t s) {
+#define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, 0, s, p)
+  if (body == kBodyRows) {
+    KVC_LAUNCH_RESTORE(kBodyRows, 8);
+  } else if (body == kBodyWaves) {
+    if (u == 8) KVC_LAUNCH_RESTORE(kBodyWaves, 8); else if (u == 4) KVC_LAUNCH_RESTORE(kBodyWaves, 4); else KVC_LAUNCH_RESTORE(kBodyWaves, 2);
+  } else {
+    if (u == 8) KVC_LAUNCH_RESTORE(kBodyLanes, 8); else if (u == 4) KVC_LAUNCH_RESTORE(kBodyLanes, 4); else KVC_LAUNCH_RESTORE(kBodyLanes, 2);
+  }
+#undef KVC_LAUNCH_RESTORE
 }
 
 }  // namespace
@@ -434,20 +441,19 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   const Geo& g = p.g;
   if (p.n_tokens <= 0) return KVC_OK;
   if (g.apt > 1024) return KVC_ERR_UNSUPPORTED;
-  // threads: a whole number of tokens per pass, about 512 threads
-#ifndef KVC_RESTORE_THREADS
-#define KVC_RESTORE_THREADS 512
-#endif
-  const int tpp = g.apt >= KVC_RESTORE_THREADS ? 1 : KVC_RESTORE_THREADS / g.apt;
   const bool waves = g.apt % 64 == 0;
-  // The "rows" body: chunk calls on tiles narrower than a 512-byte run whose rows of tiles hold whole runs, when
+  // The "rows" body: tiles narrower than a 512-byte run whose rows of tiles hold whole runs, when
   // the frames are read over the host link.  (On frames in HBM it is 0.5 % faster than "waves" when the blocks of
   // the cache are in order and 0.4 % slower under a random block table: 1.136 / 1.185 against 1.142 / 1.180 ms.)
   const int q = g.tw < 512 && 512 % g.tw == 0 ? 512 / g.tw : 0;
   const bool rows = p.host_frames && waves && q >= 2 && g.TX % q == 0 && g.th <= 16;
-  const int threads = rows ? g.th * 64 : g.apt * tpp;
   const int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
   p.rows_body = rows ? 1 : 0;
+  p.n_chunks = (int32_t)((p.n_tokens + g.T - 1) / g.T);
+  const int32_t n_last = (int32_t)(p.n_tokens - (int64_t)(p.n_chunks - 1) * g.T);  // tokens of the last chunk of the call
+  const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  int u = kPasses, tpp = 1;
+  int32_t tbl = 0;  // units of the last chunk of the call (chunk call), which need not be full
   if (rows) {
     p.rows_q = q;
     p.rows_lat = 0;
@@ -455,10 +461,26 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     const int nf = p.frame_mode ? 1 : g.F, per_row = nf * (g.TX / q);  // passes one row of tiles takes
     p.dnf = make_fastdiv((uint32_t)nf);
     p.dpr = make_fastdiv((uint32_t)per_row);
-    p.rows_trw = per_row >= KVC_RESTORE_U ? 1 : KVC_RESTORE_U / per_row;  // about one round of loads per wave
-    p.rows_tile_rows = (int32_t)(((g.T + g.F - 1) / g.F + g.TX - 1) / g.TX);  // rows of tiles that hold tokens
-    p.tb = p.rows_trw * g.TX * g.F;  // tokens (chunk call) a workgroup takes
+    p.rows_trw = per_row >= kPasses ? 1 : kPasses / per_row;  // about one round of loads per wave
+    const auto units = [&](int32_t n) { return (int32_t)ceil_div(ceil_div(ceil_div(n, g.F), g.TX), p.rows_trw); };
+    p.rows_tile_rows = (int32_t)ceil_div(ceil_div(g.T, g.F), g.TX);  // rows of tiles that hold tokens
+    p.tbc = units(p.frame_mode ? n_last : g.T);  // units of one (chunk, kind, layer) or plane
+    tbl = units(n_last);
+  } else {
+    // u passes of tpp tokens per workgroup; workgroups of a launch with `tokens` each, counting tokens that exist
+    const auto wgs = [&](int64_t tokens) {
+      if (p.frame_mode) return (int64_t)p.fm_count * 3 * ceil_div(ceil_div(n_last, g.F), tokens);
+      return 2 * (int64_t)g.L * ((p.n_chunks - 1) * ceil_div(g.T, tokens) + ceil_div(n_last, tokens));
+    };
+    const auto tokens_per_pass = [&](int t) { return g.apt >= t ? 1 : t / g.apt; };
+    tpp = tokens_per_pass(512);
+    if (!waves || wgs(u * tpp) < kManyWorkgroups) tpp = tokens_per_pass(256);
+    while (u > 2 && wgs(u * tpp) < kFillWorkgroups) u /= 2;
+    p.tb = u * tpp;
+    p.tbc = (int32_t)ceil_div(p.frame_mode ? ceil_div(n_last, g.F) : g.T, p.tb);
+    tbl = (int32_t)ceil_div(n_last, p.tb);
   }
+  const int threads = rows ? g.th * 64 : g.apt * tpp;
   p.tpp = tpp;
   p.dapt = make_fastdiv((uint32_t)g.apt);
   p.dwpt = make_fastdiv((uint32_t)(waves ? g.apt / 64 : 1));
@@ -470,44 +492,38 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     p.moff[1] = g.meta_off[1];
   }
   p.tile_row_stride = (uint32_t)g.th * (uint32_t)g.W;
-  if (!rows) {
-    if (p.tb <= 0) p.tb = waves ? KVC_RESTORE_TB : KVC_RESTORE_TB_LANES;
-    if (waves && p.tb > 64 * tpp) p.tb = 64 * tpp;  // one lane per token of a wave
-    if (p.tb > g.T) p.tb = g.T;
-  }
-  p.tbc = (g.T + p.tb - 1) / p.tb;
-  p.n_chunks = (int32_t)((p.n_tokens + g.T - 1) / g.T);
   p.dL = make_fastdiv((uint32_t)g.L);
   p.dLG = make_fastdiv((uint32_t)g.LG);
   dim3 grid, block((unsigned)threads);
-  if (rows) p.tbc = (p.rows_tile_rows + p.rows_trw - 1) / p.rows_trw;  // units of one (chunk, kind, layer) or plane
   if (p.frame_mode) {
-    if (!rows) p.tbc = ((g.T + g.F - 1) / g.F + p.tb - 1) / p.tb;  // slots of one frame
     const int64_t units = (int64_t)p.fm_count * 3 * p.tbc;
     if (units > 0x7fffffff / 8) return KVC_ERR_UNSUPPORTED;
     p.n_units = (uint32_t)units;
     p.units_per_xcd = (p.n_units + 7u) / 8u;
     grid = dim3(p.units_per_xcd * 8u);
   } else {
-    const int64_t row_units = (int64_t)p.n_chunks * p.tbc;
-    const int64_t per_xcd = (row_units + 7) / 8;
-    const int64_t wgs = per_xcd * 8 * 2 * g.L;
-    if (wgs > 0x7fffffff) return KVC_ERR_UNSUPPORTED;
-    p.row_units = (uint32_t)row_units;
-    p.drpx = make_fastdiv((uint32_t)per_xcd);
-    grid = dim3((uint32_t)wgs);
+    const int64_t row_units = (int64_t)(p.n_chunks - 1) * p.tbc + tbl;
+    const int64_t band_rows = row_units >= 64 ? 1 : ceil_div(64, row_units) < 2 * g.L ? ceil_div(64, row_units) : 2 * g.L;
+    const int64_t per_xcd = ceil_div(row_units * band_rows, 8);
+    const int64_t grid_wgs = per_xcd * 8 * ceil_div(2 * g.L, band_rows);
+    if (grid_wgs > 0x7fffffff) return KVC_ERR_UNSUPPORTED;
+    p.band_rows = (uint32_t)band_rows;
+    p.band_units = (uint32_t)(row_units * band_rows);
+    p.drow = make_fastdiv((uint32_t)row_units);
+    p.dbpx = make_fastdiv((uint32_t)per_xcd);
+    grid = dim3((uint32_t)grid_wgs);
   }
   p.dtbc = make_fastdiv((uint32_t)p.tbc);
   if (g.dtype == KVC_F16) {
     if (paged)
-      launch_variant<KVC_F16, true>(p, body, grid, block, stream);
+      launch_variant<KVC_F16, true>(p, body, u, grid, block, stream);
     else
-      launch_variant<KVC_F16, false>(p, body, grid, block, stream);
+      launch_variant<KVC_F16, false>(p, body, u, grid, block, stream);
   } else {
     if (paged)
-      launch_variant<KVC_BF16, true>(p, body, grid, block, stream);
+      launch_variant<KVC_BF16, true>(p, body, u, grid, block, stream);
     else
-      launch_variant<KVC_BF16, false>(p, body, grid, block, stream);
+      launch_variant<KVC_BF16, false>(p, body, u, grid, block, stream);
   }
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
 }

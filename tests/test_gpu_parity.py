@@ -887,3 +887,45 @@ def test_reference_expand_copy_moves_every_vector_where_the_map_says(wg):
             got = dst.view(n_vec, 4)[where]
             assert torch.equal(got, want), (use_map, shape)
             assert bool((buf[:guard] == 0x5A5A5A5A).all()) and bool((buf[guard + n_vec * 4:] == 0x5A5A5A5A).all())
+
+
+RESTORE_SHAPES = [
+    # L, H, D, T, th, tw, TX, TY, n_tokens, block_size: each launch shape of restore (passes x threads), ragged rows
+    (3, 8, 128, 64, 8, 128, 2, 8, 65, 16),       # whole waves, 2 passes, one token in the last chunk
+    (64, 8, 128, 40, 8, 128, 4, 5, 100, 16),     # 4 passes; 128 rows of 14 blocks, in bands of 5 (the last one of 3)
+    (64, 8, 128, 80, 8, 128, 4, 5, 130, 16),     # 8 passes, 256 threads
+    (66, 4, 128, 1000, 4, 128, 8, 32, 2000, 16), # 8 passes, 512 threads; rows of 32 blocks
+    (2, 32, 128, 96, 8, 512, 1, 24, 96 * 2 + 5, 7),  # C/8 = 512: one token per pass
+    (16, 4, 16, 300, 4, 16, 8, 8, 310, 16),      # lanes, 2 passes of 32 tokens
+    (33, 1, 64, 512, 1, 64, 8, 64, 4000, 32),    # lanes, 4 passes
+    (33, 1, 64, 512, 1, 64, 8, 32, 8200, 32),    # lanes, 8 passes
+    (5, 3, 128, 70, 3, 128, 3, 5, 150, 16),      # C/8 = 48: 240 threads
+]
+
+
+@pytest.mark.parametrize("shape", RESTORE_SHAPES, ids=[f"l{i}" for i in range(len(RESTORE_SHAPES))])
+def test_restore_launch_shapes(shape):
+    """Contiguous, paged and frame-wise restore where the launch is cut differently: every block of tokens is taken
+    exactly once, whatever the number of passes, threads and rows per band."""
+    L, H, D, T, th, tw, TX, TY, n, bs = shape
+    glo, olo = hz.layouts(L, H, D, "f16", T, th, tw, TX, TY)
+    kv = kv_synth.make_kv(L, H, D, n, torch.float16, seed=7000 + n, device="cuda")
+    frames, meta = full_check(glo, olo, kv, n, "f16", block_size=bs, tag="launch shape")
+    # the first chunk again, in runs of frames of three sizes, into an empty cache
+    fsz, nf = hz.kvc.frame_size(glo), 2 * ((L + 2) // 3) * hz.kvc.chunk_sizes(glo)[2]
+    n0 = min(T, n)
+    nb = (n0 + bs - 1) // bs
+    table = kv_synth.make_block_table(nb, nb + 2, 5)
+    want, _ = hz.oracle_paged(olo, frames.cpu().numpy(), meta.cpu().numpy(), 0, n0, L, nb + 2, bs, H * D, table.numpy())
+    cache, dtab, at = hz.PagedCache(L, nb + 2, bs, H * D), table.cuda(), 0
+    for k in (1, 5, nf):
+        k = min(k, nf - at)
+        if k > 0:
+            hz.kvc.kvc_restore_paged_frames(glo, frames.data_ptr() + at * fsz, meta.data_ptr(), at, k, 0, n0,
+                                            cache.ptrs.data_ptr(), nb + 2, bs, dtab.data_ptr(), nb, cache.err.data_ptr(),
+                                            hz.stream_handle())
+            at += k
+    torch.cuda.synchronize()
+    assert int(cache.err.item()) == 0
+    for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
+        hz.assert_same_bytes(f"frames, layer {l}", got, w)
