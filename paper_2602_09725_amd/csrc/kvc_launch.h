@@ -107,9 +107,11 @@ struct ScoreParams {
   int32_t n_chunks;
   uint64_t* hist;         // [n_chunks][2][L][KVC_N_RESIDUALS][256]
   FastDiv dL;             // stream -> (chunk, kind), layer
+  FastDiv dparts;         // workgroup -> stream, part of its rows
+  uint32_t part_rows;     // rows of a part
 };
 
-// Enqueues the residual-histogram kernel of the tiling proxy: one workgroup per (chunk, kind, layer).
+// Enqueues the residual-histogram kernel of the tiling proxy.
 kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream);
 
 // Enqueues the reference expand copy (measurement aid): out_bytes / 2 bytes of src -> out_bytes of dst, piece i

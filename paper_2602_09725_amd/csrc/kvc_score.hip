@@ -7,13 +7,19 @@
 // there), and that temporal residual after its own left / upper neighbour.  The kernel only counts;
 // entropies and the cost in bits are host arithmetic (kvc_proxy_cost_bits).
 //
-// One workgroup per plane sequence (chunk, kind, layer): it owns the five histograms of its stream,
-// so the result needs no atomics in global memory and no cleared buffer.  Every frame byte is read
-// from HBM once: a thread walks down a column, so the row above is its own previous read (a cache hit),
-// and the byte to the left sits in the line it is reading anyway.  Counting is done with LDS
-// atomics on 16 copies of the histograms (lanes spread over the copies, so that equal residuals in one
-// wave seldom meet in one counter), which is what bounds the kernel: five counter updates per pixel
-// against one byte of HBM traffic; with the counting switched off the same loop runs in a third of the time.
+// A plane sequence (chunk, kind, layer) is one workgroup's, or is cut into parts of whole rows (all frames) for
+// several workgroups where the streams alone would leave CUs idle; parts add their counts to the cleared output.
+// A workgroup reads every byte of its rows from HBM once: a thread walks down a column of 8-pixel pieces, so the
+// row above is its own previous read (a cache hit), and the byte to the left sits in the line it is reading anyway.
+//
+// What bounds it: five counter updates per pixel (two in the first frame of a group) against one byte of HBM
+// traffic.  The counters are LDS words and an LDS atomic instruction of 64 lanes takes 4 cycles at best (14.8
+// updates per cycle and CU measured with every lane on its own bank, 14.3 on 16 copies of the histograms as here,
+// 10 on 8 copies, 6.4 on one).  So the arithmetic around the updates must cost less than that: pixels are kept as
+// 16-bit halves (even pixels as they are, odd ones shifted down a byte; only the low byte of a half means anything),
+// one packed subtraction makes two residuals, the temporal residual after its left / upper neighbour is the
+// difference of two frames' left / upper residuals, and one dot product of bytes turns a residual into the address
+// of its counter.
 #include <hip/hip_runtime.h>
 
 #include "kvc_device.h"
@@ -24,48 +30,71 @@ namespace kvc {
 namespace {
 
 constexpr int kScoreThreads = 512;
-constexpr int kCopies = 16;  // copies of each histogram in LDS: 80 KB of the CU's 160 KB (4 copies: 2.1 ms, 16: 1.36 ms)
+constexpr int kCopies = 16;        // copies of each histogram in LDS: 80 KB of the CU's 160 KB
+constexpr int kFrames = 4;         // frames whose loads are in flight together
+// Workgroups a launch of few streams is cut into, two rounds of the two that fit a CU: a chunk of 32 layers x 1024
+// channels (64 streams) takes 499 us in one part per stream, 83 / 80 / 84 us in 512 / 1024 / 2048 workgroups; with
+// most tiles empty fewer are better (18 tokens of 1024: 30 / 32 / 43 us), with 2000 rows of 3840 pixels more (111 / 105 / 103).
+constexpr int64_t kScoreWorkgroups = 1024;
 
-// a - b on each of the four bytes of a word, modulo 256
-__device__ __forceinline__ uint32_t sub_bytes(uint32_t a, uint32_t b) {
-  const uint32_t top = 0x80808080u;
-  return ((a | top) - (b & ~top)) ^ ((a ^ ~b) & top);
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// Two pixels (or residuals): the low bytes of the two halves; what is above a low byte is not looked at.
+__device__ __forceinline__ uint32_t sub2(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
 }
 
-// The 8 pixels one position to the left of v's: v shifted up by a byte, `left` (in bits 31..24) entering.
-__device__ __forceinline__ u32x2 left_of(u32x2 v, uint32_t left) {
-  u32x2 o;
-  o.x = __builtin_amdgcn_alignbyte(v.x, left, 3);
-  o.y = __builtin_amdgcn_alignbyte(v.y, v.x, 3);
-  return o;
+// 8 pixels of a row as pairs (0,2), (1,3), (4,6), (5,7).
+struct Piece {
+  uint32_t v[4];
+};
+__device__ __forceinline__ Piece split(u32x2 w) { return Piece{{w.x, w.x >> 8, w.y, w.y >> 8}}; }
+__device__ __forceinline__ Piece operator-(const Piece& a, const Piece& b) {
+  return Piece{{sub2(a.v[0], b.v[0]), sub2(a.v[1], b.v[1]), sub2(a.v[2], b.v[2]), sub2(a.v[3], b.v[3])}};
+}
+// The pixels one position to the left; `left` is the one before the piece.
+__device__ __forceinline__ Piece left_of(const Piece& p, uint32_t left) {
+  return Piece{{__builtin_amdgcn_alignbit(p.v[1], left << 16, 16), p.v[0], __builtin_amdgcn_alignbit(p.v[3], p.v[1], 16), p.v[2]}};
 }
 
-__device__ __forceinline__ u32x2 sub_bytes(u32x2 a, u32x2 b) { return u32x2{sub_bytes(a.x, b.x), sub_bytes(a.y, b.y)}; }
+typedef uint32_t Histogram[256][kCopies];
 
-__device__ __forceinline__ void count8(uint32_t (*h)[kCopies], u32x2 v, uint32_t copy) {
+__device__ __forceinline__ void count8(Histogram& h, const Piece& p, uint32_t copy_bytes) {
+  typedef __attribute__((address_space(3))) uint32_t lds_u32;
+  typedef __attribute__((address_space(3))) char lds_char;
+  lds_char* base = (lds_char*)&h[0][0];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const uint32_t w = i < 4 ? v.x : v.y;
-    atomicAdd(&h[(w >> (8 * (i & 3))) & 0xffu][copy], 1u);
+  for (int i = 0; i < 4; ++i) {
+    // byte 0 (and byte 2) times the bytes of a bin, plus the copy
+    const uint32_t lo = __builtin_amdgcn_udot4(p.v[i], (uint32_t)sizeof(h[0]), copy_bytes, false);
+    const uint32_t hi = __builtin_amdgcn_udot4(p.v[i], (uint32_t)sizeof(h[0]) << 16, copy_bytes, false);
+    __hip_atomic_fetch_add((lds_u32*)(base + lo), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __hip_atomic_fetch_add((lds_u32*)(base + hi), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 
+__global__ void __launch_bounds__(kScoreThreads) clear_hist_kernel(u32x4* hist, uint32_t n16) {
+  const uint32_t i = blockIdx.x * kScoreThreads + threadIdx.x;
+  if (i < n16) hist[i] = u32x4{0u, 0u, 0u, 0u};
+}
+
 __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const ScoreParams p) {
-  __shared__ uint32_t hist[KVC_N_RESIDUALS][256][kCopies];
+  __shared__ __attribute__((aligned(16))) Histogram hist[KVC_N_RESIDUALS];
+  static_assert(sizeof(hist[0][0]) == 64, "the bytes of a bin are a factor of an 8-bit dot product");
   const Geo& g = p.g;
   const uint32_t tid = threadIdx.x;
-  for (uint32_t i = tid; i < KVC_N_RESIDUALS * 256u * kCopies; i += kScoreThreads) (&hist[0][0][0])[i] = 0u;
+  for (uint32_t i = tid; i < sizeof(hist) / 16u; i += kScoreThreads) reinterpret_cast<u32x4*>(&hist[0][0][0])[i] = u32x4{0u, 0u, 0u, 0u};
   __syncthreads();
 
-  const uint32_t s = blockIdx.x;  // stream = (chunk, kind, layer)
-  uint32_t ck, l;
+  uint32_t s, part, ck, l;  // stream = (chunk, kind, layer), part of its rows
+  fd_divmod(p.dparts, blockIdx.x, s, part);
   fd_divmod(p.dL, s, ck, l);
   const uint32_t kind = ck & 1u, c = ck >> 1;
   const uint32_t lg = l / 3u, pl = l - lg * 3u;
   const uint8_t* base = p.frames + (int64_t)c * g.frame_bytes + (((int64_t)kind * g.LG + lg) * g.F * 3 + pl) * g.plane;
   const int64_t frame_stride = 3 * g.plane;
-  const uint32_t W = (uint32_t)g.W, per_row = W / 8u;
-  const uint32_t copy = tid & (kCopies - 1);
+  const uint32_t W = (uint32_t)g.W, F = (uint32_t)g.F, per_row = W / 8u;
+  const uint32_t copy_bytes = (tid & (kCopies - 1)) * 4u;
 
   // A thread walks down a column of 8-pixel pieces, so the row above is what it read itself one step earlier (a
   // cache hit, never a second miss in flight for the same line).  Rows narrower than the workgroup are cut into
@@ -73,43 +102,77 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
   const uint32_t cols = per_row < (uint32_t)kScoreThreads ? per_row : (uint32_t)kScoreThreads;
   const uint32_t bands = (uint32_t)kScoreThreads / cols;
   const uint32_t band = tid / cols, col0 = tid - band * cols;
-  const uint32_t rows_per_band = ((uint32_t)g.Hp + bands - 1u) / bands;
-  const uint32_t y0 = band * rows_per_band;
-  uint32_t y1 = y0 + rows_per_band;
-  y1 = y1 < (uint32_t)g.Hp ? y1 : (uint32_t)g.Hp;
+  const uint32_t part0 = part * p.part_rows;
+  const uint32_t part1 = part0 + p.part_rows < (uint32_t)g.Hp ? part0 + p.part_rows : (uint32_t)g.Hp;
+  const uint32_t rows_per_band = (p.part_rows + bands - 1u) / bands;
+  const uint32_t y0 = part0 + band * rows_per_band;
+  const uint32_t y1 = y0 + rows_per_band < part1 ? y0 + rows_per_band : part1;
+  uint32_t zeros = 0u, zeros_later = 0u;  // pieces without any nonzero pixel around them, in all frames / frames >= 1
   for (uint32_t cb = col0; band < bands && cb < per_row; cb += cols)
   for (uint32_t y = y0; y < y1; ++y) {
-    const uint32_t q = y * per_row + cb;  // piece = 8 pixels of a row; rows are contiguous
-    const bool has_up = y > 0u, has_left = q - y * per_row > 0u;
-    u32x2 prev{0u, 0u}, prev_up{0u, 0u};
-    uint32_t prev_left = 0u;
-    for (uint32_t f = 0; f < (uint32_t)g.F; ++f) {
-      const uint8_t* px = base + (int64_t)f * frame_stride + (size_t)q * 8u;
-      const u32x2 cur = *(const KVC_GLOBAL u32x2*)px;  // cached: the next row reads it again as its upper neighbour
-      const u32x2 up = has_up ? *(const KVC_GLOBAL u32x2*)(px - W) : u32x2{0u, 0u};
-      const uint32_t left = has_left ? (uint32_t)(*(const KVC_GLOBAL uint8_t*)(px - 1)) << 24 : 0u;
-      count8(hist[KVC_RES_LEFT], sub_bytes(cur, left_of(cur, left)), copy);
-      count8(hist[KVC_RES_UP], sub_bytes(cur, up), copy);
-      if (f > 0u) {
-        const u32x2 t = sub_bytes(cur, prev);
-        const uint32_t t_left = sub_bytes(left, prev_left);  // the temporal residual of the pixel to the left
-        count8(hist[KVC_RES_TIME], t, copy);
-        count8(hist[KVC_RES_TIME_LEFT], sub_bytes(t, left_of(t, t_left)), copy);
-        count8(hist[KVC_RES_TIME_UP], sub_bytes(t, sub_bytes(up, prev_up)), copy);
+    const bool has_up = y > 0u, has_left = cb > 0u;
+    const uint8_t* row = base + (size_t)(y * per_row + cb) * 8u;
+    const uint8_t* row_up = has_up ? row - W : row;      // stays inside the plane: row 0 and column 0 read themselves
+    const uint8_t* row_left = has_left ? row - 1 : row;
+    Piece prev{}, prev_l{}, prev_u{};
+    uint32_t prev_any = 0u;
+    for (uint32_t f0 = 0; f0 < F; f0 += kFrames) {
+      u32x2 cur[kFrames], up[kFrames];
+      uint32_t left[kFrames];
+#pragma unroll
+      for (int k = 0; k < kFrames; ++k) {
+        const size_t at = (size_t)(f0 + k < F ? f0 + k : F - 1u) * (size_t)frame_stride;
+        cur[k] = *(const KVC_GLOBAL u32x2*)(row + at);  // cached: the next row reads it again as its upper neighbour
+        up[k] = *(const KVC_GLOBAL u32x2*)(row_up + at);
+        left[k] = *(const KVC_GLOBAL uint8_t*)(row_left + at);
       }
-      prev = cur;
-      prev_up = up;
-      prev_left = left;
+#pragma unroll
+      for (int k = 0; k < kFrames; ++k) {
+        if (f0 + k >= F) break;  // wave-uniform
+        if (!has_up) up[k] = u32x2{0u, 0u};
+        if (!has_left) left[k] = 0u;
+        // Tiles without a token are zero: where a whole wave sees nothing else, its residuals are counted at the end.
+        const uint32_t any = cur[k].x | cur[k].y | up[k].x | up[k].y | left[k];
+        if (__ballot((any | prev_any) != 0u) == 0u) {
+          ++zeros;
+          zeros_later += f0 + k > 0u ? 1u : 0u;
+          continue;
+        }
+        const Piece now = split(cur[k]);
+        const Piece res_l = now - left_of(now, left[k]), res_u = now - split(up[k]);
+        count8(hist[KVC_RES_LEFT], res_l, copy_bytes);
+        count8(hist[KVC_RES_UP], res_u, copy_bytes);
+        if (f0 + k > 0u) {
+          count8(hist[KVC_RES_TIME], now - prev, copy_bytes);
+          count8(hist[KVC_RES_TIME_LEFT], res_l - prev_l, copy_bytes);
+          count8(hist[KVC_RES_TIME_UP - 1], res_u - prev_u, copy_bytes + (uint32_t)sizeof(Histogram));  // an offset of 64 KB does not fit the instruction
+        }
+        prev = now;
+        prev_l = res_l;
+        prev_u = res_u;
+        prev_any = any;
+      }
     }
   }
+  if (zeros != 0u) {
+    const uint32_t copy = tid & (kCopies - 1);
+    atomicAdd(&hist[KVC_RES_LEFT][0][copy], 8u * zeros);
+    atomicAdd(&hist[KVC_RES_UP][0][copy], 8u * zeros);
+    atomicAdd(&hist[KVC_RES_TIME][0][copy], 8u * zeros_later);
+    atomicAdd(&hist[KVC_RES_TIME_LEFT][0][copy], 8u * zeros_later);
+    atomicAdd(&hist[KVC_RES_TIME_UP][0][copy], 8u * zeros_later);
+  }
   __syncthreads();
-  uint64_t* out = p.hist + (size_t)s * (KVC_N_RESIDUALS * 256);
+  unsigned long long* out = reinterpret_cast<unsigned long long*>(p.hist) + (size_t)s * (KVC_N_RESIDUALS * 256);
   for (uint32_t i = tid; i < KVC_N_RESIDUALS * 256u; i += kScoreThreads) {
-    const uint32_t* hc = &(&hist[0][0][0])[i * kCopies];
-    uint64_t n = 0;
+    const u32x4* hc = reinterpret_cast<const u32x4*>(&(&hist[0][0][0])[i * kCopies]);
+    uint32_t n = 0;  // a stream has fewer than 2^32 pixels
 #pragma unroll
-    for (int k = 0; k < kCopies; ++k) n += hc[k];
-    out[i] = n;
+    for (int k = 0; k < kCopies / 4; ++k) n += hc[k].x + hc[k].y + hc[k].z + hc[k].w;
+    if (p.dparts.d == 1u)
+      out[i] = n;
+    else if (n != 0u)
+      atomicAdd(&out[i], (unsigned long long)n);
   }
 }
 
@@ -122,7 +185,20 @@ kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream) {
   const int64_t streams = (int64_t)p.n_chunks * 2 * g.L;
   if (streams > 0x7fffffff) return KVC_ERR_UNSUPPORTED;
   p.dL = make_fastdiv((uint32_t)g.L);
-  hipLaunchKernelGGL(residual_hist_kernel, dim3((uint32_t)streams), dim3(kScoreThreads), 0, stream, p);
+  // Parts: about kScoreWorkgroups workgroups (two fit a CU), each of a whole number of rows for every band of a workgroup.
+  const int64_t cols = g.W / 8 < kScoreThreads ? g.W / 8 : kScoreThreads, bands = kScoreThreads / cols;
+  const int64_t want = streams < kScoreWorkgroups ? kScoreWorkgroups / streams : 1;
+  int64_t rows = (g.Hp + want - 1) / want;
+  rows = (rows + bands - 1) / bands * bands;
+  const int64_t parts = (g.Hp + rows - 1) / rows;
+  p.part_rows = (uint32_t)rows;
+  p.dparts = make_fastdiv((uint32_t)parts);
+  if (parts > 1) {
+    const uint32_t n16 = (uint32_t)(streams * (KVC_N_RESIDUALS * 256 * 8 / 16));
+    hipLaunchKernelGGL(clear_hist_kernel, dim3((n16 + kScoreThreads - 1) / kScoreThreads), dim3(kScoreThreads), 0, stream,
+                       reinterpret_cast<u32x4*>(p.hist), n16);
+  }
+  hipLaunchKernelGGL(residual_hist_kernel, dim3((uint32_t)(streams * parts)), dim3(kScoreThreads), 0, stream, p);
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
 }
 

@@ -79,6 +79,32 @@ def test_histograms_of_adversarial_planes():
     hz.assert_same_bytes("histograms", got, R.residual_histograms(olo, frames, n_chunks))
 
 
+PARTS = [
+    # L, H, D, T, th, tw, TX, TY, n_chunks: streams cut into parts of rows, and streams that are not
+    (2, 4, 128, 300, 8, 64, 8, 40, 1),     # 320 rows of 64 pieces: parts of 8 rows
+    (3, 2, 128, 90, 2, 128, 3, 37, 2),     # 74 rows of 48 pieces: 480 of 512 threads, a short last part
+    (1, 2, 1024, 20, 1, 2048, 3, 5, 1),    # 768 pieces a row: two blocks of columns
+    (171, 1, 8, 7, 1, 8, 1, 3, 3),         # 1026 streams: one workgroup each, F = 3
+    (2, 1, 64, 45, 2, 32, 3, 3, 2),        # F = 5: a second round of loads
+]
+
+
+@pytest.mark.parametrize("case", PARTS, ids=[f"p{i}" for i in range(len(PARTS))])
+def test_histograms_of_streams_cut_into_parts(case):
+    """Random planes with empty bands of rows (which are not counted pixel by pixel), bit-exact."""
+    L, H, D, T, th, tw, TX, TY, n_chunks = case
+    glo, olo = hz.layouts(L, H, D, "f16", T, th, tw, TX, TY)
+    fb, Hp, W = oracle.frame_bytes(olo), TY * th, TX * tw
+    rng = np.random.default_rng(900 + L)
+    frames = rng.integers(0, 256, size=(n_chunks * fb // (Hp * W), Hp, W), dtype=np.uint8)
+    frames[:, Hp // 3: Hp // 3 + max(1, Hp // 4)] = 0
+    frames[1::3, -(Hp // 5 + 1):] = 0
+    frames = frames.reshape(-1)
+    hz.say(f"[case] histograms in parts: L={L} planes {Hp} x {W}, {n_chunks} chunks")
+    got = gpu_histograms(glo, torch.from_numpy(frames).cuda(), n_chunks).reshape(n_chunks, 2, L, R.N_RESIDUALS, 256)
+    hz.assert_same_bytes("histograms", got, R.residual_histograms(olo, frames, n_chunks))
+
+
 def test_rank_tiles_orders_candidates_like_the_oracle():
     """The search loop on a small model shape: every candidate's cost equals the oracle's for the same tiling, so
     the ranking is the oracle's."""
