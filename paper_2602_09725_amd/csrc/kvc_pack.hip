@@ -795,8 +795,9 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
   // The resident body forms 32-bit byte offsets for all kResidentLoads x rows token rows of a strip, whatever
   // the chunk length (rows past the last token are clamped afterwards), and inside the chunk's frame section.
   const int64_t resident_rows = (int64_t)kResidentLoads * (kResidentThreads / p.strip_atoms);
+  // A per-token kind in the same launch needs a thread for every atom of a token.
   p.resident = p.n_kinds_ch > 0 && g.T <= resident_rows && resident_rows * p.ts * 2 < (1ll << 32) &&
-                       g.frame_bytes < (1ll << 32)
+                       g.frame_bytes < (1ll << 32) && (p.n_kinds_tok == 0 || g.apt <= kResidentThreads)
                    ? 1
                    : 0;
   // Chunks too long for that read the part of each strip that does not fit on chip twice.  Few, large

@@ -889,6 +889,15 @@ def test_reference_expand_copy_moves_every_vector_where_the_map_says(wg):
             assert bool((buf[:guard] == 0x5A5A5A5A).all()) and bool((buf[guard + n_vec * 4:] == 0x5A5A5A5A).all())
 
 
+@pytest.mark.parametrize("modes", [(0, 1), (0, 0), (1, 1)])
+def test_more_atoms_than_threads(modes):
+    """64 heads of 128: 1024 atoms a token, twice the threads of the workgroups that keep per-channel strips on chip."""
+    L, H, D, T, n = 2, 64, 128, 40, 57
+    glo, olo = hz.layouts(L, H, D, "f16", T, 64, 128, 4, 5, *modes)
+    kv = kv_synth.make_kv(L, H, D, n, torch.float16, seed=64, device="cuda")
+    full_check(glo, olo, kv, n, "f16", block_size=16, tag="64 heads")
+
+
 RESTORE_SHAPES = [
     # L, H, D, T, th, tw, TX, TY, n_tokens, block_size: each launch shape of restore (passes x threads), ragged rows
     (3, 8, 128, 64, 8, 128, 2, 8, 65, 16),       # whole waves, 2 passes, one token in the last chunk
