@@ -50,6 +50,46 @@ KVC_HD void fd_divmod(const FastDiv& f, uint32_t n, uint32_t& q, uint32_t& r) {
   r = n - q * f.d;
 }
 
+// How the units of a launch go to the 8 XCDs, to which workgroups are handed round-robin.  Units come in rows -- a
+// row is one (kind, layer), its units the pieces of work of all chunks -- and the whole chip works on one row at a
+// time, each XCD on a contiguous eighth of it; rows of few units are taken several at a time (a band), so that the
+// eighths are about equal.
+struct BandMap {
+  FastDiv per_xcd;    // units of a band that one XCD takes
+  FastDiv row_units;  // units of a row
+  uint32_t band_rows, band_units, rows;
+  uint32_t wgs_per_xcd;  // workgroups of all bands
+};
+
+// False when the launch would need more than `most` workgroups.
+inline bool make_band_map(BandMap* b, int64_t rows, int64_t row_units, int64_t most) {
+  *b = BandMap{};
+  b->per_xcd = b->row_units = make_fastdiv(1);
+  if (rows == 0 || row_units == 0) return true;
+  int64_t band_rows = row_units >= 64 ? 1 : (64 + row_units - 1) / row_units;
+  if (band_rows > rows) band_rows = rows;
+  const int64_t per_xcd = (row_units * band_rows + 7) / 8, wgs = per_xcd * ((rows + band_rows - 1) / band_rows);
+  if (wgs > most / 8) return false;
+  b->per_xcd = make_fastdiv((uint32_t)per_xcd);
+  b->row_units = make_fastdiv((uint32_t)row_units);
+  b->band_rows = (uint32_t)band_rows;
+  b->band_units = (uint32_t)(row_units * band_rows);
+  b->rows = (uint32_t)rows;
+  b->wgs_per_xcd = (uint32_t)wgs;
+  return true;
+}
+
+// Workgroup idx (of wgs_per_xcd) of an XCD -> row and unit of the row; false if it has none.
+KVC_HD bool band_unit(const BandMap& b, uint32_t xcd, uint32_t idx, uint32_t& row, uint32_t& u) {
+  uint32_t band, within;
+  fd_divmod(b.per_xcd, idx, band, within);
+  const uint32_t w = xcd * b.per_xcd.d + within;
+  if (w >= b.band_units) return false;
+  fd_divmod(b.row_units, w, row, u);
+  row += band * b.band_rows;
+  return row < b.rows;  // the last band may hold fewer rows
+}
+
 // Derived geometry of a kvc_layout (notation of include/kvc.h).
 struct Geo {
   int32_t L, H, D, C, T;

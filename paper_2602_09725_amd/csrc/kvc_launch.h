@@ -19,10 +19,7 @@ struct RestoreParams {
   uint32_t n_units;       // frame call: fm_count * 3 * tbc workgroups with work
   uint32_t units_per_xcd;
   FastDiv dtbc, dL;       // unit -> (token block, chunk), row -> (kind, layer)
-  // chunk call: rows ((kind, layer) pairs) are taken in bands of band_rows; a band's units (token blocks of its rows,
-  // those that hold tokens) are cut into 8 contiguous parts, one per XCD
-  uint32_t band_rows, band_units;
-  FastDiv drow, dbpx;     // units of a row; units of a band per XCD
+  BandMap bands;          // chunk call
   // "rows" body: a wave reads runs of 512 bytes of one plane row, i.e. one row of rows_q = 512 / tw neighbouring
   // tiles; a workgroup (th waves) takes rows_trw rows of tiles, in all F frames (chunk call) or in one (frame call)
   int32_t rows_body, rows_q, rows_lat;  // lat: log2 of the atoms of a tile row
@@ -61,6 +58,13 @@ struct RestoreParams {
 // Enqueues the fused unpack + dequantize + placement kernel.
 kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream);
 
+constexpr int kPackResident = 0, kPackStream = 1, kPackLight = 2, kPackMedium = 3;
+
+// A range of work units and the share of one XCD.
+struct PackRange {
+  uint32_t units, per_xcd;
+};
+
 struct PackParams {
   Geo g;
   const uint16_t* kv;
@@ -70,7 +74,7 @@ struct PackParams {
   uint8_t* frames;
   float* meta;
   // workgroups of per-token kinds: blocks of tb token positions
-  int32_t tb, tbc, tpp;
+  int32_t tb, tbc, tbl, tpp;  // tbc, tbl: blocks of a whole chunk, of the last chunk
   FastDiv dapt;
   int32_t n_kinds_tok;
   int32_t kinds_tok[2];
@@ -80,17 +84,23 @@ struct PackParams {
   int32_t rows;           // token rows per pass = threads / strip_atoms
   uint32_t pass_step;     // bytes the code offset of a thread grows per pass, 0 if that is not a constant
   int32_t n_kinds_ch;
-  int32_t resident;       // per-channel strips are held in registers (one read of the input)
+  int32_t body;           // kPackResident, kPackStream or kPackLight: which form the launch takes
+  int32_t resident;       // per-channel strips wait on chip as a whole (one read of the input)
   int32_t kinds_ch[2];
   // token positions of the tile rows a token can fall into: chunks of T tokens, and the call's last chunk
   int32_t positions_full, positions_last;
   // zero-fill workgroups: planes of layers beyond L, then unused tile rows of full chunks, then of the last chunk
   uint32_t pieces_plane, pieces_tail_full, pieces_tail_last;
-  uint32_t n_zero_pad, n_zero_full, n_units_zero;
-  // work units of the three kinds of workgroup and their share per XCD
-  uint32_t n_units_ch, n_units_tok;
-  uint32_t ch_per_xcd, tok_per_xcd, zero_per_xcd;
-  uint32_t units_per_xcd;
+  uint32_t n_zero_pad, n_zero_full;
+  // ... and before them the per-token pairs of the last chunk's last zero_pair_tokens tokens, which no token block covers
+  int32_t zero_pair_tokens;
+  uint32_t pieces_pairs, n_zero_pairs;
+  // workgroups of the three kinds, those of a short last chunk apart: n_whole chunks hold T tokens
+  PackRange ch[2], tok[2], zero;
+  uint32_t tok_run;       // consecutive per-token units that go to one XCD, a power of two
+  int32_t n_whole;
+  int32_t light_last;     // resident launch: the short last chunk's strips take the light form
+  uint32_t wgs_per_xcd;
 };
 
 // Host-side plan of a pack launch: which body the per-channel kinds take, block and grid

@@ -2,7 +2,8 @@
 // layout (Sec. 3.2.1 steps 1-3, Sec. 3.2.2, Sec. 4 item (1)).
 //
 // One launch covers both quantization groupings; a workgroup takes one of two
-// bodies according to the grouping of the kind it works on:
+// bodies according to the grouping of the kind it works on (the per-channel one in
+// one of four forms, by the number of tokens and strips):
 //  * per-token groups (one group = the D elements of one head of one token):
 //    statistics, quantization and the layout scatter fused in one pass.  A thread
 //    holds an atom of 8 consecutive elements; the D/8 lanes of a head reduce
@@ -26,20 +27,12 @@
 
 namespace kvc {
 
-#ifndef KVC_PACK_U_RESIDENT
-#define KVC_PACK_U_RESIDENT 8  // loads in flight per thread of the per-token body beside the resident strips (8 waves per CU)
-#endif
-#ifndef KVC_PACK_U
-#define KVC_PACK_U 4  // ... beside the streamed strips (16 waves per CU)
-#endif
-#ifndef KVC_PACK_STREAM_U
-#define KVC_PACK_STREAM_U 4  // ... of the two-pass per-channel body (next to the 16 it keeps)
-#endif
-#ifndef KVC_PACK_STREAM_ATOMS
-#define KVC_PACK_STREAM_ATOMS 8  // atoms per strip of the two-pass per-channel body
-#endif
-
 namespace {
+
+constexpr int kTokenLoadsResident = 8;  // loads in flight per thread of the per-token body beside the resident strips (8 waves per CU)
+constexpr int kTokenLoads = 4;          // ... beside the other forms (16 waves per CU)
+constexpr int kStreamLoads = 4;         // ... of the two-pass per-channel body (next to the 16 it keeps)
+constexpr int kStreamThreads = 1024, kStreamAtoms = 8;  // workgroup and strip of the two-pass body
 
 struct GroupParams {
   float scale, mn, inv;
@@ -92,6 +85,18 @@ __device__ __forceinline__ u32x2 quantize_atom(const float (&x)[8], const float 
   return o;
 }
 
+// Strips narrower than a line of codes share it with their neighbours: L2 puts the pieces together if the stores
+// do not ask to be written out at once.
+__device__ __forceinline__ void code_store(uint8_t* dst, u32x2 o, bool shared_line) {
+  if (shared_line) {
+    asm volatile("" ::: "memory");  // on both sides, or the compiler makes one plain store of the two
+    *(KVC_GLOBAL u32x2*)dst = o;
+    asm volatile("" ::: "memory");
+  } else {
+    stream_store<u32x2>(dst, o);
+  }
+}
+
 template <int DT>
 __device__ __forceinline__ void widen_atom(const u32x4& v, float (&x)[8]) {
   widen_pair<DT>(v.x, x[0], x[1]);
@@ -129,8 +134,8 @@ __device__ __forceinline__ void atom_minmax<KVC_BF16>(const u32x4& v, float& lo,
 }
 
 // Running per-channel minimum / maximum of the 8 channels of an atom over many
-// tokens.  fp16 stays packed (4 + 4 VGPRs, two channels per instruction); bf16
-// is widened first (no packed bf16 compare).
+// tokens, packed (4 + 4 VGPRs, two channels per instruction).
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
 template <int DT>
 struct ColumnStats;
 template <>
@@ -170,35 +175,37 @@ struct ColumnStats<KVC_F16> {
 };
 template <>
 struct ColumnStats<KVC_BF16> {
-  float lo[8], hi[8];
+  // bf16 as 16-bit integers in the order of the values (negative ones with their magnitude bits flipped)
+  i16x2 lo[4], hi[4];
+  static __device__ __forceinline__ i16x2 ordered(i16x2 v) { return v ^ ((v >> 15) & (short)0x7fff); }  // its own inverse
   __device__ __forceinline__ void init() {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      lo[j] = __builtin_inff();
-      hi[j] = -__builtin_inff();
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = i16x2{0x7fff, 0x7fff};
+      hi[j] = i16x2{-0x8000, -0x8000};
     }
   }
   __device__ __forceinline__ void add(const u32x4& v) {
-    float x[8];
-    widen_atom<KVC_BF16>(v, x);
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      lo[j] = __builtin_fminf(lo[j], x[j]);
-      hi[j] = __builtin_fmaxf(hi[j], x[j]);
+    for (int j = 0; j < 4; ++j) {
+      const i16x2 x = ordered(__builtin_bit_cast(i16x2, w[j]));
+      lo[j] = __builtin_elementwise_min(lo[j], x);
+      hi[j] = __builtin_elementwise_max(hi[j], x);
     }
   }
   __device__ __forceinline__ void merge_xor(int m) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      lo[j] = __builtin_fminf(lo[j], __shfl_xor(lo[j], m));
-      hi[j] = __builtin_fmaxf(hi[j], __shfl_xor(hi[j], m));
+    for (int j = 0; j < 4; ++j) {
+      lo[j] = __builtin_elementwise_min(lo[j], __builtin_bit_cast(i16x2, __shfl_xor(__builtin_bit_cast(uint32_t, lo[j]), m)));
+      hi[j] = __builtin_elementwise_max(hi[j], __builtin_bit_cast(i16x2, __shfl_xor(__builtin_bit_cast(uint32_t, hi[j]), m)));
     }
   }
   __device__ __forceinline__ void get(float (&l)[8], float (&h)[8]) const {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      l[j] = lo[j];
-      h[j] = hi[j];
+    for (int j = 0; j < 4; ++j) {
+      widen_pair<KVC_BF16>(__builtin_bit_cast(uint32_t, ordered(lo[j])), l[2 * j], l[2 * j + 1]);
+      widen_pair<KVC_BF16>(__builtin_bit_cast(uint32_t, ordered(hi[j])), h[2 * j], h[2 * j + 1]);
     }
   }
 };
@@ -233,15 +240,15 @@ __device__ __forceinline__ void head_minmax16(float& lo, float& hi) {
 }
 
 template <int DT, bool UNIFORM, int U>
-__device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t unit) {
+__device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t unit, uint32_t c0, uint32_t blocks) {
   const Geo& g = p.g;
   uint32_t uu = unit;
-  const uint32_t tbi = uu % (uint32_t)p.tbc;
-  uu /= (uint32_t)p.tbc;
+  const uint32_t tbi = uu % blocks;
+  uu /= blocks;
   const uint32_t l = uu % (uint32_t)g.L;
   uu /= (uint32_t)g.L;
   const uint32_t kind = (uint32_t)p.kinds_tok[uu % (uint32_t)p.n_kinds_tok];
-  const uint32_t c = uu / (uint32_t)p.n_kinds_tok;
+  const uint32_t c = c0 + uu / (uint32_t)p.n_kinds_tok;
   if (threadIdx.x >= (uint32_t)(g.apt * p.tpp)) return;  // the block is rounded up to whole waves
 
   const uint32_t tid = threadIdx.x;
@@ -334,7 +341,8 @@ __device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t un
     }
   }
   // Pairs of the token positions of this block that the loops did not visit (a short chunk uses fewer tile
-  // rows than a full one; every such position is past the chunk's last token): {0, 0}.
+  // rows than a full one; every such position is past the chunk's last token): {0, 0}.  The pairs of whole
+  // blocks without a position are the zero units'.
   const int32_t m1 = t0 + p.tb < g.T ? t0 + p.tb : g.T;
   for (int32_t t = (t1 > t0 ? t1 : t0) + (int32_t)tsub; t < m1; t += step)
     if (leader) *reinterpret_cast<f32x2*>(mrow + 2 * (int64_t)t * g.H) = f32x2{0.f, 0.f};
@@ -403,9 +411,9 @@ constexpr int kStreamTailLoads = 16;
 constexpr int kStreamStashLoads = 8;
 
 template <int DT>
-__device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t unit, float (*red_lo)[kMaxStripAtoms * 8],
+__device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t unit, uint32_t c0, float (*red_lo)[kMaxStripAtoms * 8],
                                                   float (*red_hi)[kMaxStripAtoms * 8], u32x4* stash) {
-  constexpr int U = KVC_PACK_STREAM_U;
+  constexpr int U = kStreamLoads;
   constexpr int NT = kStreamTailLoads, NS = kStreamStashLoads;
   static_assert(NS % U == 0, "the stash is filled in steps of U loads");
   const Geo& g = p.g;
@@ -415,7 +423,7 @@ __device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t 
   const uint32_t l = uu % (uint32_t)g.L;
   uu /= (uint32_t)g.L;
   const uint32_t kind = (uint32_t)p.kinds_ch[uu % (uint32_t)p.n_kinds_ch];
-  const uint32_t c = uu / (uint32_t)p.n_kinds_ch;
+  const uint32_t c = c0 + uu / (uint32_t)p.n_kinds_ch;
 
   const uint32_t tid = threadIdx.x;
   const uint32_t sa = (uint32_t)p.strip_atoms;  // power of two <= 64
@@ -505,7 +513,7 @@ __device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t 
       if (t >= head_n) continue;
       float x[8];
       widen_atom<DT>(v[u], x);
-      stream_store<u32x2>(code_addr(g, fbase, t), quantize_atom(x, mnv, inv));
+      code_store(code_addr(g, fbase, t), quantize_atom(x, mnv, inv), sa < (uint32_t)kStreamAtoms);
     }
   }
   // ... the kept tokens from LDS and from the registers, ...
@@ -515,7 +523,7 @@ __device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t 
     if (t >= n) continue;
     float x[8];
     widen_atom<DT>(mine[(uint32_t)i * blockDim.x], x);
-    stream_store<u32x2>(code_addr(g, fbase, t), quantize_atom(x, mnv, inv));
+    code_store(code_addr(g, fbase, t), quantize_atom(x, mnv, inv), sa < (uint32_t)kStreamAtoms);
   }
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
@@ -523,10 +531,10 @@ __device__ __forceinline__ void pack_channel_body(const PackParams& p, uint32_t 
     if (t >= n) continue;
     float x[8];
     widen_atom<DT>(tail[i], x);
-    stream_store<u32x2>(code_addr(g, fbase, t), quantize_atom(x, mnv, inv));
+    code_store(code_addr(g, fbase, t), quantize_atom(x, mnv, inv), sa < (uint32_t)kStreamAtoms);
   }
   // ... and zeros for the tile positions of the used tile rows that hold no token.
-  for (uint32_t t = n + row; t < positions; t += rows) stream_store<u32x2>(code_addr(g, fbase, t), u32x2{0u, 0u});
+  for (uint32_t t = n + row; t < positions; t += rows) code_store(code_addr(g, fbase, t), u32x2{0u, 0u}, sa < (uint32_t)kStreamAtoms);
 }
 
 // Resident variant: the strip of one (chunk, kind, layer) -- up to kResidentLoads * rows tokens x 128
@@ -543,12 +551,28 @@ constexpr int kResidentLds = 18;   // ... in LDS
 constexpr int kResidentLoads = kResidentRegs + kResidentLds;
 constexpr int kResidentGroup = 6;  // loads in flight while the LDS slots are filled
 static_assert(kResidentLds % kResidentGroup == 0, "the LDS slots are filled a whole group of loads at a time");
+// The medium form holds half as much, so that two workgroups fit a CU and one reads while the other writes: chunks of
+// 1024 tokens (32 layers x 1024 channels, 8 of them) 336 -> 296 us.
+constexpr int kMediumRegs = 24, kMediumLds = 8;
+constexpr int kMediumLoads = kMediumRegs + kMediumLds;
+constexpr int kMediumGroup = 4;
+// The light form keeps few loads, all in registers, and leaves out the groups of loads a chunk has no tokens for: a
+// strip of 128 tokens read 2048 rows before, most of them repeats of the last (128 tokens x 60 layers x 1024 channels
+// 80 -> 55 us with the zero fill of the chunk, 150 MB, in it).  It also takes launches of few strips, which are cut into
+// narrower ones (two layers of 2048 tokens, 16 strips of 128 channels: 26.5 -> 12.5 us in 128 strips of 16; with
+// 256 strips and more the full lines are worth more, 77 us against 94 for 32 layers), and per-token kinds alone up to
+// kFewTokenRows, where its smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger
+// workgroups of the streaming form are faster, 283 against 295 us for 32 layers of 8192).
+constexpr int kLightLoads = 16;
+constexpr int kRegGroup = 8;
+constexpr int kFewestAtoms = 2;
+constexpr int64_t kFewStrips = 128, kFewTokenRows = 2048 * 128, kFewTokenUnits = 512;
 
-template <int DT>
-__device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, uint32_t unit,
+template <int DT, int NR, int NS, bool SHORT>
+__device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, uint32_t unit, uint32_t c0,
                                                            float (*red_lo)[kMaxStripAtoms * 8],
                                                            float (*red_hi)[kMaxStripAtoms * 8], u32x4* stash) {
-  constexpr int NI = kResidentLoads, NR = kResidentRegs, NS = kResidentLds;
+  constexpr int NI = NR + NS, LG = NS == kResidentLds ? kResidentGroup : kMediumGroup;
   const Geo& g = p.g;
   uint32_t uu = unit;
   const uint32_t strip = uu % (uint32_t)p.n_strips;
@@ -556,7 +580,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   const uint32_t l = uu % (uint32_t)g.L;
   uu /= (uint32_t)g.L;
   const uint32_t kind = (uint32_t)p.kinds_ch[uu % (uint32_t)p.n_kinds_ch];
-  const uint32_t c = uu / (uint32_t)p.n_kinds_ch;
+  const uint32_t c = c0 + uu / (uint32_t)p.n_kinds_ch;
 
   const uint32_t tid = threadIdx.x;
   const uint32_t sa = (uint32_t)p.strip_atoms;
@@ -569,7 +593,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
 
   const int64_t chunk_first = (int64_t)c * g.T;
   const int64_t left = p.n_tokens - chunk_first;
-  const int32_t n = left < (int64_t)g.T ? (int32_t)left : g.T;
+  const uint32_t n = left < (int64_t)g.T ? (uint32_t)left : (uint32_t)g.T;  // at least 1
   const uint32_t positions = (uint32_t)((int32_t)c + 1 == p.n_chunks ? p.positions_last : p.positions_full);
 
   uint32_t r, cc;
@@ -582,41 +606,47 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   u32x4 v[NR];                       // loads NS .. NI-1
   u32x4* const mine = stash + tid;   // load i < NS: mine[i * blockDim.x]
   float mnv[8], inv[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) mnv[i] = inv[i] = 0.f;
 
-  if (n > 0) {
-    // byte offsets grow by a constant per pass; rows past the last token repeat it (min / max unchanged)
-    const uint32_t last = ((uint32_t)n - 1u) * ts2 + e * 2u, off_row = row * ts2 + e * 2u, off_step = rows * ts2;
-    ColumnStats<DT> st;
-    st.init();
-    // the loads that wait in LDS first, while the registers of the others are still free to carry them
+  // byte offsets grow by a constant per pass; rows past the last token repeat it (min / max unchanged), and groups
+  // of loads that lie past it as a whole are left out
+  const uint32_t last = (n - 1u) * ts2 + e * 2u, off_row = row * ts2 + e * 2u, off_step = rows * ts2;
+  ColumnStats<DT> st;
+  st.init();
+  // the loads that wait in LDS first, while the registers of the others are still free to carry them
 #pragma unroll
-    for (int i0 = 0; i0 < NS; i0 += kResidentGroup) {
-      u32x4 w[kResidentGroup];
+  for (int i0 = 0; i0 < NS; i0 += LG) {
+    if (SHORT && (uint32_t)i0 * rows >= n) break;
+    u32x4 w[LG];
 #pragma unroll
-      for (int u = 0; u < kResidentGroup; ++u) {
-        const uint32_t off = off_row + (uint32_t)(i0 + u) * off_step;
-        w[u] = stream_load<u32x4>(srcb + (size_t)(off < last ? off : last));
-      }
-#pragma unroll
-      for (int u = 0; u < kResidentGroup; ++u) {
-        st.add(w[u]);
-        mine[(uint32_t)(i0 + u) * blockDim.x] = w[u];
-      }
+    for (int u = 0; u < LG; ++u) {
+      const uint32_t off = off_row + (uint32_t)(i0 + u) * off_step;
+      w[u] = stream_load<u32x4>(srcb + (size_t)(off < last ? off : last));
     }
 #pragma unroll
-    for (int i = 0; i < NR; ++i) {
+    for (int u = 0; u < LG; ++u) {
+      st.add(w[u]);
+      mine[(uint32_t)(i0 + u) * blockDim.x] = w[u];
+    }
+  }
+#pragma unroll
+  for (int i0 = 0; i0 < NR; i0 += kRegGroup) {
+    if (SHORT && (uint32_t)(NS + i0) * rows >= n) break;
+#pragma unroll
+    for (int i = i0; i < NR && i < i0 + kRegGroup; ++i) {
       const uint32_t off = off_row + (uint32_t)(NS + i) * off_step;
       v[i] = stream_load<u32x4>(srcb + (size_t)(off < last ? off : last));
     }
-#pragma unroll
-    for (int i = 0; i < NR; ++i) st.add(v[i]);
-    strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
   }
+#pragma unroll
+  for (int i0 = 0; i0 < NR; i0 += kRegGroup) {
+    if (SHORT && (uint32_t)(NS + i0) * rows >= n) break;
+#pragma unroll
+    for (int i = i0; i < NR && i < i0 + kRegGroup; ++i) st.add(v[i]);
+  }
+  strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
   if (!active) return;  // after the barriers: lanes of a ragged last strip store nothing
 
-  // Quantize from the registers; tile positions without a token get zeros.  Token position
+  // Quantize from where the loads wait; tile positions without a token get zeros.  Token position
   // t -> frame t % F, tile (t / F) % TX of tile row (t / F) / TX; when the rows of a pass
   // are a whole number of tile rows (rows % (F * TX) == 0) the offset grows by a constant per pass.
   const uint32_t frame3 = (uint32_t)(3 * g.plane), trs = (uint32_t)g.th * (uint32_t)g.W;
@@ -628,10 +658,11 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   const uint32_t pass_step = p.pass_step;  // bytes per pass, 0 if not constant
 #pragma unroll
   for (int i = 0; i < NI; ++i) {
+    if (SHORT && (uint32_t)i * rows >= positions) break;
     const uint32_t t = row + (uint32_t)i * rows;
     if (t >= positions) continue;
     u32x2 o{0u, 0u};
-    if (t < (uint32_t)n) {
+    if (t < n) {
       float x[8];
       if (i < NS)
         widen_atom<DT>(mine[(uint32_t)i * blockDim.x], x);
@@ -646,7 +677,8 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
       fd_divmod(g.dTX, gi, ty, tx);
       off = f * frame3 + ty * trs + tx * (uint32_t)g.tw + lane_off;
     }
-    stream_store<u32x2>(fplane + (size_t)off, o);
+    // narrower strips share a line of codes with their neighbours, which L2 puts together
+    code_store(fplane + (size_t)off, o, NS == 0 && sa < (uint32_t)kResidentAtoms);
   }
   for (uint32_t t = row + (uint32_t)NI * rows; t < positions; t += rows) {
     uint32_t gi, f, ty, tx;
@@ -680,6 +712,19 @@ __device__ __forceinline__ void pack_zero_body(const PackParams& p, uint32_t z) 
   const Geo& g = p.g;
   const uint32_t F = (uint32_t)g.F, L = (uint32_t)g.L;
   uint32_t c, kind, l3, f, piece, start;
+  if (z < p.n_zero_pairs) {  // per-token pairs behind the last token block of the call's last chunk
+    piece = z % p.pieces_pairs;
+    z /= p.pieces_pairs;
+    const uint32_t l = z % L;
+    kind = (uint32_t)p.kinds_tok[z / L];
+    const uint64_t lo = (uint64_t)piece * kZeroPiece, all = (uint64_t)p.zero_pair_tokens * (uint32_t)g.H * 8u;
+    const uint32_t bytes = all - lo < kZeroPiece ? (uint32_t)(all - lo) : kZeroPiece;
+    float* pairs = p.meta + (int64_t)(p.n_chunks - 1) * g.meta_floats + g.meta_off[kind] +
+                   2 * ((int64_t)l * g.T + (g.T - p.zero_pair_tokens)) * g.H;
+    zero_span(reinterpret_cast<uint8_t*>(pairs) + lo, bytes);
+    return;
+  }
+  z -= p.n_zero_pairs;
   if (z < p.n_zero_pad) {  // plane of a layer that does not exist: all of it
     piece = z % p.pieces_plane;
     z /= p.pieces_plane;
@@ -723,51 +768,73 @@ __device__ __forceinline__ void pack_zero_body(const PackParams& p, uint32_t z) 
   zero_span(dst, bytes);
 }
 
-template <int DT, bool UNIFORM, bool RESIDENT>
-__global__ void __launch_bounds__(RESIDENT ? kResidentThreads : 1024) pack_kernel(const PackParams p) {
+template <int DT, bool UNIFORM, int BODY>
+__global__ void __launch_bounds__(BODY == kPackStream ? 1024 : kResidentThreads, BODY == kPackLight || BODY == kPackMedium ? 4 : 1)
+pack_kernel(const PackParams p) {
   // partial column extremes of the waves; the row after them carries the finished {mn} / {inv} of the strip
-  constexpr int kWaves = (RESIDENT ? kResidentThreads : 1024) / 64;
+  constexpr int kWaves = (BODY == kPackStream ? 1024 : kResidentThreads) / 64;
   __shared__ float red_lo[kWaves + 1][kMaxStripAtoms * 8];
   __shared__ float red_hi[kWaves + 1][kMaxStripAtoms * 8];
   extern __shared__ u32x4 stash[];  // the loads of the per-channel bodies that wait in LDS, one slot per thread each
-  // Workgroups go to the 8 XCDs round-robin.  Each XCD gets one contiguous range
-  // of the per-channel units, one of the per-token units and one of the zero-fill
-  // units, so neighbouring strips and token blocks share an L2 and every XCD has
-  // the same mix of work.
-  const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
-  if (idx < p.ch_per_xcd) {
-    const uint32_t unit = xcd * p.ch_per_xcd + idx;
-    if (unit < p.n_units_ch) {
-      if (RESIDENT)
-        pack_channel_body_resident<DT>(p, unit, red_lo, red_hi, stash);
-      else
-        pack_channel_body<DT>(p, unit, red_lo, red_hi, stash);
-    }
-  } else if (idx < p.ch_per_xcd + p.tok_per_xcd) {
-    const uint32_t unit = xcd * p.tok_per_xcd + (idx - p.ch_per_xcd);
-    if (unit < p.n_units_tok) pack_token_body<DT, UNIFORM, RESIDENT ? KVC_PACK_U_RESIDENT : KVC_PACK_U>(p, unit);
+  // Workgroups go to the 8 XCDs round-robin.  Units come in ranges: the per-channel ones, the per-token ones (each first
+  // of the whole chunks, then of a short last chunk, so that every XCD has the same mix of work: 2048 + 128 tokens of 60
+  // layers 272 -> 187 us) and the zero-fill ones.  Each XCD gets one contiguous eighth of the strips and of the
+  // zero-fill units, so neighbouring strips, which may share lines, share an L2.  Token blocks share nothing and are
+  // dealt out in turn (32K tokens of 60 layers, both kinds per token: 2.12 ms in eighths, 2.04 ms in turn; strips in turn
+  // cost 4 %).
+  const uint32_t xcd = blockIdx.x & 7u;
+  uint32_t idx = blockIdx.x >> 3;
+  const uint32_t n_ch = p.ch[0].per_xcd + p.ch[1].per_xcd, n_tok = p.tok[0].per_xcd + p.tok[1].per_xcd;
+  if (idx < n_ch) {
+    const bool last = idx >= p.ch[0].per_xcd;
+    if (last) idx -= p.ch[0].per_xcd;
+    const PackRange r = last ? p.ch[1] : p.ch[0];
+    const uint32_t unit = xcd * r.per_xcd + idx, c0 = last ? (uint32_t)p.n_whole : 0u;
+    if (unit >= r.units) return;
+    if (BODY == kPackLight || (BODY != kPackStream && last && p.light_last))
+      pack_channel_body_resident<DT, kLightLoads, 0, true>(p, unit, c0, red_lo, red_hi, stash);
+    else if (BODY == kPackMedium)
+      pack_channel_body_resident<DT, kMediumRegs, kMediumLds, false>(p, unit, c0, red_lo, red_hi, stash);
+    else if (BODY == kPackResident)
+      pack_channel_body_resident<DT, kResidentRegs, kResidentLds, false>(p, unit, c0, red_lo, red_hi, stash);
+    else
+      pack_channel_body<DT>(p, unit, c0, red_lo, red_hi, stash);
+  } else if (idx < n_ch + n_tok) {
+    idx -= n_ch;
+    const bool last = idx >= p.tok[0].per_xcd;
+    if (last) idx -= p.tok[0].per_xcd;
+    const PackRange r = last ? p.tok[1] : p.tok[0];
+    // round-robin, in runs of units that hold about as many bytes as one of 1024 channels
+    const uint32_t in_run = idx & (p.tok_run - 1u);
+    const uint32_t unit = ((idx - in_run) * 8u + xcd * p.tok_run) + in_run;
+    if (unit < r.units)
+      pack_token_body<DT, UNIFORM, BODY == kPackResident ? kTokenLoadsResident : kTokenLoads>(
+          p, unit, last ? (uint32_t)p.n_whole : 0u, (uint32_t)(last ? p.tbl : p.tbc));
   } else {
-    const uint32_t unit = xcd * p.zero_per_xcd + (idx - p.ch_per_xcd - p.tok_per_xcd);
-    if (unit < p.n_units_zero) pack_zero_body(p, unit);
+    const uint32_t unit = xcd * p.zero.per_xcd + (idx - n_ch - n_tok);
+    if (unit < p.zero.units) pack_zero_body(p, unit);
   }
 }
 
 // The per-channel bodies ask for more dynamic LDS than the 64 KB a kernel gets unasked; the limit of a kernel
 // is raised once per device (devices beyond the 64 the mask covers: on every launch).
-template <int DT, bool UNIFORM, bool RESIDENT>
-hipError_t launch_variant(dim3 grid, dim3 block, size_t lds, hipStream_t stream, const PackParams& p) {
+template <int DT, bool UNIFORM, int BODY>
+hipError_t launch_variant(dim3 grid, dim3 block, hipStream_t stream, const PackParams& p) {
   static std::atomic<uint64_t> raised{0};
-  const auto fn = pack_kernel<DT, UNIFORM, RESIDENT>;
-  int dev = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e != hipSuccess) return e;
-  const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
-  if ((raised.load(std::memory_order_acquire) & bit) == 0) {
-    constexpr size_t most = RESIDENT ? (size_t)kResidentLds * kResidentThreads * sizeof(u32x4)
-                                     : (size_t)kStreamStashLoads * 1024 * sizeof(u32x4);
-    e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+  const auto fn = pack_kernel<DT, UNIFORM, BODY>;
+  constexpr int slots = BODY == kPackResident ? kResidentLds : BODY == kPackMedium ? kMediumLds : BODY == kPackStream ? kStreamStashLoads : 0;
+  const size_t lds = (size_t)slots * block.x * sizeof(u32x4);
+  if (slots != 0) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
-    raised.fetch_or(bit, std::memory_order_release);
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
+    if ((raised.load(std::memory_order_acquire) & bit) == 0) {
+      constexpr size_t most = (size_t)slots * (BODY == kPackStream ? 1024 : kResidentThreads) * sizeof(u32x4);
+      e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
+      if (e != hipSuccess) return e;
+      raised.fetch_or(bit, std::memory_order_release);
+    }
   }
   hipLaunchKernelGGL(fn, grid, block, lds, stream, p);
   return hipGetLastError();
@@ -789,29 +856,49 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
   // per-token part: a whole number of tokens per pass, about 256 threads
   const int glanes = g.D / 8;
   if (p.n_kinds_tok > 0 && (glanes > 64 || (glanes & (glanes - 1)) != 0)) return KVC_ERR_UNSUPPORTED;
-  // Per-channel kinds whose chunk fits the resident strip run with 512 threads (the strip then spans 32 token
-  // rows x 64 loads = 2048 tokens of 128 channels: 256-byte input rows, 128-byte code rows).
+  // Which form the launch takes.  The forms that keep a strip on chip work with 512 threads; on strips of 128 channels
+  // (256-byte input rows, 128-byte code rows) a pass is 32 token rows, so a strip of kResidentLoads holds 2048 tokens.
+  // They form 32-bit byte offsets for all rows of a strip, whatever the chunk length (rows past the last token are
+  // clamped afterwards), and inside the chunk's frame section; and a per-token kind in the same launch needs a thread
+  // for every atom of a token.
+  const int64_t most_tokens = p.n_tokens < g.T ? p.n_tokens : g.T;  // of a chunk of this call
+  const auto strips = [&](int atoms) { return (int64_t)p.n_chunks * p.n_kinds_ch * g.L * ((g.apt + atoms - 1) / atoms); };
+  const auto rows_of = [&](int loads, int atoms) { return (int64_t)loads * (kResidentThreads / atoms); };
+  const auto fits = [&](int64_t tokens) { return tokens * p.ts * 2 < (1ll << 32) && g.frame_bytes < (1ll << 32); };
+  const bool wide = p.n_kinds_tok > 0 && g.apt > kResidentThreads;
+  p.body = kPackStream;
   p.strip_atoms = kResidentAtoms;
-  // The resident body forms 32-bit byte offsets for all kResidentLoads x rows token rows of a strip, whatever
-  // the chunk length (rows past the last token are clamped afterwards), and inside the chunk's frame section.
-  const int64_t resident_rows = (int64_t)kResidentLoads * (kResidentThreads / p.strip_atoms);
-  // A per-token kind in the same launch needs a thread for every atom of a token.
-  p.resident = p.n_kinds_ch > 0 && g.T <= resident_rows && resident_rows * p.ts * 2 < (1ll << 32) &&
-                       g.frame_bytes < (1ll << 32) && (p.n_kinds_tok == 0 || g.apt <= kResidentThreads)
-                   ? 1
-                   : 0;
+  if (p.n_kinds_ch == 0) {
+    if (!wide && (int64_t)g.L * p.n_kinds_tok * p.n_tokens < kFewTokenRows) p.body = kPackLight;
+  } else if (!wide) {
+    const int64_t most = rows_of(kResidentLoads, kResidentAtoms);
+    if (g.T <= most && fits(most)) p.body = most_tokens <= rows_of(kMediumLoads, kResidentAtoms) ? kPackMedium : kPackResident;
+    // The light form for few tokens, and for few strips: those are made narrower until there is one for every other CU.
+    int atoms = kResidentAtoms;
+    while (atoms > kFewestAtoms && (rows_of(kLightLoads, atoms) < most_tokens || strips(atoms) < kFewStrips)) atoms /= 2;
+    if (rows_of(kLightLoads, atoms) >= most_tokens && fits(rows_of(kLightLoads, atoms)) &&
+        (atoms == kResidentAtoms || strips(kResidentAtoms) <= kFewStrips)) {
+      p.body = kPackLight;
+      p.strip_atoms = atoms;
+    }
+  }
+  p.resident = p.n_kinds_ch > 0 && p.body != kPackStream ? 1 : 0;
   // Chunks too long for that read the part of each strip that does not fit on chip twice.  Few, large
   // workgroups (one of 1024 threads per CU) give each strip the whole CU's registers and LDS to wait in, and
   // keep the strips in flight few, so that part of the second read still finds its strip in the last-level
   // cache: 10 240-token chunks pack in 1.37 ms this way against 1.83 ms with 256-thread workgroups.
-#ifndef KVC_PACK_STREAM_THREADS
-#define KVC_PACK_STREAM_THREADS 1024
-#endif
-  if (!p.resident) p.strip_atoms = KVC_PACK_STREAM_ATOMS;
-  const int want = p.resident ? kResidentThreads : KVC_PACK_STREAM_THREADS;
+  // Few strips are made as narrow as it takes for a whole chunk to wait on chip (two layers of 10 240 tokens: 77 -> 58 us;
+  // many strips lose by it, 1.35 -> 2.55 ms with half the width, since each input and code line is then several strips').
+  if (p.body == kPackStream) {
+    const auto on_chip = [&](int atoms) { return (int64_t)(kStreamTailLoads + kStreamStashLoads) * (kStreamThreads / atoms); };
+    int atoms = kStreamAtoms;
+    while (atoms > kFewestAtoms && on_chip(atoms) < most_tokens) atoms /= 2;
+    p.strip_atoms = strips(kStreamAtoms) < kFewStrips && on_chip(atoms) >= most_tokens ? atoms : kStreamAtoms;
+  }
+  const int want = p.body == kPackStream ? kStreamThreads : kResidentThreads;
   p.tpp = g.apt >= want ? 1 : want / g.apt;
   p.dapt = make_fastdiv((uint32_t)g.apt);
-  const int threads = p.resident ? kResidentThreads : (g.apt * p.tpp + 63) / 64 * 64;
+  const int threads = p.body != kPackStream ? kResidentThreads : (g.apt * p.tpp + 63) / 64 * 64;
   // Token positions the bodies walk: those of the tile rows a token of the chunk can fall into.  What lies
   // below is zero and belongs to the zero-fill units, as do the planes of layers beyond L.
   const auto positions = [&](int64_t n) { return (int32_t)(((n + g.F - 1) / g.F + g.TX - 1) / g.TX * g.TX * g.F); };
@@ -819,32 +906,47 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
   p.positions_full = positions(g.T);
   p.positions_last = positions(n_last);
   p.tb = 128;  // token positions per workgroup of the per-token kinds (32: 1.27 ms, 64: 1.18, 128: 1.157, 256: 1.166, 512: 1.20)
-  p.tbc = (p.positions_full + p.tb - 1) / p.tb;
+  const auto token_blocks = [&](int64_t n) { return (int32_t)((n + p.tb - 1) / p.tb); };
+  p.light_last = n_last <= rows_of(kLightLoads, p.strip_atoms) ? 1 : 0;
+  p.n_whole = n_last == g.T ? p.n_chunks : p.n_chunks - 1;
+  const int64_t short_chunks = p.n_chunks - p.n_whole;  // 0 or 1
+  const auto count_blocks = [&] { return (int64_t)p.n_whole * token_blocks(p.positions_full) + short_chunks * token_blocks(p.positions_last); };
+  while (p.body == kPackLight && p.tb > 16 && count_blocks() * g.L * p.n_kinds_tok < kFewTokenUnits) p.tb /= 2;
+  p.tbc = token_blocks(p.positions_full);
+  p.tbl = token_blocks(p.positions_last);
+  // the blocks of the last chunk write the pairs of its tokens before this one, zero units the rest
+  const int64_t pair_end = (int64_t)p.tbl * p.tb;
+  p.zero_pair_tokens = p.n_kinds_tok > 0 && pair_end < g.T ? (int32_t)(g.T - pair_end) : 0;
   // per-channel part: strips of 8*strip_atoms channels
   p.n_strips = (g.apt + p.strip_atoms - 1) / p.strip_atoms;
   p.rows = threads / p.strip_atoms;
   p.pass_step = p.rows % (g.F * g.TX) == 0 ? (uint32_t)(p.rows / (g.F * g.TX)) * (uint32_t)g.th * (uint32_t)g.W : 0u;
-  const int64_t per_kind = (int64_t)p.n_chunks * g.L;
-  const int64_t units_ch = per_kind * p.n_kinds_ch * p.n_strips;
-  const int64_t units_tok = per_kind * p.n_kinds_tok * p.tbc;
   const auto pieces = [](int64_t bytes) { return (bytes + kZeroPiece - 1) / kZeroPiece; };
   const int64_t tile_row = (int64_t)g.th * g.W;
   p.pieces_plane = (uint32_t)pieces(g.plane);
   p.pieces_tail_full = (uint32_t)pieces(g.plane - p.positions_full / (g.TX * g.F) * tile_row);
   p.pieces_tail_last = (uint32_t)pieces(g.plane - p.positions_last / (g.TX * g.F) * tile_row);
+  p.pieces_pairs = (uint32_t)pieces((int64_t)p.zero_pair_tokens * g.H * 8);
+  const int64_t zero_pairs = (int64_t)p.n_kinds_tok * g.L * p.pieces_pairs;
   const int64_t zero_pad = (int64_t)p.n_chunks * 2 * (3 * g.LG - g.L) * g.F * p.pieces_plane;
   const int64_t zero_full = (int64_t)(p.n_chunks - 1) * 2 * g.L * g.F * p.pieces_tail_full;
   const int64_t zero_last = (int64_t)2 * g.L * g.F * p.pieces_tail_last;
-  if (units_ch + units_tok + zero_pad + zero_full + zero_last > 0x7fffffff / 8) return KVC_ERR_UNSUPPORTED;
-  p.n_units_ch = (uint32_t)units_ch;
-  p.n_units_tok = (uint32_t)units_tok;
+  const int64_t rows_ch = (int64_t)g.L * p.n_kinds_ch, rows_tok = (int64_t)g.L * p.n_kinds_tok;
+  const int64_t units[5] = {p.n_whole * rows_ch * p.n_strips, short_chunks * rows_ch * p.n_strips, p.n_whole * rows_tok * p.tbc,
+                            short_chunks * rows_tok * p.tbl, zero_pairs + zero_pad + zero_full + zero_last};
+  PackRange* const ranges[5] = {&p.ch[0], &p.ch[1], &p.tok[0], &p.tok[1], &p.zero};
+  int64_t wgs_per_xcd = 0;
+  p.tok_run = 1;
+  while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
+  const int64_t run[5] = {1, 1, p.tok_run, p.tok_run, 1};
+  const auto share = [&](int i) { return (units[i] + 8 * run[i] - 1) / (8 * run[i]) * run[i]; };  // of one XCD
+  for (int i = 0; i < 5; ++i) wgs_per_xcd += share(i);
+  if (wgs_per_xcd > 0x7fffffff / 64) return KVC_ERR_UNSUPPORTED;
+  for (int i = 0; i < 5; ++i) *ranges[i] = PackRange{(uint32_t)units[i], (uint32_t)share(i)};
+  p.wgs_per_xcd = (uint32_t)wgs_per_xcd;
   p.n_zero_pad = (uint32_t)zero_pad;
   p.n_zero_full = (uint32_t)zero_full;
-  p.n_units_zero = (uint32_t)(zero_pad + zero_full + zero_last);
-  p.ch_per_xcd = (p.n_units_ch + 7u) / 8u;
-  p.tok_per_xcd = (p.n_units_tok + 7u) / 8u;
-  p.zero_per_xcd = (p.n_units_zero + 7u) / 8u;
-  p.units_per_xcd = p.ch_per_xcd + p.tok_per_xcd + p.zero_per_xcd;
+  p.n_zero_pairs = (uint32_t)zero_pairs;
   *threads_out = threads;
   return KVC_OK;
 }
@@ -855,23 +957,18 @@ kvc_status launch_pack(PackParams p, hipStream_t stream) {
   const kvc_status st = plan_pack(p, &threads);
   if (st != KVC_OK) return st;
   const Geo& g = p.g;
-  const dim3 grid(p.units_per_xcd * 8u), block((unsigned)threads);
+  const dim3 grid(p.wgs_per_xcd * 8u), block((unsigned)threads);
   const bool uniform = g.apt % 64 == 0;
-  const size_t lds = (size_t)(p.resident ? kResidentLds : kStreamStashLoads) * threads * sizeof(u32x4);
   hipError_t err = hipSuccess;
-#define KVC_LAUNCH_PACK(DT_, UNI_, RES_) err = launch_variant<DT_, UNI_, RES_>(grid, block, lds, stream, p)
+#define KVC_LAUNCH_PACK(DT_, UNI_)                                                                       \
+  err = p.body == kPackResident ? launch_variant<DT_, UNI_, kPackResident>(grid, block, stream, p)       \
+        : p.body == kPackMedium ? launch_variant<DT_, UNI_, kPackMedium>(grid, block, stream, p)         \
+        : p.body == kPackLight  ? launch_variant<DT_, UNI_, kPackLight>(grid, block, stream, p)          \
+                                : launch_variant<DT_, UNI_, kPackStream>(grid, block, stream, p)
   if (g.dtype == KVC_F16) {
-    if (uniform) {
-      if (p.resident) KVC_LAUNCH_PACK(KVC_F16, true, true); else KVC_LAUNCH_PACK(KVC_F16, true, false);
-    } else {
-      if (p.resident) KVC_LAUNCH_PACK(KVC_F16, false, true); else KVC_LAUNCH_PACK(KVC_F16, false, false);
-    }
+    if (uniform) KVC_LAUNCH_PACK(KVC_F16, true); else KVC_LAUNCH_PACK(KVC_F16, false);
   } else {
-    if (uniform) {
-      if (p.resident) KVC_LAUNCH_PACK(KVC_BF16, true, true); else KVC_LAUNCH_PACK(KVC_BF16, true, false);
-    } else {
-      if (p.resident) KVC_LAUNCH_PACK(KVC_BF16, false, true); else KVC_LAUNCH_PACK(KVC_BF16, false, false);
-    }
+    if (uniform) KVC_LAUNCH_PACK(KVC_BF16, true); else KVC_LAUNCH_PACK(KVC_BF16, false);
   }
 #undef KVC_LAUNCH_PACK
   return err == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;

@@ -351,13 +351,11 @@ __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint3
 
 // Workgroups are handed to the 8 XCDs round-robin.
 //
-// Chunk call: a "row" is one (kind, layer), i.e. one region [num_blocks][block][H][D] of a paged
-// cache.  The whole chip works on one row at a time; the row's token blocks (over all chunks of the
-// call, those that hold tokens) are cut into 8 contiguous parts, one per XCD, so the workgroups that
-// share a layer's per-channel pairs and a run of block-table entries also share an L2, and the writes
-// in flight stay inside one region of the cache.  Rows of fewer than 64 blocks are taken several at a
-// time (a band), or most XCDs would idle: 200 tokens of a 2048-token chunk, 7 blocks a row, all fell
-// to one XCD when the blocks of the whole chunk were cut (32 layers x 4096 channels: 144 -> 35 us).
+// Chunk call: a row of the BandMap is one (kind, layer), i.e. one region [num_blocks][block][H][D] of a
+// paged cache, its units the token blocks that hold tokens.  The workgroups that share a layer's
+// per-channel pairs and a run of block-table entries also share an L2, and the writes in flight stay
+// inside one region of the cache.  (200 tokens of a 2048-token chunk, 7 blocks a row, all fell to one XCD
+// when the blocks of the whole chunk were cut into eighths: 32 layers x 4096 channels 144 us, now 35 us.)
 //
 // Frame call: units are (frame of the run, plane, block of token slots), each XCD one contiguous range.
 constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2;
@@ -393,13 +391,8 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
     if (l >= (uint32_t)p.g.L) return;
     fsec = run + ((int64_t)frel * 3 + pl) * p.g.plane;
   } else {
-    uint32_t band, within, row, u;
-    fd_divmod(p.dbpx, idx, band, within);
-    const uint32_t w = xcd * p.dbpx.d + within;  // unit of the band
-    if (w >= p.band_units) return;
-    fd_divmod(p.drow, w, row, u);
-    row += band * p.band_rows;
-    if (row >= 2u * (uint32_t)p.g.L) return;  // the last band may hold fewer rows
+    uint32_t row, u;
+    if (!band_unit(p.bands, xcd, idx, row, u)) return;
     fd_divmod(p.dL, row, kind, l);
     fd_divmod(p.dtbc, u, c, tbi);
     const uint32_t lg = l / 3u, pl = l - lg * 3u;
@@ -503,15 +496,8 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     grid = dim3(p.units_per_xcd * 8u);
   } else {
     const int64_t row_units = (int64_t)(p.n_chunks - 1) * p.tbc + tbl;
-    const int64_t band_rows = row_units >= 64 ? 1 : ceil_div(64, row_units) < 2 * g.L ? ceil_div(64, row_units) : 2 * g.L;
-    const int64_t per_xcd = ceil_div(row_units * band_rows, 8);
-    const int64_t grid_wgs = per_xcd * 8 * ceil_div(2 * g.L, band_rows);
-    if (grid_wgs > 0x7fffffff) return KVC_ERR_UNSUPPORTED;
-    p.band_rows = (uint32_t)band_rows;
-    p.band_units = (uint32_t)(row_units * band_rows);
-    p.drow = make_fastdiv((uint32_t)row_units);
-    p.dbpx = make_fastdiv((uint32_t)per_xcd);
-    grid = dim3((uint32_t)grid_wgs);
+    if (!make_band_map(&p.bands, 2 * (int64_t)g.L, row_units, 0x7fffffff)) return KVC_ERR_UNSUPPORTED;
+    grid = dim3(p.bands.wgs_per_xcd * 8u);
   }
   p.dtbc = make_fastdiv((uint32_t)p.tbc);
   if (g.dtype == KVC_F16) {

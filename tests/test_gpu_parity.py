@@ -938,3 +938,38 @@ def test_restore_launch_shapes(shape):
     assert int(cache.err.item()) == 0
     for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
         hz.assert_same_bytes(f"frames, layer {l}", got, w)
+
+
+PACK_FORMS = [
+    # L, H, D, T, th, tw, TX, TY, n_tokens, modes: the forms a pack launch takes by tokens and strips
+    (17, 8, 128, 1100, 8, 128, 4, 70, 1100 * 2 + 900, (0, 0)),  # resident: more than 1024 tokens, more than 128 strips, short last chunk
+    (17, 8, 128, 1100, 8, 128, 5, 56, 1100 + 45, (0, 1)),       # ... whose last chunk takes the light form; rows of tiles of 20
+    (17, 8, 128, 1024, 8, 128, 8, 32, 1024 + 513, (0, 1)),      # medium: at most 1024 tokens a chunk
+    (17, 8, 128, 600, 8, 128, 3, 25, 600 * 2 + 33, (1, 0)),     # ... not a whole number of groups of loads
+    (17, 8, 128, 512, 8, 128, 8, 16, 512 + 511, (0, 0)),        # light, 16 loads
+    (17, 8, 128, 3000, 8, 128, 8, 64, 400, (0, 1)),             # light, few tokens of a long chunk: tile rows and pairs to clear
+    (2, 8, 128, 2048, 8, 128, 8, 64, 2048, (0, 1)),             # few strips: 16 channels wide
+    (5, 8, 128, 1024, 8, 128, 8, 64, 1000, (0, 0)),             # ... 32 channels wide
+    (9, 3, 128, 900, 3, 128, 7, 20, 901, (0, 1)),               # ... ragged: 48 atoms
+    (2, 8, 128, 2100, 8, 128, 8, 80, 2100 + 7, (0, 1)),         # two-pass form, narrow strips that wait on chip whole
+    (1, 8, 128, 12400, 8, 128, 15, 135, 12400, (0, 1)),         # ... and those that do not
+    (32, 1, 64, 2048, 1, 64, 16, 64, 4200, (1, 1)),             # per token only, many rows; units of few bytes in runs
+    (3, 1, 64, 2048, 1, 64, 16, 64, 70, (1, 1)),                # ... few rows; pairs of 1900 tokens to clear
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", PACK_FORMS, ids=[f"p{i}" for i in range(len(PACK_FORMS))])
+def test_pack_launch_forms(shape, dtype):
+    """Every form of the pack launch at its edges: codes, zero fill and pairs to the bit, in a poisoned buffer."""
+    L, H, D, T, th, tw, TX, TY, n, modes = shape
+    glo, olo = hz.layouts(L, H, D, dtype, T, th, tw, TX, TY, *modes)
+    kv = kv_synth.make_kv(L, H, D, n, TD[dtype], seed=8000 + n, device="cuda")
+    kv[0, :, 0, 0, :4] = 0.0
+    kv[0, :, n // 2:, 0, 4] = -0.0                      # a channel whose minimum or maximum may be a negative zero
+    kv[0, :, :, 0, 5] = -kv[0, :, :, 0, 5].abs()
+    hz.say(f"[case] pack form L={L} H={H} T={T} n={n} modes={modes} {dtype}")
+    want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    frames, meta = hz.gpu_pack(glo, kv, n)
+    hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
+    hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
