@@ -211,7 +211,8 @@ kvc_status kvc_restore_paged(const kvc_layout* layout, const uint8_t* frames, co
 /* Pipelined fetcher (Sec. 3.3.2: transmission overlapped with decoding, the
  * restoration riding along; the compressed data waits in a host-memory buffer).
  * Chunk i (holding sequence positions i*T ...) is copied from its pinned HOST
- * blob to staging slot i % n_staging on `copy_stream`, then restored into the
+ * blob to staging slot i % n_staging on `copy_stream` (of a chunk of few tokens
+ * only the parts that a restore of those tokens reads), then restored into the
  * paged cache on `compute_stream`; a slot is reused only after the restore that
  * read it has finished.  Every chunk but the last must hold T tokens.
  *   chunks            HOST array of n_chunks descriptors (blobs PINNED HOST)
@@ -295,7 +296,8 @@ size_t kvc_meta_staging_size(const kvc_layout* layout, int32_t order);
  * staging buffer until it is full (it holds floor(frame_staging_bytes /
  * kvc_frame_size) frames, at most a chunk's), announced with one event and
  * restored with one kvc_restore_paged_frames launch per run; the pairs a run
- * needs are copied before it.  In KVC_ORDER_LAYER a buffer that holds at least
+ * needs are copied before it (or fetched on compute_stream by a kernel, where
+ * the blobs are mapped into the device).  In KVC_ORDER_LAYER a buffer that holds at least
  * 2*F frames receives the K and the V frames of a (chunk, layer group) in one
  * two-row strided copy.
  *   d_frame_staging  HOST array of n_frame_staging (2..64) DEVICE buffers of

@@ -58,6 +58,16 @@ struct RestoreParams {
 // Enqueues the fused unpack + dequantize + placement kernel.
 kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream);
 
+// A run of {scale, mn} pairs in pinned host memory that is mapped into the device, and where they go.
+struct PairSpan {
+  const void* src;
+  void* dst;
+  uint32_t pairs;  // at least 1
+};
+
+// Enqueues the copy of two spans of pairs (8-byte aligned).
+kvc_status launch_copy_pairs(const PairSpan& a, const PairSpan& b, hipStream_t stream);
+
 constexpr int kPackResident = 0, kPackStream = 1, kPackLight = 2, kPackMedium = 3;
 
 // A range of work units and the share of one XCD.

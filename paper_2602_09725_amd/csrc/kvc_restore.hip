@@ -428,7 +428,32 @@ void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 blo
 #undef KVC_LAUNCH_RESTORE
 }
 
+// Copies two spans of {scale, mn} pairs out of pinned host memory, a workgroup 8 KB of one of them.
+constexpr uint32_t kCopyThreads = 256, kCopyPerThread = 4;
+__global__ void __launch_bounds__(kCopyThreads) copy_pairs_kernel(PairSpan a, PairSpan b, uint32_t wgs_a) {
+  const bool second = blockIdx.x >= wgs_a;
+  const PairSpan s = second ? b : a;
+  const uint32_t i0 = (blockIdx.x - (second ? wgs_a : 0u)) * (kCopyThreads * kCopyPerThread) + threadIdx.x;
+  u32x2 v[kCopyPerThread];
+#pragma unroll
+  for (uint32_t k = 0; k < kCopyPerThread; ++k) {
+    const uint32_t i = i0 + k * kCopyThreads;
+    v[k] = stream_load<u32x2>(static_cast<const u32x2*>(s.src) + (i < s.pairs ? i : s.pairs - 1u));
+  }
+#pragma unroll
+  for (uint32_t k = 0; k < kCopyPerThread; ++k) {
+    const uint32_t i = i0 + k * kCopyThreads;
+    if (i < s.pairs) static_cast<u32x2*>(s.dst)[i] = v[k];
+  }
+}
+
 }  // namespace
+
+kvc_status launch_copy_pairs(const PairSpan& a, const PairSpan& b, hipStream_t stream) {
+  const auto wgs = [](uint32_t pairs) { return (pairs + kCopyThreads * kCopyPerThread - 1) / (kCopyThreads * kCopyPerThread); };
+  hipLaunchKernelGGL(copy_pairs_kernel, dim3(wgs(a.pairs) + wgs(b.pairs)), dim3(kCopyThreads), 0, stream, a, b, wgs(a.pairs));
+  return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
+}
 
 kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   const Geo& g = p.g;

@@ -703,6 +703,69 @@ def test_frame_ranges_and_small_frame_pipeline(shape, dtype):
                 assert bool((m[msz:] == 0xEE).all())
 
 
+@pytest.mark.parametrize("modes", [(0, 1), (1, 1)])
+@pytest.mark.parametrize("tail", [1, 33, 700])
+def test_staged_pipelines_copy_what_a_short_chunk_holds(tail, modes):
+    """A last chunk of few tokens: the staged pipelines copy the used rows of tiles and the pairs of its tokens only.
+    Staging is poisoned, so anything read but not copied would show; eager and replayed from a graph."""
+    L, H, D, T, bs = 4, 8, 128, 2048, 16
+    C, n = H * D, T + tail
+    glo, olo = hz.layouts(L, H, D, "f16", T, 8, 128, 8, 64, *modes)
+    kvc = hz.kvc
+    kv = kv_synth.make_kv(L, H, D, n, torch.float16, seed=600 + tail, device="cuda")
+    want_f, want_m = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    nb = (n + bs - 1) // bs
+    tab = kv_synth.make_block_table(nb, nb, 4)
+    want, _ = hz.oracle_paged(olo, want_f, want_m, 0, n, L, nb, bs, C, tab.numpy())
+    fb, mb, F = kvc.chunk_sizes(glo)
+    fs, moff = kvc.frame_size(glo), kvc.blob_meta_offset(glo)
+    blob = torch.zeros((2, moff + mb), dtype=torch.uint8, pin_memory=True)
+    for c in range(2):
+        blob[c, :fb].copy_(torch.from_numpy(want_f[c * fb:(c + 1) * fb]))
+        blob[c, moff:].copy_(torch.from_numpy(want_m.view(np.uint8)[c * mb:(c + 1) * mb]))
+    chunks = [(blob[0].data_ptr(), moff + mb, T), (blob[1].data_ptr(), moff + mb, tail)]
+    dtab, s_copy, s_comp = tab.cuda(), torch.cuda.Stream(), torch.cuda.Stream()
+
+    def poisoned(count, size):
+        return [torch.full((size,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(count)]
+
+    for order, per_slot, n_fs, n_ms in ((None, 0, 2, 0), (0, 3, 3, 2), (0, 2 * F, 2, 2), (1, 3, 3, 2), (1, 2 * F, 2, 2), (1, 7 * F, 2, 3)):
+        cache = hz.PagedCache(L, nb, bs, C)
+        if order is None:
+            slots = poisoned(n_fs, moff + mb)
+            args = (glo, chunks, [t.data_ptr() for t in slots], moff + mb)
+            call = kvc.kvc_fetch_pipeline
+            more = {}
+        else:
+            msz = kvc.meta_staging_size(glo, order)
+            slots, metas = poisoned(n_fs, per_slot * fs), poisoned(n_ms, msz)
+            args = (glo, chunks, [t.data_ptr() for t in slots], per_slot * fs, [t.data_ptr() for t in metas], msz)
+            call = kvc.kvc_fetch_pipeline_frames
+            more = {"order": order}
+        args += (cache.ptrs.data_ptr(), nb, bs, dtab.data_ptr(), nb, cache.err.data_ptr(), s_copy.cuda_stream, s_comp.cuda_stream)
+        hz.say(f"[case] short chunk of {tail}: order {order}, {per_slot} frames a slot, modes {modes}")
+        torch.cuda.synchronize()
+        call(*args, timed=True, **more)
+        torch.cuda.synchronize()
+        for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
+            hz.assert_same_bytes(f"layer {l}", got, w)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s_copy):
+            call(*args, timed=False, **more)
+            joined = torch.cuda.Event()
+            joined.record(s_comp)
+            s_copy.wait_event(joined)
+        for rep in range(2):
+            for t in cache.layers + slots:
+                t.fill_(0x6E)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            used = cache.layers[0].view(2, nb * bs, C)[:, dtab.long().repeat_interleave(bs)[:n] * bs + torch.arange(n, device="cuda") % bs]
+            ref = torch.from_numpy(want[0].view(np.int16)).cuda().view(2, nb * bs, C)[:, dtab.long().repeat_interleave(bs)[:n] * bs + torch.arange(n, device="cuda") % bs]
+            assert torch.equal(used, ref), f"graph replay {rep}"
+
+
 def test_restore_reads_frames_from_mapped_pinned_host_memory():
     """The frame pointer may be pinned host memory that is mapped into the device (no staging copy at all)."""
     L, H, D, T, n, bs = 3, 8, 128, 96, 96 + 40, 16
