@@ -428,6 +428,13 @@ kvc_status kvc_residual_histograms(const kvc_layout* layout, const uint8_t* fram
  *   hist  HOST in: the array kvc_residual_histograms wrote, copied to the host */
 double kvc_proxy_cost_bits(const kvc_layout* layout, const uint64_t* hist, int64_t n_chunks);
 
+/* The same cost on the device, per plane sequence, for searches that would wait for
+ * every candidate's histograms otherwise: the costs add up to what
+ * kvc_proxy_cost_bits returns (double; the sums are taken in another order).
+ *   d_hist  DEVICE in : as kvc_residual_histograms wrote it, 8-byte aligned
+ *   d_cost  DEVICE out: double [n_chunks][2][L], every entry written */
+kvc_status kvc_proxy_costs(const kvc_layout* layout, const uint64_t* d_hist, int64_t n_chunks, double* d_cost, void* stream);
+
 /* The tilings left by rules i-iii of Sec. 3.2.2 for H heads of D elements:
  * head_num = h1*h2 and head_dim = d1*d2 with all four powers of two, tile
  * (h1*d1, h2*d2), tile_seg = d2 >= 8 (an 8-element atom of the kernels stays in

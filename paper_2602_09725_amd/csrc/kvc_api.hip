@@ -328,6 +328,18 @@ kvc_status kvc_residual_histograms(const kvc_layout* layout, const uint8_t* fram
   return launch_residual_histograms(p, as_stream(stream));
 }
 
+kvc_status kvc_proxy_costs(const kvc_layout* layout, const uint64_t* d_hist, int64_t n_chunks, double* d_cost, void* stream) {
+  ScoreParams p{};
+  const kvc_status st = make_geo(layout, &p.g);
+  if (st != KVC_OK) return st;
+  if (n_chunks < 0 || n_chunks > (1 << 24)) return KVC_ERR_INVALID_ARG;
+  if (n_chunks == 0) return KVC_OK;
+  if (!d_hist || !d_cost || !aligned(d_hist, 8) || !aligned(d_cost, 8)) return KVC_ERR_INVALID_ARG;
+  p.n_chunks = (int32_t)n_chunks;
+  p.hist = const_cast<uint64_t*>(d_hist);
+  return launch_proxy_costs(p, d_cost, as_stream(stream));
+}
+
 double kvc_proxy_cost_bits(const kvc_layout* layout, const uint64_t* hist, int64_t n_chunks) {
   Geo g;
   if (make_geo(layout, &g) != KVC_OK || !hist || n_chunks < 0) return -1.0;

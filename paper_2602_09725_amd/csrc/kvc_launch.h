@@ -134,6 +134,9 @@ struct ScoreParams {
 // Enqueues the residual-histogram kernel of the tiling proxy.
 kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream);
 
+// Enqueues the cost of every stream from its histograms: hist as above, cost [n_chunks][2][L].
+kvc_status launch_proxy_costs(const ScoreParams& p, double* cost, hipStream_t stream);
+
 // Enqueues the reference expand copy (measurement aid): out_bytes / 2 bytes of src -> out_bytes of dst, piece i
 // of 2^log2_piece output bytes going to position piece_map[i] (nullptr: in place); wg_bytes is 4096 or 32768;
 // shape: KVC_PROBE_* bits (4 KB workgroups, a multiple of 8 of them).

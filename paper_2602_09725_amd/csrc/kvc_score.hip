@@ -176,7 +176,52 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
   }
 }
 
+// One workgroup per stream, one thread per bin: entropies of the five histograms, then the stream's cost in bits.
+// (On the host the logarithms of a candidate of 12 streams take about 100 us, longer than packing and counting it.)
+__global__ void __launch_bounds__(256) proxy_cost_kernel(const uint64_t* hist, double* cost, double pixels, double later) {
+  __shared__ double part[2][KVC_N_RESIDUALS][4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint64_t* h = hist + (size_t)blockIdx.x * (KVC_N_RESIDUALS * 256) + tid;
+  double n[KVC_N_RESIDUALS];
+#pragma unroll
+  for (int k = 0; k < KVC_N_RESIDUALS; ++k) n[k] = (double)h[k * 256];
+  // sum over the 256 threads; the barrier after the partial sums is also the one before the next use of the other half
+  const auto total = [&](double v, int half, int k) {
+    for (int m = 32; m; m >>= 1) v += __shfl_xor(v, m);
+    if (lane == 0) part[half][k][wave] = v;
+  };
+#pragma unroll
+  for (int k = 0; k < KVC_N_RESIDUALS; ++k) total(n[k], 0, k);
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < KVC_N_RESIDUALS; ++k) {
+    const double all = part[0][k][0] + part[0][k][1] + part[0][k][2] + part[0][k][3];
+    const double q = n[k] > 0.0 ? n[k] / all : 0.0;
+    total(q > 0.0 ? -q * log2(q) : 0.0, 1, k);
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  double e[KVC_N_RESIDUALS];
+#pragma unroll
+  for (int k = 0; k < KVC_N_RESIDUALS; ++k) e[k] = part[1][k][0] + part[1][k][1] + part[1][k][2] + part[1][k][3];
+  const double first = e[KVC_RES_LEFT] < e[KVC_RES_UP] ? e[KVC_RES_LEFT] : e[KVC_RES_UP];
+  double inter = e[KVC_RES_TIME];
+  if (e[KVC_RES_TIME_LEFT] < inter) inter = e[KVC_RES_TIME_LEFT];
+  if (e[KVC_RES_TIME_UP] < inter) inter = e[KVC_RES_TIME_UP];
+  cost[blockIdx.x] = pixels * first + later * inter;
+}
+
 }  // namespace
+
+kvc_status launch_proxy_costs(const ScoreParams& p, double* cost, hipStream_t stream) {
+  const Geo& g = p.g;
+  if (p.n_chunks <= 0) return KVC_OK;
+  const int64_t streams = (int64_t)p.n_chunks * 2 * g.L;
+  if (streams > 0x7fffffff) return KVC_ERR_UNSUPPORTED;
+  hipLaunchKernelGGL(proxy_cost_kernel, dim3((uint32_t)streams), dim3(256), 0, stream, p.hist, cost, (double)g.plane,
+                     (double)(g.F - 1) * (double)g.plane);
+  return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
+}
 
 kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream) {
   const Geo& g = p.g;

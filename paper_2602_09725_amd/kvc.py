@@ -99,6 +99,7 @@ def load(path=None):
     lib.kvc_residual_histograms.argtypes = [LP, vp, i64, vp, sz, vp]
     lib.kvc_proxy_cost_bits.argtypes = [LP, vp, i64]
     lib.kvc_proxy_cost_bits.restype = C.c_double
+    lib.kvc_proxy_costs.argtypes = [LP, vp, i64, vp, vp]
     ip = C.POINTER(i32)
     lib.kvc_tile_candidates.argtypes = [i32, i32, ip, ip, ip, i32]
     lib.kvc_tile_candidates.restype = i32
@@ -183,6 +184,10 @@ def kvc_residual_histograms(layout, frames_ptr, n_chunks, hist_ptr, hist_cap, st
 def proxy_cost_bits(layout, hist_host_ptr, n_chunks):
     """hist_host_ptr: address of the uint64 histogram array in host memory."""
     return load().kvc_proxy_cost_bits(C.byref(layout), hist_host_ptr, n_chunks)
+
+
+def kvc_proxy_costs(layout, hist_ptr, n_chunks, cost_ptr, stream=0):
+    _check(load().kvc_proxy_costs(C.byref(layout), hist_ptr, n_chunks, cost_ptr, stream), "kvc_proxy_costs")
 
 
 def tile_candidates(num_kv_heads, head_dim):

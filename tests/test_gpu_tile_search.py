@@ -62,6 +62,15 @@ def test_residual_histograms_equal_the_oracle(case):
     cost = hz.kvc.proxy_cost_bits(glo, got.ctypes.data, n_chunks)
     want_cost = R.total_cost_bits(olo, want)
     assert abs(cost - want_cost) <= 1e-12 * max(want_cost, 1.0)
+    # and on the device, stream by stream: the same double terms summed in another order
+    dhist = torch.from_numpy(got.view(np.int64).copy()).cuda()
+    dcost = torch.full((n_chunks * 2 * L + 2,), -1.0, dtype=torch.float64, device="cuda")
+    hz.kvc.kvc_proxy_costs(glo, dhist.data_ptr(), n_chunks, dcost[1:].data_ptr(), hz.stream_handle())
+    per_stream = dcost.cpu()
+    assert per_stream[0] == -1.0 and per_stream[-1] == -1.0
+    for s, c in enumerate(per_stream[1:-1].tolist()):
+        one = R.total_cost_bits(olo, want.reshape(n_chunks * 2 * L, R.N_RESIDUALS, 256)[s].reshape(1, 1, 1, R.N_RESIDUALS, 256))
+        assert abs(c - one) <= 1e-12 * max(one, 1.0), s
 
 
 def test_histograms_of_adversarial_planes():
