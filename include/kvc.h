@@ -222,10 +222,10 @@ kvc_status kvc_restore_paged(const kvc_layout* layout, const uint8_t* frames, co
  *                     the blobs in place over the host link (the blobs must then
  *                     be mapped into the device, as hipHostMalloc memory is, and
  *                     8-byte aligned; d_staging, staging_bytes and copy_stream
- *                     are not looked at).  With tiles narrower than 512 bytes in
- *                     rows of tiles of at least 512 the kernel's reads are long
- *                     enough to draw the link's full rate, and this form is the
- *                     faster one
+ *                     are not looked at).  With tiles narrower than 512 bytes
+ *                     the kernel reads rows of tiles in runs of 512, long
+ *                     enough to draw the link's full rate where the runs fill
+ *                     the rows, and this form is the faster one
  *   copy_stream, compute_stream : two distinct non-NULL hipStream_t
  *   fetch_to_ready_ms HOST out, may be NULL.  If non-NULL the call blocks until
  *                     the last restore has finished and stores the time from

@@ -25,7 +25,7 @@ struct RestoreParams {
   int32_t rows_body, rows_q, rows_lat;  // lat: log2 of the atoms of a tile row
   int32_t rows_trw, rows_tile_rows;     // rows of tiles per workgroup; rows of tiles that hold tokens
   FastDiv dnf, dpr;                     // frames a unit covers (F or 1); passes per row of tiles = that * TX / q
-  int32_t host_frames;    // `frames` is host memory mapped into the device: prefer the "rows" body
+  int32_t host_frames;    // `frames` is host memory mapped into the device: take the "rows" body
   FastDiv dapt;           // atoms per token
   FastDiv dwpt;           // waves per token (apt / 64) when apt is a multiple of 64
   uint32_t frame_stride;     // bytes from a frame to the next of the same layer group: 3 planes (0 for a frame call)

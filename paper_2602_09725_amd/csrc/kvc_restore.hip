@@ -19,12 +19,12 @@
 // i.e. a few contiguous runs of th rows in each of F planes (Sec. 3.2.1 step 3).
 //
 // Three bodies:
-//  * "rows" (chunk calls on tiles narrower than 512 bytes, e.g. the (8,128) tile of the paper's GQA shapes): a
+//  * "rows" (tiles narrower than 512 bytes, e.g. the (8,128) and (16,64) tiles of the paper's GQA shapes): a
 //    wave reads runs of 512 bytes along a plane row -- the same row of 512 / tw neighbouring tiles, which hold
 //    tokens F positions apart (Sec. 3.2.1 step 3) -- and writes tw * 2 bytes of each of those tokens; the th waves
 //    of a workgroup take the th rows of the tiles, so together they write whole tokens.  Reads as long as this
 //    are what a kernel needs to draw the full rate from pinned host memory over PCIe (128-byte pieces reach 80 % of
-//    it), and they suit HBM at least as well as the "waves" body's.
+//    it, 64-byte pieces less than half), and from HBM they spare the halves of lines that tiles of 64 bytes leave.
 //  * "waves" (C/8 a multiple of 64, every model shape of the paper): a wave works
 //    on one token at a time, so everything that depends on the token only (frame,
 //    tile position, cache slot, block-table entry, pair address) is the same for
@@ -225,8 +225,8 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
     obase = reinterpret_cast<uint8_t*>(as_const(p.layer_cache)[l]) + ((int64_t)kind * p.num_blocks * p.dbs.d * g.C + e) * 2;
   else
     obase = reinterpret_cast<uint8_t*>(p.out + (int64_t)l * p.ls + (int64_t)kind * p.ks + chunk_first * p.ts + e);
-  const uint8_t* src = fsec + ((ty0 * (uint32_t)g.th + r) * (uint32_t)g.W + lane * 8u);
-  const uint32_t tile0 = ty0 * (uint32_t)g.TX + tl;  // the lane's tile in run 0 of the unit's first row
+  const uint8_t* src = fsec + (ty0 * (uint32_t)g.th + r) * (uint32_t)g.W;
+  const uint32_t tile0 = ty0 * (uint32_t)g.TX;  // first tile of the unit's first row
   const uint32_t pos0 = (uint32_t)(p.first_token + chunk_first);
   // pass k: frame k % nf, run (k / nf) % runs of row of tiles k / (nf * runs); nf = F, or 1 in a frame call
   const uint32_t rows_left = (uint32_t)p.rows_tile_rows - ty0;
@@ -237,15 +237,17 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
   for (uint32_t k0 = 0; k0 < passes; k0 += U) {
     u32x2 code[U];
     f32x2 sm[U];
-    uint32_t tok[U];
+    uint32_t tok[U];  // 2^32 - 1 for a lane past the end of the row of tiles
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t k = k0 + u < passes ? k0 + u : passes - 1;
       uint32_t j, kk, run, f;
       fd_divmod(p.dpr, k, j, kk);    // row of tiles of the unit, pass inside the row
       fd_divmod(p.dnf, kk, run, f);
-      tok[u] = (tile0 + j * (uint32_t)g.TX + run * (uint32_t)p.rows_q) * (uint32_t)g.F + f + ff;
-      code[u] = stream_load<u32x2>(src + ((size_t)f * p.frame_stride + j * row_bytes + run * 512u));
+      const uint32_t x = run * (uint32_t)p.rows_q + tl;  // the lane's tile in its row of tiles
+      const bool inside = x < (uint32_t)g.TX;
+      tok[u] = inside ? (tile0 + j * (uint32_t)g.TX + x) * (uint32_t)g.F + f + ff : 0xffffffffu;
+      code[u] = stream_load<u32x2>(src + ((size_t)f * p.frame_stride + j * row_bytes + (inside ? run * 512u + lane * 8u : 0u)));
       if (MODE == KVC_Q_PER_TOKEN) {
         const uint32_t tp = tok[u] < n ? tok[u] : n - 1u;  // positions without a token: any pair in bounds
         sm[u] = *(const KVC_GLOBAL f32x2*)(mrow + (size_t)tp * ((uint32_t)g.H * 8u));
@@ -460,30 +462,44 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   if (p.n_tokens <= 0) return KVC_OK;
   if (g.apt > 1024) return KVC_ERR_UNSUPPORTED;
   const bool waves = g.apt % 64 == 0;
-  // The "rows" body: tiles narrower than a 512-byte run whose rows of tiles hold whole runs, when
-  // the frames are read over the host link.  (On frames in HBM it is 0.5 % faster than "waves" when the blocks of
-  // the cache are in order and 0.4 % slower under a random block table: 1.136 / 1.185 against 1.142 / 1.180 ms.)
-  const int q = g.tw < 512 && 512 % g.tw == 0 ? 512 / g.tw : 0;
-  const bool rows = p.host_frames && waves && q >= 2 && g.TX % q == 0 && g.th <= 16;
-  const int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
-  p.rows_body = rows ? 1 : 0;
   p.n_chunks = (int32_t)((p.n_tokens + g.T - 1) / g.T);
   const int32_t n_last = (int32_t)(p.n_tokens - (int64_t)(p.n_chunks - 1) * g.T);  // tokens of the last chunk of the call
   const auto ceil_div = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  // The "rows" body, on tiles narrower than a 512-byte run: a run covers q tiles, the last one of a row what is left.
+  const int q = g.tw < 512 && 512 % g.tw == 0 ? 512 / g.tw : 0;
+  const int nf = p.frame_mode ? 1 : g.F, runs = q ? (g.TX + q - 1) / q : 1;
+  const int per_row = nf * runs;                                         // passes one row of tiles takes
+  const int trw = per_row >= kPasses ? 1 : kPasses / per_row;            // about one round of loads per wave
+  const auto row_units = [&](int32_t n) { return (int32_t)ceil_div(ceil_div(ceil_div(n, g.F), g.TX), trw); };
+  bool rows = q >= 2 && g.th <= 16;
+  if (rows && !p.host_frames) {
+    // Over the host link always (see above; 8 tiles of 64 bytes in runs of 13, 80 layers: 23.8 -> 44.0 GB/s).  From HBM
+    // where the other bodies would read half lines (tiles of 64 bytes: 6000 tokens x 80 layers x 1024 channels 643 ->
+    // 505 us, random table 520), unless runs are much longer than what is left for the last one (17 tiles: 585 -> 727 us)
+    // or a token is one head (paged 137 -> 148 us); and for tiles of 128 bytes into a contiguous tensor, where rows of
+    // tiles are whole runs (8192 tokens x 32 layers 283 -> 274 us; under a random table 284 -> 287).  A launch that
+    // would not fill the chip is better cut finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us,
+    // 644 tokens in groups of 10 frames 21.6 against 24.8).
+    const bool half_lines = g.tw < 128 && 4 * g.TX >= 3 * q * runs && g.apt >= 32;
+    const bool linear = g.tw == 128 && !paged && g.TX % q == 0 && g.apt >= 64;
+    const int64_t wgs = p.frame_mode ? (int64_t)p.fm_count * 3 * row_units(n_last)
+                                     : 2 * (int64_t)g.L * ((p.n_chunks - 1) * (int64_t)row_units(g.T) + row_units(n_last));
+    rows = (half_lines || linear) && wgs >= kFillWorkgroups;
+  }
+  const int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
+  p.rows_body = rows ? 1 : 0;
   int u = kPasses, tpp = 1;
   int32_t tbl = 0;  // units of the last chunk of the call (chunk call), which need not be full
   if (rows) {
     p.rows_q = q;
     p.rows_lat = 0;
     while ((8 << p.rows_lat) < g.tw) ++p.rows_lat;
-    const int nf = p.frame_mode ? 1 : g.F, per_row = nf * (g.TX / q);  // passes one row of tiles takes
     p.dnf = make_fastdiv((uint32_t)nf);
     p.dpr = make_fastdiv((uint32_t)per_row);
-    p.rows_trw = per_row >= kPasses ? 1 : kPasses / per_row;  // about one round of loads per wave
-    const auto units = [&](int32_t n) { return (int32_t)ceil_div(ceil_div(ceil_div(n, g.F), g.TX), p.rows_trw); };
+    p.rows_trw = trw;
     p.rows_tile_rows = (int32_t)ceil_div(ceil_div(g.T, g.F), g.TX);  // rows of tiles that hold tokens
-    p.tbc = units(p.frame_mode ? n_last : g.T);  // units of one (chunk, kind, layer) or plane
-    tbl = units(n_last);
+    p.tbc = row_units(p.frame_mode ? n_last : g.T);  // units of one (chunk, kind, layer) or plane
+    tbl = row_units(n_last);
   } else {
     // u passes of tpp tokens per workgroup; workgroups of a launch with `tokens` each, counting tokens that exist
     const auto wgs = [&](int64_t tokens) {
@@ -520,8 +536,7 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     p.units_per_xcd = (p.n_units + 7u) / 8u;
     grid = dim3(p.units_per_xcd * 8u);
   } else {
-    const int64_t row_units = (int64_t)(p.n_chunks - 1) * p.tbc + tbl;
-    if (!make_band_map(&p.bands, 2 * (int64_t)g.L, row_units, 0x7fffffff)) return KVC_ERR_UNSUPPORTED;
+    if (!make_band_map(&p.bands, 2 * (int64_t)g.L, (int64_t)(p.n_chunks - 1) * p.tbc + tbl, 0x7fffffff)) return KVC_ERR_UNSUPPORTED;
     grid = dim3(p.bands.wgs_per_xcd * 8u);
   }
   p.dtbc = make_fastdiv((uint32_t)p.tbc);

@@ -105,6 +105,9 @@ ROW_RUNS = [
     (4, 8, 128, 96, 8, 128, 64, 4, 8, 96 + 50, 16),      # two-level (4,2)x(2,64): a tile row holds halves of two heads
     (2, 4, 128, 70, 8, 64, 64, 8, 3, 70 + 33, 16),       # C = 512, two-level with d2 = 64
     (3, 32, 128, 40, 16, 256, 128, 2, 5, 40 + 11, 16),   # 32 heads: tile (16,256) = (16,2)x(1,128)
+    (4, 8, 128, 96, 8, 128, 0, 3, 11, 96 + 50, 16),      # rows of 3 tiles: one run, a quarter of it past the end
+    (3, 4, 64, 70, 4, 64, 0, 13, 3, 70 + 31, 16),        # C = 256; rows of 13 tiles: a run of 8 and one of 5
+    (2, 1, 128, 90, 2, 64, 0, 17, 2, 90 * 2 + 1, 8),     # C = 128, two waves; rows of 17 tiles
 ]
 
 
@@ -972,6 +975,8 @@ RESTORE_SHAPES = [
     (33, 1, 64, 512, 1, 64, 8, 64, 4000, 32),    # lanes, 4 passes
     (33, 1, 64, 512, 1, 64, 8, 32, 8200, 32),    # lanes, 8 passes
     (5, 3, 128, 70, 3, 128, 3, 5, 150, 16),      # C/8 = 48: 240 threads
+    (16, 4, 64, 3000, 4, 64, 13, 60, 3100, 16),  # tiles of 64 bytes: runs along plane rows, the last of 5 tiles
+    (16, 8, 128, 512, 8, 128, 8, 16, 3007, 16),  # tiles of 128 bytes: the same into a contiguous tensor only
 ]
 
 
