@@ -107,7 +107,7 @@ struct PackParams {
   uint32_t pieces_pairs, n_zero_pairs;
   // workgroups of the three kinds, those of a short last chunk apart: n_whole chunks hold T tokens
   PackRange ch[2], tok[2], zero;
-  uint32_t tok_run;       // consecutive per-token units that go to one XCD, a power of two
+  uint32_t tok_run;       // consecutive per-token units that go to one XCD in turn, a power of two; 0: an eighth of them each
   int32_t n_whole;
   int32_t light_last;     // resident launch: the short last chunk's strips take the light form
   uint32_t wgs_per_xcd;

@@ -48,7 +48,10 @@ __device__ __forceinline__ GroupParams group_params(float lo, float hi) {
     q.scale = 0.0f;
     q.inv = 0.0f;
   } else {
-    q.scale = range / 255.0f;
+    // range / 255, correctly rounded: a quotient from the rounded reciprocal and one correction with its exact remainder
+    // (Markstein; compared with the division over every significand)
+    const float y = 1.0f / 255.0f, s0 = range * y;
+    q.scale = __builtin_fmaf(__builtin_fmaf(-s0, 255.0f, range), y, s0);
     q.inv = 255.0f / range;
   }
   return q;
@@ -219,6 +222,43 @@ __device__ __forceinline__ uint8_t* code_addr(const Geo& g, uint8_t* fbase, uint
   return fbase + (int64_t)f * 3 * g.plane + ((int64_t)ty * g.th * g.W + tx * (uint32_t)g.tw);
 }
 
+// The same address for the token positions first, first + step, first + 2 step, ...: two sums and two carries a step
+// instead of two divisions.
+struct TokenWalk {
+  int64_t off;  // bytes from fbase
+  uint32_t f, tx;
+  const uint32_t F, TX;
+  uint32_t step_f, step_x;
+  int64_t step_off, carry_f, carry_x;
+  __device__ __forceinline__ TokenWalk(const Geo& g, uint32_t first, uint32_t step) : F((uint32_t)g.F), TX((uint32_t)g.TX) {
+    const int64_t frame3 = 3 * g.plane, trs = (int64_t)g.th * g.W;
+    uint32_t gi, ty;
+    fd_divmod(g.dF, first, gi, f);
+    fd_divmod(g.dTX, gi, ty, tx);
+    off = f * frame3 + ty * trs + tx * g.tw;
+    uint32_t step_g, step_y;
+    fd_divmod(g.dF, step, step_g, step_f);
+    fd_divmod(g.dTX, step_g, step_y, step_x);
+    step_off = step_f * frame3 + step_y * trs + step_x * g.tw;
+    carry_f = g.tw - F * frame3;  // next group: frame 0, one tile to the right
+    carry_x = trs - (int64_t)TX * g.tw;
+  }
+  __device__ __forceinline__ void next() {
+    f += step_f;
+    tx += step_x;
+    off += step_off;
+    if (f >= F) {
+      f -= F;
+      ++tx;
+      off += carry_f;
+    }
+    if (tx >= TX) {
+      tx -= TX;
+      off += carry_x;
+    }
+  }
+};
+
 // ------------------------------------------------------------ per-token groups
 
 // min / max over the 16 lanes of a DPP row (every lane gets the result).  Each step pairs a lane
@@ -237,6 +277,18 @@ __device__ __forceinline__ void head_minmax16(float& lo, float& hi) {
   hi = __builtin_fmaxf(hi, dpp_move<0x141>(hi));
   lo = __builtin_fminf(lo, dpp_move<0x140>(lo));  // row_mirror
   hi = __builtin_fmaxf(hi, dpp_move<0x140>(hi));
+}
+
+// min / max over the lanes of a head (a power of two of them); every lane gets the result.
+__device__ __forceinline__ void head_minmax(uint32_t lanes, float& lo, float& hi) {
+  if (lanes == 16u) {  // D = 128: the 16 lanes of a head are one DPP row
+    head_minmax16(lo, hi);
+    return;
+  }
+  for (uint32_t m = 1; m < lanes; m <<= 1) {
+    lo = __builtin_fminf(lo, __shfl_xor(lo, (int)m));
+    hi = __builtin_fmaxf(hi, __shfl_xor(hi, (int)m));
+  }
 }
 
 template <int DT, bool UNIFORM, int U>
@@ -278,34 +330,27 @@ __device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t un
 
   const int32_t step = p.tpp;
   int32_t tb0 = t0;
+  TokenWalk walk(g, (uint32_t)(t0 + (int32_t)tsub), (uint32_t)step);
   // whole passes of U tokens that all exist: no branches between the loads and the stores
   const int32_t full_end = n < t1 ? n : t1;
   for (; tb0 + U * step <= full_end; tb0 += U * step) {
     u32x4 v[U];
+    const uint16_t* sp = src + (int64_t)(tb0 + (int32_t)tsub) * p.ts;
+    float* mp = mrow + 2 * (int64_t)(tb0 + (int32_t)tsub) * g.H;
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = stream_load<u32x4>(sp + (int64_t)(u * step) * p.ts);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int32_t t = tb0 + u * step + (int32_t)tsub;
-      v[u] = stream_load<u32x4>(src + (int64_t)t * p.ts);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int32_t t = tb0 + u * step + (int32_t)tsub;
       float lo, hi;
       atom_minmax<DT>(v[u], lo, hi);
-      if (glanes == 16u) {  // D = 128: the 16 lanes of a head are one DPP row
-        head_minmax16(lo, hi);
-      } else {
-        for (uint32_t m = 1; m < glanes; m <<= 1) {
-          lo = __builtin_fminf(lo, __shfl_xor(lo, (int)m));
-          hi = __builtin_fmaxf(hi, __shfl_xor(hi, (int)m));
-        }
-      }
+      head_minmax(glanes, lo, hi);
       const GroupParams q = group_params(lo, hi);
       float x[8];
       widen_atom<DT>(v[u], x);
       const u32x2 o = quantize_atom(x, q.mn, q.inv);
-      stream_store<u32x2>(code_addr(g, fbase, (uint32_t)t), o);
-      if (leader) *reinterpret_cast<f32x2*>(mrow + 2 * (int64_t)t * g.H) = f32x2{q.scale, q.mn};
+      stream_store<u32x2>(fbase + walk.off, o);
+      if (leader) *reinterpret_cast<f32x2*>(mp + (int64_t)(2 * u * step) * g.H) = f32x2{q.scale, q.mn};
+      walk.next();
     }
   }
   for (; tb0 < t1; tb0 += U * step) {
@@ -319,8 +364,9 @@ __device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t un
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int32_t t = tb0 + u * step + (int32_t)tsub;
+      uint8_t* dst = fbase + walk.off;
+      walk.next();
       if (t >= t1) continue;
-      uint8_t* dst = code_addr(g, fbase, (uint32_t)t);
       if (t >= n) {  // no token here: zero codes, zero pair
         stream_store<u32x2>(dst, u32x2{0u, 0u});
         if (leader && t < g.T) *reinterpret_cast<f32x2*>(mrow + 2 * (int64_t)t * g.H) = f32x2{0.f, 0.f};
@@ -328,10 +374,7 @@ __device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t un
       }
       float lo, hi;
       atom_minmax<DT>(v[u], lo, hi);
-      for (uint32_t m = 1; m < glanes; m <<= 1) {  // butterfly over the lanes of the head
-        lo = __builtin_fminf(lo, __shfl_xor(lo, (int)m));
-        hi = __builtin_fmaxf(hi, __shfl_xor(hi, (int)m));
-      }
+      head_minmax(glanes, lo, hi);
       const GroupParams q = group_params(lo, hi);
       float x[8];
       widen_atom<DT>(v[u], x);
@@ -562,11 +605,11 @@ constexpr int kMediumGroup = 4;
 // narrower ones (two layers of 2048 tokens, 16 strips of 128 channels: 26.5 -> 12.5 us in 128 strips of 16; with
 // 256 strips and more the full lines are worth more, 77 us against 94 for 32 layers), and per-token kinds alone up to
 // kFewTokenRows, where its smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger
-// workgroups of the streaming form are faster, 283 against 295 us for 32 layers of 8192).
+// workgroups of the streaming form are faster, two layers of 20 000 tokens 58 against 65 us).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
-constexpr int64_t kFewStrips = 128, kFewTokenRows = 2048 * 128, kFewTokenUnits = 512;
+constexpr int64_t kFewStrips = 128, kFewTokenRows = 512 * 128, kFewTokenUnits = 512;
 
 template <int DT, int NR, int NS, bool SHORT>
 __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, uint32_t unit, uint32_t c0,
@@ -780,8 +823,8 @@ pack_kernel(const PackParams p) {
   // of the whole chunks, then of a short last chunk, so that every XCD has the same mix of work: 2048 + 128 tokens of 60
   // layers 272 -> 187 us) and the zero-fill ones.  Each XCD gets one contiguous eighth of the strips and of the
   // zero-fill units, so neighbouring strips, which may share lines, share an L2.  Token blocks share nothing and are
-  // dealt out in turn (32K tokens of 60 layers, both kinds per token: 2.12 ms in eighths, 2.04 ms in turn; strips in turn
-  // cost 4 %).
+  // dealt out in turn, but for some shapes (32K tokens of 60 layers, both kinds per token: 2.12 ms in eighths, 2.06 in
+  // turn; strips in turn cost 4 %).
   const uint32_t xcd = blockIdx.x & 7u;
   uint32_t idx = blockIdx.x >> 3;
   const uint32_t n_ch = p.ch[0].per_xcd + p.ch[1].per_xcd, n_tok = p.tok[0].per_xcd + p.tok[1].per_xcd;
@@ -804,9 +847,8 @@ pack_kernel(const PackParams p) {
     const bool last = idx >= p.tok[0].per_xcd;
     if (last) idx -= p.tok[0].per_xcd;
     const PackRange r = last ? p.tok[1] : p.tok[0];
-    // round-robin, in runs of units that hold about as many bytes as one of 1024 channels
     const uint32_t in_run = idx & (p.tok_run - 1u);
-    const uint32_t unit = ((idx - in_run) * 8u + xcd * p.tok_run) + in_run;
+    const uint32_t unit = p.tok_run ? (idx - in_run) * 8u + xcd * p.tok_run + in_run : xcd * r.per_xcd + idx;
     if (unit < r.units)
       pack_token_body<DT, UNIFORM, BODY == kPackResident ? kTokenLoadsResident : kTokenLoads>(
           p, unit, last ? (uint32_t)p.n_whole : 0u, (uint32_t)(last ? p.tbl : p.tbc));
@@ -906,6 +948,10 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
   p.positions_full = positions(g.T);
   p.positions_last = positions(n_last);
   p.tb = 128;  // token positions per workgroup of the per-token kinds (32: 1.27 ms, 64: 1.18, 128: 1.157, 256: 1.166, 512: 1.20)
+  // ... and at least those a workgroup has loads in flight for, or it never runs whole passes (128 channels and 1024
+  // threads, 256 positions: 12 000 tokens of 80 layers 270 -> 155 us)
+  const int in_flight = p.tpp * (p.body == kPackResident ? kTokenLoadsResident : kTokenLoads);
+  while (p.tb < in_flight) p.tb *= 2;
   const auto token_blocks = [&](int64_t n) { return (int32_t)((n + p.tb - 1) / p.tb); };
   p.light_last = n_last <= rows_of(kLightLoads, p.strip_atoms) ? 1 : 0;
   p.n_whole = n_last == g.T ? p.n_chunks : p.n_chunks - 1;
@@ -936,9 +982,16 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
                             short_chunks * rows_tok * p.tbl, zero_pairs + zero_pad + zero_full + zero_last};
   PackRange* const ranges[5] = {&p.ch[0], &p.ch[1], &p.tok[0], &p.tok[1], &p.zero};
   int64_t wgs_per_xcd = 0;
-  p.tok_run = 1;
-  while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
-  const int64_t run[5] = {1, 1, p.tok_run, p.tok_run, 1};
+  // Token blocks in turn, in runs that hold about as many bytes as a block of 1024 channels.  Where blocks end inside a
+  // row of tiles, neighbours stay on one XCD: in longer runs (rows of 36 positions, 8192 tokens of 32 layers x 1024
+  // channels 307 -> 296 us; blocks of whole rows lose 1 % by it), or narrower ones in eighths (4096 x 32 x 256 54 -> 51 us).
+  const bool whole_rows = p.tb % (g.F * g.TX) == 0;
+  p.tok_run = 0;
+  if (whole_rows || g.C >= 1024) {
+    p.tok_run = whole_rows ? 1 : 4;
+    while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
+  }
+  const int64_t tok_run = p.tok_run ? p.tok_run : 1, run[5] = {1, 1, tok_run, tok_run, 1};
   const auto share = [&](int i) { return (units[i] + 8 * run[i] - 1) / (8 * run[i]) * run[i]; };  // of one XCD
   for (int i = 0; i < 5; ++i) wgs_per_xcd += share(i);
   if (wgs_per_xcd > 0x7fffffff / 64) return KVC_ERR_UNSUPPORTED;

@@ -1022,6 +1022,8 @@ PACK_FORMS = [
     (2, 8, 128, 2100, 8, 128, 8, 80, 2100 + 7, (0, 1)),         # two-pass form, narrow strips that wait on chip whole
     (1, 8, 128, 12400, 8, 128, 15, 135, 12400, (0, 1)),         # ... and those that do not
     (32, 1, 64, 2048, 1, 64, 16, 64, 4200, (1, 1)),             # per token only, many rows; units of few bytes in runs
+    (32, 1, 128, 2048, 1, 128, 8, 64, 4200, (1, 1)),            # ... 64 tokens a pass, blocks of 256
+    (9, 2, 128, 2048, 2, 128, 6, 60, 4100, (0, 1)),             # 128 strips; rows of 36 positions, blocks that end inside them
     (3, 1, 64, 2048, 1, 64, 16, 64, 70, (1, 1)),                # ... few rows; pairs of 1900 tokens to clear
 ]
 
