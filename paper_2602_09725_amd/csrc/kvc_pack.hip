@@ -13,8 +13,11 @@
 //    A chunk of up to 2048 tokens is loaded once into the registers and the
 //    LDS of a 512-thread workgroup that has its CU to itself, reduced to the
 //    column min/max (registers + one LDS step across waves) and quantized from
-//    where it waits; of longer chunks the last 3072 tokens wait like that and
-//    the tokens before them are read twice (statistics, then quantization).
+//    where it waits; chunks of up to 1024 tokens take half as much, two
+//    workgroups to a CU; few tokens, or few strips cut narrower, a light form
+//    with 16 loads a thread; of longer chunks the last 3072 tokens wait on chip
+//    and the tokens before them are read twice (statistics, then quantization),
+//    unless strips are so few that they are cut to hold a whole chunk.
 // Both kernels write every byte of their part of the frame section, zero for
 // tile positions without a token and for the planes of layers beyond L, so the
 // caller never has to clear the buffer.
@@ -895,7 +898,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
     else
       p.kinds_tok[p.n_kinds_tok++] = kind;
   }
-  // per-token part: a whole number of tokens per pass, about 256 threads
+  // per-token part: the lanes of a head reduce with each other
   const int glanes = g.D / 8;
   if (p.n_kinds_tok > 0 && (glanes > 64 || (glanes & (glanes - 1)) != 0)) return KVC_ERR_UNSUPPORTED;
   // Which form the launch takes.  The forms that keep a strip on chip work with 512 threads; on strips of 128 channels
