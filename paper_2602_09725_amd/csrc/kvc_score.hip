@@ -31,7 +31,7 @@ namespace {
 
 constexpr int kScoreThreads = 512;
 constexpr int kCopies = 16;        // copies of each histogram in LDS: 80 KB of the CU's 160 KB
-constexpr int kFrames = 4;         // frames whose loads are in flight together
+constexpr int kFrames = 4;         // pieces whose loads are in flight together: frames, or rows of few frames
 // Workgroups a launch of few streams is cut into, two rounds of the two that fit a CU: a chunk of 32 layers x 1024
 // channels (64 streams) takes 499 us in one part per stream, 83 / 80 / 84 us in 512 / 1024 / 2048 workgroups; with
 // most tiles empty fewer are better (18 tokens of 1024: 30 / 32 / 43 us), with 2000 rows of 3840 pixels more (111 / 105 / 103).
@@ -107,42 +107,50 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
   const uint32_t rows_per_band = (p.part_rows + bands - 1u) / bands;
   const uint32_t y0 = part0 + band * rows_per_band;
   const uint32_t y1 = y0 + rows_per_band < part1 ? y0 + rows_per_band : part1;
+  // groups of fewer frames than are loaded together take several rows at once (F = 1, two chunks of 80 layers: 300 -> 131 us)
+  const uint32_t rows_at_once = F < (uint32_t)kFrames ? (uint32_t)kFrames / F : 1u;
   uint32_t zeros = 0u, zeros_later = 0u;  // pieces without any nonzero pixel around them, in all frames / frames >= 1
   for (uint32_t cb = col0; band < bands && cb < per_row; cb += cols)
-  for (uint32_t y = y0; y < y1; ++y) {
-    const bool has_up = y > 0u, has_left = cb > 0u;
+  for (uint32_t y = y0; y < y1; y += rows_at_once) {
+    const bool has_left = cb > 0u;
     const uint8_t* row = base + (size_t)(y * per_row + cb) * 8u;
-    const uint8_t* row_up = has_up ? row - W : row;      // stays inside the plane: row 0 and column 0 read themselves
-    const uint8_t* row_left = has_left ? row - 1 : row;
+    // item k of these rows: frame k % F of row y + k / F
+    const uint32_t items = (y1 - y < rows_at_once ? y1 - y : rows_at_once) * F;
     Piece prev{}, prev_l{}, prev_u{};
     uint32_t prev_any = 0u;
-    for (uint32_t f0 = 0; f0 < F; f0 += kFrames) {
+    for (uint32_t k0 = 0; k0 < items; k0 += kFrames) {
       u32x2 cur[kFrames], up[kFrames];
       uint32_t left[kFrames];
 #pragma unroll
       for (int k = 0; k < kFrames; ++k) {
-        const size_t at = (size_t)(f0 + k < F ? f0 + k : F - 1u) * (size_t)frame_stride;
-        cur[k] = *(const KVC_GLOBAL u32x2*)(row + at);  // cached: the next row reads it again as its upper neighbour
-        up[k] = *(const KVC_GLOBAL u32x2*)(row_up + at);
-        left[k] = *(const KVC_GLOBAL uint8_t*)(row_left + at);
+        uint32_t dy, f;
+        fd_divmod(g.dF, k0 + k < items ? k0 + k : items - 1u, dy, f);
+        const uint8_t* px = row + (dy * W + (size_t)f * (size_t)frame_stride);
+        cur[k] = *(const KVC_GLOBAL u32x2*)px;  // cached: the next row reads it again as its upper neighbour
+        up[k] = *(const KVC_GLOBAL u32x2*)(y + dy > 0u ? px - W : px);  // stays inside the plane: row 0 and column 0 read themselves
+        left[k] = *(const KVC_GLOBAL uint8_t*)(has_left ? px - 1 : px);
       }
 #pragma unroll
       for (int k = 0; k < kFrames; ++k) {
-        if (f0 + k >= F) break;  // wave-uniform
-        if (!has_up) up[k] = u32x2{0u, 0u};
+        if (k0 + k >= items) break;
+        uint32_t dy, f;
+        fd_divmod(g.dF, k0 + k, dy, f);
+        if (y + dy == 0u) up[k] = u32x2{0u, 0u};
         if (!has_left) left[k] = 0u;
+        if (f == 0u) prev_any = 0u;
         // Tiles without a token are zero: where a whole wave sees nothing else, its residuals are counted at the end.
         const uint32_t any = cur[k].x | cur[k].y | up[k].x | up[k].y | left[k];
         if (__ballot((any | prev_any) != 0u) == 0u) {
           ++zeros;
-          zeros_later += f0 + k > 0u ? 1u : 0u;
+          zeros_later += f > 0u ? 1u : 0u;
+          prev = prev_l = prev_u = Piece{};
           continue;
         }
         const Piece now = split(cur[k]);
         const Piece res_l = now - left_of(now, left[k]), res_u = now - split(up[k]);
         count8(hist[KVC_RES_LEFT], res_l, copy_bytes);
         count8(hist[KVC_RES_UP], res_u, copy_bytes);
-        if (f0 + k > 0u) {
+        if (f > 0u) {
           count8(hist[KVC_RES_TIME], now - prev, copy_bytes);
           count8(hist[KVC_RES_TIME_LEFT], res_l - prev_l, copy_bytes);
           count8(hist[KVC_RES_TIME_UP - 1], res_u - prev_u, copy_bytes + (uint32_t)sizeof(Histogram));  // an offset of 64 KB does not fit the instruction

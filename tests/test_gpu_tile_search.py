@@ -95,6 +95,8 @@ PARTS = [
     (1, 2, 1024, 20, 1, 2048, 3, 5, 1),    # 768 pieces a row: two blocks of columns
     (171, 1, 8, 7, 1, 8, 1, 3, 3),         # 1026 streams: one workgroup each, F = 3
     (2, 1, 64, 45, 2, 32, 3, 3, 2),        # F = 5: a second round of loads
+    (3, 2, 64, 100, 2, 64, 5, 21, 2),      # F = 1: four rows at once, ragged bands
+    (3, 2, 64, 100, 2, 64, 5, 11, 1),      # F = 2: two rows at once
 ]
 
 
