@@ -52,8 +52,9 @@ __device__ __forceinline__ GroupParams group_params(float lo, float hi) {
     q.inv = 0.0f;
   } else {
     // range / 255, correctly rounded: a quotient from the rounded reciprocal and one correction with its exact remainder
-    // (Markstein; compared with the division over every significand)
-    const float y = 1.0f / 255.0f, s0 = range * y;
+    // (Markstein; compared with the division over every positive range, subnormal and infinite ones among them).  A range
+    // that overflows has no remainder to correct with: the quotient is kept finite so that the correction gives infinity.
+    const float y = 1.0f / 255.0f, s0 = __builtin_fminf(range * y, __FLT_MAX__);
     q.scale = __builtin_fmaf(__builtin_fmaf(-s0, 255.0f, range), y, s0);
     q.inv = 255.0f / range;
   }

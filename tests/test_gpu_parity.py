@@ -1043,3 +1043,20 @@ def test_pack_launch_forms(shape, dtype):
     frames, meta = hz.gpu_pack(glo, kv, n)
     hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
     hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+
+
+@pytest.mark.parametrize("modes", [(0, 1), (1, 0)])
+def test_groups_whose_range_overflows(modes):
+    """bf16 values whose difference is beyond the largest fp32: the scale is infinite, as range / 255 is, never NaN, and
+    the rest of the call is as ever."""
+    L, H, D, T, n = 2, 4, 128, 48, 48 + 17
+    glo, olo = hz.layouts(L, H, D, "bf16", T, 4, 128, 4, 4, *modes)
+    kv = kv_synth.make_kv(L, H, D, n, torch.bfloat16, seed=31, device="cuda")
+    for first, second in ((0, 1), (T + 2, T + 5)):     # in the full and in the short chunk
+        kv[0, :, first, 1, 2:5], kv[0, :, second, 1, 5:7] = 3e38, -1e38
+        kv[0, :, second, 1, 2:5], kv[0, :, first, 1, 5:7] = -1e38, 3e38
+    want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    assert np.isinf(want_meta).any() and not np.isnan(want_meta).any()
+    frames, meta = hz.gpu_pack(glo, kv, n)
+    hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
+    hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
