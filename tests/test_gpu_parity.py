@@ -1060,3 +1060,25 @@ def test_groups_whose_range_overflows(modes):
     frames, meta = hz.gpu_pack(glo, kv, n)
     hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
     hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("T,n", [(48, 48 + 17), (2100, 2100)])
+def test_nan_does_not_spread_over_its_group(T, n, dtype):
+    """Inputs have to be finite, but one that is not a number costs its own element alone: code 0, and the minimum and
+    maximum of its group are those of the others (NaNs of either sign, infinities and -0.0 beside them)."""
+    L, H, D = 2, 4, 128
+    glo, olo = hz.layouts(L, H, D, dtype, T, 4, 128, 4, -(-T // 12), 0, 0)
+    kv = kv_synth.make_kv(L, H, D, n, TD[dtype], seed=32, device="cuda")
+    kv[:, :, 3::7, 1, 3] = float("nan")
+    bits = kv.view(torch.int16)
+    bits[0, :, 5::11, 2, 9] = -1                           # negative, all mantissa bits
+    bits[1, :, 1, 2, 10], bits[1, :, 2, 2, 10] = -1, 0x7FFF  # one of each in a group
+    kv[0, :, 4, 0, 8], kv[0, :, 6, 0, 9] = float("inf"), -float("inf")
+    kv[1, :, :, 3, 5] = -kv[1, :, :, 3, 5].abs()
+    kv[1, :, 7, 3, 5] = -0.0
+    want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)   # a comparison with a NaN is false
+    assert np.isinf(want_meta).any() and not np.isnan(want_meta).any()
+    frames, meta = hz.gpu_pack(glo, kv, n)
+    hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+    hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
