@@ -73,9 +73,10 @@ __device__ __forceinline__ void count8(Histogram& h, const Piece& p, uint32_t co
   }
 }
 
-__global__ void __launch_bounds__(kScoreThreads) clear_hist_kernel(u32x4* hist, uint32_t n16) {
+// Counter by counter: the caller's array is 8-byte aligned, no more.
+__global__ void __launch_bounds__(kScoreThreads) clear_hist_kernel(uint64_t* hist, uint32_t n) {
   const uint32_t i = blockIdx.x * kScoreThreads + threadIdx.x;
-  if (i < n16) hist[i] = u32x4{0u, 0u, 0u, 0u};
+  if (i < n) hist[i] = 0;
 }
 
 __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const ScoreParams p) {
@@ -247,9 +248,8 @@ kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream) {
   p.part_rows = (uint32_t)rows;
   p.dparts = make_fastdiv((uint32_t)parts);
   if (parts > 1) {
-    const uint32_t n16 = (uint32_t)(streams * (KVC_N_RESIDUALS * 256 * 8 / 16));
-    hipLaunchKernelGGL(clear_hist_kernel, dim3((n16 + kScoreThreads - 1) / kScoreThreads), dim3(kScoreThreads), 0, stream,
-                       reinterpret_cast<u32x4*>(p.hist), n16);
+    const uint32_t n = (uint32_t)(streams * (KVC_N_RESIDUALS * 256));  // fewer than kScoreWorkgroups streams
+    hipLaunchKernelGGL(clear_hist_kernel, dim3((n + kScoreThreads - 1) / kScoreThreads), dim3(kScoreThreads), 0, stream, p.hist, n);
   }
   hipLaunchKernelGGL(residual_hist_kernel, dim3((uint32_t)(streams * parts)), dim3(kScoreThreads), 0, stream, p);
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;

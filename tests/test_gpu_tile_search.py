@@ -116,6 +116,18 @@ def test_histograms_of_streams_cut_into_parts(case):
     hz.assert_same_bytes("histograms", got, R.residual_histograms(olo, frames, n_chunks))
 
 
+@pytest.mark.parametrize("guard", [64, 63])
+@pytest.mark.parametrize("layers", [3, 513])
+def test_histograms_anywhere_at_8_byte_alignment(layers, guard):
+    """The array of counters inside a larger one, at an even and at an odd counter: cleared and added to in parts (6
+    streams), stored whole (1026 streams); nothing around it is touched."""
+    H, D, T = 1, 16, 50
+    glo, olo = hz.layouts(layers, H, D, "f16", T, 1, 16, 4, 9)
+    frames = np.random.default_rng(guard).integers(0, 256, size=oracle.frame_bytes(olo), dtype=np.uint8)
+    got = gpu_histograms(glo, torch.from_numpy(frames).cuda(), 1, guard).reshape(1, 2, layers, R.N_RESIDUALS, 256)
+    hz.assert_same_bytes("histograms", got, R.residual_histograms(olo, frames, 1))
+
+
 def test_rank_tiles_orders_candidates_like_the_oracle():
     """The search loop on a small model shape: every candidate's cost equals the oracle's for the same tiling, so
     the ranking is the oracle's."""
