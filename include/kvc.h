@@ -216,7 +216,9 @@ kvc_status kvc_restore_paged(const kvc_layout* layout, const uint8_t* frames, co
  * only the parts that a restore of those tokens reads), then restored into the
  * paged cache on `compute_stream`; a slot is reused only after the restore that
  * read it has finished.  Every chunk but the last must hold T tokens.
- *   chunks            HOST array of n_chunks descriptors (blobs PINNED HOST)
+ *   chunks            HOST array of n_chunks descriptors (blobs PINNED HOST; they
+ *                     are read until copy_stream has drained, in place until
+ *                     compute_stream has)
  *   d_staging         HOST array of n_staging DEVICE buffers, each >= blob size
  *   staging_bytes     capacity of each staging buffer
  *   n_staging         2..64, or 0: nothing is copied, the restore kernels read
@@ -298,7 +300,9 @@ size_t kvc_meta_staging_size(const kvc_layout* layout, int32_t order);
  * kvc_frame_size) frames, at most a chunk's), announced with one event and
  * restored with one kvc_restore_paged_frames launch per run; the pairs a run
  * needs are copied before it (or fetched on compute_stream by a kernel, where
- * the blobs are mapped into the device).  In KVC_ORDER_LAYER a buffer that holds at least
+ * the blobs are mapped into the device; copy_stream waits for the last of these
+ * at its end, so that a blob may be written again or freed once copy_stream has
+ * drained, as after kvc_fetch_pipeline).  In KVC_ORDER_LAYER a buffer that holds at least
  * 2*F frames receives the K and the V frames of a (chunk, layer group) in one
  * two-row strided copy.
  *   d_frame_staging  HOST array of n_frame_staging (2..64) DEVICE buffers of

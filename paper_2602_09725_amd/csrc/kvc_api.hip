@@ -632,23 +632,27 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
     cs = xs;  // the only stream in use
     n_meta_staging = 0;
   }
-  // "copied" after the copies into a frame slot, "freed" after the last kernel that read a slot (frame slots, then
-  // meta slots); with timing: begin, end, then one per layer group
   // In layer order the pairs of a unit are fetched by a small kernel on the compute stream, ahead of the restore that
   // reads them, instead of by two small copies between the large ones: each copy costs the copy stream about 12 us
-  // beyond its bytes, the kernel costs it nothing, and a meta slot needs no events.  (8192 tokens x 32 layers through 4
-  // slots of 8 frames: 13.0 -> 11.7 ms; the bytes alone take 10.0.)  Pairs that a kernel cannot read in place are copied.
+  // beyond its bytes, the kernel costs it nothing, and a meta slot needs no event of its own.  (8192 tokens x 32 layers
+  // through 4 slots of 8 frames: 13.0 -> 11.7 ms; the bytes alone take 10.0.)  Pairs that a kernel cannot read in place
+  // are copied.
   bool pairs_by_kernel = !in_place && order == KVC_ORDER_LAYER && 3 * pairs_per_layer(g, 0) < (1ll << 30) &&
                          3 * pairs_per_layer(g, 1) < (1ll << 30);
   for (int i = 0; i < n_chunks && pairs_by_kernel; ++i) {
     const uint8_t* meta = static_cast<const uint8_t*>(chunks[i].host_blob) + meta_off;
     pairs_by_kernel = aligned(meta, 8) && mapped_host_span(meta, meta_bytes);
   }
+  // "copied" after the copies into a frame slot, "freed" after the last kernel that read a slot (frame slots, then
+  // meta slots); with timing: begin, end, then one per layer group
   EventLease ev(2 * n_frame_staging + n_meta_staging, blocking ? 2 + (group_ready_ms ? g.LG : 0) : 0);
   bool ok = ev.ok();
   const auto frames_copied = [&](int s) { return ev.sync(s); };
   const auto frames_freed = [&](int s) { return ev.sync(n_frame_staging + s); };
   const auto meta_freed = [&](int s) { return ev.sync(2 * n_frame_staging + s); };
+  // the events of meta slots (two at least) that pairs fetched by a kernel leave unused
+  const hipEvent_t blobs_written = ok && pairs_by_kernel ? meta_freed(0) : nullptr;
+  const hipEvent_t pairs_read = ok && pairs_by_kernel ? meta_freed(1) : nullptr;
   const hipEvent_t t_begin = ok && blocking ? ev.timed(0) : nullptr, t_end = ok && blocking ? ev.timed(1) : nullptr;
   const auto t_group = [&](int lg) { return ev.timed(2 + lg); };
   kvc_status result = ok ? KVC_OK : KVC_ERR_RUNTIME;
@@ -731,6 +735,7 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
                         (uint32_t)(nl * ppl)};
       };
       if (ok) ok = launch_copy_pairs(span(0), span(1), xs) == KVC_OK;
+      if (ok && unit_no + 1 == (int64_t)g.LG * n_chunks) ok = hipEventRecord(pairs_read, xs) == hipSuccess;
       return ms;
     }
     if (ok && unit_no >= n_meta_staging) ok = hipStreamWaitEvent(cs, meta_freed(ms), 0) == hipSuccess;
@@ -834,8 +839,8 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
   } else if (ok) {
     if (t_begin) ok = hipEventRecord(t_begin, cs) == hipSuccess;
     if (pairs_by_kernel && ok) {  // the compute stream starts after what is ahead on the copy stream (and joins its capture)
-      ok = hipEventRecord(meta_freed(0), cs) == hipSuccess;
-      if (ok) ok = hipStreamWaitEvent(xs, meta_freed(0), 0) == hipSuccess;
+      ok = hipEventRecord(blobs_written, cs) == hipSuccess;
+      if (ok) ok = hipStreamWaitEvent(xs, blobs_written, 0) == hipSuccess;
     }
     if (order == KVC_ORDER_CHUNK) {
       for (int i = 0; i < n_chunks && ok; ++i) {
@@ -853,6 +858,8 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
         }
     }
     flush();
+    // A copy stream that has drained is done with the blobs, whoever reads them.
+    if (pairs_by_kernel && ok) ok = hipStreamWaitEvent(cs, pairs_read, 0) == hipSuccess;
   }
   if (ev.ok()) {
     if (!ok && result == KVC_OK) result = KVC_ERR_RUNTIME;

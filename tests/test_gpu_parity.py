@@ -769,6 +769,52 @@ def test_staged_pipelines_copy_what_a_short_chunk_holds(tail, modes):
             assert torch.equal(used, ref), f"graph replay {rep}"
 
 
+@pytest.mark.parametrize("order", [None, 0, 1])
+def test_blobs_may_be_written_again_once_the_copy_stream_has_drained(order):
+    """The compute stream is held up by other work while the staged pipelines copy; when the copy stream has drained the
+    blobs are overwritten, and the restores that come after must not see that."""
+    L, H, D, T, n, bs = 5, 8, 128, 96, 96 + 50, 16
+    kvc, C = hz.kvc, H * D
+    glo, olo = hz.layouts(L, H, D, "f16", T, 8, 128, 4, 8)
+    kv = kv_synth.make_kv(L, H, D, n, torch.float16, seed=41, device="cuda")
+    want_f, want_m = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    nb = (n + bs - 1) // bs
+    tab = kv_synth.make_block_table(nb, nb, 4)
+    want, _ = hz.oracle_paged(olo, want_f, want_m, 0, n, L, nb, bs, C, tab.numpy())
+    fb, mb, F = kvc.chunk_sizes(glo)
+    fs, moff = kvc.frame_size(glo), kvc.blob_meta_offset(glo)
+    blob = torch.zeros((2, moff + mb), dtype=torch.uint8, pin_memory=True)
+    for c in range(2):
+        blob[c, :fb].copy_(torch.from_numpy(want_f[c * fb:(c + 1) * fb]))
+        blob[c, moff:].copy_(torch.from_numpy(want_m.view(np.uint8)[c * mb:(c + 1) * mb]))
+    chunks = [(blob[0].data_ptr(), moff + mb, T), (blob[1].data_ptr(), moff + mb, n - T)]
+    dtab, cache = tab.cuda(), hz.PagedCache(L, nb, bs, C)
+    s_copy, s_comp = torch.cuda.Stream(), torch.cuda.Stream()
+    frames_a_slot, slots = 2 * F, 4          # room for every frame: no copy waits for a restore
+    tail = (cache.ptrs.data_ptr(), nb, bs, dtab.data_ptr(), nb, cache.err.data_ptr(), s_copy.cuda_stream, s_comp.cuda_stream)
+    if order is None:
+        staging = [torch.full((moff + mb,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(2)]
+        args = (glo, chunks, [t.data_ptr() for t in staging], moff + mb) + tail
+        call, more = kvc.kvc_fetch_pipeline, {}
+    else:
+        msz = kvc.meta_staging_size(glo, order)
+        staging = [torch.full((frames_a_slot * fs,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(slots)]
+        metas = [torch.full((msz,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(slots)]
+        args = (glo, chunks, [t.data_ptr() for t in staging], frames_a_slot * fs, [t.data_ptr() for t in metas], msz) + tail
+        call, more = kvc.kvc_fetch_pipeline_frames, {"order": order}
+    hz.say(f"[case] blobs written again after the copies, order {order}")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s_comp):
+        torch.cuda._sleep(100_000_000)
+    call(*args, timed=False, **more)
+    s_copy.synchronize()
+    blob.fill_(0xFF)
+    torch.cuda.synchronize()
+    assert int(cache.err.item()) == 0
+    for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
+        hz.assert_same_bytes(f"layer {l}", got, w)
+
+
 def test_restore_reads_frames_from_mapped_pinned_host_memory():
     """The frame pointer may be pinned host memory that is mapped into the device (no staging copy at all)."""
     L, H, D, T, n, bs = 3, 8, 128, 96, 96 + 40, 16
