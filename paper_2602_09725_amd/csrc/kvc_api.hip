@@ -60,15 +60,18 @@ bool in_host_memory(const void* p) {
   return a.type == hipMemoryTypeHost;
 }
 
-// Whether a kernel can read [p, p + bytes) where it is: pinned host memory, mapped at its own address.
+// Whether a kernel of the current device can read [p, p + bytes) where it is: pinned host memory, mapped into this device
+// at its own address.  Memory pinned while another device was current may be mapped into that one only.
 bool mapped_host_span(const void* p, size_t bytes) {
+  int device = -1;
+  if (hipGetDevice(&device) != hipSuccess) return false;
   for (const void* q : {p, static_cast<const void*>(static_cast<const uint8_t*>(p) + bytes - 1)}) {
     hipPointerAttribute_t a;
     if (hipPointerGetAttributes(&a, q) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
-    if (a.type != hipMemoryTypeHost || a.devicePointer != q) return false;
+    if (a.type != hipMemoryTypeHost || a.device != device || a.devicePointer != q) return false;
   }
   return true;
 }
