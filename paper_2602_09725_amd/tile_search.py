@@ -21,10 +21,12 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
     C = H * D
     strides = (2 * n_tokens * C, n_tokens * C, C)
     n_chunks = (n_tokens + chunk_tokens - 1) // chunk_tokens
-    candidates = candidates or kvc.tile_candidates(H, D)
+    candidates = list(candidates or kvc.tile_candidates(H, D))  # any iterable
     rows = []
     # everything is enqueued before the first cost is looked at; buffers a candidate leaves are the next one's
     stream = stream or torch.cuda.current_stream()
+    if not isinstance(stream, torch.cuda.Stream):  # anything that carries a stream's handle
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=kv.device)
     with torch.cuda.stream(stream):
         sh = stream.cuda_stream
         costs = torch.empty((len(candidates), n_chunks * 2 * L), dtype=torch.float64, device=kv.device)

@@ -152,3 +152,21 @@ def test_rank_tiles_orders_candidates_like_the_oracle():
         assert abs(r["cost_bits"] - w) <= 1e-12 * w, r
     assert [r["cost_bits"] for r in rows] == sorted(r["cost_bits"] for r in rows)
     hz.say("[case] tile ranking: " + ", ".join(f"({r['tile_h']},{r['tile_w']},{r['tile_seg']}) {r['bits_per_element']:.3f}" for r in rows[:5]))
+
+
+def test_rank_tiles_takes_any_iterable_and_any_stream_handle():
+    from types import SimpleNamespace
+
+    from paper_2602_09725_amd import tile_search
+
+    L, H, D, n = 2, 2, 32, 48
+    kv = kv_synth.make_kv_correlated(L, H, D, n, torch.float16, seed=78, device="cuda")
+    torch.cuda.synchronize()
+    args = (kv, n, hz.kvc.KVC_F16, 32, 64, 32)
+    want = tile_search.rank_tiles(*args)
+    some = [(r["tile_h"], r["tile_w"], r["tile_seg"]) for r in want[:3]]
+    side = torch.cuda.Stream()
+    handle = SimpleNamespace(cuda_stream=side.cuda_stream)
+    for candidates, stream in ((iter(some), None), ((c for c in some), side), (tuple(some), handle), (None, handle), ([], None)):
+        got = tile_search.rank_tiles(*args, candidates=candidates, stream=stream)
+        assert got == (want[:3] if candidates else want)
