@@ -164,19 +164,39 @@ size_t kvc_blob_meta_offset(const kvc_layout* layout);
 kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens,
                     uint8_t* frames, size_t frames_cap, void* meta, size_t meta_cap, void* stream);
 
-/* How kvc_pack would run for this layout and these strides: host arithmetic
- * only, nothing is enqueued (Sec. 4 item (1), the offline compression pass).
+/* How kvc_pack would run a call of many chunks with this layout and these
+ * strides: host arithmetic only, nothing is enqueued (Sec. 4 item (1), the
+ * offline compression pass).
  *   *resident  HOST out, nullable: 1 when the strip of channels a workgroup
  *              quantizes per channel is held on chip for a whole chunk, so that
  *              the input is read from memory once; 0 when the last 3072 tokens
  *              of a chunk's strip wait on chip and the tokens before them are
- *              read twice (chunk_tokens > 2048, or 2048 * token_stride * 2
- *              bytes does not fit the 32-bit offsets of the resident body; a
- *              call of few tokens or few layers may hold all of a chunk even
- *              so), or when no kind is quantized per channel
+ *              read twice (chunk_tokens > 2048, or the token_stride * 2 bytes
+ *              of a strip's rows, 2048 or for chunks of up to 512 tokens 512 of
+ *              them, do not fit 32-bit offsets), or when no kind is quantized
+ *              per channel
  *   *threads   HOST out, nullable: threads per workgroup of the launch
- * Returns the status kvc_pack would return for the same layout and strides. */
+ * Returns the status kvc_pack would return for the same layout and strides.  A
+ * call of few tokens or few layers may hold all of a chunk even where *resident
+ * is 0: kvc_pack_form has the answer for a call. */
 kvc_status kvc_pack_plan(const kvc_layout* layout, kvc_strides strides, int32_t* resident, int32_t* threads);
+
+/* Forms a kvc_pack launch takes. */
+typedef enum kvc_pack_launch_form {
+  KVC_PACK_RESIDENT = 0, /* a strip of up to 2048 tokens waits on chip, its workgroup has a CU to itself    */
+  KVC_PACK_TWO_PASS = 1, /* all but the last tokens of a strip are read twice; also per-token kinds alone   */
+  KVC_PACK_LIGHT = 2,    /* few loads a thread: few tokens, or few strips, which are then made narrower      */
+  KVC_PACK_MEDIUM = 3    /* up to 1024 tokens of a strip wait on chip, two workgroups to a CU                */
+} kvc_pack_launch_form;
+
+/* The form kvc_pack takes for n_tokens >= 1 tokens: host arithmetic only.
+ *   *form            HOST out, nullable: a kvc_pack_launch_form
+ *   *strip_channels  HOST out, nullable: channels of a per-channel workgroup's
+ *                    strip, 0 when no kind is quantized per channel
+ *   *threads         HOST out, nullable: threads per workgroup
+ * Returns the status kvc_pack would return, pointers and capacities apart. */
+kvc_status kvc_pack_form(const kvc_layout* layout, kvc_strides strides, int64_t n_tokens, int32_t* form,
+                         int32_t* strip_channels, int32_t* threads);
 
 /* Fetch side into a contiguous tensor (Sec. 3.3.2 frame-wise restoration:
  * unpack + dequantize).

@@ -229,19 +229,42 @@ kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides stride
   return launch_pack(p, as_stream(stream));
 }
 
-kvc_status kvc_pack_plan(const kvc_layout* layout, kvc_strides strides, int32_t* resident, int32_t* threads) {
-  PackParams p{};
-  kvc_status st = make_geo(layout, &p.g);
+namespace {
+
+// Plan of a pack call on n_tokens tokens, or of a call of many chunks (n_tokens < 0).
+kvc_status plan_of_pack(const kvc_layout* layout, kvc_strides strides, int64_t n_tokens, PackParams* p, int* threads) {
+  kvc_status st = make_geo(layout, &p->g);
   if (st != KVC_OK) return st;
   if ((st = check_strides(strides)) != KVC_OK) return st;
-  if (strides.token_stride < p.g.C) return KVC_ERR_INVALID_ARG;
-  p.ls = strides.layer_stride;
-  p.ks = strides.kv_stride;
-  p.ts = strides.token_stride;
-  p.n_tokens = p.g.T;
+  if (strides.token_stride < p->g.C) return KVC_ERR_INVALID_ARG;
+  p->ls = strides.layer_stride;
+  p->ks = strides.kv_stride;
+  p->ts = strides.token_stride;
+  p->n_tokens = n_tokens < 0 ? p->g.T : n_tokens;
+  return plan_pack(*p, threads, n_tokens < 0);
+}
+
+}  // namespace
+
+kvc_status kvc_pack_plan(const kvc_layout* layout, kvc_strides strides, int32_t* resident, int32_t* threads) {
+  PackParams p{};
   int th = 0;
-  if ((st = plan_pack(p, &th)) != KVC_OK) return st;
+  const kvc_status st = plan_of_pack(layout, strides, -1, &p, &th);
+  if (st != KVC_OK) return st;
   if (resident) *resident = p.resident;
+  if (threads) *threads = th;
+  return KVC_OK;
+}
+
+kvc_status kvc_pack_form(const kvc_layout* layout, kvc_strides strides, int64_t n_tokens, int32_t* form,
+                         int32_t* strip_channels, int32_t* threads) {
+  if (n_tokens < 1 || n_tokens >= (1ll << 31)) return KVC_ERR_INVALID_ARG;
+  PackParams p{};
+  int th = 0;
+  const kvc_status st = plan_of_pack(layout, strides, n_tokens, &p, &th);
+  if (st != KVC_OK) return st;
+  if (form) *form = p.body;
+  if (strip_channels) *strip_channels = p.n_kinds_ch > 0 ? 8 * p.strip_atoms : 0;
   if (threads) *threads = th;
   return KVC_OK;
 }

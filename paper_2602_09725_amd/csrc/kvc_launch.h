@@ -68,7 +68,7 @@ struct PairSpan {
 // Enqueues the copy of two spans of pairs (8-byte aligned).
 kvc_status launch_copy_pairs(const PairSpan& a, const PairSpan& b, hipStream_t stream);
 
-constexpr int kPackResident = 0, kPackStream = 1, kPackLight = 2, kPackMedium = 3;
+constexpr int kPackResident = KVC_PACK_RESIDENT, kPackStream = KVC_PACK_TWO_PASS, kPackLight = KVC_PACK_LIGHT, kPackMedium = KVC_PACK_MEDIUM;
 
 // A range of work units and the share of one XCD.
 struct PackRange {
@@ -94,7 +94,7 @@ struct PackParams {
   int32_t rows;           // token rows per pass = threads / strip_atoms
   uint32_t pass_step;     // bytes the code offset of a thread grows per pass, 0 if that is not a constant
   int32_t n_kinds_ch;
-  int32_t body;           // kPackResident, kPackStream or kPackLight: which form the launch takes
+  int32_t body;           // which of the four forms above the launch takes
   int32_t resident;       // per-channel strips wait on chip as a whole (one read of the input)
   int32_t kinds_ch[2];
   // token positions of the tile rows a token can fall into: chunks of T tokens, and the call's last chunk
@@ -113,9 +113,10 @@ struct PackParams {
   uint32_t wgs_per_xcd;
 };
 
-// Host-side plan of a pack launch: which body the per-channel kinds take, block and grid
-// shape.  Fills the derived fields of `p` (geometry, strides and n_tokens must be set).
-kvc_status plan_pack(PackParams& p, int* threads_out);
+// Host-side plan of a pack launch: which form it takes, block and grid shape.  Fills the derived
+// fields of `p` (geometry, strides and n_tokens must be set).  many_chunks: the form and the threads
+// of a call of many chunks of T tokens.
+kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks);
 
 // Enqueues statistics + quantize + layout for every kind, plus the zero fill of
 // unused planes and tile positions.

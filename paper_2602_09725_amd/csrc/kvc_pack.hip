@@ -927,7 +927,7 @@ hipError_t launch_variant(dim3 grid, dim3 block, hipStream_t stream, const PackP
 
 }  // namespace
 
-kvc_status plan_pack(PackParams& p, int* threads_out) {
+kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   const Geo& g = p.g;
   p.n_chunks = (int32_t)((p.n_tokens + g.T - 1) / g.T);
   if (g.apt > 1024) return KVC_ERR_UNSUPPORTED;
@@ -947,14 +947,15 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
   // clamped afterwards), and inside the chunk's frame section; and a per-token kind in the same launch needs a thread
   // for every atom of a token.
   const int64_t most_tokens = p.n_tokens < g.T ? p.n_tokens : g.T;  // of a chunk of this call
-  const auto strips = [&](int atoms) { return (int64_t)p.n_chunks * p.n_kinds_ch * g.L * ((g.apt + atoms - 1) / atoms); };
+  const int64_t chunks = many_chunks ? 1 << 24 : p.n_chunks;
+  const auto strips = [&](int atoms) { return chunks * p.n_kinds_ch * g.L * ((g.apt + atoms - 1) / atoms); };
   const auto rows_of = [&](int loads, int atoms) { return (int64_t)loads * (kResidentThreads / atoms); };
   const auto fits = [&](int64_t tokens) { return tokens * p.ts * 2 < (1ll << 32) && g.frame_bytes < (1ll << 32); };
   const bool wide = p.n_kinds_tok > 0 && g.apt > kResidentThreads;
   p.body = kPackStream;
   p.strip_atoms = kResidentAtoms;
   if (p.n_kinds_ch == 0) {
-    if (!wide && (int64_t)g.L * p.n_kinds_tok * p.n_tokens < kFewTokenRows) p.body = kPackLight;
+    if (!wide && !many_chunks && (int64_t)g.L * p.n_kinds_tok * p.n_tokens < kFewTokenRows) p.body = kPackLight;
   } else if (!wide) {
     const int64_t most = rows_of(kResidentLoads, kResidentAtoms);
     if (g.T <= most && fits(most)) p.body = most_tokens <= rows_of(kMediumLoads, kResidentAtoms) ? kPackMedium : kPackResident;
@@ -1050,7 +1051,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out) {
 kvc_status launch_pack(PackParams p, hipStream_t stream) {
   if (p.n_tokens <= 0) return KVC_OK;
   int threads = 0;
-  const kvc_status st = plan_pack(p, &threads);
+  const kvc_status st = plan_pack(p, &threads, false);
   if (st != KVC_OK) return st;
   const Geo& g = p.g;
   const dim3 grid(p.wgs_per_xcd * 8u), block((unsigned)threads);

@@ -69,6 +69,7 @@ def load(path=None):
     lib.kvc_blob_meta_offset.restype = sz
     lib.kvc_pack.argtypes = [LP, vp, Strides, i64, vp, sz, vp, sz, vp]
     lib.kvc_pack_plan.argtypes = [LP, Strides, C.POINTER(i32), C.POINTER(i32)]
+    lib.kvc_pack_form.argtypes = [LP, Strides, i64, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     lib.kvc_restore.argtypes = [LP, vp, vp, i64, vp, Strides, vp]
     lib.kvc_restore_paged.argtypes = [LP, vp, vp, i64, i64, vp, i64, i32, vp, i64, vp, vp]
     lib.kvc_fetch_pipeline.argtypes = [LP, C.POINTER(HostChunk), i32, C.POINTER(vp), sz, i32, vp, i64, i32, vp, i64,
@@ -138,6 +139,13 @@ def pack_plan(layout, strides):
     r, t = C.c_int32(), C.c_int32()
     _check(load().kvc_pack_plan(C.byref(layout), Strides(*strides), C.byref(r), C.byref(t)), "kvc_pack_plan")
     return r.value, t.value
+
+
+def pack_form(layout, strides, n_tokens):
+    """-> (form, channels of a per-channel strip, threads per workgroup) kvc_pack takes for n_tokens tokens."""
+    f, w, t = C.c_int32(), C.c_int32(), C.c_int32()
+    _check(load().kvc_pack_form(C.byref(layout), Strides(*strides), n_tokens, C.byref(f), C.byref(w), C.byref(t)), "kvc_pack_form")
+    return f.value, w.value, t.value
 
 
 def blob_meta_offset(layout):

@@ -303,6 +303,36 @@ def test_pack_keeps_strips_resident_only_while_32_bit_row_offsets_hold(kvc_lib):
         kvc.pack_plan(good(), (0, 0, C - 8))
 
 
+RESIDENT, TWO_PASS, LIGHT, MEDIUM = 0, 1, 2, 3  # kvc_pack_launch_form
+
+
+def test_pack_plan_describes_calls_of_many_chunks(kvc_lib):
+    """The plan knows no number of tokens: it is that of a call of many chunks, whatever one chunk alone would take."""
+    for kw in (dict(num_layers=1, chunk_tokens=4000, tiles_y=500), dict(num_layers=2, chunk_tokens=4096, tiles_y=512)):
+        lo, strides, T = good(**kw), (0, 0, 1024), kw["chunk_tokens"]
+        assert kvc.pack_form(lo, strides, T)[0] == LIGHT                    # few strips: a chunk waits on chip
+        assert kvc.pack_form(lo, strides, 20 * T) == (TWO_PASS, 64, 1024)   # many: its tokens are read twice
+        assert kvc.pack_plan(lo, strides) == (0, 1024)
+    lo = good(num_layers=2, k_mode=1)
+    assert kvc.pack_form(lo, (0, 0, 1024), 2048) == (LIGHT, 0, 512) and kvc.pack_plan(lo, (0, 0, 1024)) == (0, 1024)
+    for n in (0, -1, 2**31):
+        with pytest.raises(kvc.KvcError):
+            kvc.pack_form(good(), (0, 0, 1024), n)
+    with pytest.raises(kvc.KvcError):
+        kvc.pack_form(good(), (0, 0, 1016), 5)
+
+
+def test_pack_launch_forms_are_those_the_parity_test_names(kvc_lib):
+    import test_gpu_parity as parity
+
+    want = [(RESIDENT, 128), (RESIDENT, 128), (MEDIUM, 128), (MEDIUM, 128), (LIGHT, 128), (LIGHT, 128), (LIGHT, 16), (LIGHT, 64),
+            (LIGHT, 32), (LIGHT, 16), (TWO_PASS, 64), (TWO_PASS, 0), (TWO_PASS, 0), (LIGHT, 32), (LIGHT, 0), (TWO_PASS, 32)]
+    assert len(want) == len(parity.PACK_FORMS)
+    for w, (L, H, D, T, th, tw, TX, TY, n, modes) in zip(want, parity.PACK_FORMS):
+        lo, C = kvc.Layout(L, H, D, 0, T, th, tw, TX, TY, *modes), H * D
+        assert kvc.pack_form(lo, (2 * n * C, n * C, C), n)[:2] == w, (L, H, T, n, modes)
+
+
 def test_tile_candidates_equal_the_oracles_enumeration(kvc_lib):
     from oracle import residuals as R
 
