@@ -171,14 +171,13 @@ kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides stride
  *              quantizes per channel is held on chip for a whole chunk, so that
  *              the input is read from memory once; 0 when the last 3072 tokens
  *              of a chunk's strip wait on chip and the tokens before them are
- *              read twice (chunk_tokens > 2048, or the token_stride * 2 bytes
- *              of a strip's rows, 2048 or for chunks of up to 512 tokens 512 of
- *              them, do not fit 32-bit offsets), or when no kind is quantized
- *              per channel
+ *              read twice (chunk_tokens > 2048, or 2048 * token_stride * 2
+ *              bytes does not fit the 32-bit offsets of the resident body), or
+ *              when no kind is quantized per channel
  *   *threads   HOST out, nullable: threads per workgroup of the launch
  * Returns the status kvc_pack would return for the same layout and strides.  A
- * call of few tokens or few layers may hold all of a chunk even where *resident
- * is 0: kvc_pack_form has the answer for a call. */
+ * call of few tokens, few layers or short chunks may hold all of a chunk even
+ * where *resident is 0: kvc_pack_form has the answer for a call. */
 kvc_status kvc_pack_plan(const kvc_layout* layout, kvc_strides strides, int32_t* resident, int32_t* threads);
 
 /* Forms a kvc_pack launch takes. */

@@ -115,7 +115,8 @@ struct PackParams {
 
 // Host-side plan of a pack launch: which form it takes, block and grid shape.  Fills the derived
 // fields of `p` (geometry, strides and n_tokens must be set).  many_chunks: the form and the threads
-// of a call of many chunks of T tokens.
+// of a call of many chunks of T tokens (light only where strips of 2048 tokens would be resident, which is
+// what kvc_pack_plan promises).
 kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks);
 
 // Enqueues statistics + quantize + layout for every kind, plus the zero fill of

@@ -963,7 +963,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
     int atoms = kResidentAtoms;
     while (atoms > kFewestAtoms && (rows_of(kLightLoads, atoms) < most_tokens || strips(atoms) < kFewStrips)) atoms /= 2;
     if (rows_of(kLightLoads, atoms) >= most_tokens && fits(rows_of(kLightLoads, atoms)) &&
-        (atoms == kResidentAtoms || strips(kResidentAtoms) <= kFewStrips)) {
+        (atoms == kResidentAtoms || strips(kResidentAtoms) <= kFewStrips) && !(many_chunks && p.body == kPackStream)) {
       p.body = kPackLight;
       p.strip_atoms = atoms;
     }
