@@ -79,6 +79,10 @@ __global__ void __launch_bounds__(kScoreThreads) clear_hist_kernel(uint64_t* his
   if (i < n) hist[i] = 0;
 }
 
+// FEW_FRAMES: groups of fewer than kFrames frames, of which several rows are loaded together (F = 1, two chunks of 80
+// layers: 300 -> 131 us).  A form of its own, since the index of a row and a frame for every piece costs the others 4 %
+// (F = 4, one chunk of 32 layers: 80.2 -> 83.4 us).
+template <bool FEW_FRAMES>
 __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const ScoreParams p) {
   __shared__ __attribute__((aligned(16))) Histogram hist[KVC_N_RESIDUALS];
   static_assert(sizeof(hist[0][0]) == 64, "the bytes of a bin are a factor of an 8-bit dot product");
@@ -108,15 +112,22 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
   const uint32_t rows_per_band = (p.part_rows + bands - 1u) / bands;
   const uint32_t y0 = part0 + band * rows_per_band;
   const uint32_t y1 = y0 + rows_per_band < part1 ? y0 + rows_per_band : part1;
-  // groups of fewer frames than are loaded together take several rows at once (F = 1, two chunks of 80 layers: 300 -> 131 us)
-  const uint32_t rows_at_once = F < (uint32_t)kFrames ? (uint32_t)kFrames / F : 1u;
+  const uint32_t rows_at_once = FEW_FRAMES ? (uint32_t)kFrames / F : 1u;
+  // item k of the rows that are taken together: frame k % F of row k / F
+  const auto item = [&](uint32_t k, uint32_t& dy, uint32_t& f) {
+    if (FEW_FRAMES) {
+      fd_divmod(g.dF, k, dy, f);
+    } else {
+      dy = 0u;
+      f = k;
+    }
+  };
   uint32_t zeros = 0u, zeros_later = 0u;  // pieces without any nonzero pixel around them, in all frames / frames >= 1
   for (uint32_t cb = col0; band < bands && cb < per_row; cb += cols)
   for (uint32_t y = y0; y < y1; y += rows_at_once) {
     const bool has_left = cb > 0u;
     const uint8_t* row = base + (size_t)(y * per_row + cb) * 8u;
-    // item k of these rows: frame k % F of row y + k / F
-    const uint32_t items = (y1 - y < rows_at_once ? y1 - y : rows_at_once) * F;
+    const uint32_t items = FEW_FRAMES ? (y1 - y < rows_at_once ? y1 - y : rows_at_once) * F : F;
     Piece prev{}, prev_l{}, prev_u{};
     uint32_t prev_any = 0u;
     for (uint32_t k0 = 0; k0 < items; k0 += kFrames) {
@@ -125,7 +136,7 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
 #pragma unroll
       for (int k = 0; k < kFrames; ++k) {
         uint32_t dy, f;
-        fd_divmod(g.dF, k0 + k < items ? k0 + k : items - 1u, dy, f);
+        item(k0 + k < items ? k0 + k : items - 1u, dy, f);
         const uint8_t* px = row + (dy * W + (size_t)f * (size_t)frame_stride);
         cur[k] = *(const KVC_GLOBAL u32x2*)px;  // cached: the next row reads it again as its upper neighbour
         up[k] = *(const KVC_GLOBAL u32x2*)(y + dy > 0u ? px - W : px);  // stays inside the plane: row 0 and column 0 read themselves
@@ -135,16 +146,16 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
       for (int k = 0; k < kFrames; ++k) {
         if (k0 + k >= items) break;
         uint32_t dy, f;
-        fd_divmod(g.dF, k0 + k, dy, f);
+        item(k0 + k, dy, f);
         if (y + dy == 0u) up[k] = u32x2{0u, 0u};
         if (!has_left) left[k] = 0u;
-        if (f == 0u) prev_any = 0u;
+        if (FEW_FRAMES && f == 0u) prev_any = 0u;
         // Tiles without a token are zero: where a whole wave sees nothing else, its residuals are counted at the end.
         const uint32_t any = cur[k].x | cur[k].y | up[k].x | up[k].y | left[k];
         if (__ballot((any | prev_any) != 0u) == 0u) {
           ++zeros;
           zeros_later += f > 0u ? 1u : 0u;
-          prev = prev_l = prev_u = Piece{};
+          if (FEW_FRAMES) prev = prev_l = prev_u = Piece{};  // a row may start here; else they are zero already
           continue;
         }
         const Piece now = split(cur[k]);
@@ -251,7 +262,7 @@ kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream) {
     const uint32_t n = (uint32_t)(streams * (KVC_N_RESIDUALS * 256));  // fewer than kScoreWorkgroups streams
     hipLaunchKernelGGL(clear_hist_kernel, dim3((n + kScoreThreads - 1) / kScoreThreads), dim3(kScoreThreads), 0, stream, p.hist, n);
   }
-  hipLaunchKernelGGL(residual_hist_kernel, dim3((uint32_t)(streams * parts)), dim3(kScoreThreads), 0, stream, p);
+  hipLaunchKernelGGL(g.F < kFrames ? residual_hist_kernel<true> : residual_hist_kernel<false>, dim3((uint32_t)(streams * parts)), dim3(kScoreThreads), 0, stream, p);
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
 }
 
