@@ -58,15 +58,16 @@ struct RestoreParams {
 // Enqueues the fused unpack + dequantize + placement kernel.
 kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream);
 
-// A run of {scale, mn} pairs in pinned host memory that is mapped into the device, and where they go.
-struct PairSpan {
+// {scale, mn} pairs of one kind in pinned host memory that is mapped into the device, and where they go: the same number
+// of each layer, layers a pitch apart.
+struct PairRows {
   const void* src;
   void* dst;
-  uint32_t pairs;  // at least 1
+  uint32_t pairs, pitch;  // of a layer (at least 1), from one layer to the next
 };
 
-// Enqueues the copy of two spans of pairs (8-byte aligned).
-kvc_status launch_copy_pairs(const PairSpan& a, const PairSpan& b, hipStream_t stream);
+// Enqueues the copy of the pairs of a few layers (8-byte aligned).
+kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t layers, hipStream_t stream);
 
 constexpr int kPackResident = KVC_PACK_RESIDENT, kPackStream = KVC_PACK_TWO_PASS, kPackLight = KVC_PACK_LIGHT, kPackMedium = KVC_PACK_MEDIUM;
 

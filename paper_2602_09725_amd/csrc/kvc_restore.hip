@@ -430,30 +430,35 @@ void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 blo
 #undef KVC_LAUNCH_RESTORE
 }
 
-// Copies two spans of {scale, mn} pairs out of pinned host memory, a workgroup 8 KB of one of them.
+// Copies {scale, mn} pairs of a few layers out of pinned host memory: one row of the grid for each layer of each kind, a
+// workgroup 8 KB of it.
 constexpr uint32_t kCopyThreads = 256, kCopyPerThread = 4;
-__global__ void __launch_bounds__(kCopyThreads) copy_pairs_kernel(PairSpan a, PairSpan b, uint32_t wgs_a) {
-  const bool second = blockIdx.x >= wgs_a;
-  const PairSpan s = second ? b : a;
-  const uint32_t i0 = (blockIdx.x - (second ? wgs_a : 0u)) * (kCopyThreads * kCopyPerThread) + threadIdx.x;
-  u32x2 v[kCopyPerThread];
+__global__ void __launch_bounds__(kCopyThreads) copy_pairs_kernel(PairRows k, PairRows v, uint32_t layers) {
+  const bool second = blockIdx.y >= layers;
+  const PairRows s = second ? v : k;
+  const uint32_t i0 = blockIdx.x * (kCopyThreads * kCopyPerThread) + threadIdx.x;
+  if (blockIdx.x * (kCopyThreads * kCopyPerThread) >= s.pairs) return;
+  const size_t row = (size_t)(blockIdx.y - (second ? layers : 0u)) * s.pitch;
+  const u32x2* const src = static_cast<const u32x2*>(s.src) + row;
+  u32x2* const dst = static_cast<u32x2*>(s.dst) + row;
+  u32x2 w[kCopyPerThread];
 #pragma unroll
-  for (uint32_t k = 0; k < kCopyPerThread; ++k) {
-    const uint32_t i = i0 + k * kCopyThreads;
-    v[k] = stream_load<u32x2>(static_cast<const u32x2*>(s.src) + (i < s.pairs ? i : s.pairs - 1u));
+  for (uint32_t j = 0; j < kCopyPerThread; ++j) {
+    const uint32_t i = i0 + j * kCopyThreads;
+    w[j] = stream_load<u32x2>(src + (i < s.pairs ? i : s.pairs - 1u));
   }
 #pragma unroll
-  for (uint32_t k = 0; k < kCopyPerThread; ++k) {
-    const uint32_t i = i0 + k * kCopyThreads;
-    if (i < s.pairs) static_cast<u32x2*>(s.dst)[i] = v[k];
+  for (uint32_t j = 0; j < kCopyPerThread; ++j) {
+    const uint32_t i = i0 + j * kCopyThreads;
+    if (i < s.pairs) dst[i] = w[j];
   }
 }
 
 }  // namespace
 
-kvc_status launch_copy_pairs(const PairSpan& a, const PairSpan& b, hipStream_t stream) {
-  const auto wgs = [](uint32_t pairs) { return (pairs + kCopyThreads * kCopyPerThread - 1) / (kCopyThreads * kCopyPerThread); };
-  hipLaunchKernelGGL(copy_pairs_kernel, dim3(wgs(a.pairs) + wgs(b.pairs)), dim3(kCopyThreads), 0, stream, a, b, wgs(a.pairs));
+kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t layers, hipStream_t stream) {
+  const uint32_t most = k.pairs > v.pairs ? k.pairs : v.pairs, per_wg = kCopyThreads * kCopyPerThread;
+  hipLaunchKernelGGL(copy_pairs_kernel, dim3((most + per_wg - 1) / per_wg, 2 * layers), dim3(kCopyThreads), 0, stream, k, v, layers);
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
 }
 

@@ -735,7 +735,7 @@ def test_staged_pipelines_copy_what_a_short_chunk_holds(tail, modes):
     for order, per_slot, n_fs, n_ms in ((None, 0, 2, 0), (0, 3, 3, 2), (0, 2 * F, 2, 2), (1, 3, 3, 2), (1, 2 * F, 2, 2), (1, 7 * F, 2, 3)):
         cache = hz.PagedCache(L, nb, bs, C)
         if order is None:
-            slots = poisoned(n_fs, moff + mb)
+            slots, metas = poisoned(n_fs, moff + mb), []
             args = (glo, chunks, [t.data_ptr() for t in slots], moff + mb)
             call = kvc.kvc_fetch_pipeline
             more = {}
@@ -759,7 +759,7 @@ def test_staged_pipelines_copy_what_a_short_chunk_holds(tail, modes):
             joined.record(s_comp)
             s_copy.wait_event(joined)
         for rep in range(2):
-            for t in cache.layers + slots:
+            for t in cache.layers + slots + metas:
                 t.fill_(0x6E)
             torch.cuda.synchronize()
             graph.replay()
@@ -1129,3 +1129,43 @@ def test_nan_does_not_spread_over_its_group(T, n, dtype):
     frames, meta = hz.gpu_pack(glo, kv, n)
     hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
     hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
+
+
+@pytest.mark.parametrize("off", [0, 4])
+@pytest.mark.parametrize("modes", [(0, 1), (1, 1)])
+def test_layer_order_moves_the_pairs_of_tokens_that_exist(modes, off):
+    """A short chunk of a long layout: of the per-token pairs of a layer only those of its tokens reach the staging, fetched
+    by the kernel (off = 0) and by copies (a blob at an address the kernel does not take)."""
+    L, H, D, T, n, bs = 6, 8, 16, 8192, 33, 16
+    kvc, C = hz.kvc, H * D
+    glo, olo = hz.layouts(L, H, D, "f16", T, 1, 128, 8, 256, *modes)
+    kv = kv_synth.make_kv(L, H, D, n, torch.float16, seed=43, device="cuda")
+    want_f, want_m = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    nb = (n + bs - 1) // bs
+    tab = kv_synth.make_block_table(nb, nb, 4)
+    want, _ = hz.oracle_paged(olo, want_f, want_m, 0, n, L, nb, bs, C, tab.numpy())
+    fb, mb, F = kvc.chunk_sizes(glo)
+    fs, moff, msz = kvc.frame_size(glo), kvc.blob_meta_offset(glo), kvc.meta_staging_size(glo, 1)
+    blob = torch.zeros((off + moff + mb,), dtype=torch.uint8, pin_memory=True)
+    blob[off:off + fb].copy_(torch.from_numpy(want_f))
+    blob[off + moff:].copy_(torch.from_numpy(want_m.view(np.uint8)))
+    staging = [torch.full((2 * F * fs,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    metas = [torch.full((msz,), 0xEE, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    dtab, cache = tab.cuda(), hz.PagedCache(L, nb, bs, C)
+    s_copy, s_comp = torch.cuda.Stream(), torch.cuda.Stream()
+    hz.say(f"[case] pairs of a short chunk in layer order, modes {modes}, blob off by {off}")
+    torch.cuda.synchronize()
+    kvc.kvc_fetch_pipeline_frames(glo, [(blob.data_ptr() + off, moff + mb, n)], [t.data_ptr() for t in staging], 2 * F * fs,
+                                  [t.data_ptr() for t in metas], msz, cache.ptrs.data_ptr(), nb, bs, dtab.data_ptr(), nb,
+                                  cache.err.data_ptr(), s_copy.cuda_stream, s_comp.cuda_stream, order=1, timed=False)
+    torch.cuda.synchronize()
+    for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
+        hz.assert_same_bytes(f"layer {l}", got, w)
+    per_layer = [T * H * 8 if m else C * 8 for m in modes]
+    for m in metas:  # [3 layers] of K, then of V
+        at = 0
+        for mode, size in zip(modes, per_layer):
+            for _ in range(3):
+                if mode:
+                    assert bool((m[at + n * H * 8:at + size] == 0xEE).all())
+                at += size
