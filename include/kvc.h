@@ -456,7 +456,9 @@ double kvc_proxy_cost_bits(const kvc_layout* layout, const uint64_t* hist, int64
  * every candidate's histograms otherwise: the costs add up to what
  * kvc_proxy_cost_bits returns (double; the sums are taken in another order).
  *   d_hist  DEVICE in : as kvc_residual_histograms wrote it, 8-byte aligned
- *   d_cost  DEVICE out: double [n_chunks][2][L], every entry written */
+ *   d_cost  DEVICE out: double [n_chunks][2][L], every entry written; 8-byte
+ *           aligned and n_chunks * 2 * L * 8 bytes long, which is not checked
+ * KVC_ERR_INVALID_ARG for a null or misaligned pointer (but for n_chunks 0). */
 kvc_status kvc_proxy_costs(const kvc_layout* layout, const uint64_t* d_hist, int64_t n_chunks, double* d_cost, void* stream);
 
 /* The tilings left by rules i-iii of Sec. 3.2.2 for H heads of D elements:

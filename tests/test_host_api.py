@@ -379,6 +379,19 @@ def test_residual_histograms_reject_bad_arguments(kvc_lib):
     kvc.kvc_residual_histograms(lo, A, 0, A, 0)   # nothing to do: returns before anything is enqueued
 
 
+def test_proxy_costs_reject_bad_arguments(kvc_lib):
+    """Pointers that are null or not 8-byte aligned, numbers of chunks and layouts that no call takes; nothing is enqueued."""
+    lo, A = good(), 0x7F0000000000
+    for args in ((0, 2, A), (A, 2, 0), (A + 4, 2, A), (A, 2, A + 4), (A, -1, A), (A, (1 << 24) + 1, A)):
+        with pytest.raises(kvc.KvcError) as e:
+            kvc.kvc_proxy_costs(lo, *args)
+        assert e.value.status == 1, args
+    with pytest.raises(kvc.KvcError) as e:
+        kvc.kvc_proxy_costs(good(num_layers=0), A, 2, A)
+    assert e.value.status == kvc.layout_validate(good(num_layers=0)) != 0
+    kvc.kvc_proxy_costs(lo, 0, 0, 0)   # nothing to do
+
+
 def test_probe_expand_rejects_bad_arguments(kvc_lib):
     A = 0x7F0000000000
     ok = dict(out=1 << 20, mp=0, piece=32768, wg=4096, shape=0)
