@@ -477,8 +477,18 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   const int trw = per_row >= kPasses ? 1 : kPasses / per_row;            // about one round of loads per wave
   const auto row_units = [&](int32_t n) { return (int32_t)ceil_div(ceil_div(ceil_div(n, g.F), g.TX), trw); };
   bool rows = q >= 2 && g.th <= 16;
-  if (rows && !p.host_frames) {
-    // Over the host link always (see above; 8 tiles of 64 bytes in runs of 13, 80 layers: 23.8 -> 44.0 GB/s).  From HBM
+  if (p.host_frames) {
+    // Over the host link what counts is the length of a read (below: GB/s of codes, 2048 tokens, the others' against that of
+    // "rows").  "rows" reads along a plane row of W bytes, the others the rows of a tile: pieces of tw bytes, but the whole
+    // tile where a row of tiles is one tile, and neighbouring tiles where they are one row high and a frame call takes them
+    // in turn (1 head, (1,128), 13 a row: 52.8 against 49.1).  Tiles of 256 bytes reach the link's rate either way (17 of
+    // (4,256) a row 56.9 against 53.9).  Planes of at most 128 bytes a row gain nothing by it (one tile of (8,128) 56.8
+    // against 46.9, two of (8,64) 52.1 against 45.9, four of (16,32) 51.1 against 47.6), but for two whole tiles of tokens
+    // of 1024 channels (two of (16,64) 43.2 against 48.6), wider ones do (three of (16,64) 40.3 against 53.0, two of
+    // (8,128) 42.9 against 56.7, 13 of (8,128) 43.9 against 52.3).
+    rows = rows && g.tw < 256 && (g.W > 128 || (g.W == 128 && g.TX == 2 && g.apt >= 128)) && !(p.frame_mode && g.th == 1);
+  } else if (rows) {
+    // From HBM
     // where the other bodies would read half lines (tiles of 64 bytes: 6000 tokens x 80 layers x 1024 channels 643 ->
     // 505 us, random table 520), unless runs are much longer than what is left for the last one (17 tiles: 585 -> 727 us)
     // or a token is one head (paged 137 -> 148 us); and for tiles of 128 bytes into a contiguous tensor, where rows of

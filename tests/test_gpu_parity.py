@@ -108,6 +108,12 @@ ROW_RUNS = [
     (4, 8, 128, 96, 8, 128, 0, 3, 11, 96 + 50, 16),      # rows of 3 tiles: one run, a quarter of it past the end
     (3, 4, 64, 70, 4, 64, 0, 13, 3, 70 + 31, 16),        # C = 256; rows of 13 tiles: a run of 8 and one of 5
     (2, 1, 128, 90, 2, 64, 0, 17, 2, 90 * 2 + 1, 8),     # C = 128, two waves; rows of 17 tiles
+    # ... and those that the other bodies take from host memory as well
+    (4, 8, 128, 96, 8, 128, 0, 1, 25, 96 + 50, 16),      # one tile a row: a token's tile is contiguous
+    (3, 2, 128, 70, 4, 64, 0, 2, 9, 70 + 33, 16),        # planes of 128 bytes a row, C = 256
+    (5, 4, 128, 50, 16, 32, 0, 4, 3, 50 * 2 + 7, 7),     # ... C = 512
+    (4, 8, 128, 96, 4, 256, 0, 3, 9, 96 + 17, 16),       # tile (4,256), rows of 3 tiles
+    (3, 1, 128, 90, 1, 128, 0, 5, 6, 90 + 1, 8),         # tiles one row high: chunk calls "rows", frame calls not
 ]
 
 
