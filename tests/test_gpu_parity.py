@@ -1027,8 +1027,11 @@ RESTORE_SHAPES = [
     (33, 1, 64, 512, 1, 64, 8, 64, 4000, 32),    # lanes, 4 passes
     (33, 1, 64, 512, 1, 64, 8, 32, 8200, 32),    # lanes, 8 passes
     (5, 3, 128, 70, 3, 128, 3, 5, 150, 16),      # C/8 = 48: 240 threads
-    (16, 4, 64, 3000, 4, 64, 13, 60, 3100, 16),  # tiles of 64 bytes: runs along plane rows, the last of 5 tiles
+    (16, 4, 64, 3000, 4, 64, 13, 60, 3100, 16),  # tiles of 64 bytes: runs along plane rows, the last of 5 tiles (contiguous)
     (16, 8, 128, 512, 8, 128, 8, 16, 3007, 16),  # tiles of 128 bytes: the same into a contiguous tensor only
+    (14, 4, 128, 2000, 8, 64, 13, 40, 2031, 16), # tiles of 64 bytes under a table, too
+    (14, 4, 128, 2000, 8, 64, 12, 42, 2031, 16), # ... a run and a half
+    (16, 8, 128, 512, 8, 128, 12, 8, 3007, 16),  # tiles of 128 bytes, 18 passes a row of tiles: whole waves
 ]
 
 
