@@ -644,14 +644,19 @@ constexpr int kMediumGroup = 4;
 // The light form keeps few loads, all in registers, and leaves out the groups of loads a chunk has no tokens for: a
 // strip of 128 tokens read 2048 rows before, most of them repeats of the last (128 tokens x 60 layers x 1024 channels
 // 80 -> 55 us with the zero fill of the chunk, 150 MB, in it).  It also takes launches of few strips, which are cut into
-// narrower ones (two layers of 2048 tokens, 16 strips of 128 channels: 26.5 -> 12.5 us in 128 strips of 16; with
-// 256 strips and more the full lines are worth more, 77 us against 94 for 32 layers), and per-token kinds alone up to
-// kFewTokenRows, where its smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger
-// workgroups of the streaming form are faster, two layers of 20 000 tokens 58 against 65 us).
+// narrower ones (two layers of 2048 tokens, 16 strips of 128 channels, in 128 strips of 16: 25 -> 10.8 us with the input
+// in the last-level cache, 27 -> 14.5 us with it in HBM; with 256 strips and more the full lines are worth more, 77 us
+// against 94 for 32 layers).  Narrow strips have to be no more than the CUs, or the few of the second round cost a whole
+// one (K per channel beside V per token, 4096-token chunks, strips of 16: 4 layers, 256 of them, 31 against 35.5 us in
+// the two-pass form, 5 layers 46 against 35, 16 layers 122 against 89; both kinds per channel, 2048 tokens, strips of 32:
+// 4 layers 18.5 against 26, 5 layers 28.5 against 26.5); strips of 32 beside per-token blocks, which fill that round, may be
+// more (10 layers, 320 of them, 33 against 39 us, 15 layers 42.3 against 42.6, 16 layers, 512, 47 against 44).  Per-token kinds
+// alone take the light form up to kFewTokenRows, where its smaller blocks fill the chip (two layers of 2048 tokens
+// 15.8 -> 7.6 us; beyond, the larger workgroups of the streaming form are faster, two layers of 20 000 tokens 58 against 65 us).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
-constexpr int64_t kFewStrips = 128, kFewTokenRows = 512 * 128, kFewTokenUnits = 512;
+constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kNarrowLong = 384, kFewTokenRows = 512 * 128, kFewTokenUnits = 512;
 
 template <int DT, int NR, int NS, bool SHORT>
 __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, uint32_t unit, uint32_t c0,
@@ -960,10 +965,12 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
     const int64_t most = rows_of(kResidentLoads, kResidentAtoms);
     if (g.T <= most && fits(most)) p.body = most_tokens <= rows_of(kMediumLoads, kResidentAtoms) ? kPackMedium : kPackResident;
     // The light form for few tokens, and for few strips: those are made narrower until there is one for every other CU.
+    const auto most_narrow = [&](int a) { return p.n_kinds_tok > 0 && a > kFewestAtoms ? kNarrowBesideTokens : kNarrow; };
     int atoms = kResidentAtoms;
     while (atoms > kFewestAtoms && (rows_of(kLightLoads, atoms) < most_tokens || strips(atoms) < kFewStrips)) atoms /= 2;
     if (rows_of(kLightLoads, atoms) >= most_tokens && fits(rows_of(kLightLoads, atoms)) &&
-        (atoms == kResidentAtoms || strips(kResidentAtoms) <= kFewStrips) && !(many_chunks && p.body == kPackStream)) {
+        (atoms == kResidentAtoms || (strips(kResidentAtoms) <= kFewStrips && strips(atoms) <= most_narrow(atoms))) &&
+        !(many_chunks && p.body == kPackStream)) {
       p.body = kPackLight;
       p.strip_atoms = atoms;
     }
@@ -974,12 +981,13 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // keep the strips in flight few, so that part of the second read still finds its strip in the last-level
   // cache: 10 240-token chunks pack in 1.37 ms this way against 1.83 ms with 256-thread workgroups.
   // Few strips are made as narrow as it takes for a whole chunk to wait on chip (two layers of 10 240 tokens: 77 -> 58 us;
+  // in strips of 16 six layers, 384 of them, 122 -> 109 us, seven, 448, 119 -> 126;
   // many strips lose by it, 1.35 -> 2.55 ms with half the width, since each input and code line is then several strips').
   if (p.body == kPackStream) {
     const auto on_chip = [&](int atoms) { return (int64_t)(kStreamTailLoads + kStreamStashLoads) * (kStreamThreads / atoms); };
     int atoms = kStreamAtoms;
     while (atoms > kFewestAtoms && on_chip(atoms) < most_tokens) atoms /= 2;
-    p.strip_atoms = strips(kStreamAtoms) < kFewStrips && on_chip(atoms) >= most_tokens ? atoms : kStreamAtoms;
+    p.strip_atoms = strips(kStreamAtoms) < kFewStrips && strips(atoms) <= kNarrowLong && on_chip(atoms) >= most_tokens ? atoms : kStreamAtoms;
   }
   const int want = p.body == kPackStream ? kStreamThreads : kResidentThreads;
   p.tpp = g.apt >= want ? 1 : want / g.apt;

@@ -333,6 +333,18 @@ def test_pack_launch_forms_are_those_the_parity_test_names(kvc_lib):
         assert kvc.pack_form(lo, (2 * n * C, n * C, C), n)[:2] == w, (L, H, T, n, modes)
 
 
+@pytest.mark.parametrize("modes,T,layers,want", [
+    ((0, 1), 2048, 15, (LIGHT, 32)), ((0, 1), 2048, 16, (RESIDENT, 128)),       # 480 strips of 32 channels, 512
+    ((0, 0), 2048, 4, (LIGHT, 32)), ((0, 0), 2048, 5, (RESIDENT, 128)),         # 256, 320: no per-token blocks beside them
+    ((0, 1), 4096, 4, (LIGHT, 16)), ((0, 1), 4096, 5, (TWO_PASS, 32)),          # 256 strips of 16, 320
+    ((0, 1), 1024, 16, (LIGHT, 64)), ((0, 1), 1024, 17, (MEDIUM, 128)),
+    ((0, 1), 10240, 6, (TWO_PASS, 16)), ((0, 1), 10240, 7, (TWO_PASS, 64)),     # 384 strips of 16, 448
+])
+def test_pack_cuts_few_strips_into_no_more_narrow_ones_than_pay(kvc_lib, modes, T, layers, want):
+    lo = good(num_layers=layers, chunk_tokens=T, tiles_y=T // 32, k_mode=modes[0], v_mode=modes[1])
+    assert kvc.pack_form(lo, (0, 0, 1024), T)[:2] == want
+
+
 def test_tile_candidates_equal_the_oracles_enumeration(kvc_lib):
     from oracle import residuals as R
 
