@@ -390,7 +390,7 @@ __device__ __forceinline__ void pack_token_body(const PackParams& p, uint32_t un
     for (int u = 0; u < U; ++u) {
       const int32_t t = tb0 + u * step + (int32_t)tsub;
       v[u] = u32x4{0u, 0u, 0u, 0u};
-      if (t < n) v[u] = stream_load<u32x4>(src + (int64_t)t * p.ts);
+      if (t < full_end) v[u] = stream_load<u32x4>(src + (int64_t)t * p.ts);  // what lies past the block is another's
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -651,8 +651,9 @@ constexpr int kMediumGroup = 4;
 // the two-pass form, 5 layers 46 against 35, 16 layers 122 against 89; both kinds per channel, 2048 tokens, strips of 32:
 // 4 layers 18.5 against 26, 5 layers 28.5 against 26.5); strips of 32 beside per-token blocks, which fill that round, may be
 // more (10 layers, 320 of them, 33 against 39 us, 15 layers 42.3 against 42.6, 16 layers, 512, 47 against 44).  Per-token kinds
-// alone take the light form up to kFewTokenRows, where its smaller blocks fill the chip (two layers of 2048 tokens
-// 15.8 -> 7.6 us; beyond, the larger workgroups of the streaming form are faster, two layers of 20 000 tokens 58 against 65 us).
+// alone take the light form up to kFewTokenRows rows, or as many bytes as that many rows of 1024 channels have, where its
+// smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger workgroups of the streaming
+// form are faster: two layers of 20 000 tokens 58 against 65 us, six layers of 2048 tokens of 4096 channels 64 against 76).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
@@ -960,7 +961,8 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   p.body = kPackStream;
   p.strip_atoms = kResidentAtoms;
   if (p.n_kinds_ch == 0) {
-    if (!wide && !many_chunks && (int64_t)g.L * p.n_kinds_tok * p.n_tokens < kFewTokenRows) p.body = kPackLight;
+    const int64_t rows = (int64_t)g.L * p.n_kinds_tok * p.n_tokens;
+    if (!wide && !many_chunks && rows < kFewTokenRows && rows * g.C < kFewTokenRows * 1024) p.body = kPackLight;
   } else if (!wide) {
     const int64_t most = rows_of(kResidentLoads, kResidentAtoms);
     if (g.T <= most && fits(most)) p.body = most_tokens <= rows_of(kMediumLoads, kResidentAtoms) ? kPackMedium : kPackResident;
@@ -1009,7 +1011,12 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   p.n_whole = n_last == g.T ? p.n_chunks : p.n_chunks - 1;
   const int64_t short_chunks = p.n_chunks - p.n_whole;  // 0 or 1
   const auto count_blocks = [&] { return (int64_t)p.n_whole * token_blocks(p.positions_full) + short_chunks * token_blocks(p.positions_last); };
-  while (p.body == kPackLight && p.tb > 16 && count_blocks() * g.L * p.n_kinds_tok < kFewTokenUnits) p.tb /= 2;
+  // Few blocks are made shorter until there are two for every CU; those of narrow tokens only as long as they are no more
+  // than that, or the few of the second round cost a whole one (128 channels, 3 layers of 2048 tokens: 384 blocks of 32
+  // tokens 5.3 us, 768 of 16 6.8; 256 channels 6.1 against 7.9), while wide tokens gain by the even spread (4096 channels, 3
+  // layers of 2048 tokens: 38 against 34; 1024 channels, 3 layers of 6000 tokens: 31 against 28.8).
+  const auto few = [&](int64_t blocks) { return g.C <= 256 ? 2 * blocks <= kFewTokenUnits : blocks < kFewTokenUnits; };
+  while (p.body == kPackLight && p.tb > 16 && few(count_blocks() * g.L * p.n_kinds_tok)) p.tb /= 2;
   p.tbc = token_blocks(p.positions_full);
   p.tbl = token_blocks(p.positions_last);
   // the blocks of the last chunk write the pairs of its tokens before this one, zero units the rest
