@@ -1076,11 +1076,12 @@ PACK_FORMS = [
     (9, 3, 128, 900, 3, 128, 7, 20, 901, (0, 1)),               # ... ragged: 48 atoms
     (2, 8, 128, 2100, 8, 128, 8, 80, 2100 + 7, (0, 1)),         # ... of chunks longer than a resident strip
     (1, 8, 128, 12400, 8, 128, 15, 135, 12400, (0, 1)),         # two-pass form, 64 channels: no strip holds a chunk
-    (32, 1, 64, 2048, 1, 64, 16, 64, 4200, (1, 1)),             # per token only, many rows; units of few bytes in runs
+    (32, 1, 64, 2048, 1, 64, 16, 64, 4200, (1, 1)),             # per token only, many rows; units of few bytes in eighths
     (32, 1, 128, 2048, 1, 128, 8, 64, 4200, (1, 1)),            # ... 64 tokens a pass, blocks of 256
     (9, 2, 128, 2048, 2, 128, 6, 60, 4100, (0, 1)),             # 128 strips; rows of 36 positions, blocks that end inside them
     (3, 1, 64, 2048, 1, 64, 16, 64, 70, (1, 1)),                # ... few rows; pairs of 1900 tokens to clear
     (2, 8, 128, 5000, 8, 128, 8, 80, 5000 + 7, (0, 1)),         # two-pass form, narrow strips that wait on chip whole
+    (45, 1, 128, 2048, 1, 128, 8, 64, 4200, (0, 1)),            # narrow tokens beside strips: blocks in runs of 8
 ]
 
 

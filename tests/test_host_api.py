@@ -326,7 +326,8 @@ def test_pack_launch_forms_are_those_the_parity_test_names(kvc_lib):
     import test_gpu_parity as parity
 
     want = [(RESIDENT, 128), (RESIDENT, 128), (MEDIUM, 128), (MEDIUM, 128), (LIGHT, 128), (LIGHT, 128), (LIGHT, 16), (LIGHT, 64),
-            (LIGHT, 32), (LIGHT, 16), (TWO_PASS, 64), (TWO_PASS, 0), (TWO_PASS, 0), (LIGHT, 32), (LIGHT, 0), (TWO_PASS, 32)]
+            (LIGHT, 32), (LIGHT, 16), (TWO_PASS, 64), (TWO_PASS, 0), (TWO_PASS, 0), (LIGHT, 32), (LIGHT, 0), (TWO_PASS, 32),
+            (RESIDENT, 128)]
     assert len(want) == len(parity.PACK_FORMS)
     for w, (L, H, D, T, th, tw, TX, TY, n, modes) in zip(want, parity.PACK_FORMS):
         lo, C = kvc.Layout(L, H, D, 0, T, th, tw, TX, TY, *modes), H * D
