@@ -22,10 +22,10 @@ struct RestoreParams {
   BandMap bands;          // chunk call
   // "rows" body: a wave reads runs of 512 bytes of one plane row, i.e. one row of rows_q = 512 / tw neighbouring
   // tiles; a workgroup (th waves) takes rows_trw rows of tiles, in all F frames (chunk call) or in one (frame call)
-  int32_t rows_body, rows_q, rows_lat;  // lat: log2 of the atoms of a tile row
+  int32_t rows_q, rows_lat;             // lat: log2 of the atoms of a tile row
   int32_t rows_trw, rows_tile_rows;     // rows of tiles per workgroup; rows of tiles that hold tokens
-  FastDiv dnf, dpr;                     // frames a unit covers (F or 1); passes per row of tiles = that * TX / q
-  int32_t host_frames;    // `frames` is host memory mapped into the device: take the "rows" body
+  FastDiv dnf, dpr;                     // frames a unit covers (F or 1); passes per row of tiles = that * runs of q tiles
+  int32_t host_frames;    // `frames` is host memory mapped into the device: the body with the longest reads
   FastDiv dapt;           // atoms per token
   FastDiv dwpt;           // waves per token (apt / 64) when apt is a multiple of 64
   uint32_t frame_stride;     // bytes from a frame to the next of the same layer group: 3 planes (0 for a frame call)

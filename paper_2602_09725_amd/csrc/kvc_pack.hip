@@ -641,19 +641,20 @@ static_assert(kResidentLds % kResidentGroup == 0, "the LDS slots are filled a wh
 constexpr int kMediumRegs = 24, kMediumLds = 8;
 constexpr int kMediumLoads = kMediumRegs + kMediumLds;
 constexpr int kMediumGroup = 4;
-// The light form keeps few loads, all in registers, and leaves out the groups of loads a chunk has no tokens for: a
-// strip of 128 tokens read 2048 rows before, most of them repeats of the last (128 tokens x 60 layers x 1024 channels
-// 80 -> 55 us with the zero fill of the chunk, 150 MB, in it).  It also takes launches of few strips, which are cut into
-// narrower ones (two layers of 2048 tokens, 16 strips of 128 channels, in 128 strips of 16: 25 -> 10.8 us with the input
-// in the last-level cache, 27 -> 14.5 us with it in HBM; with 256 strips and more the full lines are worth more, 77 us
-// against 94 for 32 layers).  Narrow strips have to be no more than the CUs, or the few of the second round cost a whole
-// one (K per channel beside V per token, 4096-token chunks, strips of 16: 4 layers, 256 of them, 31 against 35.5 us in
-// the two-pass form, 5 layers 46 against 35, 16 layers 122 against 89; both kinds per channel, 2048 tokens, strips of 32:
-// 4 layers 18.5 against 26, 5 layers 28.5 against 26.5); strips of 32 beside per-token blocks, which fill that round, may be
-// more (10 layers, 320 of them, 33 against 39 us, 15 layers 42.3 against 42.6, 16 layers, 512, 47 against 44).  Per-token kinds
+// The light form keeps few loads, all in registers, and leaves out the groups of loads a chunk has no tokens for: a strip
+// of 128 tokens read 2048 rows before, most of them repeats of the last (128 tokens x 60 layers x 1024 channels 80 -> 55
+// us with the zero fill of the chunk, 150 MB, in it).  It also takes launches of few strips, which are cut into narrower
+// ones (two layers of 2048 tokens, 16 strips of 128 channels, in 128 strips of 16: 25 -> 10.8 us with the input in the
+// last-level cache, 27 -> 14.5 us with it in HBM; with 256 strips and more the full lines are worth more, 77 us against 94
+// for 32 layers).  Narrow strips have to be no more than the CUs, or the few of the second round cost a whole one (K per
+// channel beside V per token, 4096-token chunks, strips of 16: 4 layers, 256 of them, 31 against 35.5 us in the two-pass
+// form, 5 layers 46 against 35, 16 layers 122 against 89; both kinds per channel, 2048 tokens, strips of 32: 4 layers 18.5
+// against 26, 5 layers 28.5 against 26.5); strips of 32 beside per-token blocks, which fill that round, may be more (10
+// layers, 320 of them, 33 against 39 us, 15 layers 42.3 against 42.6, 16 layers, 512, 47 against 44).  Per-token kinds
 // alone take the light form up to kFewTokenRows rows, or as many bytes as that many rows of 1024 channels have, where its
 // smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger workgroups of the streaming
-// form are faster: two layers of 20 000 tokens 58 against 65 us, six layers of 2048 tokens of 4096 channels 64 against 76).
+// form are faster: two layers of 20 000 tokens 58 against 65 us, six layers of 2048 tokens of 4096 channels 64 against
+// 76).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;

@@ -488,16 +488,16 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     // (8,128) 42.9 against 56.7, 13 of (8,128) 43.9 against 52.3).
     rows = rows && g.tw < 256 && (g.W > 128 || (g.W == 128 && g.TX == 2 && g.apt >= 128)) && !(p.frame_mode && g.th == 1);
   } else if (rows) {
-    // From HBM where the other bodies would read half lines (tiles of 64 bytes: 6000 tokens x 80 layers x 1024 channels 643 ->
-    // 505 us, random table 520), unless runs are much longer than what is left for the last one: into a contiguous tensor
-    // at least three quarters of a row's runs have to exist (17 tiles a row: 585 -> 727 us; 8192 tokens x 32 layers, 6 tiles 318 ->
-    // 294), under a table more (6 tiles a row 316 -> 331, 7 of them 324 -> 306), but for tokens of
-    // one wave (512 channels, 6 tiles a row 172 -> 156), and the token has to be more than two heads of 128 (two: 39 -> 43 us,
-    // one: 137 -> 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole runs and one
-    // round of loads takes them (8192 tokens x 32 layers, 8 tiles a row, F = 4: 283 -> 275 us; 12 tiles 287 -> 310, 16 tiles
-    // 283 -> 294, F = 16 148 -> 190 for 16 layers; under a random table 284 -> 287).  A launch that would not fill the chip is
-    // better cut finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us, 644 tokens in groups of 10 frames
-    // 21.6 against 24.8).
+    // From HBM where the other bodies would read half lines (tiles of 64 bytes: 6000 tokens x 80 layers x 1024 channels 643
+    // -> 505 us, random table 520), unless runs are much longer than what is left for the last one: into a contiguous tensor
+    // at least three quarters of a row's runs have to exist (17 tiles a row: 585 -> 727 us; 8192 tokens x 32 layers, 6 tiles
+    // 318 -> 294), under a table more (6 tiles a row 316 -> 331, 7 of them 324 -> 306), but for tokens of one wave (512
+    // channels, 6 tiles a row 172 -> 156), and the token has to be more than two heads of 128 (two: 39 -> 43 us, one: 137 ->
+    // 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole runs and one round of loads
+    // takes them (8192 tokens x 32 layers, 8 tiles a row, F = 4: 283 -> 275 us; 12 tiles 287 -> 310, 16 tiles 283 -> 294, F
+    // = 16 148 -> 190 for 16 layers; under a random table 284 -> 287).  A launch that would not fill the chip is better cut
+    // finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us, 644 tokens in groups of 10 frames 21.6 against
+    // 24.8).
     const int tiles4 = 4 * g.TX, runs3 = 3 * q * runs;
     const bool half_lines = g.tw < 128 && (paged ? g.apt > 32 && (tiles4 > runs3 || (tiles4 == runs3 && g.apt == 64))
                                                  : g.apt >= 32 && tiles4 >= runs3);
@@ -507,7 +507,6 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     rows = (half_lines || linear) && wgs >= kFillWorkgroups;
   }
   const int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
-  p.rows_body = rows ? 1 : 0;
   int u = kPasses, tpp = 1;
   int32_t tbl = 0;  // units of the last chunk of the call (chunk call), which need not be full
   if (rows) {

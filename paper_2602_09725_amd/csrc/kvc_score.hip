@@ -4,8 +4,8 @@
 // the search here ranks them by what a predictive coder would have to store: histograms of the
 // residuals of the 8-bit codes against the predictors a video codec has -- the pixel to the left,
 // the pixel above, the same pixel of the previous frame (Sec. 3.2.1 step 3 puts the next token
-// there), and that temporal residual after its own left / upper neighbour.  The kernel only counts;
-// entropies and the cost in bits are host arithmetic (kvc_proxy_cost_bits).
+// there), and that temporal residual after its own left / upper neighbour.  residual_hist_kernel only
+// counts; entropies and the cost in bits are proxy_cost_kernel's, or host arithmetic on copied counts (kvc_proxy_cost_bits).
 //
 // A plane sequence (chunk, kind, layer) is one workgroup's, or is cut into parts of whole rows (all frames) for
 // several workgroups where the streams alone would leave CUs idle; parts add their counts to the cleared output.
