@@ -28,7 +28,7 @@ HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, published peak
 # this command, not in this one, and are keyed by the identifier the library carries (a hash of its sources,
 # header and compiler flags): for any other build the figure is reported as null.
 MEASURED_TRAFFIC = {
-    "ce7eb51afb1997e3": {"pack": 6582142362, "restore": 6513961165},
+    "5183f408b0ed7c44": {"pack": 6582113382, "restore": 6513943654},
 }
 TRAFFIC_PROFILE = "profiles/pack_restore_llama3_8b_32k_paged.txt"
 
@@ -121,6 +121,8 @@ def main():
     pack_avg, rest_avg = sum(pack_ms) / len(pack_ms), sum(rest_ms) / len(rest_ms)
 
     traffic = MEASURED_TRAFFIC.get(kvc.build_id(), {}) if w.name == "llama3_8b_32k_paged" else {}
+    if w.name == "llama3_8b_32k_paged" and not traffic:
+        print(f"no measured HBM traffic for build {kvc.build_id()}: {TRAFFIC_PROFILE} is of another", file=sys.stderr)
 
     def roof(name, nbytes, avg_ms, all_ms):
         gbps = nbytes / (avg_ms * 1e-3) / 1e9

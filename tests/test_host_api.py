@@ -346,6 +346,15 @@ def test_pack_cuts_few_strips_into_no_more_narrow_ones_than_pay(kvc_lib, modes, 
     assert kvc.pack_form(lo, (0, 0, 1024), T)[:2] == want
 
 
+def test_measured_traffic_is_of_the_build_that_the_profile_names():
+    """The traffic figures that bench.py reports and the profile they were taken from are of one build."""
+    import bench
+
+    with open(os.path.join(ROOT, bench.TRAFFIC_PROFILE)) as f:
+        profile = f.read()
+    assert bench.MEASURED_TRAFFIC and all(f"build id {b}." in profile for b in bench.MEASURED_TRAFFIC)
+
+
 def test_tile_candidates_equal_the_oracles_enumeration(kvc_lib):
     from oracle import residuals as R
 
