@@ -164,14 +164,22 @@ size_t kvc_blob_meta_offset(const kvc_layout* layout);
 kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens,
                     uint8_t* frames, size_t frames_cap, void* meta, size_t meta_cap, void* stream);
 
+/* kvc_pack with another bound on a wait (test aid).  Workgroups that share a
+ * strip of a long chunk (kvc_pack_launch_form) tell each other the extremes of
+ * its columns; one that does not see all of them after `waits` further looks
+ * reads the whole chunk's columns itself.  The results are the same. */
+kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens,
+                          uint8_t* frames, size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits,
+                          void* stream);
+
 /* How kvc_pack would run a call of many chunks with this layout and these
  * strides: host arithmetic only, nothing is enqueued (Sec. 4 item (1), the
  * offline compression pass).
  *   *resident  HOST out, nullable: 1 when the strip of channels a workgroup
  *              quantizes per channel is held on chip for a whole chunk, so that
- *              the input is read from memory once; 0 when the last 3072 tokens
- *              of a chunk's strip wait on chip and the tokens before them are
- *              read twice (chunk_tokens > 2048, or 2048 * token_stride * 2
+ *              the input is read from memory once; 0 when a chunk's strip
+ *              is shared by several workgroups or all but its last 3072 tokens
+ *              are read twice (chunk_tokens > 2048, or 2048 * token_stride * 2
  *              bytes does not fit the 32-bit offsets of the resident body), or
  *              when no kind is quantized per channel
  *   *threads   HOST out, nullable: threads per workgroup of the launch
@@ -183,7 +191,9 @@ kvc_status kvc_pack_plan(const kvc_layout* layout, kvc_strides strides, int32_t*
 /* Forms a kvc_pack launch takes. */
 typedef enum kvc_pack_launch_form {
   KVC_PACK_RESIDENT = 0, /* a strip of up to 2048 tokens waits on chip, its workgroup has a CU to itself    */
-  KVC_PACK_TWO_PASS = 1, /* all but the last tokens of a strip are read twice; also per-token kinds alone   */
+  KVC_PACK_TWO_PASS = 1, /* long chunks: several workgroups share a strip, each of which holds a part of its
+                            tokens, or (few or unshareable strips) all but its last tokens are read twice;
+                            also per-token kinds alone                                                  */
   KVC_PACK_LIGHT = 2,    /* few loads a thread: few tokens, or few strips, which are then made narrower      */
   KVC_PACK_MEDIUM = 3    /* up to 1024 tokens of a strip wait on chip, two workgroups to a CU                */
 } kvc_pack_launch_form;

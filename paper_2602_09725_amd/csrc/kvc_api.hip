@@ -60,6 +60,17 @@ bool in_host_memory(const void* p) {
   return a.type == hipMemoryTypeHost;
 }
 
+// Whether p is memory of the current device.
+bool on_this_device(const void* p) {
+  int device = -1;
+  hipPointerAttribute_t a;
+  if (hipGetDevice(&device) != hipSuccess || hipPointerGetAttributes(&a, p) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return a.type == hipMemoryTypeDevice && a.device == device;
+}
+
 // Whether a kernel of the current device can read [p, p + bytes) where it is: pinned host memory, mapped into this device
 // at its own address.  Memory pinned while another device was current may be mapped into that one only.
 bool mapped_host_span(const void* p, size_t bytes) {
@@ -207,7 +218,13 @@ size_t kvc_blob_meta_offset(const kvc_layout* layout) {
 
 kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
                     size_t frames_cap, void* meta, size_t meta_cap, void* stream) {
+  return kvc_probe_pack(layout, kv, strides, n_tokens, frames, frames_cap, meta, meta_cap, kPackWaits, stream);
+}
+
+kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
+                          size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits, void* stream) {
   PackParams p{};
+  p.waits = waits;
   kvc_status st = make_geo(layout, &p.g);
   if (st != KVC_OK) return st;
   if (n_tokens < 0 || n_tokens >= (1ll << 31)) return KVC_ERR_INVALID_ARG;
@@ -226,6 +243,7 @@ kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides stride
   p.n_tokens = n_tokens;
   p.frames = frames;
   p.meta = static_cast<float*>(meta);
+  p.shareable = p.g.T > 2048 && on_this_device(frames);  // (shorter chunks have no strips to share)
   return launch_pack(p, as_stream(stream));
 }
 
@@ -241,6 +259,7 @@ kvc_status plan_of_pack(const kvc_layout* layout, kvc_strides strides, int64_t n
   p->ks = strides.kv_stride;
   p->ts = strides.token_stride;
   p->n_tokens = n_tokens < 0 ? p->g.T : n_tokens;
+  p->shareable = 1;
   return plan_pack(*p, threads, n_tokens < 0);
 }
 

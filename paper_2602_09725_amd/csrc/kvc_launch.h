@@ -71,6 +71,10 @@ kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t laye
 
 constexpr int kPackResident = KVC_PACK_RESIDENT, kPackStream = KVC_PACK_TWO_PASS, kPackLight = KVC_PACK_LIGHT, kPackMedium = KVC_PACK_MEDIUM;
 
+// How often the members of a shared strip look for each other's extremes before they do without: about a microsecond
+// each, where the others start within a few.
+constexpr uint32_t kPackWaits = 1024;
+
 // A range of work units and the share of one XCD.
 struct PackRange {
   uint32_t units, per_xcd;
@@ -110,6 +114,11 @@ struct PackParams {
   PackRange ch[2], tok[2], zero;
   uint32_t tok_run;       // consecutive per-token units that go to one XCD in turn, a power of two; 0: an eighth of them each
   int32_t n_whole;
+  // chunks whose strips several workgroups share (0 tokens: none does): tokens of a workgroup, workgroups of a strip of a
+  // whole chunk and of the last chunk, and how often they look for each other's extremes
+  int32_t shareable;  // `frames` is memory of the device, where workgroups can count each other
+  int32_t member_tokens, members_full, members_last;
+  uint32_t waits;
   int32_t light_last;     // resident launch: the short last chunk's strips take the light form
   uint32_t wgs_per_xcd;
 };

@@ -15,9 +15,11 @@
 //    column min/max (registers + one LDS step across waves) and quantized from
 //    where it waits; chunks of up to 1024 tokens take half as much, two
 //    workgroups to a CU; few tokens, or few strips cut narrower, a light form
-//    with 16 loads a thread; of longer chunks the last 3072 tokens wait on chip
-//    and the tokens before them are read twice (statistics, then quantization),
-//    unless strips are so few that they are cut to hold a whole chunk.
+//    with 16 loads a thread; the strips of longer chunks are shared by several
+//    workgroups that tell each other their column min/max; where that does not
+//    pay, the last 3072 tokens wait on chip and the tokens before them are read
+//    twice (statistics, then quantization), unless strips are so few that they
+//    are cut to hold a whole chunk.
 // Both kernels write every byte of their part of the frame section, zero for
 // tile positions without a token and for the planes of layers beyond L, so the
 // caller never has to clear the buffer.
@@ -440,11 +442,17 @@ __device__ __forceinline__ void add_numbers_again(ColumnStats<DT>& st, const voi
 // parameters: lanes of a wave that hold the same atom differ by multiples of strip_atoms and are merged first, one
 // lane per atom leaves the wave's extremes in LDS, one thread per channel finishes the reduction, derives the
 // parameters, writes the channel's {scale, mn} pair, and hands {mn, inv} to all threads through LDS.  Two barriers;
-// every thread of the workgroup must come here.
-template <int DT>
+// every thread of the workgroup must come here.  `others` makes the extremes of the workgroup's tokens those of the whole
+// strip where several workgroups share it.
+struct Alone {  // the workgroup has all tokens of its strip
+  __device__ __forceinline__ void exchange(float&, float&) {}
+};
+
+template <int DT, typename Others = Alone>
 __device__ __forceinline__ void strip_parameters(const PackParams& p, ColumnStats<DT>& st, uint32_t strip, uint32_t kind,
                                                  uint32_t l, uint32_t c, float (*red_lo)[kMaxStripAtoms * 8],
-                                                 float (*red_hi)[kMaxStripAtoms * 8], float (&mnv)[8], float (&inv)[8]) {
+                                                 float (*red_hi)[kMaxStripAtoms * 8], float (&mnv)[8], float (&inv)[8],
+                                                 Others others = Alone{}) {
   const Geo& g = p.g;
   const uint32_t tid = threadIdx.x;
   const uint32_t sa = (uint32_t)p.strip_atoms;
@@ -470,6 +478,7 @@ __device__ __forceinline__ void strip_parameters(const PackParams& p, ColumnStat
       l0 = __builtin_fminf(l0, red_lo[w][tid]);
       h0 = __builtin_fmaxf(h0, red_hi[w][tid]);
     }
+    others.exchange(l0, h0);
     const GroupParams q = group_params(l0, h0);
     par_mn[tid] = q.mn;
     par_inv[tid] = q.inv;
@@ -658,15 +667,101 @@ constexpr int kMediumGroup = 4;
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
+constexpr int64_t kFewLineStrips = 64, kCus = 256;
 constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kNarrowLong = 384, kFewTokenRows = 512 * 128, kFewTokenUnits = 512;
 
-template <int DT, int NR, int NS, bool SHORT>
+// Shared strips: chunks longer than a strip that waits on chip are cut along their tokens for several workgroups (members),
+// each of which holds its tokens as a resident strip does and needs from the others only the extremes of their columns.  So
+// the input is read once, and strips can be as wide as a line of codes (10 240-token chunks of 32 layers x 1024 channels,
+// three of them on 1080P frames: 1333 us with strips of 64 channels read twice, 1180 shared, 128 channels wide, 1312 shared
+// with 64; 4096-token chunks 1187 -> 1075; 1024 threads with 16 + 8 loads each, one workgroup a CU; two of 512 threads with 24 +
+// 8 took 1203, one with 46 + 18 1229).
+//
+// The exchange needs no memory of its own: member j leaves the extremes of channel ch, two 16-bit values, in a word of the
+// codes of the chunk's token 4 j + (ch % 8) / 2, and the codes of token 4 * members hold the number of members that have
+// read all words.  A kernel ahead on the stream has set the words to a value that no extremes have (a NaN twice) and the
+// number to zero.  Every word is written once, by one atomic store, and says itself whether it has been, so no fence and no
+// order between different words is needed.  The member that finds itself the last reader stores the codes of those tokens;
+// nobody reads a word after that.
+//
+// The members of a strip are neighbours in the order of dispatch and on one XCD.  A member that does not see all words after
+// `waits` tries waits no longer: it reads the columns of the whole chunk itself, with the same result.  So the kernel ends
+// wherever and in whatever order its workgroups run.
+constexpr int kSharedRegs = 16, kSharedLds = 8, kSharedLoads = kSharedRegs + kSharedLds;  // loads of a thread that wait
+static_assert(kSharedLds == kStreamStashLoads, "the launch of the two-pass form is theirs");
+constexpr uint32_t kEmptySlot = 0xffffffffu;
+constexpr uint32_t kSlotTokens = 4;    // tokens whose codes are a member's slots: 4 bytes a channel, 1 byte a code
+constexpr uint32_t kClearThreads = 256;
+constexpr int kMostMembers = 128;      // the slots are in the first member's tokens
+
+// The word of channel ch (of a strip that starts with element strip_e) in the codes of token t.
+struct StripSlots {
+  const Geo& g;
+  uint8_t* fplane;
+  uint32_t strip_e;
+  __device__ __forceinline__ KVC_GLOBAL uint32_t* at(uint32_t t, uint32_t ch) const {
+    uint32_t r, cc;
+    tile_pos(g, strip_e + (ch & ~7u), r, cc);
+    return (KVC_GLOBAL uint32_t*)(code_addr(g, fplane + (r * (uint32_t)g.W + cc), t)) + (ch & 1u);
+  }
+};
+
+// The members of a strip, as one of them sees them: thread ch of the workgroup brings the extremes of channel ch.
+template <int DT>
+struct Members {
+  StripSlots slots;
+  uint32_t me, members, waits;
+  uint32_t* late;  // LDS, set when a word did not come
+  bool real;       // the thread's channel exists
+  __device__ __forceinline__ void exchange(float& lo, float& hi) {
+    if (members == 1u || !real) return;
+    const uint32_t ch = threadIdx.x, sub = (ch & 7u) >> 1;
+    // both values are 16-bit ones, so nothing is rounded
+    __hip_atomic_store(slots.at(me * kSlotTokens + sub, ch), narrow_pair<DT>(lo, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    constexpr uint32_t J = 4;  // words asked for at once
+    uint32_t tries = 0;
+    for (uint32_t j0 = 0; j0 < members; j0 += J) {
+      KVC_GLOBAL uint32_t* at[J];
+      uint32_t w[J];
+#pragma unroll
+      for (uint32_t j = 0; j < J; ++j) at[j] = slots.at((j0 + j < members ? j0 + j : me) * kSlotTokens + sub, ch);
+      for (;;) {
+        bool all = true;
+#pragma unroll
+        for (uint32_t j = 0; j < J; ++j) w[j] = __hip_atomic_load(at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (uint32_t j = 0; j < J; ++j) all = all && w[j] != kEmptySlot;
+        if (all) break;
+        if (tries++ >= waits) {
+          *late = 1u;
+          return;
+        }
+        __builtin_amdgcn_s_sleep(4);
+      }
+#pragma unroll
+      for (uint32_t j = 0; j < J; ++j) {
+        float l, h;
+        widen_pair<DT>(w[j], l, h);
+        lo = __builtin_fminf(lo, l);
+        hi = __builtin_fmaxf(hi, h);
+      }
+    }
+  }
+};
+
+template <int DT, int NR, int NS, bool SHORT, bool SHARED = false>
 __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, uint32_t unit, uint32_t c0,
                                                            float (*red_lo)[kMaxStripAtoms * 8],
-                                                           float (*red_hi)[kMaxStripAtoms * 8], u32x4* stash) {
+                                                           float (*red_hi)[kMaxStripAtoms * 8], u32x4* stash, uint32_t* flags = nullptr,
+                                                           uint32_t members = 1u) {
   constexpr int NI = NR + NS, LG = NS == kResidentLds ? kResidentGroup : kMediumGroup;
   const Geo& g = p.g;
   uint32_t uu = unit;
+  uint32_t me = 0;  // which of the members of its strip this workgroup is
+  if (SHARED) {
+    me = uu % members;
+    uu /= members;
+  }
   const uint32_t strip = uu % (uint32_t)p.n_strips;
   uu /= (uint32_t)p.n_strips;
   const uint32_t l = uu % (uint32_t)g.L;
@@ -685,14 +780,23 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
 
   const int64_t chunk_first = (int64_t)c * g.T;
   const int64_t left = p.n_tokens - chunk_first;
-  const uint32_t n = left < (int64_t)g.T ? (uint32_t)left : (uint32_t)g.T;  // at least 1
-  const uint32_t positions = (uint32_t)((int32_t)c + 1 == p.n_chunks ? p.positions_last : p.positions_full);
+  const uint32_t n_chunk = left < (int64_t)g.T ? (uint32_t)left : (uint32_t)g.T;  // at least 1
+  uint32_t positions = (uint32_t)((int32_t)c + 1 == p.n_chunks ? p.positions_last : p.positions_full);
+  // of a shared strip, this workgroup's tokens start with `first`, and n and the positions count from there
+  const uint32_t first = SHARED ? me * (uint32_t)p.member_tokens : 0u;
+  uint32_t n = n_chunk;
+  if (SHARED) {
+    n = me + 1u < members ? (uint32_t)p.member_tokens : n_chunk - first;
+    positions = !active ? 0u : me + 1u < members ? n : positions - first;
+  }
+  // slots that the last reader stores
+  const uint32_t skip = SHARED && members > 1u && me == 0u ? kSlotTokens * members + 1u : 0u;
 
   uint32_t r, cc;
   tile_pos(g, e, r, cc);
   const uint32_t lg = l / 3u, pl = l - lg * 3u;
   uint8_t* fplane = p.frames + (int64_t)c * g.frame_bytes + (((int64_t)kind * g.LG + lg) * g.F * 3 + pl) * g.plane;
-  const uint8_t* srcb = reinterpret_cast<const uint8_t*>(p.kv + (int64_t)l * p.ls + (int64_t)kind * p.ks + chunk_first * p.ts);
+  const uint8_t* srcb = reinterpret_cast<const uint8_t*>(p.kv + (int64_t)l * p.ls + (int64_t)kind * p.ks + (chunk_first + first) * p.ts);
   const uint32_t ts2 = (uint32_t)p.ts * 2u;
 
   u32x4 v[NR];                       // loads NS .. NI-1
@@ -736,8 +840,23 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
     for (int i = i0; i < NR && i < i0 + kRegGroup; ++i) st.add(v[i]);
   }
   if (__ballot(st.met_nan()) != 0u) add_numbers_again(st, srcb, off_row, off_step, last);
-  strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
-  if (!active) return;  // after the barriers: lanes of a ragged last strip store nothing
+  uint32_t left_before = 0;
+  if (SHARED) {
+    const StripSlots slots{g, fplane, strip * sa * 8u};
+    if (tid == 0) flags[0] = 0u;  // seen by all after the first barrier
+    strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv,
+                         Members<DT>{slots, me, members, p.waits, flags, strip * sa * 8u + tid < (uint32_t)g.C});
+    if (flags[0] != 0u) {  // the others did not come in time: the columns of the whole chunk from memory
+      __syncthreads();
+      add_numbers_again(st, srcb - (size_t)first * ts2, off_row, off_step, (n_chunk - 1u) * (uint64_t)ts2 + e * 2u);
+      strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
+    }
+    if (members > 1u && tid == 0)  // (all of the workgroup's words have been read before the second barrier)
+      left_before = __hip_atomic_fetch_add(slots.at(kSlotTokens * members, 0u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
+    if (!active) return;  // after the barriers: lanes of a ragged last strip store nothing
+  }
 
   // Quantize from where the loads wait; tile positions without a token get zeros.  Token position
   // t -> frame t % F, tile (t / F) % TX of tile row (t / F) / TX; when the rows of a pass
@@ -745,7 +864,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   const uint32_t frame3 = (uint32_t)(3 * g.plane), trs = (uint32_t)g.th * (uint32_t)g.W;
   const uint32_t lane_off = r * (uint32_t)g.W + cc;
   uint32_t gi0, f0, ty0, tx0;
-  fd_divmod(g.dF, row, gi0, f0);
+  fd_divmod(g.dF, first + row, gi0, f0);
   fd_divmod(g.dTX, gi0, ty0, tx0);
   const uint32_t off0 = f0 * frame3 + ty0 * trs + tx0 * (uint32_t)g.tw + lane_off;
   const uint32_t pass_step = p.pass_step;  // bytes per pass, 0 if not constant
@@ -753,7 +872,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   for (int i = 0; i < NI; ++i) {
     if (SHORT && (uint32_t)i * rows >= positions) break;
     const uint32_t t = row + (uint32_t)i * rows;
-    if (t >= positions) continue;
+    if (t >= positions || (SHARED && t < skip)) continue;
     u32x2 o{0u, 0u};
     if (t < n) {
       float x[8];
@@ -766,7 +885,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
     uint32_t off = off0 + (uint32_t)i * pass_step;
     if (pass_step == 0u) {
       uint32_t gi, f, ty, tx;
-      fd_divmod(g.dF, t, gi, f);
+      fd_divmod(g.dF, first + t, gi, f);
       fd_divmod(g.dTX, gi, ty, tx);
       off = f * frame3 + ty * trs + tx * (uint32_t)g.tw + lane_off;
     }
@@ -775,9 +894,21 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   }
   for (uint32_t t = row + (uint32_t)NI * rows; t < positions; t += rows) {
     uint32_t gi, f, ty, tx;
-    fd_divmod(g.dF, t, gi, f);
+    fd_divmod(g.dF, first + t, gi, f);
     fd_divmod(g.dTX, gi, ty, tx);
     stream_store<u32x2>(fplane + (size_t)(f * frame3 + ty * trs + tx * (uint32_t)g.tw + lane_off), u32x2{0u, 0u});
+  }
+  if (SHARED && members > 1u) {  // the last to have read the slots stores the codes that belong there
+    if (tid == 0) flags[1] = left_before;
+    __syncthreads();
+    if (flags[1] != members - 1u || !active) return;
+    const uint8_t* chunk = srcb - (size_t)first * ts2;
+    uint8_t* fbase = fplane + lane_off;
+    for (uint32_t t = row; t <= kSlotTokens * members; t += rows) {
+      float x[8];
+      widen_atom<DT>(stream_load<u32x4>(chunk + (size_t)t * ts2 + e * 2u), x);
+      stream_store<u32x2>(code_addr(g, fbase, t), quantize_atom(x, mnv, inv));
+    }
   }
 }
 
@@ -868,6 +999,7 @@ pack_kernel(const PackParams p) {
   constexpr int kWaves = (BODY == kPackStream ? 1024 : kResidentThreads) / 64;
   __shared__ float red_lo[kWaves + 1][kMaxStripAtoms * 8];
   __shared__ float red_hi[kWaves + 1][kMaxStripAtoms * 8];
+  __shared__ uint32_t flags[2];  // of shared strips
   extern __shared__ u32x4 stash[];  // the loads of the per-channel bodies that wait in LDS, one slot per thread each
   // Workgroups go to the 8 XCDs round-robin.  Units come in ranges: the per-channel ones, the per-token ones (each first
   // of the whole chunks, then of a short last chunk, so that every XCD has the same mix of work: 2048 + 128 tokens of 60
@@ -890,6 +1022,9 @@ pack_kernel(const PackParams p) {
       pack_channel_body_resident<DT, kMediumRegs, kMediumLds, false>(p, unit, c0, red_lo, red_hi, stash);
     else if (BODY == kPackResident)
       pack_channel_body_resident<DT, kResidentRegs, kResidentLds, false>(p, unit, c0, red_lo, red_hi, stash);
+    else if (p.member_tokens != 0)
+      pack_channel_body_resident<DT, kSharedRegs, kSharedLds, false, true>(p, unit, c0, red_lo, red_hi, stash, flags,
+                                                                           (uint32_t)(last ? p.members_last : p.members_full));
     else
       pack_channel_body<DT>(p, unit, c0, red_lo, red_hi, stash);
   } else if (idx < n_ch + n_tok) {
@@ -906,6 +1041,27 @@ pack_kernel(const PackParams p) {
     const uint32_t unit = xcd * p.zero.per_xcd + (idx - n_ch - n_tok);
     if (unit < p.zero.units) pack_zero_body(p, unit);
   }
+}
+
+// Prepares the slots of shared strips: unit = (chunk, kind and layer, piece of the atoms of the slots' tokens).
+__global__ void __launch_bounds__(kClearThreads) clear_slots_kernel(const PackParams p, uint32_t pieces) {
+  const Geo& g = p.g;
+  uint32_t u = blockIdx.x;
+  const uint32_t piece = u % pieces;
+  u /= pieces;
+  const uint32_t l = u % (uint32_t)g.L;
+  u /= (uint32_t)g.L;
+  const uint32_t kind = (uint32_t)p.kinds_ch[u % (uint32_t)p.n_kinds_ch], c = u / (uint32_t)p.n_kinds_ch;
+  const uint32_t members = (uint32_t)((int32_t)c < p.n_whole ? p.members_full : p.members_last);
+  uint32_t t, a;
+  fd_divmod(p.dapt, piece * kClearThreads + threadIdx.x, t, a);
+  if (members == 1u || t > kSlotTokens * members) return;
+  const uint32_t lg = l / 3u, pl = l - lg * 3u;
+  uint32_t r, cc;
+  tile_pos(g, a * 8u, r, cc);
+  uint8_t* fbase = p.frames + (int64_t)c * g.frame_bytes + (((int64_t)kind * g.LG + lg) * g.F * 3 + pl) * g.plane + (r * (uint32_t)g.W + cc);
+  const uint32_t w = t < kSlotTokens * members ? kEmptySlot : 0u;
+  *(KVC_GLOBAL u32x2*)code_addr(g, fbase, t) = u32x2{w, w};
 }
 
 // The per-channel bodies ask for more dynamic LDS than the 64 KB a kernel gets unasked; the limit of a kernel
@@ -979,10 +1135,10 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
     }
   }
   p.resident = p.n_kinds_ch > 0 && p.body != kPackStream ? 1 : 0;
-  // Chunks too long for that read the part of each strip that does not fit on chip twice.  Few, large
+  // Chunks too long for that share strips (below) or read the part of each that does not fit on chip twice.  Few, large
   // workgroups (one of 1024 threads per CU) give each strip the whole CU's registers and LDS to wait in, and
   // keep the strips in flight few, so that part of the second read still finds its strip in the last-level
-  // cache: 10 240-token chunks pack in 1.37 ms this way against 1.83 ms with 256-thread workgroups.
+  // cache: 10 240-token chunks pack in 1.37 ms this way (1.18 shared) against 1.83 ms with 256-thread workgroups.
   // Few strips are made as narrow as it takes for a whole chunk to wait on chip (two layers of 10 240 tokens: 77 -> 58 us;
   // in strips of 16 six layers, 384 of them, 122 -> 109 us, seven, 448, 119 -> 126;
   // many strips lose by it, 1.35 -> 2.55 ms with half the width, since each input and code line is then several strips').
@@ -996,10 +1152,36 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   p.tpp = g.apt >= want ? 1 : want / g.apt;
   p.dapt = make_fastdiv((uint32_t)g.apt);
   const int threads = p.body != kPackStream ? kResidentThreads : (g.apt * p.tpp + 63) / 64 * 64;
+  const int64_t n_last = p.n_tokens - (int64_t)(p.n_chunks - 1) * g.T;
+  // Strips that no workgroup can hold, shared by several, in equal parts of whole passes.  128 channels wide where that is
+  // a line of codes, but for calls of fewer than 64 such strips a chunk: theirs stay 64 wide, the width that kvc_pack_form
+  // has for them (128 would be 5 % faster: 7 layers of 10 240 tokens 104 against 97 us, two-pass 122).  Tiles of less than
+  // 128 bytes: 64 channels (80 layers x 30 720 tokens, tiles of 64 bytes, 3323 us, 128 wide 3480, two-pass 3376; a single
+  // head 409, 413, 428).  Strips of 64 channels of tiles of 128 bytes share only while they are fewer than the CUs (2 layers
+  // of 20 000 tokens, two chunks, 195 -> 132 us; 640 strips of 4096 tokens 220 two-pass, 224 shared).
+  p.member_tokens = 0;
+  p.members_full = p.members_last = 1;
+  if (p.body == kPackStream && p.shareable && p.n_kinds_ch > 0 && p.strip_atoms == kStreamAtoms) {
+    const int64_t per_chunk = (int64_t)p.n_kinds_ch * g.L * ((g.apt + kResidentAtoms - 1) / kResidentAtoms);
+    const bool lines = g.tw >= 8 * kResidentAtoms && per_chunk >= kFewLineStrips;
+    const int atoms = lines ? kResidentAtoms : kStreamAtoms, rows = threads / atoms;
+    const int64_t most = (int64_t)kSharedLoads * rows, members = (most_tokens + most - 1) / most;
+    const int64_t slots = ((kSlotTokens * members + 1) * g.apt + kClearThreads - 1) / kClearThreads;
+    // what one workgroup holds of a strip of 64 channels is better off there where two would be filled by less than three
+    // quarters (32 layers of 2100 tokens 92.1 against 95.1 us, of 2500 tokens 103 against 101, of 3072 124 against 118)
+    const bool one_holds = most_tokens <= kSharedLoads * (int64_t)(threads / kStreamAtoms) && 2 * most_tokens < 3 * most;
+    if (members > 1 && members <= kMostMembers && fits(most) && !one_holds && (lines || g.tw < 128 || strips(atoms) < kCus) &&
+        slots * p.n_chunks * p.n_kinds_ch * g.L < (1ll << 31)) {
+      p.strip_atoms = atoms;
+      p.member_tokens = (int32_t)(((most_tokens + members - 1) / members + rows - 1) / rows * rows);
+      const auto parts = [&](int64_t n) { return (int32_t)((n + p.member_tokens - 1) / p.member_tokens); };
+      p.members_full = parts(most_tokens);
+      p.members_last = parts(n_last);
+    }
+  }
   // Token positions the bodies walk: those of the tile rows a token of the chunk can fall into.  What lies
   // below is zero and belongs to the zero-fill units, as do the planes of layers beyond L.
   const auto positions = [&](int64_t n) { return (int32_t)(((n + g.F - 1) / g.F + g.TX - 1) / g.TX * g.TX * g.F); };
-  const int64_t n_last = p.n_tokens - (int64_t)(p.n_chunks - 1) * g.T;
   p.positions_full = positions(g.T);
   p.positions_last = positions(n_last);
   p.tb = 128;  // token positions per workgroup of the per-token kinds (32: 1.27 ms, 64: 1.18, 128: 1.157, 256: 1.166, 512: 1.20)
@@ -1038,7 +1220,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   const int64_t zero_full = (int64_t)(p.n_chunks - 1) * 2 * g.L * g.F * p.pieces_tail_full;
   const int64_t zero_last = (int64_t)2 * g.L * g.F * p.pieces_tail_last;
   const int64_t rows_ch = (int64_t)g.L * p.n_kinds_ch, rows_tok = (int64_t)g.L * p.n_kinds_tok;
-  const int64_t units[5] = {p.n_whole * rows_ch * p.n_strips, short_chunks * rows_ch * p.n_strips, p.n_whole * rows_tok * p.tbc,
+  const int64_t units[5] = {p.n_whole * rows_ch * p.n_strips * p.members_full, short_chunks * rows_ch * p.n_strips * p.members_last, p.n_whole * rows_tok * p.tbc,
                             short_chunks * rows_tok * p.tbl, zero_pairs + zero_pad + zero_full + zero_last};
   PackRange* const ranges[5] = {&p.ch[0], &p.ch[1], &p.tok[0], &p.tok[1], &p.zero};
   int64_t wgs_per_xcd = 0;
@@ -1054,7 +1236,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
     p.tok_run = whole_rows ? 1 : 4;
     while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
   }
-  const int64_t tok_run = p.tok_run ? p.tok_run : 1, run[5] = {1, 1, tok_run, tok_run, 1};
+  const int64_t tok_run = p.tok_run ? p.tok_run : 1, run[5] = {p.members_full, p.members_last, tok_run, tok_run, 1};
   const auto share = [&](int i) { return (units[i] + 8 * run[i] - 1) / (8 * run[i]) * run[i]; };  // of one XCD
   for (int i = 0; i < 5; ++i) wgs_per_xcd += share(i);
   if (wgs_per_xcd > 0x7fffffff / 64) return KVC_ERR_UNSUPPORTED;
@@ -1074,6 +1256,12 @@ kvc_status launch_pack(PackParams p, hipStream_t stream) {
   if (st != KVC_OK) return st;
   const Geo& g = p.g;
   const dim3 grid(p.wgs_per_xcd * 8u), block((unsigned)threads);
+  if (p.members_full > 1 || p.members_last > 1) {
+    const uint32_t members = (uint32_t)(p.members_full > p.members_last ? p.members_full : p.members_last);
+    const uint32_t pieces = ((kSlotTokens * members + 1u) * (uint32_t)g.apt + kClearThreads - 1u) / kClearThreads;
+    hipLaunchKernelGGL(clear_slots_kernel, dim3(pieces * (uint32_t)(p.n_chunks * p.n_kinds_ch * g.L)), dim3(kClearThreads), 0, stream, p, pieces);
+    if (hipGetLastError() != hipSuccess) return KVC_ERR_RUNTIME;
+  }
   const bool uniform = g.apt % 64 == 0;
   hipError_t err = hipSuccess;
 #define KVC_LAUNCH_PACK(DT_, UNI_)                                                                       \

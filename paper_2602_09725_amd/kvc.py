@@ -68,6 +68,7 @@ def load(path=None):
     lib.kvc_blob_meta_offset.argtypes = [LP]
     lib.kvc_blob_meta_offset.restype = sz
     lib.kvc_pack.argtypes = [LP, vp, Strides, i64, vp, sz, vp, sz, vp]
+    lib.kvc_probe_pack.argtypes = [LP, vp, Strides, i64, vp, sz, vp, sz, C.c_uint32, vp]
     lib.kvc_pack_plan.argtypes = [LP, Strides, C.POINTER(i32), C.POINTER(i32)]
     lib.kvc_pack_form.argtypes = [LP, Strides, i64, C.POINTER(i32), C.POINTER(i32), C.POINTER(i32)]
     lib.kvc_restore.argtypes = [LP, vp, vp, i64, vp, Strides, vp]
@@ -167,6 +168,11 @@ def kvc_restore_paged(layout, frames_ptr, meta_ptr, first_token, n_tokens, layer
     _check(load().kvc_restore_paged(C.byref(layout), frames_ptr, meta_ptr, first_token, n_tokens,
                                     layer_cache_ptrs_dev, num_blocks, block_size, block_table_ptr, table_len, err_ptr,
                                     stream), "kvc_restore_paged")
+
+
+def kvc_probe_pack(layout, kv_ptr, strides, n_tokens, frames_ptr, frames_cap, meta_ptr, meta_cap, waits, stream=0):
+    _check(load().kvc_probe_pack(C.byref(layout), kv_ptr, Strides(*strides), n_tokens, frames_ptr, frames_cap, meta_ptr,
+                                 meta_cap, waits, stream), "kvc_probe_pack")
 
 
 PROBE_ONE_XCD_PER_PIECE, PROBE_LINE_READS = 1, 2

@@ -1179,3 +1179,64 @@ def test_layer_order_moves_the_pairs_of_tokens_that_exist(modes, off):
                 if mode:
                     assert bool((m[at + n * H * 8:at + size] == 0xEE).all())
                 at += size
+
+
+SHARED_STRIPS = [
+    # L, H, D, T, th, tw, TX, TY, n_tokens, modes, seg: chunks that several workgroups hold together
+    (8, 8, 128, 2305, 8, 128, 8, 40, 2305 + 1, (0, 1), 0),         # two members; one token in the last chunk, not shared
+    (8, 8, 128, 3100, 8, 128, 7, 64, 3100 * 2 + 1700, (0, 0), 0),  # three, and two of the last chunk; rows of 49 positions
+    (8, 8, 128, 2900, 8, 128, 5, 30, 2900 + 2899, (1, 0), 64),     # a two-level tile, padding behind the chunk
+    (33, 3, 64, 2400, 1, 192, 6, 90, 2400 + 1500, (0, 1), 0),      # half of the last strip's channels do not exist
+    (13, 10, 64, 4000, 5, 128, 8, 64, 4000 + 1441, (0, 1), 0),     # 960 threads, 60 rows a pass
+    (2, 8, 128, 13000, 16, 64, 16, 64, 13000, (0, 1), 0),          # tiles of 64 bytes: strips of 64 channels, five members
+    (8, 8, 128, 20000, 8, 128, 8, 64, 20000, (0, 0), 0),           # 14 members
+]
+
+
+@pytest.mark.parametrize("waits", [None, 0])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", SHARED_STRIPS, ids=[f"m{i}" for i in range(len(SHARED_STRIPS))])
+def test_workgroups_that_share_a_strip(shape, dtype, waits):
+    """Codes, zero fill and pairs of shared strips to the bit, packed twice into the same buffers, where the workgroups see
+    each other's extremes and (waits = 0) where most do without; extremes in any part, NaNs, -0.0."""
+    L, H, D, T, th, tw, TX, TY, n, modes, seg = shape
+    glo, olo = hz.layouts(L, H, D, dtype, T, th, tw, TX, TY, *modes, seg)
+    C = H * D
+    kv = kv_synth.make_kv(L, H, D, n, TD[dtype], seed=9000 + n, device="cuda")
+    kv[0, :, 0, 0, :4] = 30.0
+    kv[0, :, min(n, T) - 1, 0, 2:6] = -40.0
+    kv[0, :, :, 0, 6] = -kv[0, :, :, 0, 6].abs()
+    kv[0, :, T // 2, 0, 6] = -0.0
+    kv[0, :, 5::9, 0, 7] = float("nan")
+    kv[1, :, :, H - 1, D - 1] = 1.5
+    hz.say(f"[case] shared strips L={L} H={H} T={T} n={n} modes={modes} seg={seg} {dtype} waits={waits}")
+    want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), n)
+    frames, meta = hz.gpu_pack(glo, kv, n)
+    for _ in range(2):
+        hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+        hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
+        args = (glo, kv.data_ptr(), (2 * n * C, n * C, C), n, frames.data_ptr(), frames.numel(), meta.data_ptr(), meta.numel() * 4)
+        if waits is None:
+            hz.kvc.kvc_pack(*args, hz.stream_handle())
+        else:
+            hz.kvc.kvc.kvc_probe_pack(*args, waits, hz.stream_handle())
+        torch.cuda.synchronize()
+    hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+    hz.assert_same_bytes("frames", frames.cpu().numpy(), want_frames)
+
+
+def test_long_chunks_packed_into_pinned_host_memory():
+    """Frames in host memory that is mapped into the device: no strip is shared there, and the bytes are the same."""
+    L, H, D, T = 8, 8, 128, 3100
+    glo, olo = hz.layouts(L, H, D, "f16", T, 8, 128, 8, 60)
+    C = H * D
+    kv = kv_synth.make_kv(L, H, D, T, torch.float16, seed=77, device="cuda")
+    fb, mb, _ = hz.kvc.chunk_sizes(glo)
+    frames = torch.full((fb,), 0xA5, dtype=torch.uint8, pin_memory=True)
+    meta = torch.empty(mb // 4, dtype=torch.float32, device="cuda")
+    hz.say("[case] long chunk packed into pinned host memory")
+    hz.kvc.kvc_pack(glo, kv.data_ptr(), (2 * T * C, T * C, C), T, frames.data_ptr(), fb, meta.data_ptr(), mb, hz.stream_handle())
+    torch.cuda.synchronize()
+    want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), T)
+    hz.assert_same_bytes("frames", frames.numpy(), want_frames)
+    hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))

@@ -426,3 +426,29 @@ def test_probe_expand_rejects_bad_arguments(kvc_lib):
             kvc.kvc_probe_expand(a["src"], a["dst"], a["out"], a["mp"], a["piece"], a["wg"], shape=a["shape"])
         assert e.value.status == status, kw
     kvc.kvc_probe_expand(A, A, 0, 0, 32768, 4096)   # nothing to do
+
+
+def test_long_chunks_share_strips_as_wide_as_a_line_of_codes(kvc_lib):
+    """Strips of 128 channels in the two-pass form are shared ones; calls whose token stride does not fit the 32-bit offsets
+    of a workgroup's tokens, and longer chunks than 128 workgroups hold or 32-bit offsets reach, are not."""
+    def form(T, n=None, ts=1024, layers=32, **kw):
+        lo = good(num_layers=layers, chunk_tokens=T, tiles_y=-(-T // 8), **kw)
+        return kvc.pack_form(lo, (0, 0, ts), n or T)
+    assert form(2304) == form(10240) == form(10240, 30720) == form(10240, 2304) == (TWO_PASS, 128, 1024)
+    assert form(2303) == form(2100, 30720) == form(10240, 2100) == (TWO_PASS, 64, 1024)   # one workgroup holds them
+    assert form(10240, k_mode=1, v_mode=0)[1] == 128 and form(10240, k_mode=1)[1] == 0
+    assert form(128 * 1536, layers=8)[1] == 128 and form(128 * 1536 + 1, layers=8)[1] == 64
+    assert form(60000)[1] == 128 and form(64000)[1] == 64     # 2^32 bytes of frames
+    edge = 2**32 // (1536 * 2)
+    assert form(4096, ts=edge // 8 * 8)[1] == 128 and form(4096, ts=edge // 8 * 8 + 8)[1] == 64
+    assert form(10240, tile_h=16, tile_w=64)[1] == 64
+    assert kvc.pack_form(good(num_layers=8, chunk_tokens=4096, tiles_y=512), (0, 0, 1024), 4096)[1] == 128   # 64 strips a chunk
+    assert kvc.pack_form(good(num_layers=7, chunk_tokens=4096, tiles_y=512), (0, 0, 1024), 8192)[1] == 64
+
+
+def test_shared_strips_of_the_parity_test(kvc_lib):
+    import test_gpu_parity as parity
+
+    for (L, H, D, T, th, tw, TX, TY, n, modes, seg) in parity.SHARED_STRIPS:
+        lo, C = kvc.Layout(L, H, D, 0, T, th, tw, TX, TY, *modes, seg), H * D
+        assert kvc.pack_form(lo, (2 * n * C, n * C, C), n)[:2] == (TWO_PASS, 64 if tw < 128 else 128), (L, H, T, n)
