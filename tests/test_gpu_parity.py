@@ -1240,3 +1240,48 @@ def test_long_chunks_packed_into_pinned_host_memory():
     want_frames, want_meta = oracle.pack(olo, kv_synth.to_u16(kv.cpu()).reshape(-1), T)
     hz.assert_same_bytes("frames", frames.numpy(), want_frames)
     hz.assert_same_bytes("meta", meta.cpu().numpy().view(np.uint32), want_meta.view(np.uint32))
+
+
+@pytest.mark.parametrize("off", [0, 8])
+@pytest.mark.parametrize("geo", [(5, 8, 128, 2048, 8, 128, 8, 64), (2, 3, 24, 100, 3, 24, 5, 7), (4, 1, 8, 70, 1, 8, 3, 3)],
+                         ids=["1.5 MB frames", "7.5 KB frames", "216-byte frames"])
+def test_staged_copies_by_kernel_and_by_the_runtime(geo, off):
+    """Pieces of every kind through the staging: small ones that a kernel copies out of the mapped blobs (last pass of a row
+    cut short), pieces beyond its size, and (blobs or frames that are not whole 16-byte words) the runtime's copies; every
+    one of them as often as the ring goes round.  The cache is what one restore of the same bytes gives."""
+    L, H, D, T, th, tw, TX, TY = geo
+    kvc, C, bs, n = hz.kvc, H * D, 16, 2 * T + T // 2 + 3
+    glo, _ = hz.layouts(L, H, D, "f16", T, th, tw, TX, TY)
+    fb, mb, F = kvc.chunk_sizes(glo)
+    fs, moff, nc, LG = kvc.frame_size(glo), kvc.blob_meta_offset(glo), 3, (L + 2) // 3
+    g = torch.Generator().manual_seed(fb)
+    blobs = torch.zeros((nc, (off + moff + mb + 255) // 256 * 256), dtype=torch.uint8, pin_memory=True)
+    frames, meta = torch.empty((nc, fb), dtype=torch.uint8), torch.rand((nc, mb // 4), generator=g)
+    for i in range(nc):
+        frames[i] = torch.randint(0, 256, (fb,), dtype=torch.uint8, generator=g)
+        blobs[i, off:off + fb] = frames[i]
+        blobs[i, off + moff:off + moff + mb] = meta[i].view(torch.uint8)
+    nb = (n + bs - 1) // bs
+    tab = kv_synth.make_block_table(nb, nb, 5).cuda()
+    want = hz.PagedCache(L, nb, bs, C)
+    hz.gpu_restore_paged(glo, frames.cuda(), meta.cuda(), 0, n, want, tab)
+    chunks = [(blobs[i].data_ptr() + off, moff + mb, min(T, n - i * T)) for i in range(nc)]
+    s_copy, s_comp = torch.cuda.Stream(), torch.cuda.Stream()
+    for order, per_slot in ((None, 0), (0, 1), (0, 3), (0, 12), (1, 1), (1, 2 * F), (1, 2 * F + 1)):
+        cache = hz.PagedCache(L, nb, bs, C)
+        hz.say(f"[case] staged copies {geo} off={off} order={order} frames per slot={per_slot}")
+        torch.cuda.synchronize()
+        tail = (cache.ptrs.data_ptr(), nb, bs, tab.data_ptr(), nb, cache.err.data_ptr(), s_copy.cuda_stream, s_comp.cuda_stream)
+        if order is None:
+            st = [torch.empty(moff + mb, dtype=torch.uint8, device="cuda") for _ in range(2)]
+            kvc.kvc_fetch_pipeline(glo, chunks, [t.data_ptr() for t in st], moff + mb, *tail, timed=False)
+        else:
+            ms = kvc.meta_staging_size(glo, order)
+            st = [torch.empty(per_slot * fs, dtype=torch.uint8, device="cuda") for _ in range(3)]
+            mt = [torch.empty(ms, dtype=torch.uint8, device="cuda") for _ in range(2)]
+            kvc.kvc_fetch_pipeline_frames(glo, chunks, [t.data_ptr() for t in st], per_slot * fs, [t.data_ptr() for t in mt], ms,
+                                          *tail, order=order, timed=False)
+        torch.cuda.synchronize()
+        assert int(cache.err.item()) == 0
+        for l in range(L):
+            assert torch.equal(cache.layers[l], want.layers[l]), (order, per_slot, l)
