@@ -10,6 +10,34 @@ import torch
 from . import kvc
 
 
+# Candidates under way at a time, one a stream.  Packing one waits for memory, counting it for LDS, and both start and end
+# with part of the chip idle: side by side they fill it better (20 candidates of 6 layers x 2048 tokens x 1024 channels in
+# one stream 1118 us, in 2 / 3 / 4 streams 997 / 961 / 915; of 32 layers 6310 and 6125 / 6130 / 6060).
+LANES = 4
+
+
+class _Lane:
+    """A stream and the buffers of the candidate that is under way on it, which are then its next one's."""
+
+    def __init__(self, stream, device):
+        self.stream, self.device, self.handle = stream, device, stream.cuda_stream
+        self.sizes, self.pointers, self.tensors = (0, 0, 0), (), ()
+
+    def release(self):
+        for t in self.tensors:
+            t.record_stream(self.stream)  # allocated on the caller's stream
+        self.sizes, self.pointers, self.tensors = (0, 0, 0), (), ()
+
+    def buffers(self, sizes):
+        """Addresses of buffers of at least these many bytes."""
+        if any(a < b for a, b in zip(self.sizes, sizes)):
+            most = tuple(max(a, b) for a, b in zip(self.sizes, sizes))
+            self.release()
+            self.tensors = [torch.empty(n, dtype=torch.uint8, device=self.device) for n in most]
+            self.sizes, self.pointers = most, tuple(t.data_ptr() for t in self.tensors)
+        return self.pointers
+
+
 def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_mode=kvc.KVC_Q_PER_CHANNEL,
                v_mode=kvc.KVC_Q_PER_TOKEN, candidates=None, stream=None):
     """kv: contiguous CUDA tensor [L][2][n_tokens][H][D] (fp16 or bf16 bits); dtype: kvc.KVC_F16 | kvc.KVC_BF16.
@@ -23,29 +51,44 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
     n_chunks = (n_tokens + chunk_tokens - 1) // chunk_tokens
     candidates = list(candidates or kvc.tile_candidates(H, D))  # any iterable
     rows = []
-    # everything is enqueued before the first cost is looked at; buffers a candidate leaves are the next one's
     stream = stream or torch.cuda.current_stream()
     if not isinstance(stream, torch.cuda.Stream):  # anything that carries a stream's handle
         stream = torch.cuda.ExternalStream(stream.cuda_stream, device=kv.device)
     with torch.cuda.stream(stream):
-        sh = stream.cuda_stream
         costs = torch.empty((len(candidates), n_chunks * 2 * L), dtype=torch.float64, device=kv.device)
-        for th, tw, seg in candidates:
-            lo = kvc.Layout(L, H, D, dtype, chunk_tokens, th, tw, 1, 1, k_mode, v_mode, seg)
-            if kvc.layout_set_resolution(lo, frame_width, frame_height) != 0:
-                continue
-            fb, mb, F = kvc.chunk_sizes(lo)
-            frames = torch.empty(n_chunks * fb, dtype=torch.uint8, device=kv.device)
-            meta = torch.empty(n_chunks * mb, dtype=torch.uint8, device=kv.device)
-            hbytes = kvc.residual_histograms_size(lo, n_chunks)
-            hist = torch.empty(hbytes // 8, dtype=torch.int64, device=kv.device)
-            kvc.kvc_pack(lo, kv.data_ptr(), strides, n_tokens, frames.data_ptr(), frames.numel(), meta.data_ptr(),
-                         meta.numel(), sh)
-            kvc.kvc_residual_histograms(lo, frames.data_ptr(), n_chunks, hist.data_ptr(), hbytes, sh)
-            kvc.kvc_proxy_costs(lo, hist.data_ptr(), n_chunks, costs[len(rows)].data_ptr(), sh)
-            rows.append({"tile_h": th, "tile_w": tw, "tile_seg": seg, "tile_grid": [lo.tiles_x, lo.tiles_y],
-                         "frames_per_group": F, "frame_bytes_per_chunk": fb})
-        host = costs[:len(rows)].cpu()   # synchronizes with the stream the work was enqueued on
+        kv_ptr, cost_ptr, cost_bytes = kv.data_ptr(), costs.data_ptr(), costs.stride(0) * 8
+        lanes, most_lanes, ready = [_Lane(stream, kv.device)], LANES, stream.record_event()
+        sides = []
+        try:
+            # everything is enqueued before the first cost is looked at
+            for th, tw, seg in candidates:
+                lo = kvc.Layout(L, H, D, dtype, chunk_tokens, th, tw, 1, 1, k_mode, v_mode, seg)
+                if kvc.layout_set_resolution(lo, frame_width, frame_height) != 0:
+                    continue
+                fb, mb, F = kvc.chunk_sizes(lo)
+                i, sizes = len(rows), (n_chunks * fb, n_chunks * mb, kvc.residual_histograms_size(lo, n_chunks))
+                if 0 < i and len(lanes) < most_lanes:
+                    sides.append(torch.cuda.Stream(kv.device))
+                    sides[-1].wait_event(ready)
+                    lanes.append(_Lane(sides[-1], kv.device))
+                lane = lanes[i % len(lanes)]
+                try:
+                    frames, meta, hist = lane.buffers(sizes)
+                except torch.OutOfMemoryError:  # one lane needs no more than one candidate does
+                    for other in lanes[1:]:
+                        other.release()
+                    lanes, most_lanes = lanes[:1], 1
+                    lane = lanes[0]
+                    frames, meta, hist = lane.buffers(sizes)
+                kvc.kvc_pack(lo, kv_ptr, strides, n_tokens, frames, sizes[0], meta, sizes[1], lane.handle)
+                kvc.kvc_residual_histograms(lo, frames, n_chunks, hist, sizes[2], lane.handle)
+                kvc.kvc_proxy_costs(lo, hist, n_chunks, cost_ptr + i * cost_bytes, lane.handle)
+                rows.append({"tile_h": th, "tile_w": tw, "tile_seg": seg, "tile_grid": [lo.tiles_x, lo.tiles_y],
+                             "frames_per_group": F, "frame_bytes_per_chunk": fb})
+        finally:  # the buffers are the caller's stream's, and so is what comes after them
+            for side in sides:
+                stream.wait_stream(side)
+        host = costs[:len(rows)].cpu()   # synchronizes with the streams the work was enqueued on
     for r, per_stream in zip(rows, host.tolist()):
         r["cost_bits"] = sum(per_stream)
         r["bits_per_element"] = r["cost_bits"] / (L * 2 * n_tokens * C)

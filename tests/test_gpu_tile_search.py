@@ -170,3 +170,31 @@ def test_rank_tiles_takes_any_iterable_and_any_stream_handle():
     for candidates, stream in ((iter(some), None), ((c for c in some), side), (tuple(some), handle), (None, handle), ([], None)):
         got = tile_search.rank_tiles(*args, candidates=candidates, stream=stream)
         assert got == (want[:3] if candidates else want)
+
+
+@pytest.mark.parametrize("refuse", [None, "others", "growth"])
+def test_rank_tiles_side_by_side_and_one_after_the_other(monkeypatch, refuse):
+    """Candidates of different sizes (tiles wider than the frame make frames larger) in any order, several under way at a
+    time, with memory for the first lane alone, and with memory that ends when a later candidate needs more: the same rows."""
+    from paper_2602_09725_amd import tile_search
+
+    L, H, D, n = 4, 8, 64, 150
+    kv = kv_synth.make_kv_correlated(L, H, D, n, torch.bfloat16, seed=79, device="cuda")
+    args = (kv, n, hz.kvc.KVC_BF16, 64, 96, 48)
+    cands = hz.kvc.tile_candidates(H, D)
+    want = [tile_search.rank_tiles(*args, candidates=[c])[0] for c in cands]
+    want.sort(key=lambda r: r["cost_bits"])
+    real, calls = tile_search._Lane.buffers, []
+
+    def buffers(lane, sizes):
+        calls.append(lane)
+        first = lane is calls[0]
+        if (refuse == "others" and not first) or (refuse == "growth" and not first and len(calls) > 6):
+            raise torch.OutOfMemoryError("no memory")
+        return real(lane, sizes)
+
+    monkeypatch.setattr(tile_search._Lane, "buffers", buffers)
+    for order in (cands, cands[::-1]):
+        calls.clear()
+        assert tile_search.rank_tiles(*args, candidates=order) == want
+        assert len(set(map(id, calls[8:]))) == (tile_search.LANES if refuse is None else 1)
