@@ -996,6 +996,7 @@ template <int DT, bool UNIFORM, int BODY>
 __global__ void __launch_bounds__(BODY == kPackStream ? 1024 : kResidentThreads, BODY == kPackLight || BODY == kPackMedium ? 4 : 1)
 pack_kernel(const PackParams p) {
   // partial column extremes of the waves; the row after them carries the finished {mn} / {inv} of the strip
+  fetch_params<PackParams>();
   constexpr int kWaves = (BODY == kPackStream ? 1024 : kResidentThreads) / 64;
   __shared__ float red_lo[kWaves + 1][kMaxStripAtoms * 8];
   __shared__ float red_hi[kWaves + 1][kMaxStripAtoms * 8];
@@ -1045,6 +1046,7 @@ pack_kernel(const PackParams p) {
 
 // Prepares the slots of shared strips: unit = (chunk, kind and layer, piece of the atoms of the slots' tokens).
 __global__ void __launch_bounds__(kClearThreads) clear_slots_kernel(const PackParams p, uint32_t pieces) {
+  fetch_params<PackParams>();
   const Geo& g = p.g;
   uint32_t u = blockIdx.x;
   const uint32_t piece = u % pieces;

@@ -364,6 +364,7 @@ constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2;
 
 template <int DT, bool PAGED, int BODY, int U>
 __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
+  fetch_params<RestoreParams>();
   const uint32_t xcd = blockIdx.x & 7u, idx = blockIdx.x >> 3;
   uint32_t tbi, l, kind, c, ff = 0;
   const uint8_t* fsec;  // plane of layer l: frame 0 of its group (chunk call) or the one frame (frame call)
