@@ -54,6 +54,14 @@ constexpr int64_t kFillWorkgroups = 1024;
 // 656 tokens x 60 layers x 512 channels 28.3 -> 26.9 us).  The "lanes" body always takes 256: 12 345 tokens of 80
 // layers x 128 channels 141 -> 136 us, 52 172 tokens of 32 layers 230 -> 221 us.
 constexpr int64_t kManyWorkgroups = 4096;
+// Four workgroups of 512 threads fit a CU.  Launches of full passes let in two (dynamic LDS that nobody uses keeps the others
+// out): fewer reads between the writes and fewer regions of the cache under way (2048 tokens x 32 layers x 4096 channels 289 us
+// with four, 285 with three, 272 with two; 32K tokens x 1024 channels in block order 1157 / 1130 / 1114; 5000 tokens into a
+// contiguous tensor 744 / 743 / 727; but 50 tokens in passes of two 12.0 / 12.5 / 13.9).  Three where a (kind, layer)'s tokens
+// take 40 MB and more of a paged cache and a token 2 KB and more (32K tokens in a random order 1186 / 1178 / 1190, 20 000 tokens
+// of 60 layers 1386 / 1373 / 1382; 20 000 x 512 channels, 20 MB, 698 / 691 / 685).
+constexpr unsigned kLdsForTwo = 64000, kLdsForThree = 53000;
+constexpr int64_t kLargeRegion = 40 << 20;
 
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
@@ -124,23 +132,15 @@ __device__ __forceinline__ void restore_body_waves(const RestoreParams& p, uint3
   fd_divmod(g.dF, tc, gi, f);
   fd_divmod(g.dTX, gi, ty, tx);
   const uint32_t src_tok = f * p.frame_stride + ty * p.tile_row_stride + tx * (uint32_t)g.tw;  // bytes inside the section
-  uint64_t dst_tok;  // bytes from the layer's (kind) base
-  bool ok = in_range;
+  const uint32_t passes = (uint32_t)__popcll(__ballot(in_range));  // at most U; in_range is a prefix of the lanes
+  // All loads are under way before the first is waited for: block table, pairs, codes.
+  uint32_t slot = 0u;
+  int32_t phys = 0;
   if (PAGED) {
-    uint32_t b, slot;
+    uint32_t b;
     fd_divmod(p.dbs, (uint32_t)(p.first_token + chunk_first) + tc, b, slot);
-    const int32_t phys = as_const(p.table)[b];
-    const bool in_cache = (uint32_t)phys < (uint32_t)p.num_blocks;
-    // an id outside the cache: skip the block's writes and report it (Sec. 3.3.2 placement)
-    if (in_range && !in_cache && wslab == 0 && p.err) atomicOr(p.err, 1u);
-    ok = in_range && in_cache;
-    dst_tok = ((uint64_t)(in_cache ? (uint32_t)phys : 0u) * p.dbs.d + slot) * (uint32_t)g.C * 2u;
-  } else {
-    dst_tok = (uint64_t)tc * (uint64_t)p.ts * 2u;
+    phys = as_const(p.table)[b];
   }
-  const uint64_t live_mask = __ballot(ok);
-  const uint32_t passes = (uint32_t)__popcll(__ballot(in_range));  // in_range is a prefix of the lanes
-  const uint32_t dst_lo = (uint32_t)dst_tok, dst_hi = (uint32_t)(dst_tok >> 32);
 
   // ---- per-lane constants
   uint32_t r, cc;
@@ -155,30 +155,47 @@ __device__ __forceinline__ void restore_body_waves(const RestoreParams& p, uint3
   } else {
     mrow = reinterpret_cast<const uint8_t*>(mbase + 2 * ((int64_t)lm * g.T * g.H + fd_div(g.dD, e)));
   }
-  uint8_t* obase;
-  if (PAGED)
-    obase = reinterpret_cast<uint8_t*>(as_const(p.layer_cache)[l]) + ((int64_t)kind * p.num_blocks * p.dbs.d * g.C + e) * 2;
-  else
-    obase = reinterpret_cast<uint8_t*>(p.out + (int64_t)l * p.ls + (int64_t)kind * p.ks + chunk_first * p.ts + e);
+  u32x2 code[U];
+  f32x2 sm[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t k = (uint32_t)u < passes ? (uint32_t)u : passes - 1u;
+    code[u] = stream_load<u32x2>(fsec + (lane_value(src_tok, k) + src_lane));
+    if (MODE == KVC_Q_PER_TOKEN)
+      sm[u] = *(const KVC_GLOBAL f32x2*)(mrow + (size_t)lane_value(tc, k) * ((uint32_t)g.H * 8u));
+  }
 
-  // ---- the tokens of this wave, U at a time
-  for (uint32_t k0 = 0; k0 < passes; k0 += U) {
-    u32x2 code[U];
-    f32x2 sm[U];
+  uint64_t dst_tok;  // bytes from the layer's (kind) base
+  bool ok = in_range;
+  uint8_t* obase;
+  if (PAGED) {
+    obase = reinterpret_cast<uint8_t*>(as_const(p.layer_cache)[l]) + ((int64_t)kind * p.num_blocks * p.dbs.d * g.C + e) * 2;
+    const bool in_cache = (uint32_t)phys < (uint32_t)p.num_blocks;
+    // an id outside the cache: skip the block's writes and report it (Sec. 3.3.2 placement)
+    if (in_range && !in_cache && wslab == 0 && p.err) atomicOr(p.err, 1u);
+    ok = in_range && in_cache;
+    dst_tok = ((uint64_t)(in_cache ? (uint32_t)phys : 0u) * p.dbs.d + slot) * (uint32_t)g.C * 2u;
+  } else {
+    obase = reinterpret_cast<uint8_t*>(p.out + (int64_t)l * p.ls + (int64_t)kind * p.ks + chunk_first * p.ts + e);
+    dst_tok = (uint64_t)tc * (uint64_t)p.ts * 2u;
+  }
+  const uint64_t live_mask = __ballot(ok);
+  const uint32_t dst_lo = (uint32_t)dst_tok, dst_hi = (uint32_t)(dst_tok >> 32);
+  const auto store = [&](int u) {
+    const uint64_t off = ((uint64_t)lane_value(dst_hi, u) << 32) | lane_value(dst_lo, u);
+    dequant_store<MODE, DT>(reinterpret_cast<uint16_t*>(obase + off), code[u], sc, mn, sm[u]);
+  };
+  // Where every pass has a live token the stores stand in a row without branches: the counter that a wait for a load looks
+  // at counts stores as well, and with stores that may or may not have been made the compiler has to wait for all of them
+  // before the next load's value is used.  (This and the order of the loads: 2048 tokens x 32 layers x 1024 channels 71.2 ->
+  // 68.3 us, 8192 tokens 281.6 -> 272.3, 50 tokens of 4096 channels 13.5 -> 12.0.)
+  if ((live_mask & ((1ull << U) - 1ull)) == (1ull << U) - 1ull) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t k = k0 + u < passes ? k0 + u : passes - 1;
-      code[u] = stream_load<u32x2>(fsec + (lane_value(src_tok, k) + src_lane));
-      if (MODE == KVC_Q_PER_TOKEN)
-        sm[u] = *(const KVC_GLOBAL f32x2*)(mrow + (size_t)lane_value(tc, k) * ((uint32_t)g.H * 8u));
-    }
+    for (int u = 0; u < U; ++u) store(u);
+  } else {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const uint32_t k = k0 + u;
-      if (k >= passes || !((live_mask >> k) & 1ull)) continue;  // wave-uniform
-      const uint64_t off = ((uint64_t)lane_value(dst_hi, k) << 32) | lane_value(dst_lo, k);
-      dequant_store<MODE, DT>(reinterpret_cast<uint16_t*>(obase + off), code[u], sc, mn, sm[u]);
-    }
+    for (int u = 0; u < U; ++u)
+      if ((live_mask >> u) & 1ull) store(u);  // wave-uniform
   }
 }
 
@@ -419,8 +436,8 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
 }
 
 template <int DT, bool PAGED>
-void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, hipStream_t s) {
-#define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, 0, s, p)
+void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, unsigned lds, hipStream_t s) {
+#define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, lds, s, p)
   if (body == kBodyRows) {
     KVC_LAUNCH_RESTORE(kBodyRows, 8);
   } else if (body == kBodyWaves) {
@@ -604,16 +621,19 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     grid = dim3(p.bands.wgs_per_xcd * 8u);
   }
   p.dtbc = make_fastdiv((uint32_t)p.tbc);
+  unsigned lds = 0;
+  if (body == kBodyWaves && u == kPasses && threads == 512 && !p.frame_mode && !p.host_frames)
+    lds = paged && g.C >= 1024 && p.n_tokens * g.C * 2 >= kLargeRegion ? kLdsForThree : kLdsForTwo;
   if (g.dtype == KVC_F16) {
     if (paged)
-      launch_variant<KVC_F16, true>(p, body, u, grid, block, stream);
+      launch_variant<KVC_F16, true>(p, body, u, grid, block, lds, stream);
     else
-      launch_variant<KVC_F16, false>(p, body, u, grid, block, stream);
+      launch_variant<KVC_F16, false>(p, body, u, grid, block, lds, stream);
   } else {
     if (paged)
-      launch_variant<KVC_BF16, true>(p, body, u, grid, block, stream);
+      launch_variant<KVC_BF16, true>(p, body, u, grid, block, lds, stream);
     else
-      launch_variant<KVC_BF16, false>(p, body, u, grid, block, stream);
+      launch_variant<KVC_BF16, false>(p, body, u, grid, block, lds, stream);
   }
   return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
 }

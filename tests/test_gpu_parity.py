@@ -1285,3 +1285,29 @@ def test_staged_copies_by_kernel_and_by_the_runtime(geo, off):
         assert int(cache.err.item()) == 0
         for l in range(L):
             assert torch.equal(cache.layers[l], want.layers[l]), (order, per_slot, l)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("bad", [0, 1, 7])
+@pytest.mark.parametrize("shape", [(66, 4, 128, 512, 4, 128, 8, 16, 1029, 16), (2, 32, 128, 64, 8, 512, 2, 4, 77, 3),
+                                   (40, 32, 128, 512, 8, 512, 2, 64, 600, 8)], ids=["512 channels", "short passes", "4096 channels"])
+def test_passes_with_and_without_dead_tokens(shape, bad, dtype):
+    """Whole waves under a table: passes that are all live, passes at a ragged end, and (every 3rd, ..., block id outside the
+    cache) dead tokens between live ones; the others' values to the bit and the error reported."""
+    L, H, D, T, th, tw, TX, TY, n, bs = shape
+    glo, olo = hz.layouts(L, H, D, dtype, T, th, tw, TX, TY)
+    fb, mb, _ = hz.kvc.chunk_sizes(glo)
+    nc, nb, C = -(-n // T), -(-n // bs), H * D
+    g = torch.Generator(device="cuda").manual_seed(n)
+    frames = torch.randint(0, 256, (nc * fb,), dtype=torch.uint8, generator=g, device="cuda")
+    meta = torch.rand(nc * mb // 4, generator=g, device="cuda")
+    tab = kv_synth.make_block_table(nb, nb, 7)
+    if bad:
+        tab[bad::3] = torch.tensor([-1, nb, 2**31 - 1], dtype=torch.int32)[torch.arange(len(tab[bad::3])) % 3]
+    hz.say(f"[case] dead tokens in a pass: L={L} C={C} n={n} bad={bad} {dtype}")
+    want, err = hz.oracle_paged(olo, frames.cpu().numpy(), meta.cpu().numpy(), 0, n, L, nb, bs, C, tab.numpy())
+    cache = hz.PagedCache(L, nb, bs, C)
+    hz.gpu_restore_paged(glo, frames, meta, 0, n, cache, tab.cuda())
+    assert int(cache.err.item()) == (1 if bad else 0)
+    for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
+        hz.assert_same_bytes(f"layer {l}", got, w)
