@@ -211,7 +211,8 @@ __device__ __forceinline__ uint32_t tile_elem(const Geo& g, uint32_t r, uint32_t
 
 // Unit `tg` is a group of rows_trw rows of tiles of one (chunk, kind, layer), in all F frames (chunk call) or in
 // frame ff alone (frame call: fsec is then that frame's plane and frame_stride 0).
-template <int MODE, int DT, bool PAGED, int U>
+// LINE: rounds without a dead lane store in a straight line, as above; for a contiguous destination.
+template <int MODE, int DT, bool PAGED, int U, bool LINE>
 __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                   uint32_t tg, const uint8_t* fsec, uint32_t ff) {
   const Geo& g = p.g;
@@ -269,6 +270,24 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
         const uint32_t tp = tok[u] < n ? tok[u] : n - 1u;  // positions without a token: any pair in bounds
         sm[u] = *(const KVC_GLOBAL f32x2*)(mrow + (size_t)tp * ((uint32_t)g.H * 8u));
       }
+    }
+    if (LINE) {
+      uint16_t* dst[U];
+      bool all = true;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        all = all && k0 + u < passes && tok[u] < n;
+        dst[u] = reinterpret_cast<uint16_t*>(obase + (uint64_t)(tok[u] < n ? tok[u] : n - 1u) * (uint64_t)p.ts * 2u);
+      }
+      if (__ballot(!all) == 0u) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) dequant_store<MODE, DT>(dst[u], code[u], sc, mn, sm[u]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (k0 + u < passes && tok[u] < n) dequant_store<MODE, DT>(dst[u], code[u], sc, mn, sm[u]);
+      }
+      continue;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -362,9 +381,19 @@ __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint3
       }
     }
     if (PAGED && bad && e == 0 && p.err) atomicOr(p.err, 1u);
+    // without branches, as above (8000 tokens of 80 layers x 128 channels 92 -> 88.7 us, 12 345 of 60 layers x 256 204 -> 200.5;
+    // under a table it loses as much as it gains: 36.4 -> 35.6 and 298.7 -> 303)
+    bool all = !PAGED;
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (live[u]) dequant_store<MODE, DT>(dst[u], code[u], sc, mn, sm[u]);
+    for (int u = 0; u < U; ++u) all = all && live[u];
+    if (!PAGED && __ballot(!all) == 0u) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) dequant_store<MODE, DT>(dst[u], code[u], sc, mn, sm[u]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (live[u]) dequant_store<MODE, DT>(dst[u], code[u], sc, mn, sm[u]);
+    }
   }
 }
 
@@ -377,7 +406,7 @@ __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint3
 // when the blocks of the whole chunk were cut into eighths: 32 layers x 4096 channels 144 us, now 35 us.)
 //
 // Frame call: units are (frame of the run, plane, block of token slots), each XCD one contiguous range.
-constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2;
+constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2, kBodyRowsLine = 3;
 
 template <int DT, bool PAGED, int BODY, int U>
 __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
@@ -419,15 +448,15 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
     fsec = p.frames + (int64_t)c * p.g.frame_bytes + (((int64_t)kind * p.g.LG + lg) * p.g.F * 3 + pl) * p.g.plane;
   }
   if (p.g.mode[kind] == KVC_Q_PER_CHANNEL) {
-    if (BODY == kBodyRows)
-      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
+    if (BODY == kBodyRows || BODY == kBodyRowsLine)
+      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
       restore_body_lanes<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
   } else {
-    if (BODY == kBodyRows)
-      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
+    if (BODY == kBodyRows || BODY == kBodyRowsLine)
+      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
@@ -438,7 +467,9 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
 template <int DT, bool PAGED>
 void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, unsigned lds, hipStream_t s) {
 #define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, lds, s, p)
-  if (body == kBodyRows) {
+  if (!PAGED && body == kBodyRowsLine) {
+    KVC_LAUNCH_RESTORE(kBodyRowsLine, 8);
+  } else if (body == kBodyRows) {
     KVC_LAUNCH_RESTORE(kBodyRows, 8);
   } else if (body == kBodyWaves) {
     if (u == 8) KVC_LAUNCH_RESTORE(kBodyWaves, 8); else if (u == 4) KVC_LAUNCH_RESTORE(kBodyWaves, 4); else KVC_LAUNCH_RESTORE(kBodyWaves, 2);
@@ -568,7 +599,7 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
                                      : 2 * (int64_t)g.L * ((p.n_chunks - 1) * (int64_t)row_units(g.T) + row_units(n_last));
     rows = (half_lines || linear) && wgs >= kFillWorkgroups;
   }
-  const int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
+  int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
   int u = kPasses, tpp = 1;
   int32_t tbl = 0;  // units of the last chunk of the call (chunk call), which need not be full
   if (rows) {
@@ -624,6 +655,12 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   unsigned lds = 0;
   if (body == kBodyWaves && u == kPasses && threads == 512 && !p.frame_mode && !p.host_frames)
     lds = paged && g.C >= 1024 && p.n_tokens * g.C * 2 >= kLargeRegion ? kLdsForThree : kLdsForTwo;
+  // "rows" into a contiguous tensor on tiles 8 high: stores in a straight line and two workgroups a CU (8192 tokens x 32 layers
+  // x 1024 channels 274 -> 267 -> 262 us, 32K tokens 1136 -> 1145 -> 1108).  Tiles 16 high, 1024 threads, are left: 675 -> 682.
+  if (body == kBodyRows && !paged && threads == 512 && !p.host_frames) {
+    body = kBodyRowsLine;
+    lds = kLdsForTwo;
+  }
   if (g.dtype == KVC_F16) {
     if (paged)
       launch_variant<KVC_F16, true>(p, body, u, grid, block, lds, stream);

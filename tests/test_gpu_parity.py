@@ -1311,3 +1311,20 @@ def test_passes_with_and_without_dead_tokens(shape, bad, dtype):
     assert int(cache.err.item()) == (1 if bad else 0)
     for l, (got, w) in enumerate(zip(cache.numpy_layers(), want)):
         hz.assert_same_bytes(f"layer {l}", got, w)
+
+
+@pytest.mark.parametrize("modes", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("shape", [(66, 8, 128, 512, 8, 128, 8, 16, 512 * 2 + 77), (40, 4, 128, 600, 8, 64, 8, 32, 1500),
+                                   (70, 1, 128, 512, 1, 128, 8, 16, 1300)], ids=["rows", "rows of 64", "lanes"])
+def test_rounds_with_and_without_dead_lanes(shape, modes):
+    """Restore into a contiguous tensor: rounds of loads whose lanes are all live, and rounds at ragged ends."""
+    L, H, D, T, th, tw, TX, TY, n = shape
+    glo, olo = hz.layouts(L, H, D, "bf16", T, th, tw, TX, TY, *modes)
+    fb, mb, _ = hz.kvc.chunk_sizes(glo)
+    nc = -(-n // T)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    frames = torch.randint(0, 256, (nc * fb,), dtype=torch.uint8, generator=g, device="cuda")
+    meta = torch.rand(nc * mb // 4, generator=g, device="cuda")
+    hz.say(f"[case] rounds with dead lanes: L={L} C={H * D} n={n} modes={modes}")
+    want = oracle.restore(olo, frames.cpu().numpy(), meta.cpu().numpy(), n)
+    hz.assert_same_bytes("restore", hz.u16(hz.gpu_restore(glo, frames, meta, n, torch.bfloat16)), want)
