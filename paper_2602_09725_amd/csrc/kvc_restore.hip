@@ -133,6 +133,7 @@ __device__ __forceinline__ void restore_body_waves(const RestoreParams& p, uint3
   fd_divmod(g.dTX, gi, ty, tx);
   const uint32_t src_tok = f * p.frame_stride + ty * p.tile_row_stride + tx * (uint32_t)g.tw;  // bytes inside the section
   const uint32_t passes = (uint32_t)__popcll(__ballot(in_range));  // at most U; in_range is a prefix of the lanes
+  if (passes == 0u) return;  // the block ends before this wave's first token
   // All loads are under way before the first is waited for: block table, pairs, codes.
   uint32_t slot = 0u;
   int32_t phys = 0;
