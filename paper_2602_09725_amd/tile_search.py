@@ -17,25 +17,39 @@ LANES = 4
 
 
 class _Lane:
-    """A stream and the buffers of the candidate that is under way on it, which are then its next one's."""
+    """A stream and the buffers of the candidate that is under way on it, which are then its next one's.  Buffers are
+    allocated on the caller's stream `home`, whose allocator knows the order of that stream only: a block that it hands out
+    may be in use by what was enqueued there before, by the lane on that stream or by anyone else who shares it.  So a lane
+    on another stream waits for what `home` held when it allocated; and what it gives back is not reused before it is done."""
 
-    def __init__(self, stream, device):
-        self.stream, self.device, self.handle = stream, device, stream.cuda_stream
-        self.sizes, self.pointers, self.tensors = (0, 0, 0), (), ()
+    def __init__(self, home, device, stream=None):
+        self.home, self.device, self.stream = home, device, stream  # None: one of its own, from the first use on
+        self.ready = None
+        self.sizes, self.pointers, self.memory = (0, 0, 0), (), None
 
     def release(self):
-        for t in self.tensors:
-            t.record_stream(self.stream)  # allocated on the caller's stream
-        self.sizes, self.pointers, self.tensors = (0, 0, 0), (), ()
+        if self.memory is not None and self.stream is not None:
+            self.memory.record_stream(self.stream)
+        self.sizes, self.pointers, self.memory = (0, 0, 0), (), None
 
     def buffers(self, sizes):
         """Addresses of buffers of at least these many bytes."""
         if any(a < b for a, b in zip(self.sizes, sizes)):
-            most = tuple(max(a, b) for a, b in zip(self.sizes, sizes))
+            most = tuple((max(a, b) + 255) // 256 * 256 for a, b in zip(self.sizes, sizes))
             self.release()
-            self.tensors = [torch.empty(n, dtype=torch.uint8, device=self.device) for n in most]
-            self.sizes, self.pointers = most, tuple(t.data_ptr() for t in self.tensors)
+            self.memory = torch.empty(sum(most), dtype=torch.uint8, device=self.device)
+            at, self.ready = self.memory.data_ptr(), None
+            self.sizes, self.pointers = most, (at, at + most[0], at + most[0] + most[1])
+            if self.stream is not None and self.stream is not self.home:
+                self.stream.wait_event(self.home.record_event())
         return self.pointers
+
+    def handle(self):
+        """Of the stream, on which the buffers may be used; `ready`, if set, is an event of `home` after their allocation."""
+        if self.stream is None:
+            self.stream = torch.cuda.Stream(self.device)
+            self.stream.wait_event(self.ready or self.home.record_event())
+        return self.stream.cuda_stream
 
 
 def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_mode=kvc.KVC_Q_PER_CHANNEL,
@@ -57,37 +71,45 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
     with torch.cuda.stream(stream):
         costs = torch.empty((len(candidates), n_chunks * 2 * L), dtype=torch.float64, device=kv.device)
         kv_ptr, cost_ptr, cost_bytes = kv.data_ptr(), costs.data_ptr(), costs.stride(0) * 8
-        lanes, most_lanes, ready = [_Lane(stream, kv.device)], LANES, stream.record_event()
-        sides = []
+        lanes, used = [], []
         try:
             # everything is enqueued before the first cost is looked at
-            for th, tw, seg in candidates:
+            for at, (th, tw, seg) in enumerate(candidates):
                 lo = kvc.Layout(L, H, D, dtype, chunk_tokens, th, tw, 1, 1, k_mode, v_mode, seg)
                 if kvc.layout_set_resolution(lo, frame_width, frame_height) != 0:
                     continue
                 fb, mb, F = kvc.chunk_sizes(lo)
                 i, sizes = len(rows), (n_chunks * fb, n_chunks * mb, kvc.residual_histograms_size(lo, n_chunks))
-                if 0 < i and len(lanes) < most_lanes:
-                    sides.append(torch.cuda.Stream(kv.device))
-                    sides[-1].wait_event(ready)
-                    lanes.append(_Lane(sides[-1], kv.device))
-                lane = lanes[i % len(lanes)]
                 try:
+                    if not lanes:  # all buffers before the caller's stream has work that the others would wait for
+                        lanes.append(_Lane(stream, kv.device, stream))
+                        lanes[0].buffers(sizes)
+                        while len(lanes) < min(LANES, len(candidates) - at):
+                            lanes.append(_Lane(stream, kv.device))
+                            lanes[-1].buffers(sizes)
+                        ready = stream.record_event()
+                        for lane in lanes:
+                            lane.ready = ready
+                    lane = lanes[i % len(lanes)]
                     frames, meta, hist = lane.buffers(sizes)
                 except torch.OutOfMemoryError:  # one lane needs no more than one candidate does
                     for other in lanes[1:]:
                         other.release()
-                    lanes, most_lanes = lanes[:1], 1
+                    del lanes[1:]
                     lane = lanes[0]
                     frames, meta, hist = lane.buffers(sizes)
-                kvc.kvc_pack(lo, kv_ptr, strides, n_tokens, frames, sizes[0], meta, sizes[1], lane.handle)
-                kvc.kvc_residual_histograms(lo, frames, n_chunks, hist, sizes[2], lane.handle)
-                kvc.kvc_proxy_costs(lo, hist, n_chunks, cost_ptr + i * cost_bytes, lane.handle)
+                sh = lane.handle()
+                if lane not in used:
+                    used.append(lane)
+                kvc.kvc_pack(lo, kv_ptr, strides, n_tokens, frames, sizes[0], meta, sizes[1], sh)
+                kvc.kvc_residual_histograms(lo, frames, n_chunks, hist, sizes[2], sh)
+                kvc.kvc_proxy_costs(lo, hist, n_chunks, cost_ptr + i * cost_bytes, sh)
                 rows.append({"tile_h": th, "tile_w": tw, "tile_seg": seg, "tile_grid": [lo.tiles_x, lo.tiles_y],
                              "frames_per_group": F, "frame_bytes_per_chunk": fb})
         finally:  # the buffers are the caller's stream's, and so is what comes after them
-            for side in sides:
-                stream.wait_stream(side)
+            for lane in used:
+                if lane.stream is not stream:
+                    stream.wait_stream(lane.stream)
         host = costs[:len(rows)].cpu()   # synchronizes with the streams the work was enqueued on
     for r, per_stream in zip(rows, host.tolist()):
         r["cost_bits"] = sum(per_stream)

@@ -1,0 +1,201 @@
+"""The tiling search's streams and buffers against a model of a stream-ordered allocator, on the CPU: whatever two
+candidates do to one address has to be ordered by the streams they are on."""
+import types
+
+import pytest
+
+import paper_2602_09725_amd as kvc
+from paper_2602_09725_amd import tile_search
+
+
+class Model:
+    """Streams with vector clocks, and an allocator that hands a dropped block out again at once to whoever allocates on the
+    stream it was allocated on, in the order of the host's calls: what was enqueued on other streams it does not wait for,
+    unless record_stream named them (such a block is not reused here)."""
+
+    def __init__(self):
+        self.streams, self.current, self.accesses, self.races = [], None, [], []
+        self.free, self.top, self.live, self.peak, self.refuse_above = {}, 1 << 20, 0, 0, None
+        self.caller = self.current = Stream(self)
+
+    def allocate(self, n):
+        n = (n + 511) // 512 * 512
+        if self.refuse_above is not None and self.live + n > self.refuse_above:
+            raise OutOfMemory()
+        blocks = self.free.setdefault(self.current, [])
+        fits = sorted((size, at) for at, size in blocks if size >= n)
+        if fits:
+            size, at = fits[0]
+            blocks.remove((at, size))
+            if size > n:
+                blocks.append((at + n, size - n))
+        else:
+            at = self.top
+            self.top += n
+        self.live += n
+        self.peak = max(self.peak, self.live)
+        return at, n
+
+    def access(self, stream, at, n, write, what):
+        stream.clock[stream] += 1
+        for at0, n0, s0, when, write0, what0 in self.accesses:
+            if at < at0 + n0 and at0 < at + n and (write or write0) and stream.clock.get(s0, 0) < when:
+                self.races.append((what0, what))
+        self.accesses.append((at, n, stream, stream.clock[stream], write, what))
+
+
+class Event:
+    def __init__(self, clock):
+        self.clock = clock
+
+
+class Stream:
+    def __init__(self, model):  # which stands for the device
+        self.model, self.clock = model, {self: 0}
+        model.streams.append(self)
+        self.cuda_stream = len(model.streams)
+
+    def record_event(self):
+        return Event(dict(self.clock))
+
+    def wait_event(self, event):
+        for s, t in event.clock.items():
+            self.clock[s] = max(self.clock.get(s, 0), t)
+
+    def wait_stream(self, other):
+        self.wait_event(other.record_event())
+
+
+class OutOfMemory(Exception):
+    pass
+
+
+class Tensor:
+    def __init__(self, model, shape, item):
+        self.model, self.shape, self.item, self.owner, self.users = model, tuple(shape), item, model.current, set()
+        n = item
+        for k in self.shape:
+            n *= k
+        self.at, self.n = model.allocate(n)
+
+    def data_ptr(self):
+        return self.at
+
+    def stride(self, dim):
+        assert dim == 0 and len(self.shape) == 2
+        return self.shape[1]
+
+    def record_stream(self, stream):
+        self.users.add(stream)
+
+    def __getitem__(self, rows):
+        assert rows.start is None
+        self.rows = rows.stop
+        return self
+
+    def cpu(self):
+        self.model.access(self.model.current, self.at, self.n, False, "costs read")
+        return types.SimpleNamespace(tolist=lambda: [[float(i)] for i in range(self.rows)])
+
+    def __del__(self):
+        if not hasattr(self, "n"):  # there was no memory for it
+            return
+        self.model.live -= self.n
+        if self.users <= {self.owner}:
+            self.model.free.setdefault(self.owner, []).append((self.at, self.n))
+
+
+def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, candidates=None, meanwhile=None, refuse_above=None):
+    """rank_tiles on the model; `meanwhile(model)` runs after the first candidate is enqueued."""
+    m = Model()
+    m.refuse_above = refuse_above
+
+    class Scope:
+        def __init__(self, stream):
+            self.stream = stream
+
+        def __enter__(self):
+            self.before, m.current = m.current, self.stream
+
+        def __exit__(self, *a):
+            m.current = self.before
+
+    def empty(shape, dtype, device):
+        return Tensor(m, (shape,) if isinstance(shape, int) else shape, {"u8": 1, "f64": 8}[dtype])
+
+    cuda = types.SimpleNamespace(current_stream=lambda: m.current, Stream=Stream, stream=Scope)
+    fake = types.SimpleNamespace(cuda=cuda, empty=empty, uint8="u8", float64="f64", OutOfMemoryError=OutOfMemory)
+    monkeypatch.setattr(tile_search, "torch", fake)
+    count = [0]
+
+    def by(handle):
+        return m.streams[handle - 1]
+
+    def pack(lo, kv, strides, n, frames, fb, meta, mb, handle):
+        count[0] += 1
+        m.access(by(handle), frames, fb, True, f"{count[0]} pack: frames")
+        m.access(by(handle), meta, mb, True, f"{count[0]} pack: pairs")
+        if count[0] == 1 and meanwhile:
+            meanwhile(m)
+
+    def histograms(lo, frames, n_chunks, hist, hb, handle):
+        m.access(by(handle), frames, kvc.chunk_sizes(lo)[0] * n_chunks, False, f"{count[0]} count: frames")
+        m.access(by(handle), hist, hb, True, f"{count[0]} count: counters")
+
+    def costs(lo, hist, n_chunks, cost, handle):
+        m.access(by(handle), hist, kvc.residual_histograms_size(lo, n_chunks), False, f"{count[0]} cost: counters")
+        m.access(by(handle), cost, n_chunks * 2 * layers * 8, True, f"{count[0]} cost")
+
+    monkeypatch.setattr(tile_search.kvc, "kvc_pack", pack)
+    monkeypatch.setattr(tile_search.kvc, "kvc_residual_histograms", histograms)
+    monkeypatch.setattr(tile_search.kvc, "kvc_proxy_costs", costs)
+    kv = types.SimpleNamespace(shape=(layers, 2, tokens, heads, head_dim), is_cuda=True, is_contiguous=lambda: True,
+                               element_size=lambda: 2, device=m, data_ptr=lambda: 1 << 60)
+    rows = tile_search.rank_tiles(kv, tokens, kvc.KVC_F16, chunk, width, height, candidates=candidates, stream=m.caller)
+    return m, rows
+
+
+def sets_of(layers, heads, head_dim, tokens, chunk, width, height):
+    """Bytes of frames, pairs and counters of every candidate."""
+    out = []
+    for th, tw, seg in kvc.tile_candidates(heads, head_dim):
+        lo = kvc.Layout(layers, heads, head_dim, kvc.KVC_F16, chunk, th, tw, 1, 1, 0, 1, seg)
+        if kvc.layout_set_resolution(lo, width, height) == 0:
+            fb, mb, _ = kvc.chunk_sizes(lo)
+            nc = -(-tokens // chunk)
+            out.append(nc * (fb + mb) + kvc.residual_histograms_size(lo, nc))
+    return out
+
+
+SHAPES = [
+    (32, 8, 64, 2048, 2048, 1920, 1080),
+    (32, 8, 128, 2048, 2048, 1920, 1080),
+    (32, 8, 128, 10240, 10240, 1138, 640),
+    (6, 32, 128, 4096, 2048, 1920, 1080),
+    (6, 8, 128, 2048, 2048, 1024, 512),     # all sizes alike
+    (2, 8, 128, 300, 128, 96, 48),          # frames that grow with the width of the tile
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"s{i}" for i in range(len(SHAPES))])
+def test_no_address_is_used_on_two_streams_without_an_order(kvc_lib, monkeypatch, shape):
+    """Candidates in the default order, in reverse and from small to large; another thread that allocates, uses and drops
+    memory on the caller's stream while the search goes on; and memory that ends when a second candidate needs some."""
+    default = kvc.tile_candidates(shape[1], shape[2])
+    sizes = sets_of(*shape)
+
+    def another_thread(m):
+        for n in (max(sizes), max(sizes) // 3, 1 << 20):
+            t = Tensor(m, (n,), 1)
+            m.access(m.caller, t.at, t.n, True, "another thread's work")
+            del t
+
+    orders = [default, default[::-1]]
+    if len(sizes) == len(default):
+        orders.append([c for _, c in sorted(zip(sizes, default))])
+    for order in orders:
+        for meanwhile in (None, another_thread):
+            m, rows = search(monkeypatch, *shape, candidates=order, meanwhile=meanwhile)
+            assert len(rows) == len(sizes) and not m.races, m.races[:5]
+        m, rows = search(monkeypatch, *shape, candidates=order, refuse_above=max(sizes) * 3 // 2 + (1 << 20))
+        assert len(rows) == len(sizes) and not m.races, m.races[:5]
