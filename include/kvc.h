@@ -333,8 +333,7 @@ size_t kvc_meta_staging_size(const kvc_layout* layout, int32_t order);
  * at its end, so that a blob may be written again or freed once copy_stream has
  * drained, as after kvc_fetch_pipeline).  In KVC_ORDER_LAYER a buffer that holds at least
  * 2*F frames receives the K and the V frames of a (chunk, layer group) in one
- * two-row strided copy.  Pieces of up to 16 MiB of blobs that are mapped into
- * the device are copied by a kernel on copy_stream, larger ones by the runtime.
+ * two-row strided copy.
  *   d_frame_staging  HOST array of n_frame_staging (2..64) DEVICE buffers of
  *                    frame_staging_bytes >= kvc_frame_size, 256-byte aligned.
  *                    n_frame_staging = 0: nothing is copied; every run of

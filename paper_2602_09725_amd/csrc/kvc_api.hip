@@ -87,18 +87,6 @@ bool mapped_host_span(const void* p, size_t bytes) {
   return true;
 }
 
-// Whether that holds for the first `bytes` of every blob, for kernels on `stream`.
-bool blobs_are_mapped(const kvc_host_chunk* chunks, int32_t n_chunks, size_t bytes, hipStream_t stream) {
-  int device = -1, streams = -1;
-  if (hipGetDevice(&device) != hipSuccess || hipStreamGetDevice(stream, &streams) != hipSuccess || streams != device) {
-    (void)hipGetLastError();
-    return false;
-  }
-  for (int32_t i = 0; i < n_chunks; ++i)
-    if (!mapped_host_span(chunks[i].host_blob, bytes)) return false;
-  return true;
-}
-
 // Entropy in bits per symbol of a 256-bin histogram (0 for an empty one).
 double histogram_entropy(const uint64_t* bins) {
   double n = 0.0;
@@ -534,22 +522,12 @@ int64_t used_pairs(const Geo& g, int kind, int64_t n) {
 // host link's work in the time that a further copy takes beyond its bytes.
 constexpr int64_t kWorthStrided = 1 << 20;
 
-
-// by_kernel: the source is mapped into the device.  A kernel then copies pieces of up to kKernelCopyMost bytes: one of the
-// runtime's copies between two events costs the stream 30 us and more beyond its bytes, a kernel about 15, but its rate is
-// a little lower (8192 tokens x 32 layers x 1024 channels, pieces of 1.6 / 6.3 / 12.6 / 25 MB: 18.2 / 13.7 / 11.1 / 10.6 ms
-// with the runtime's copies, 14.3 / 11.3 / 10.7 / 11.8 with the kernel's).
-constexpr size_t kKernelCopyMost = 16 << 20;
-
-bool copy_rows_h2d(void* dst, size_t dst_pitch, const void* src, size_t src_pitch, size_t width, size_t rows, bool by_kernel, hipStream_t s) {
-  const HostRows r{src, dst, width, src_pitch, dst_pitch, (uint32_t)rows};
-  if (by_kernel && width * rows <= kKernelCopyMost && can_copy_rows(r)) return launch_copy_rows(r, s) == KVC_OK;
-  if (rows == 1) return hipMemcpyAsync(dst, src, width, hipMemcpyHostToDevice, s) == hipSuccess;
-  return hipMemcpy2DAsync(dst, dst_pitch, src, src_pitch, width, rows, hipMemcpyHostToDevice, s) == hipSuccess;
+bool copy_h2d(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s) == hipSuccess;
 }
 
-bool copy_h2d(void* dst, const void* src, size_t bytes, bool by_kernel, hipStream_t s) {
-  return copy_rows_h2d(dst, bytes, src, bytes, bytes, 1, by_kernel, s);
+bool copy_rows_h2d(void* dst, const void* src, size_t width, size_t pitch, size_t rows, hipStream_t s) {
+  return hipMemcpy2DAsync(dst, pitch, src, pitch, width, rows, hipMemcpyHostToDevice, s) == hipSuccess;
 }
 
 // Bytes at the start of each plane that hold the tiles of n tokens.
@@ -562,9 +540,9 @@ bool frames_are_padded(const Geo& g, int64_t n, int64_t n_frames) {
 }
 
 // n_frames consecutive frames of a chunk of n tokens.
-bool copy_frames_h2d(const Geo& g, void* dst, const void* src, int64_t n_frames, int64_t n, bool by_kernel, hipStream_t s) {
-  if (!frames_are_padded(g, n, n_frames)) return copy_h2d(dst, src, (size_t)(3 * n_frames * g.plane), by_kernel, s);
-  return copy_rows_h2d(dst, (size_t)g.plane, src, (size_t)g.plane, (size_t)used_plane_bytes(g, n), (size_t)(3 * n_frames), by_kernel, s);
+bool copy_frames_h2d(const Geo& g, void* dst, const void* src, int64_t n_frames, int64_t n, hipStream_t s) {
+  if (!frames_are_padded(g, n, n_frames)) return copy_h2d(dst, src, (size_t)(3 * n_frames * g.plane), s);
+  return copy_rows_h2d(dst, src, (size_t)used_plane_bytes(g, n), (size_t)g.plane, (size_t)(3 * n_frames), s);
 }
 
 bool meta_is_padded(const Geo& g, int64_t n) {
@@ -575,14 +553,13 @@ bool meta_is_padded(const Geo& g, int64_t n) {
 }
 
 // The meta section of a chunk of n tokens.
-bool copy_meta_h2d(const Geo& g, uint8_t* dst, const uint8_t* src, int64_t n, bool by_kernel, hipStream_t s) {
-  if (!meta_is_padded(g, n)) return copy_h2d(dst, src, (size_t)g.meta_floats * 4, by_kernel, s);
+bool copy_meta_h2d(const Geo& g, uint8_t* dst, const uint8_t* src, int64_t n, hipStream_t s) {
+  if (!meta_is_padded(g, n)) return copy_h2d(dst, src, (size_t)g.meta_floats * 4, s);
   for (int kind = 0; kind < 2; ++kind) {
     const int64_t at = g.meta_off[kind] * 4;
     const bool ok = g.mode[kind] == KVC_Q_PER_CHANNEL
-                        ? copy_h2d(dst + at, src + at, (size_t)g.L * g.C * 8, by_kernel, s)
-                        : copy_rows_h2d(dst + at, (size_t)g.T * g.H * 8, src + at, (size_t)g.T * g.H * 8, (size_t)n * g.H * 8,
-                                        (size_t)g.L, by_kernel, s);
+                        ? copy_h2d(dst + at, src + at, (size_t)g.L * g.C * 8, s)
+                        : copy_rows_h2d(dst + at, src + at, (size_t)n * g.H * 8, (size_t)g.T * g.H * 8, (size_t)g.L, s);
     if (!ok) return false;
   }
   return true;
@@ -712,10 +689,9 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
   // are copied.
   bool pairs_by_kernel = !in_place && order == KVC_ORDER_LAYER && 3 * pairs_per_layer(g, 0) < (1ll << 30) &&
                          3 * pairs_per_layer(g, 1) < (1ll << 30);
-  const bool by_kernel = !in_place && blobs_are_mapped(chunks, n_chunks, blob_bytes, cs);
   for (int i = 0; i < n_chunks && pairs_by_kernel; ++i) {
     const uint8_t* meta = static_cast<const uint8_t*>(chunks[i].host_blob) + meta_off;
-    pairs_by_kernel = aligned(meta, 8) && (by_kernel || mapped_host_span(meta, meta_bytes));
+    pairs_by_kernel = aligned(meta, 8) && mapped_host_span(meta, meta_bytes);
   }
   // "copied" after the copies into a frame slot, "freed" after the last kernel that read a slot (frame slots, then
   // meta slots); with timing: begin, end, then one per layer group
@@ -814,13 +790,13 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
     }
     if (ok && unit_no >= n_meta_staging) ok = hipStreamWaitEvent(cs, meta_freed(ms), 0) == hipSuccess;
     if (lg < 0) {
-      if (ok) ok = copy_meta_h2d(g, dst, src, chunks[i].n_tokens, by_kernel, cs);
+      if (ok) ok = copy_meta_h2d(g, dst, src, chunks[i].n_tokens, cs);
     } else {
       for (int kind = 0; kind < 2 && ok; ++kind) {
         const PairRows r = group_pairs(kind);
         const size_t used = (size_t)r.pairs * 8, pitch = (size_t)r.pitch * 8;
-        ok = (pitch - used) * nl >= (size_t)kWorthStrided ? copy_rows_h2d(r.dst, pitch, r.src, pitch, used, nl, by_kernel, cs)
-                                                          : copy_h2d(r.dst, r.src, pitch * nl, by_kernel, cs);
+        ok = (pitch - used) * nl >= (size_t)kWorthStrided ? copy_rows_h2d(r.dst, r.src, used, pitch, nl, cs)
+                                                          : copy_h2d(r.dst, r.src, pitch * nl, cs);
       }
     }
     return ms;
@@ -840,7 +816,7 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
       const size_t off = (size_t)fill_frames * frame_size;
       if (ok)
         ok = copy_frames_h2d(g, static_cast<uint8_t*>(d_frame_staging[fs]) + off, blob + (size_t)first * frame_size, n,
-                             chunks[i].n_tokens, by_kernel, cs);
+                             chunks[i].n_tokens, cs);
       fill.push_back(Piece{i, first, n, off, ms, lg, last_of_unit && n == count});
       fill_frames += n;
       first += n;
@@ -861,8 +837,8 @@ kvc_status kvc_fetch_pipeline_frames(const kvc_layout* layout, const kvc_host_ch
     }
     const size_t off = (size_t)fill_frames * frame_size, run = (size_t)g.F * frame_size;
     if (ok)
-      ok = copy_rows_h2d(static_cast<uint8_t*>(d_frame_staging[fs]) + off, run, blob + (size_t)lg * run, (size_t)g.LG * run,
-                         run, 2, by_kernel, cs);
+      ok = hipMemcpy2DAsync(static_cast<uint8_t*>(d_frame_staging[fs]) + off, run, blob + (size_t)lg * run,
+                            (size_t)g.LG * run, run, 2, hipMemcpyHostToDevice, cs) == hipSuccess;
     fill.push_back(Piece{i, (int64_t)lg * g.F, g.F, off, ms, lg, false});
     fill.push_back(Piece{i, ((int64_t)g.LG + lg) * g.F, g.F, off + run, ms, lg, true});
     fill_frames += 2 * (int64_t)g.F;
@@ -1065,7 +1041,6 @@ kvc_status kvc_fetch_pipeline(const kvc_layout* layout, const kvc_host_chunk* ch
   hipStream_t cs = as_stream(copy_stream), xs = as_stream(compute_stream);
   // Per staging slot: "copied" after the copy into it, "slot free" after the restore that read it.
   if (in_place) cs = xs;  // the only stream in use
-  const bool by_kernel = !in_place && blobs_are_mapped(chunks, n_chunks, blob_bytes, cs);
   EventLease ev(2 * n_staging, fetch_to_ready_ms ? 2 : 0);
   bool ok = ev.ok();
   const auto copied = [&](int slot) { return ev.sync(slot); };
@@ -1086,10 +1061,10 @@ kvc_status kvc_fetch_pipeline(const kvc_layout* layout, const kvc_host_chunk* ch
         const bool whole = !frames_are_padded(base.g, n, (int64_t)2 * base.g.LG * base.g.F) && !meta_is_padded(base.g, n);
         uint8_t* slot = static_cast<uint8_t*>(d_staging[s]);
         if (ok && whole) {
-          ok = copy_h2d(slot, blob, blob_bytes, by_kernel, cs);
+          ok = copy_h2d(slot, blob, blob_bytes, cs);
         } else if (ok) {
-          ok = copy_frames_h2d(base.g, slot, blob, (int64_t)2 * base.g.LG * base.g.F, n, by_kernel, cs);
-          if (ok) ok = copy_meta_h2d(base.g, slot + meta_off, static_cast<const uint8_t*>(blob) + meta_off, n, by_kernel, cs);
+          ok = copy_frames_h2d(base.g, slot, blob, (int64_t)2 * base.g.LG * base.g.F, n, cs);
+          if (ok) ok = copy_meta_h2d(base.g, slot + meta_off, static_cast<const uint8_t*>(blob) + meta_off, n, cs);
         }
         if (ok) ok = hipEventRecord(copied(s), cs) == hipSuccess;
         if (ok) ok = hipStreamWaitEvent(xs, copied(s), 0) == hipSuccess;

@@ -66,20 +66,6 @@ struct PairRows {
   uint32_t pairs, pitch;  // of a layer (at least 1), from one layer to the next
 };
 
-// Rows of `width` bytes in pinned host memory that is mapped into the device, and where they go.
-struct HostRows {
-  const void* src;
-  void* dst;
-  size_t width, src_pitch, dst_pitch;
-  uint32_t rows;
-};
-
-// Whether launch_copy_rows takes it: everything in whole 16-byte words.
-bool can_copy_rows(const HostRows& r);
-
-// Enqueues the copy of the rows.
-kvc_status launch_copy_rows(const HostRows& r, hipStream_t stream);
-
 // Enqueues the copy of the pairs of a few layers (8-byte aligned).
 kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t layers, hipStream_t stream);
 

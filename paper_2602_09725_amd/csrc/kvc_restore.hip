@@ -504,51 +504,7 @@ __global__ void __launch_bounds__(kCopyThreads) copy_pairs_kernel(PairRows k, Pa
   }
 }
 
-// Copies rows of 16-byte words out of pinned host memory, 16 KB at a time.  The host link bounds it: what it needs is about
-// 200 KB of reads on the way, and more only fills the queues that other kernels' reads wait in: with 64 workgroups the
-// restore of a slot that runs beside it (8 us alone) takes up to 190 us, with 16 about 20, with 8 11.5 but the copy itself
-// is slower (12.6 MB 234 us with 8, 231 with 16; 8192 tokens of 32 layers x 1024 channels in layer order through slots of
-// that size 11.1 ms with the runtime's copies, 10.87 / 10.74 / 10.71 / 10.85 with 8 / 12 / 16 / 64 workgroups).
-constexpr uint32_t kRowsWorkgroups = 12, kRowsThreads = 256, kRowsLoads = 4, kRowsPass = kRowsThreads * kRowsLoads;
-__global__ void __launch_bounds__(kRowsThreads) copy_rows_kernel(const u32x4* src, u32x4* dst, uint32_t width, uint64_t src_pitch,
-                                                                 uint64_t dst_pitch, uint32_t rows, uint32_t passes) {
-  uint32_t row = blockIdx.x / passes, pass = blockIdx.x - row * passes;  // a workgroup takes every gridDim.x-th pass of all rows
-  while (row < rows) {
-    const u32x4* s = src + row * src_pitch;
-    u32x4* d = dst + row * dst_pitch;
-    const uint32_t i0 = pass * kRowsPass + threadIdx.x;
-    u32x4 w[kRowsLoads];
-#pragma unroll
-    for (uint32_t j = 0; j < kRowsLoads; ++j) {
-      const uint32_t i = i0 + j * kRowsThreads;
-      w[j] = stream_load<u32x4>(s + (i < width ? i : width - 1u));
-    }
-#pragma unroll
-    for (uint32_t j = 0; j < kRowsLoads; ++j) {
-      const uint32_t i = i0 + j * kRowsThreads;
-      if (i < width) *(KVC_GLOBAL u32x4*)(d + i) = w[j];
-    }
-    pass += gridDim.x;
-    row += pass / passes;
-    pass %= passes;
-  }
-}
-
 }  // namespace
-
-bool can_copy_rows(const HostRows& r) {
-  const uint64_t all = reinterpret_cast<uintptr_t>(r.src) | reinterpret_cast<uintptr_t>(r.dst) | r.width | r.src_pitch | r.dst_pitch;
-  return (all & 15u) == 0 && r.width > 0 && r.width < (1ull << 32) && r.rows > 0 && r.rows < (1u << 31);
-}
-
-kvc_status launch_copy_rows(const HostRows& r, hipStream_t stream) {
-  const uint32_t width = (uint32_t)(r.width / 16), passes = (width + kRowsPass - 1) / kRowsPass;
-  const uint64_t all = (uint64_t)passes * r.rows;
-  hipLaunchKernelGGL(copy_rows_kernel, dim3(all < kRowsWorkgroups ? (uint32_t)all : kRowsWorkgroups), dim3(kRowsThreads), 0, stream,
-                     static_cast<const u32x4*>(r.src), static_cast<u32x4*>(r.dst), width, (uint64_t)(r.src_pitch / 16),
-                     (uint64_t)(r.dst_pitch / 16), r.rows, passes);
-  return hipGetLastError() == hipSuccess ? KVC_OK : KVC_ERR_RUNTIME;
-}
 
 kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t layers, hipStream_t stream) {
   const uint32_t most = k.pairs > v.pairs ? k.pairs : v.pairs, per_wg = kCopyThreads * kCopyPerThread;

@@ -1245,10 +1245,9 @@ def test_long_chunks_packed_into_pinned_host_memory():
 @pytest.mark.parametrize("off", [0, 8])
 @pytest.mark.parametrize("geo", [(5, 8, 128, 2048, 8, 128, 8, 64), (2, 3, 24, 100, 3, 24, 5, 7), (4, 1, 8, 70, 1, 8, 3, 3)],
                          ids=["1.5 MB frames", "7.5 KB frames", "216-byte frames"])
-def test_staged_copies_by_kernel_and_by_the_runtime(geo, off):
-    """Pieces of every kind through the staging: small ones that a kernel copies out of the mapped blobs (last pass of a row
-    cut short), pieces beyond its size, and (blobs or frames that are not whole 16-byte words) the runtime's copies; every
-    one of them as often as the ring goes round.  The cache is what one restore of the same bytes gives."""
+def test_staged_copies_of_pieces_of_every_kind(geo, off):
+    """Pieces of every kind through the staging, from blobs and of frames that are whole 16-byte words or are not, every one
+    of them as often as the ring goes round.  The cache is what one restore of the same bytes gives."""
     L, H, D, T, th, tw, TX, TY = geo
     kvc, C, bs, n = hz.kvc, H * D, 16, 2 * T + T // 2 + 3
     glo, _ = hz.layouts(L, H, D, "f16", T, th, tw, TX, TY)
@@ -1285,6 +1284,55 @@ def test_staged_copies_by_kernel_and_by_the_runtime(geo, off):
         assert int(cache.err.item()) == 0
         for l in range(L):
             assert torch.equal(cache.layers[l], want.layers[l]), (order, per_slot, l)
+
+
+@pytest.mark.parametrize("order,per_slot", [(None, 0), (0, 4), (1, 8)], ids=["whole chunks", "chunk order", "layer order"])
+def test_staged_copies_need_no_compute_unit(order, per_slot):
+    """A fetch goes on beside a chip that is full of other work, and leaves that work its rate: what it captures is a kernel
+    for every restore (and in layer order one for the pairs of a unit), and all other transfers are copies."""
+    import ctypes
+
+    L, H, D, T, F, LG, nc, bs = 5, 8, 128, 512, 4, 2, 2, 16
+    kvc, C, n = hz.kvc, H * D, nc * T
+    glo, _ = hz.layouts(L, H, D, "f16", T, 8, 128, 8, 16)
+    fb, mb, f = kvc.chunk_sizes(glo)
+    assert f == F
+    fs, moff, nb = kvc.frame_size(glo), kvc.blob_meta_offset(glo), n // bs
+    blobs = torch.zeros((nc, (moff + mb + 255) // 256 * 256), dtype=torch.uint8, pin_memory=True)
+    tab = torch.arange(nb, dtype=torch.int32, device="cuda")
+    cache = hz.PagedCache(L, nb, bs, C)
+    chunks = [(blobs[i].data_ptr(), moff + mb, T) for i in range(nc)]
+    s_copy, s_comp = torch.cuda.Stream(), torch.cuda.Stream()
+    size = moff + mb if order is None else per_slot * fs
+    ms = 1 if order is None else kvc.meta_staging_size(glo, order)
+    slots = [torch.empty(size, dtype=torch.uint8, device="cuda") for _ in range(3)]
+    metas = [torch.empty(ms, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    tail = (cache.ptrs.data_ptr(), nb, bs, tab.data_ptr(), nb, cache.err.data_ptr(), s_copy.cuda_stream, s_comp.cuda_stream)
+    torch.cuda.synchronize()
+    hz.say(f"[case] nodes of a captured fetch, order={order}")
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=s_copy):
+        if order is None:
+            kvc.kvc_fetch_pipeline(glo, chunks, [t.data_ptr() for t in slots], size, *tail, timed=False)
+        else:
+            kvc.kvc_fetch_pipeline_frames(glo, chunks, [t.data_ptr() for t in slots], size, [t.data_ptr() for t in metas], ms,
+                                          *tail, order=order, timed=False)
+        s_copy.wait_event(s_comp.record_event())
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    kinds = []
+    for node in nodes:
+        kind = ctypes.c_int(-1)
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        kinds.append(kind.value)
+    kernels, copies = kinds.count(0), kinds.count(1)   # hipGraphNodeTypeKernel, hipGraphNodeTypeMemcpy
+    restores = {None: nc, 0: nc * (2 * LG * F // 4), 1: nc * LG * 2}[order]
+    assert kernels == restores + (nc * LG if order == 1 else 0), kinds
+    assert copies == {None: nc, 0: restores + nc, 1: nc * LG}[order], kinds
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
