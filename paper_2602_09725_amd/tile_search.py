@@ -14,6 +14,9 @@ from . import kvc
 # with part of the chip idle: side by side they fill it better (20 candidates of 6 layers x 2048 tokens x 1024 channels in
 # one stream 1118 us, in 2 / 3 / 4 streams 997 / 961 / 915; of 32 layers 6310 and 6125 / 6130 / 6060).
 LANES = 4
+# Bytes of a candidate's frames, pairs and counters up to which that many are under way.  Of larger ones two are, which is
+# nearly as fast (the 32 layers above: a set is 151 MB) and takes no more memory than a candidate and its successor.
+SMALL_SET = 64 << 20
 
 
 class _Lane:
@@ -84,12 +87,16 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
                     if not lanes:  # all buffers before the caller's stream has work that the others would wait for
                         lanes.append(_Lane(stream, kv.device, stream))
                         lanes[0].buffers(sizes)
-                        while len(lanes) < min(LANES, len(candidates) - at):
+                        while len(lanes) < min(LANES if sum(sizes) <= SMALL_SET else 2, len(candidates) - at):
                             lanes.append(_Lane(stream, kv.device))
                             lanes[-1].buffers(sizes)
                         ready = stream.record_event()
                         for lane in lanes:
                             lane.ready = ready
+                    if sum(sizes) > SMALL_SET:
+                        for other in lanes[2:]:
+                            other.release()
+                        del lanes[2:]
                     lane = lanes[i % len(lanes)]
                     frames, meta, hist = lane.buffers(sizes)
                 except torch.OutOfMemoryError:  # one lane needs no more than one candidate does

@@ -1,5 +1,5 @@
 """The tiling search's streams and buffers against a model of a stream-ordered allocator, on the CPU: whatever two
-candidates do to one address has to be ordered by the streams they are on."""
+candidates do to one address has to be ordered by the streams they are on, and memory stays what a search may take."""
 import types
 
 import pytest
@@ -199,3 +199,14 @@ def test_no_address_is_used_on_two_streams_without_an_order(kvc_lib, monkeypatch
             assert len(rows) == len(sizes) and not m.races, m.races[:5]
         m, rows = search(monkeypatch, *shape, candidates=order, refuse_above=max(sizes) * 3 // 2 + (1 << 20))
         assert len(rows) == len(sizes) and not m.races, m.races[:5]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=[f"s{i}" for i in range(len(SHAPES))])
+def test_memory_of_a_search(kvc_lib, monkeypatch, shape):
+    """Two candidates' buffers at a time, and up to LANES only while they are small."""
+    sizes = sets_of(*shape)
+    for order in (None, kvc.tile_candidates(shape[1], shape[2])[::-1]):
+        m, _ = search(monkeypatch, *shape, candidates=order)
+        slack = 64 * 1024 + len(sizes) * 16 * 1024
+        assert m.peak <= max(2 * max(sizes), tile_search.LANES * min(max(sizes), tile_search.SMALL_SET)) + slack
+        assert m.live <= slack   # all given back but what the result rests on
