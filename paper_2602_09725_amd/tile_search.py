@@ -5,6 +5,8 @@ resolution (kvc_pack), its residual histograms are counted (kvc_residual_histogr
 bits (kvc_proxy_costs); candidates are ranked by that cost.  This module only loops and marshals: every
 byte of every candidate is produced and counted by the library's kernels.
 """
+import threading
+
 import torch
 
 from . import kvc
@@ -19,14 +21,32 @@ LANES = 4
 SMALL_SET = 64 << 20
 
 
+# Streams beside the caller's, device -> up to LANES - 1, kept by each thread for its next search: a stream's first use takes
+# 130-190 us (3.7 ms where it brings a hardware queue, of which a process has four), and a candidate about 50.
+class _Own(threading.local):
+    def __init__(self):
+        self.streams = {}
+
+
+_own = _Own()
+
+
+def _side_stream(device, i):
+    streams = _own.streams.setdefault(device, [])
+    while len(streams) <= i:
+        streams.append(torch.cuda.Stream(device))
+    return streams[i]
+
+
 class _Lane:
     """A stream and the buffers of the candidate that is under way on it, which are then its next one's.  Buffers are
     allocated on the caller's stream `home`, whose allocator knows the order of that stream only: a block that it hands out
     may be in use by what was enqueued there before, by the lane on that stream or by anyone else who shares it.  So a lane
     on another stream waits for what `home` held when it allocated; and what it gives back is not reused before it is done."""
 
-    def __init__(self, home, device, stream=None):
-        self.home, self.device, self.stream = home, device, stream  # None: one of its own, from the first use on
+    def __init__(self, home, device, stream=None, side=0):
+        self.home, self.device, self.stream = home, device, stream  # None: the thread's side stream, from the first use on
+        self.side = side
         self.ready = None
         self.sizes, self.pointers, self.memory = (0, 0, 0), (), None
 
@@ -50,7 +70,7 @@ class _Lane:
     def handle(self):
         """Of the stream, on which the buffers may be used; `ready`, if set, is an event of `home` after their allocation."""
         if self.stream is None:
-            self.stream = torch.cuda.Stream(self.device)
+            self.stream = _side_stream(self.device, self.side)
             self.stream.wait_event(self.ready or self.home.record_event())
         return self.stream.cuda_stream
 
@@ -88,7 +108,7 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
                         lanes.append(_Lane(stream, kv.device, stream))
                         lanes[0].buffers(sizes)
                         while len(lanes) < min(LANES if sum(sizes) <= SMALL_SET else 2, len(candidates) - at):
-                            lanes.append(_Lane(stream, kv.device))
+                            lanes.append(_Lane(stream, kv.device, side=len(lanes) - 1))
                             lanes[-1].buffers(sizes)
                         ready = stream.record_event()
                         for lane in lanes:

@@ -105,9 +105,10 @@ class Tensor:
             self.model.free.setdefault(self.owner, []).append((self.at, self.n))
 
 
-def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, candidates=None, meanwhile=None, refuse_above=None):
+def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, candidates=None, meanwhile=None, refuse_above=None,
+           model=None, stream=None):
     """rank_tiles on the model; `meanwhile(model)` runs after the first candidate is enqueued."""
-    m = Model()
+    m = model or Model()
     m.refuse_above = refuse_above
 
     class Scope:
@@ -151,7 +152,7 @@ def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, c
     monkeypatch.setattr(tile_search.kvc, "kvc_proxy_costs", costs)
     kv = types.SimpleNamespace(shape=(layers, 2, tokens, heads, head_dim), is_cuda=True, is_contiguous=lambda: True,
                                element_size=lambda: 2, device=m, data_ptr=lambda: 1 << 60)
-    rows = tile_search.rank_tiles(kv, tokens, kvc.KVC_F16, chunk, width, height, candidates=candidates, stream=m.caller)
+    rows = tile_search.rank_tiles(kv, tokens, kvc.KVC_F16, chunk, width, height, candidates=candidates, stream=stream or m.caller)
     return m, rows
 
 
@@ -210,3 +211,22 @@ def test_memory_of_a_search(kvc_lib, monkeypatch, shape):
         slack = 64 * 1024 + len(sizes) * 16 * 1024
         assert m.peak <= max(2 * max(sizes), tile_search.LANES * min(max(sizes), tile_search.SMALL_SET)) + slack
         assert m.live <= slack   # all given back but what the result rests on
+
+
+def test_streams_are_made_once(kvc_lib, monkeypatch):
+    """The first use of a stream costs as much as a candidate, so a thread's next search has those of its last one, on
+    whatever stream it is called, and each thread has its own."""
+    import threading
+
+    shape, m = SHAPES[0], Model()
+    other = Stream(m)
+    for stream in (m.caller, other, m.caller, other):
+        search(monkeypatch, *shape, model=m, stream=stream)
+        assert len(m.streams) <= 2 + tile_search.LANES - 1
+    small = SHAPES[4]
+    search(monkeypatch, *small, model=m, stream=other)
+    assert not m.races and len(m.streams) == 2 + tile_search.LANES - 1
+    thread = threading.Thread(target=lambda: search(monkeypatch, *small, model=m, stream=m.caller))
+    thread.start()
+    thread.join()
+    assert not m.races and len(m.streams) == 2 + 2 * (tile_search.LANES - 1)
