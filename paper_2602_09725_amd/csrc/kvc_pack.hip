@@ -680,9 +680,10 @@ constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kN
 // The exchange needs no memory of its own: member j leaves the extremes of channel ch, two 16-bit values, in a word of the
 // codes of the chunk's token 4 j + (ch % 8) / 2, and the codes of token 4 * members hold the number of members that have
 // read all words.  A kernel ahead on the stream has set the words to a value that no extremes have (a NaN twice) and the
-// number to zero.  Every word is written once, by one atomic store, and says itself whether it has been, so no fence and no
-// order between different words is needed.  The member that finds itself the last reader stores the codes of those tokens;
-// nobody reads a word after that.
+// number to zero.  A word is written by one atomic store and says itself whether it has been, so its readers need no fence
+// and no order between different words.  The member that finds itself the last reader stores the codes of those tokens;
+// nobody reads a word after that.  These codes overwrite the words, so the words have to have arrived: a thread waits for the
+// acknowledgement of its store, made at the scope of the device, before the barrier behind which its member is counted.
 //
 // The members of a strip are neighbours in the order of dispatch and on one XCD.  A member that does not see all words after
 // `waits` tries waits no longer: it reads the columns of the whole chunk itself, with the same result.  So the kernel ends
@@ -715,6 +716,10 @@ struct Members {
   bool real;       // the thread's channel exists
   __device__ __forceinline__ void exchange(float& lo, float& hi) {
     if (members == 1u || !real) return;
+    tell_and_ask(lo, hi);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // also where it gave up, and has not read its own word back
+  }
+  __device__ __forceinline__ void tell_and_ask(float& lo, float& hi) {
     const uint32_t ch = threadIdx.x, sub = (ch & 7u) >> 1;
     // both values are 16-bit ones, so nothing is rounded
     __hip_atomic_store(slots.at(me * kSlotTokens + sub, ch), narrow_pair<DT>(lo, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -851,7 +856,7 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
       add_numbers_again(st, srcb - (size_t)first * ts2, off_row, off_step, (n_chunk - 1u) * (uint64_t)ts2 + e * 2u);
       strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
     }
-    if (members > 1u && tid == 0)  // (all of the workgroup's words have been read before the second barrier)
+    if (members > 1u && tid == 0)  // (the workgroup's words have arrived, and been read, before the second barrier)
       left_before = __hip_atomic_fetch_add(slots.at(kSlotTokens * members, 0u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
     strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
