@@ -693,7 +693,10 @@ static_assert(kSharedLds == kStreamStashLoads, "the launch of the two-pass form 
 constexpr uint32_t kEmptySlot = 0xffffffffu;
 constexpr uint32_t kSlotTokens = 4;    // tokens whose codes are a member's slots: 4 bytes a channel, 1 byte a code
 constexpr uint32_t kClearThreads = 256;
-constexpr int kMostMembers = 128;      // the slots are in the first member's tokens
+// The members of a strip have to be on chip together, and are on one XCD: each takes one of its 32 CUs.  (32 layers x 1024
+// channels, one chunk of 24 576 / 36 864 / 49 152 tokens: 1219 / 1926 / 2640 us two-pass, 944 / 1491 / 1951 with 16 / 24 / 32
+// members.  With more, those that start wait in vain for the rest.)
+constexpr int kMostMembers = 32;
 
 // The word of channel ch (of a strip that starts with element strip_e) in the codes of token t.
 struct StripSlots {

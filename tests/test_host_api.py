@@ -430,15 +430,17 @@ def test_probe_expand_rejects_bad_arguments(kvc_lib):
 
 def test_long_chunks_share_strips_as_wide_as_a_line_of_codes(kvc_lib):
     """Strips of 128 channels in the two-pass form are shared ones; calls whose token stride does not fit the 32-bit offsets
-    of a workgroup's tokens, and longer chunks than 128 workgroups hold or 32-bit offsets reach, are not."""
+    of a workgroup's tokens, and longer chunks than 32 workgroups hold (the CUs of an XCD, each of which takes one of them) or
+    32-bit offsets reach, are not."""
     def form(T, n=None, ts=1024, layers=32, **kw):
         lo = good(num_layers=layers, chunk_tokens=T, tiles_y=-(-T // 8), **kw)
         return kvc.pack_form(lo, (0, 0, ts), n or T)
     assert form(2304) == form(10240) == form(10240, 30720) == form(10240, 2304) == (TWO_PASS, 128, 1024)
     assert form(2303) == form(2100, 30720) == form(10240, 2100) == (TWO_PASS, 64, 1024)   # one workgroup holds them
     assert form(10240, k_mode=1, v_mode=0)[1] == 128 and form(10240, k_mode=1)[1] == 0
-    assert form(128 * 1536, layers=8)[1] == 128 and form(128 * 1536 + 1, layers=8)[1] == 64
-    assert form(60000)[1] == 128 and form(64000)[1] == 64     # 2^32 bytes of frames
+    assert form(32 * 1536, layers=8)[1] == 128 and form(32 * 1536 + 1, layers=8)[1] == form(60000)[1] == form(128 * 1536, layers=8)[1] == 64
+    wide = dict(num_kv_heads=32, tile_h=32, layers=32, ts=4096)
+    assert form(15000, **wide)[1] == 128 and form(16500, **wide)[1] == 64     # 2^32 bytes of frames
     edge = 2**32 // (1536 * 2)
     assert form(4096, ts=edge // 8 * 8)[1] == 128 and form(4096, ts=edge // 8 * 8 + 8)[1] == 64
     assert form(10240, tile_h=16, tile_w=64)[1] == 64
