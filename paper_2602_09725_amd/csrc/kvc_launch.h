@@ -71,9 +71,11 @@ kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t laye
 
 constexpr int kPackResident = KVC_PACK_RESIDENT, kPackStream = KVC_PACK_TWO_PASS, kPackLight = KVC_PACK_LIGHT, kPackMedium = KVC_PACK_MEDIUM;
 
-// How often the members of a shared strip look for each other's extremes before they do without: about a microsecond
-// each, where the others start within a few.
-constexpr uint32_t kPackWaits = 1024;
+// How often the members of a shared strip look for each other's extremes before they read what is missing: about a
+// microsecond each.  On an idle chip up to 27 members need between 64 and 128 looks (three chunks of 10 240 tokens 1225 us with 64,
+// 1217 with 128 and more), and beside other work every look is lost (four calls at a time of 16 members each 1138 us a call
+// with 64, 1275 with 128, 1605 with 256, 3562 with 1024).
+constexpr uint32_t kPackWaits = 128;
 
 // A range of work units and the share of one XCD.
 struct PackRange {

@@ -443,9 +443,9 @@ __device__ __forceinline__ void add_numbers_again(ColumnStats<DT>& st, const voi
 // lane per atom leaves the wave's extremes in LDS, one thread per channel finishes the reduction, derives the
 // parameters, writes the channel's {scale, mn} pair, and hands {mn, inv} to all threads through LDS.  Two barriers;
 // every thread of the workgroup must come here.  `others` makes the extremes of the workgroup's tokens those of the whole
-// strip where several workgroups share it.
+// strip where several workgroups share it, or says that it cannot yet: the channel's parameters are then not stored.
 struct Alone {  // the workgroup has all tokens of its strip
-  __device__ __forceinline__ void exchange(float&, float&) {}
+  __device__ __forceinline__ bool exchange(float&, float&) { return true; }
 };
 
 template <int DT, typename Others = Alone>
@@ -478,12 +478,12 @@ __device__ __forceinline__ void strip_parameters(const PackParams& p, ColumnStat
       l0 = __builtin_fminf(l0, red_lo[w][tid]);
       h0 = __builtin_fmaxf(h0, red_hi[w][tid]);
     }
-    others.exchange(l0, h0);
+    const bool whole = others.exchange(l0, h0);
     const GroupParams q = group_params(l0, h0);
     par_mn[tid] = q.mn;
     par_inv[tid] = q.inv;
     const uint32_t ch = strip * sa * 8u + tid;
-    if (ch < (uint32_t)g.C) {
+    if (whole && ch < (uint32_t)g.C) {
       float* mp = p.meta + (int64_t)c * g.meta_floats + g.meta_off[kind] + 2 * ((int64_t)l * g.C + ch);
       *reinterpret_cast<f32x2*>(mp) = f32x2{q.scale, q.mn};
     }
@@ -686,12 +686,19 @@ constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kN
 // acknowledgement of its store, made at the scope of the device, before the barrier behind which its member is counted.
 //
 // The members of a strip are neighbours in the order of dispatch and on one XCD.  A member that does not see all words after
-// `waits` tries waits no longer: it reads the columns of the whole chunk itself, with the same result.  So the kernel ends
-// wherever and in whatever order its workgroups run.
+// `waits` looks waits no longer: it reads the tokens of one member whose words are missing (of several, those that wait take
+// different ones), stores that member's words itself, the same ones, and looks again.  So the kernel ends wherever and in
+// whatever order its workgroups run, and costs no more than reading twice where few of them are on chip together: with no
+// look at all (chunks of 10 240 / 24 576 / 49 152 tokens x 32 layers) 437 / 1044 / 2161 us, shared 390 / 932 / 1952, two-pass
+// 449 / 1219 / 2640; two calls at a time of 32 members each 2674 us a call, two-pass 2668 (12.4 ms when each that was late read
+// the whole chunk); beside a loop of HBM copies 4.3 and 3.7 ms (17.8).  Beside large matrix products two passes are faster (10 240
+// tokens 9.9 against 14.7 ms, 24 576 2.7 against 9.4): every workgroup needs a CU of its own, and shared strips have more.
 constexpr int kSharedRegs = 16, kSharedLds = 8, kSharedLoads = kSharedRegs + kSharedLds;  // loads of a thread that wait
 static_assert(kSharedLds == kStreamStashLoads, "the launch of the two-pass form is theirs");
 constexpr uint32_t kEmptySlot = 0xffffffffu;
 constexpr uint32_t kSlotTokens = 4;    // tokens whose codes are a member's slots: 4 bytes a channel, 1 byte a code
+constexpr uint32_t kHelpLoads = 4;     // loads of a thread in flight while it reads another member's tokens
+static_assert(kSharedLoads % kHelpLoads == 0, "whole groups of loads stay within a member's 32-bit offsets");
 constexpr uint32_t kClearThreads = 256;
 // The members of a strip have to be on chip together, and are on one XCD: each takes one of its 32 CUs.  (32 layers x 1024
 // channels, one chunk of 24 576 / 36 864 / 49 152 tokens: 1219 / 1926 / 2640 us two-pass, 944 / 1491 / 1951 with 16 / 24 / 32
@@ -710,50 +717,53 @@ struct StripSlots {
   }
 };
 
-// The members of a strip, as one of them sees them: thread ch of the workgroup brings the extremes of channel ch.
+// The members of a strip, as one of them sees them: thread ch of the workgroup brings the extremes of channel ch, of its own
+// tokens or (further turns) of those of member `whose`, and leaves with those of the strip.  Bit j of missing[turn & 1]: the
+// word of member j was not there for some channel.
 template <int DT>
 struct Members {
   StripSlots slots;
-  uint32_t me, members, waits;
-  uint32_t* late;  // LDS, set when a word did not come
-  bool real;       // the thread's channel exists
-  __device__ __forceinline__ void exchange(float& lo, float& hi) {
-    if (members == 1u || !real) return;
-    tell_and_ask(lo, hi);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // also where it gave up, and has not read its own word back
-  }
-  __device__ __forceinline__ void tell_and_ask(float& lo, float& hi) {
+  uint32_t members, whose, turn, waits;
+  uint32_t* missing;  // LDS
+  bool real;          // the thread's channel exists
+  __device__ __forceinline__ bool exchange(float& lo, float& hi) {
+    if (threadIdx.x == 0) missing[~turn & 1u] = 0u;  // nobody looks at the last turn's any more, nor yet at the next one's
+    if (members == 1u || !real) return true;
     const uint32_t ch = threadIdx.x, sub = (ch & 7u) >> 1;
     // both values are 16-bit ones, so nothing is rounded
-    __hip_atomic_store(slots.at(me * kSlotTokens + sub, ch), narrow_pair<DT>(lo, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(slots.at(whose * kSlotTokens + sub, ch), narrow_pair<DT>(lo, hi), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     constexpr uint32_t J = 4;  // words asked for at once
-    uint32_t tries = 0;
+    uint32_t tries = 0, gone = 0;
     for (uint32_t j0 = 0; j0 < members; j0 += J) {
       KVC_GLOBAL uint32_t* at[J];
       uint32_t w[J];
 #pragma unroll
-      for (uint32_t j = 0; j < J; ++j) at[j] = slots.at((j0 + j < members ? j0 + j : me) * kSlotTokens + sub, ch);
+      for (uint32_t j = 0; j < J; ++j) at[j] = slots.at((j0 + j < members ? j0 + j : whose) * kSlotTokens + sub, ch);
       for (;;) {
         bool all = true;
 #pragma unroll
         for (uint32_t j = 0; j < J; ++j) w[j] = __hip_atomic_load(at[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (uint32_t j = 0; j < J; ++j) all = all && w[j] != kEmptySlot;
-        if (all) break;
-        if (tries++ >= waits) {
-          *late = 1u;
-          return;
-        }
+        if (all || tries >= waits) break;
+        ++tries;
         __builtin_amdgcn_s_sleep(4);
       }
 #pragma unroll
       for (uint32_t j = 0; j < J; ++j) {
-        float l, h;
-        widen_pair<DT>(w[j], l, h);
-        lo = __builtin_fminf(lo, l);
-        hi = __builtin_fmaxf(hi, h);
+        if (w[j] == kEmptySlot) {
+          if (j0 + j < members) gone |= 1u << (j0 + j);
+        } else {
+          float l, h;
+          widen_pair<DT>(w[j], l, h);
+          lo = __builtin_fminf(lo, l);
+          hi = __builtin_fmaxf(hi, h);
+        }
       }
     }
+    if (gone != 0u) __hip_atomic_fetch_or(&missing[turn & 1u], gone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the word has arrived, also where it was not read back
+    return gone == 0u;
   }
 };
 
@@ -852,12 +862,33 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
   if (SHARED) {
     const StripSlots slots{g, fplane, strip * sa * 8u};
     if (tid == 0) flags[0] = 0u;  // seen by all after the first barrier
-    strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv,
-                         Members<DT>{slots, me, members, p.waits, flags, strip * sa * 8u + tid < (uint32_t)g.C});
-    if (flags[0] != 0u) {  // the others did not come in time: the columns of the whole chunk from memory
-      __syncthreads();
-      add_numbers_again(st, srcb - (size_t)first * ts2, off_row, off_step, (n_chunk - 1u) * (uint64_t)ts2 + e * 2u);
-      strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv);
+    Members<DT> others{slots, members, me, 0u, p.waits, flags, strip * sa * 8u + tid < (uint32_t)g.C};
+    strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv, others);
+    // Members that did not come in time, one of them a turn, until there is none.
+    for (;;) {
+      uint32_t gone = wave_uniform(flags[others.turn & 1u]);
+      if (gone == 0u) break;
+      for (uint32_t k = me % (uint32_t)__popc(gone); k != 0u; --k) gone &= gone - 1u;
+      const uint32_t j = (uint32_t)__ffs((int)gone) - 1u;
+      const uint32_t n_j = j + 1u < members ? (uint32_t)p.member_tokens : n_chunk - j * (uint32_t)p.member_tokens;
+      const uint8_t* src_j = srcb + ((int64_t)j - (int64_t)me) * p.member_tokens * (int64_t)ts2;
+      const uint32_t last_j = (n_j - 1u) * ts2 + e * 2u;
+      st.init();
+#pragma unroll 1
+      for (uint32_t i0 = 0; i0 < (uint32_t)NI && i0 * rows < n_j; i0 += kHelpLoads) {
+        u32x4 w[kHelpLoads];
+#pragma unroll
+        for (uint32_t u = 0; u < kHelpLoads; ++u) {
+          const uint32_t off = off_row + (i0 + u) * off_step;
+          w[u] = *(const KVC_GLOBAL u32x4*)(src_j + (size_t)(off < last_j ? off : last_j));
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < kHelpLoads; ++u) st.add_numbers(w[u]);
+      }
+      others.whose = j;
+      others.waits = p.waits / 4u;  // others may be reading what else is missing
+      ++others.turn;
+      strip_parameters<DT>(p, st, strip, kind, l, c, red_lo, red_hi, mnv, inv, others);
     }
     if (members > 1u && tid == 0)  // (the workgroup's words have arrived, and been read, before the second barrier)
       left_before = __hip_atomic_fetch_add(slots.at(kSlotTokens * members, 0u), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -907,9 +938,9 @@ __device__ __forceinline__ void pack_channel_body_resident(const PackParams& p, 
     stream_store<u32x2>(fplane + (size_t)(f * frame3 + ty * trs + tx * (uint32_t)g.tw + lane_off), u32x2{0u, 0u});
   }
   if (SHARED && members > 1u) {  // the last to have read the slots stores the codes that belong there
-    if (tid == 0) flags[1] = left_before;
+    if (tid == 0) flags[2] = left_before;
     __syncthreads();
-    if (flags[1] != members - 1u || !active) return;
+    if (flags[2] != members - 1u || !active) return;
     const uint8_t* chunk = srcb - (size_t)first * ts2;
     uint8_t* fbase = fplane + lane_off;
     for (uint32_t t = row; t <= kSlotTokens * members; t += rows) {
@@ -1008,7 +1039,7 @@ pack_kernel(const PackParams p) {
   constexpr int kWaves = (BODY == kPackStream ? 1024 : kResidentThreads) / 64;
   __shared__ float red_lo[kWaves + 1][kMaxStripAtoms * 8];
   __shared__ float red_hi[kWaves + 1][kMaxStripAtoms * 8];
-  __shared__ uint32_t flags[2];  // of shared strips
+  __shared__ uint32_t flags[3];  // of shared strips
   extern __shared__ u32x4 stash[];  // the loads of the per-channel bodies that wait in LDS, one slot per thread each
   // Workgroups go to the 8 XCDs round-robin.  Units come in ranges: the per-channel ones, the per-token ones (each first
   // of the whole chunks, then of a short last chunk, so that every XCD has the same mix of work: 2048 + 128 tokens of 60
