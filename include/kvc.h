@@ -167,7 +167,8 @@ kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides stride
 /* kvc_pack with another bound on a wait (test aid).  Workgroups that share a
  * strip of a long chunk (kvc_pack_launch_form) tell each other the extremes of
  * its columns; one that does not see all of them after `waits` further looks
- * reads the tokens of those that are missing.  The results are the same. */
+ * reads the tokens of those that are missing.  The results are the same, and
+ * no bound is longer than kvc_pack's. */
 kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens,
                           uint8_t* frames, size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits,
                           void* stream);

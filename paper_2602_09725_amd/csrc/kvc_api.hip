@@ -216,13 +216,10 @@ size_t kvc_blob_meta_offset(const kvc_layout* layout) {
   return (fb + 255) & ~(size_t)255;
 }
 
-kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
-                    size_t frames_cap, void* meta, size_t meta_cap, void* stream) {
-  return kvc_probe_pack(layout, kv, strides, n_tokens, frames, frames_cap, meta, meta_cap, kPackWaits, stream);
-}
+namespace {
 
-kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
-                          size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits, void* stream) {
+kvc_status pack_call(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
+                     size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits, void* stream) {
   PackParams p{};
   p.waits = waits;
   kvc_status st = make_geo(layout, &p.g);
@@ -245,6 +242,18 @@ kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides 
   p.meta = static_cast<float*>(meta);
   p.shareable = p.g.T > 2048 && on_this_device(frames);  // (shorter chunks have no strips to share)
   return launch_pack(p, as_stream(stream));
+}
+
+}  // namespace
+
+kvc_status kvc_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
+                    size_t frames_cap, void* meta, size_t meta_cap, void* stream) {
+  return pack_call(layout, kv, strides, n_tokens, frames, frames_cap, meta, meta_cap, kPackWaits, stream);
+}
+
+kvc_status kvc_probe_pack(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, uint8_t* frames,
+                          size_t frames_cap, void* meta, size_t meta_cap, uint32_t waits, void* stream) {
+  return pack_call(layout, kv, strides, n_tokens, frames, frames_cap, meta, meta_cap, waits < kPackWaits ? waits : kPackWaits, stream);
 }
 
 namespace {

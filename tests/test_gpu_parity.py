@@ -1241,7 +1241,7 @@ def test_strips_of_as_many_members_as_an_xcd_has_cus(dtype):
     fb, mb, _ = hz.kvc.chunk_sizes(glo)
     streams = [torch.cuda.Stream() for _ in range(4)]
     out = [(torch.full((fb,), 0xA5, dtype=torch.uint8, device="cuda"), torch.empty(mb, dtype=torch.uint8, device="cuda")) for _ in streams]
-    for waits in (128, 5, 0):
+    for waits in (128, 5, 0, 2**32 - 1):   # no bound is longer than the usual one
         hz.say(f"[case] 32 members, four calls at a time, {dtype}, waits={waits}")
         torch.cuda.synchronize()
         for _ in range(3):
