@@ -58,10 +58,13 @@ constexpr int64_t kManyWorkgroups = 4096;
 // out): fewer reads between the writes and fewer regions of the cache under way (2048 tokens x 32 layers x 4096 channels 289 us
 // with four, 285 with three, 272 with two; 32K tokens x 1024 channels in block order 1157 / 1130 / 1114; 5000 tokens into a
 // contiguous tensor 744 / 743 / 727; but 50 tokens in passes of two 12.0 / 12.5 / 13.9).  Three where a (kind, layer)'s tokens
-// take 40 MB and more of a paged cache and a token 2 KB and more (32K tokens in a random order 1186 / 1178 / 1190, 20 000 tokens
-// of 60 layers 1386 / 1373 / 1382; 20 000 x 512 channels, 20 MB, 698 / 691 / 685).
+// take 40 MB and more of a paged cache and a token 2 KB and more: in a random order two gain nothing there (32K tokens 1186 /
+// 1178 / 1190, 64K 2418 / 2403 / 2421, 20 000 of 60 layers 1372 / 1363 / 1364; 20 000 x 512 channels, 20 MB, 698 / 691 / 685),
+// and beside other work three are better (32K tokens beside matrix products 1872 / 1872 / 1913-2615, beside matrix-vector
+// products 1690 / 1541 / 1680); blocks in order, or tokens of 8 KB, would take 2-5 % less alone with two.
+// Beside a kernel that copies within HBM four would be better than either (1907 / 2034 / 2018).
 constexpr unsigned kLdsForTwo = 64000, kLdsForThree = 53000;
-constexpr int64_t kLargeRegion = 40 << 20;
+constexpr int64_t kLargeRegion = 40 * 1000 * 1000;
 
 __device__ __forceinline__ uint32_t lane_value(uint32_t v, uint32_t k) {
   return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k);
@@ -613,7 +616,9 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   if (body == kBodyWaves && u == kPasses && threads == 512 && !p.frame_mode && !p.host_frames)
     lds = paged && g.C >= 1024 && p.n_tokens * g.C * 2 >= kLargeRegion ? kLdsForThree : kLdsForTwo;
   // "rows" into a contiguous tensor on tiles 8 high: stores in a straight line and two workgroups a CU (8192 tokens x 32 layers
-  // x 1024 channels 274 -> 267 -> 262 us, 32K tokens 1136 -> 1145 -> 1108).  Tiles 16 high, 1024 threads, are left: 675 -> 682.
+  // x 1024 channels 274 -> 267 -> 262 us, 32K tokens 1136 -> 1145 -> 1108).  Other heights are left: with half the waves a CU can
+  // hold, 8192 / 30 000 tokens x 32 layers of tiles 4 high take 137.5 / 531 -> 135 / 525 us, 5 high 175 / 654 -> 173 / 658, 6 high
+  // 210 / 782 -> 208 / 776, 10 high 353 / 1311 -> 350 / 1304, 12 high 428 / 1572 -> 432 / 1590, 16 high 551 / 2000 -> 562 / 2048.
   if (body == kBodyRows && !paged && threads == 512 && !p.host_frames) {
     body = kBodyRowsLine;
     lds = kLdsForTwo;
