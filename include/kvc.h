@@ -204,6 +204,8 @@ typedef enum kvc_pack_launch_form {
  *   *strip_channels  HOST out, nullable: channels of a per-channel workgroup's
  *                    strip, 0 when no kind is quantized per channel
  *   *threads         HOST out, nullable: threads per workgroup
+ * For frames in memory of the device: kvc_pack shares no strips where they are
+ * elsewhere (two passes over strips of 64 channels then).
  * Returns the status kvc_pack would return, pointers and capacities apart. */
 kvc_status kvc_pack_form(const kvc_layout* layout, kvc_strides strides, int64_t n_tokens, int32_t* form,
                          int32_t* strip_channels, int32_t* threads);

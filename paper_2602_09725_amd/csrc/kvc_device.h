@@ -59,8 +59,9 @@ __device__ __forceinline__ uint32_t wave_uniform(uint32_t v) { return __builtin_
 
 // A launch's parameters (the kernel's only argument, or its first) fill several lines of the scalar cache, which at the
 // start of a launch are far away, and kernels come to need them one after the other.  Asking for a word of every line
-// first makes one wait of these (restore, 552 bytes: one frame of 1.5 MB 5.4 -> 4.8 us, 50 tokens x 32 layers x 4096 channels
-// 14.5 -> 13.4, 300 tokens of 60 layers x 512 channels 15.7 -> 14.4; pack, two layers of 2048 tokens 10.6 -> 10.2).
+// first makes one wait of these (kernels in a loop, restore, 552 bytes: one frame of 1.5 MB 5.4 -> 4.8 us, where the host's
+// launch path takes as long, 50 tokens x 32 layers x 4096 channels 14.5 -> 13.4, 300 tokens of 60 layers x 512 channels 15.7 ->
+// 14.4; pack, two layers of 2048 tokens 10.6 -> 10.2).
 template <typename Params>
 __device__ __forceinline__ void fetch_params() {
   const KVC_CONST uint32_t* words = (const KVC_CONST uint32_t*)__builtin_amdgcn_kernarg_segment_ptr();

@@ -673,7 +673,7 @@ constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kN
 // Shared strips: chunks longer than a strip that waits on chip are cut along their tokens for several workgroups (members),
 // each of which holds its tokens as a resident strip does and needs from the others only the extremes of their columns.  So
 // the input is read once, and strips can be as wide as a line of codes (10 240-token chunks of 32 layers x 1024 channels,
-// three of them on 1080P frames: 1333 us with strips of 64 channels read twice, 1180 shared, 128 channels wide, 1312 shared
+// three of them on 1080P frames: 1333 us with strips of 64 channels read twice, 1189 shared, 128 channels wide, 1312 shared
 // with 64; 4096-token chunks 1187 -> 1075; 1024 threads with 16 + 8 loads each, one workgroup a CU; two of 512 threads with 24 +
 // 8 took 1203, one with 46 + 18 1229).
 //
@@ -1034,12 +1034,12 @@ __device__ __forceinline__ void pack_zero_body(const PackParams& p, uint32_t z) 
 template <int DT, bool UNIFORM, int BODY>
 __global__ void __launch_bounds__(BODY == kPackStream ? 1024 : kResidentThreads, BODY == kPackLight || BODY == kPackMedium ? 4 : 1)
 pack_kernel(const PackParams p) {
-  // partial column extremes of the waves; the row after them carries the finished {mn} / {inv} of the strip
   fetch_params<PackParams>();
+  // partial column extremes of the waves; the row after them carries the finished {mn} / {inv} of the strip
   constexpr int kWaves = (BODY == kPackStream ? 1024 : kResidentThreads) / 64;
   __shared__ float red_lo[kWaves + 1][kMaxStripAtoms * 8];
   __shared__ float red_hi[kWaves + 1][kMaxStripAtoms * 8];
-  __shared__ uint32_t flags[3];  // of shared strips
+  __shared__ uint32_t flags[3];  // of shared strips: members missing (two turns), who was the last reader
   extern __shared__ u32x4 stash[];  // the loads of the per-channel bodies that wait in LDS, one slot per thread each
   // Workgroups go to the 8 XCDs round-robin.  Units come in ranges: the per-channel ones, the per-token ones (each first
   // of the whole chunks, then of a short last chunk, so that every XCD has the same mix of work: 2048 + 128 tokens of 60
@@ -1179,7 +1179,7 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // Chunks too long for that share strips (below) or read the part of each that does not fit on chip twice.  Few, large
   // workgroups (one of 1024 threads per CU) give each strip the whole CU's registers and LDS to wait in, and
   // keep the strips in flight few, so that part of the second read still finds its strip in the last-level
-  // cache: 10 240-token chunks pack in 1.37 ms this way (1.18 shared) against 1.83 ms with 256-thread workgroups.
+  // cache: 10 240-token chunks pack in 1.37 ms this way (1.19 shared) against 1.83 ms with 256-thread workgroups.
   // Few strips are made as narrow as it takes for a whole chunk to wait on chip (two layers of 10 240 tokens: 77 -> 58 us;
   // in strips of 16 six layers, 384 of them, 122 -> 109 us, seven, 448, 119 -> 126;
   // many strips lose by it, 1.35 -> 2.55 ms with half the width, since each input and code line is then several strips').
