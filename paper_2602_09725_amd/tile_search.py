@@ -22,10 +22,11 @@ SMALL_SET = 64 << 20
 
 
 # Streams beside the caller's, device -> up to LANES - 1, kept by each thread for its next search: a stream's first use takes
-# 130-190 us (3.7 ms where it brings a hardware queue, of which a process has four), and a candidate about 50.
+# 130-190 us (3.7 ms where it brings a hardware queue, of which a process has four), and a candidate about 50.  So a thread's
+# first search, which may be its only one, does without (the first of a process 12.7 ms with them, 3.9 without).
 class _Own(threading.local):
     def __init__(self):
-        self.streams = {}
+        self.streams, self.searched = {}, False
 
 
 _own = _Own()
@@ -107,7 +108,8 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
                     if not lanes:  # all buffers before the caller's stream has work that the others would wait for
                         lanes.append(_Lane(stream, kv.device, stream))
                         lanes[0].buffers(sizes)
-                        while len(lanes) < min(LANES if sum(sizes) <= SMALL_SET else 2, len(candidates) - at):
+                        most = 1 if not _own.searched else LANES if sum(sizes) <= SMALL_SET else 2
+                        while len(lanes) < min(most, len(candidates) - at):
                             lanes.append(_Lane(stream, kv.device, side=len(lanes) - 1))
                             lanes[-1].buffers(sizes)
                         ready = stream.record_event()
@@ -137,6 +139,7 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
             for lane in used:
                 if lane.stream is not stream:
                     stream.wait_stream(lane.stream)
+        _own.searched = True
         host = costs[:len(rows)].cpu()   # synchronizes with the streams the work was enqueued on
     for r, per_stream in zip(rows, host.tolist()):
         r["cost_bits"] = sum(per_stream)

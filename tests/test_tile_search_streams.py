@@ -106,9 +106,11 @@ class Tensor:
 
 
 def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, candidates=None, meanwhile=None, refuse_above=None,
-           model=None, stream=None):
-    """rank_tiles on the model; `meanwhile(model)` runs after the first candidate is enqueued."""
+           model=None, stream=None, searched=True):
+    """rank_tiles on the model, by a thread that has searched before; `meanwhile(model)` runs after the first candidate is
+    enqueued."""
     m = model or Model()
+    tile_search._own.searched = searched
     m.refuse_above = refuse_above
 
     class Scope:
@@ -214,12 +216,14 @@ def test_memory_of_a_search(kvc_lib, monkeypatch, shape):
 
 
 def test_streams_are_made_once(kvc_lib, monkeypatch):
-    """The first use of a stream costs as much as a candidate, so a thread's next search has those of its last one, on
-    whatever stream it is called, and each thread has its own."""
+    """The first use of a stream costs more than a candidate, so a thread's first search makes none, the later ones have
+    those of the second, on whatever stream they are called, and each thread has its own."""
     import threading
 
     shape, m = SHAPES[0], Model()
     other = Stream(m)
+    search(monkeypatch, *shape, model=m, searched=False)
+    assert tile_search._own.searched and len(m.streams) == 2 and not m.races
     for stream in (m.caller, other, m.caller, other):
         search(monkeypatch, *shape, model=m, stream=stream)
         assert len(m.streams) <= 2 + tile_search.LANES - 1
