@@ -691,8 +691,10 @@ constexpr int64_t kFewStrips = 128, kNarrow = 256, kNarrowBesideTokens = 480, kN
 // whatever order its workgroups run, and costs no more than reading twice where few of them are on chip together: with no
 // look at all (chunks of 10 240 / 24 576 / 49 152 tokens x 32 layers) 437 / 1044 / 2161 us, shared 390 / 932 / 1952, two-pass
 // 449 / 1219 / 2640; two calls at a time of 32 members each 2674 us a call, two-pass 2668 (12.4 ms when each that was late read
-// the whole chunk); beside a loop of HBM copies 4.3 and 3.7 ms (17.8).  Beside large matrix products two passes are faster (10 240
-// tokens 9.9 against 14.7 ms, 24 576 2.7 against 9.4): every workgroup needs a CU of its own, and shared strips have more.
+// the whole chunk); beside a loop of HBM copies 4.3 and 3.7 ms (17.8).  Beside large matrix products a call takes longer than
+// in two passes (10 240 tokens 14.7 against 9.9 ms), since every workgroup needs a CU of its own and shared strips have more of
+// them; but the products then get on faster, and the chip does as much (99 calls and 150 products end after 238 ms, 88 and 150
+// in two passes after 237).
 constexpr int kSharedRegs = 16, kSharedLds = 8, kSharedLoads = kSharedRegs + kSharedLds;  // loads of a thread that wait
 static_assert(kSharedLds == kStreamStashLoads, "the launch of the two-pass form is theirs");
 constexpr uint32_t kEmptySlot = 0xffffffffu;
@@ -700,9 +702,9 @@ constexpr uint32_t kSlotTokens = 4;    // tokens whose codes are a member's slot
 constexpr uint32_t kHelpLoads = 4;     // loads of a thread in flight while it reads another member's tokens
 static_assert(kSharedLoads % kHelpLoads == 0, "whole groups of loads stay within a member's 32-bit offsets");
 constexpr uint32_t kClearThreads = 256;
-// The members of a strip have to be on chip together, and are on one XCD: each takes one of its 32 CUs.  (32 layers x 1024
+// The members of a strip are to be on chip together, and are on one XCD: each takes one of its 32 CUs.  (32 layers x 1024
 // channels, one chunk of 24 576 / 36 864 / 49 152 tokens: 1219 / 1926 / 2640 us two-pass, 944 / 1491 / 1951 with 16 / 24 / 32
-// members.  With more, those that start wait in vain for the rest.)
+// members.)  They are also the bits of a word in which a member notes the missing ones.
 constexpr int kMostMembers = 32;
 
 // The word of channel ch (of a strip that starts with element strip_e) in the codes of token t.
