@@ -483,6 +483,30 @@ kvc_status kvc_proxy_costs(const kvc_layout* layout, const uint64_t* d_hist, int
 int32_t kvc_tile_candidates(int32_t num_kv_heads, int32_t head_dim, int32_t* tile_h, int32_t* tile_w,
                             int32_t* tile_seg, int32_t cap);
 
+/* Costs of several tilings of one tensor in one call: what kvc_pack,
+ * kvc_residual_histograms and kvc_proxy_costs give for each, to the bit, from one
+ * packed copy of the codes and with every pair of pixels that tilings share
+ * counted once.
+ *   layout      everything but the tile, which is not looked at
+ *   tile_h, tile_w, tile_seg  HOST in: n_tilings tiles, each on the grid that
+ *               kvc_layout_set_resolution gives it for width x height.  The
+ *               planes must be alike (tiles_x * tile_w and tiles_y * tile_h the
+ *               same for all), head_dim a power of two, and a tile one of runs:
+ *               tile_seg > 0, or tile_w a divisor or a multiple of head_dim;
+ *               at most 32 of them
+ *   workspace   DEVICE, 256-byte aligned, of at least the bytes that
+ *               kvc_tiling_costs_workspace returns; its contents mean nothing
+ *   d_cost      DEVICE out: double [n_tilings][n_chunks][2][L], every entry
+ *               written, 8-byte aligned; its length is not checked
+ * KVC_ERR_UNSUPPORTED where the tilings cannot be counted together (score them one
+ * by one); kvc_tiling_costs_workspace returns 0 then and on a bad argument. */
+size_t kvc_tiling_costs_workspace(const kvc_layout* layout, int64_t n_tokens, int32_t n_tilings, const int32_t* tile_h,
+                                  const int32_t* tile_w, const int32_t* tile_seg, int32_t width, int32_t height);
+kvc_status kvc_tiling_costs(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens,
+                            int32_t n_tilings, const int32_t* tile_h, const int32_t* tile_w, const int32_t* tile_seg,
+                            int32_t width, int32_t height, void* workspace, size_t workspace_bytes, double* d_cost,
+                            void* stream);
+
 /* Measurement aid, not a step of the paper's path: a streaming copy with the byte
  * ratio of restore (8 bytes read and 16 written per lane).  The benchmark runs it
  * to show what the part delivers for sequential output and for output cut into

@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvc.so")
-SOURCES = ["kvc_api.hip", "kvc_restore.hip", "kvc_pack.hip", "kvc_score.hip", "kvc_probe.hip"]
+SOURCES = ["kvc_api.hip", "kvc_restore.hip", "kvc_pack.hip", "kvc_score.hip", "kvc_search.hip", "kvc_probe.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

@@ -413,6 +413,96 @@ double kvc_proxy_cost_bits(const kvc_layout* layout, const uint64_t* hist, int64
   return total;
 }
 
+namespace {
+
+// A search among tilings: the layout of the matrix of codes, and what the kernels are told.
+struct TilingSearch {
+  kvc_layout matrix;
+  SearchTurnParams turning;
+  SearchParams counting;
+  SearchCostParams pricing;
+  size_t frame_bytes, meta_bytes, turned_bytes, edge_bytes, counts_bytes, bytes;  // of the workspace, each rounded up to 256 bytes
+};
+
+// KVC_ERR_UNSUPPORTED where the tilings cannot be counted together.
+kvc_status plan_tilings(const kvc_layout* layout, int64_t n_tokens, int32_t n_tilings, const int32_t* tile_h, const int32_t* tile_w,
+                        const int32_t* tile_seg, int32_t width, int32_t height, TilingSearch* s) {
+  if (!layout || n_tokens < 1 || n_tokens >= (1ll << 31) || n_tilings < 1 || !tile_h || !tile_w || !tile_seg) return KVC_ERR_INVALID_ARG;
+  if (n_tilings > kMostTilings) return KVC_ERR_UNSUPPORTED;
+  Geo g{};
+  SearchRuns runs[kMostTilings];
+  for (int32_t i = 0; i < n_tilings; ++i) {
+    kvc_layout lo = *layout;
+    lo.tile_h = tile_h[i];
+    lo.tile_w = tile_w[i];
+    lo.tile_seg = tile_seg[i];
+    kvc_status st = kvc_layout_set_resolution(&lo, width, height);
+    if (st != KVC_OK) return st;
+    Geo gi;
+    if ((st = make_geo(&lo, &gi)) != KVC_OK) return st;
+    if (i == 0) g = gi;
+    // all planes alike, and runs whose lengths divide each other
+    if (gi.W != g.W || gi.Hp != g.Hp || (g.D & (g.D - 1)) != 0) return KVC_ERR_UNSUPPORTED;
+    int32_t d2 = lo.tile_seg;
+    if (d2 == 0) d2 = lo.tile_w < g.D ? lo.tile_w : g.D;  // a row-major tile is one of runs if it cuts no head unevenly
+    if (g.D % d2 != 0 || lo.tile_w % d2 != 0 || (lo.tile_w / d2 > 1 && lo.tile_seg == 0 && d2 < g.D)) return KVC_ERR_UNSUPPORTED;
+    runs[i] = SearchRuns{d2, lo.tile_w / d2};
+    if (g.H % runs[i].h2 != 0) return KVC_ERR_UNSUPPORTED;
+  }
+  if ((int64_t)g.F * g.plane >= (1ll << 31)) return KVC_ERR_UNSUPPORTED;  // 32-bit counters of pixels and of empty positions
+  s->matrix = *layout;
+  s->matrix.tile_h = 1;
+  s->matrix.tile_w = g.C;
+  s->matrix.tile_seg = 0;
+  s->matrix.tiles_x = 1;
+  s->matrix.tiles_y = g.T;
+  Geo gm;
+  const kvc_status st = make_geo(&s->matrix, &gm);
+  if (st != KVC_OK) return st;
+  if (!plan_search(g, n_tokens, n_tilings, runs, &s->turning, &s->counting, &s->pricing)) return KVC_ERR_UNSUPPORTED;
+  const auto whole = [](int64_t bytes) { return (size_t)((bytes + 255) / 256 * 256); };
+  const int64_t n_chunks = ceil_div(n_tokens, gm.T);
+  s->frame_bytes = whole(n_chunks * gm.frame_bytes);
+  s->meta_bytes = whole(n_chunks * gm.meta_floats * 4);
+  s->turned_bytes = whole((int64_t)s->turning.atom_bytes);
+  s->edge_bytes = whole((int64_t)s->turning.edge_bytes);
+  s->counts_bytes = whole((int64_t)s->turning.n_counts * 4);
+  s->bytes = s->frame_bytes + s->meta_bytes + s->turned_bytes + s->edge_bytes + s->counts_bytes;
+  return KVC_OK;
+}
+
+}  // namespace
+
+size_t kvc_tiling_costs_workspace(const kvc_layout* layout, int64_t n_tokens, int32_t n_tilings, const int32_t* tile_h,
+                                  const int32_t* tile_w, const int32_t* tile_seg, int32_t width, int32_t height) {
+  TilingSearch s;
+  if (plan_tilings(layout, n_tokens, n_tilings, tile_h, tile_w, tile_seg, width, height, &s) != KVC_OK) return 0;
+  return s.bytes;
+}
+
+kvc_status kvc_tiling_costs(const kvc_layout* layout, const void* kv, kvc_strides strides, int64_t n_tokens, int32_t n_tilings,
+                            const int32_t* tile_h, const int32_t* tile_w, const int32_t* tile_seg, int32_t width, int32_t height,
+                            void* workspace, size_t workspace_bytes, double* d_cost, void* stream) {
+  TilingSearch s;
+  kvc_status st = plan_tilings(layout, n_tokens, n_tilings, tile_h, tile_w, tile_seg, width, height, &s);
+  if (st != KVC_OK) return st;
+  if (!workspace || !d_cost || !aligned(workspace, 256) || !aligned(d_cost, 8)) return KVC_ERR_INVALID_ARG;
+  if (s.bytes > workspace_bytes) return KVC_ERR_BUFFER_TOO_SMALL;
+  uint8_t* const frames = static_cast<uint8_t*>(workspace);
+  uint8_t* const meta = frames + s.frame_bytes;
+  s.turning.matrix = frames;
+  s.turning.turned = meta + s.meta_bytes;
+  s.turning.edges = s.turning.turned + s.turned_bytes;
+  s.counting.codes = s.turning.turned;
+  s.counting.edges = s.turning.edges;
+  s.counting.counts = reinterpret_cast<uint32_t*>(s.turning.edges + s.edge_bytes);
+  s.turning.counts = s.counting.counts;
+  s.pricing.counts = s.counting.counts;
+  s.pricing.cost = d_cost;
+  if ((st = kvc_pack(&s.matrix, kv, strides, n_tokens, frames, s.frame_bytes, meta, s.meta_bytes, stream)) != KVC_OK) return st;
+  return launch_search(s.turning, s.counting, s.pricing, as_stream(stream));
+}
+
 int32_t kvc_tile_candidates(int32_t num_kv_heads, int32_t head_dim, int32_t* tile_h, int32_t* tile_w, int32_t* tile_seg,
                             int32_t cap) {
   if (num_kv_heads < 1 || head_dim < 1 || cap < 0 || (cap > 0 && (!tile_h || !tile_w || !tile_seg))) return -1;

@@ -151,6 +151,73 @@ kvc_status launch_residual_histograms(ScoreParams p, hipStream_t stream);
 // Enqueues the cost of every stream from its histograms: hist as above, cost [n_chunks][2][L].
 kvc_status launch_proxy_costs(const ScoreParams& p, double* cost, hipStream_t stream);
 
+// Costs of several tilings of one tensor, counted from the plain matrix of its codes (kvc_search.hip).
+constexpr int kMostTilings = 32, kMostSearchTasks = 72;  // a launch's parameters are at most 4 KB
+enum { kSearchInside, kSearchTime, kSearchSeam, kSearchEdge, kSearchInner, kSearchUpper };
+constexpr uint32_t kSlotInside = 0, kSlotTime = 2, kSlotSeams = 3;  // of a stream's histograms; two for each level of seams
+
+// A tiling as runs of d2 elements, h2 heads side by side.
+struct SearchRuns {
+  int32_t d2, h2;
+};
+
+struct SearchTask {
+  uint8_t type;
+  uint8_t log_span;       // 2^log_span parts of a stream are one workgroup's
+  uint16_t slot;          // first of its histograms in a stream's
+  uint32_t first, per_xcd;  // workgroups of an XCD, in a group of streams
+  uint32_t d2;
+  FastDiv dh2;
+  uint32_t rows;          // atoms of a tile position, or of single elements those that hold one
+  FastDiv dx;             // edge, upper: tiles of a row; inner: atoms of a head below its first run
+};
+
+// Where the codes of all streams are turned: the matrices of a pack -> [stream][F][C / 8][columns][8] and, of the first and
+// the last bytes of the atoms, [stream][F][2][C / 8][columns].
+struct SearchTurnParams {
+  const uint8_t* matrix;  // [chunk][kind][LG * 3][T][C]
+  uint8_t *turned, *edges;
+  uint32_t* counts;       // cleared
+  uint32_t n_counts;
+  int64_t n_tokens;
+  int32_t T, C, LG;
+  uint32_t columns;       // positions that hold a token and those that are looked at beside them, a multiple of 8
+  FastDiv dF, dL, dpositions, datoms;  // blocks of positions and of atoms
+  uint32_t workgroups;
+  size_t atom_bytes, edge_bytes;
+};
+
+struct SearchParams {
+  const uint8_t *codes, *edges;  // turned
+  uint32_t* counts;       // [stream][slots][256]
+  int64_t n_tokens;
+  int32_t T, C, D, F, G;
+  uint32_t columns, slots, n_streams, group_streams, group_slices, workgroups;
+  int32_t n_tasks;
+  FastDiv dround, dparts, dstreams;  // dround: workgroups of an XCD in a group of streams
+  SearchTask tasks[kMostSearchTasks];
+};
+
+struct SearchTiling {
+  uint32_t upper, edge, inner, seams;  // slots (inner 0: none) and levels of seams
+};
+
+struct SearchCostParams {
+  const uint32_t* counts;
+  double* cost;  // [tiling][stream]
+  uint32_t slots, n_tilings, streams;
+  double pixels, later, all_frames;
+  SearchTiling tilings[kMostTilings];
+};
+
+// Plan of a search among tilings that share the planes of g (its W, F and G; its own tile is not looked at).  False if it
+// is not one for these kernels: too many tilings, or streams.
+bool plan_search(const Geo& g, int64_t n_tokens, int32_t n_tilings, const SearchRuns* runs, SearchTurnParams* m, SearchParams* p,
+                 SearchCostParams* k);
+
+// Enqueues the turning of the codes, the counting and the costs.
+kvc_status launch_search(const SearchTurnParams& m, const SearchParams& p, const SearchCostParams& k, hipStream_t stream);
+
 // Enqueues the reference expand copy (measurement aid): out_bytes / 2 bytes of src -> out_bytes of dst, piece i
 // of 2^log2_piece output bytes going to position piece_map[i] (nullptr: in place); wg_bytes is 4096 or 32768;
 // shape: KVC_PROBE_* bits (4 KB workgroups, a multiple of 8 of them).

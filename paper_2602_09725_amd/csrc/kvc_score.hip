@@ -22,7 +22,7 @@
 // of its counter.
 #include <hip/hip_runtime.h>
 
-#include "kvc_device.h"
+#include "kvc_count.h"
 #include "kvc_launch.h"
 
 namespace kvc {
@@ -30,48 +30,11 @@ namespace kvc {
 namespace {
 
 constexpr int kScoreThreads = 512;
-constexpr int kCopies = 16;        // copies of each histogram in LDS: 80 KB of the CU's 160 KB
 constexpr int kFrames = 4;         // pieces whose loads are in flight together: frames, or rows of few frames
 // Workgroups a launch of few streams is cut into, two rounds of the two that fit a CU: a chunk of 32 layers x 1024
 // channels (64 streams) takes 499 us in one part per stream, 83 / 80 / 84 us in 512 / 1024 / 2048 workgroups; with
 // most tiles empty fewer are better (18 tokens of 1024: 30 / 32 / 43 us), with 2000 rows of 3840 pixels more (111 / 105 / 103).
 constexpr int64_t kScoreWorkgroups = 1024;
-
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-
-// Two pixels (or residuals): the low bytes of the two halves; what is above a low byte is not looked at.
-__device__ __forceinline__ uint32_t sub2(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, (u16x2)(__builtin_bit_cast(u16x2, a) - __builtin_bit_cast(u16x2, b)));
-}
-
-// 8 pixels of a row as pairs (0,2), (1,3), (4,6), (5,7).
-struct Piece {
-  uint32_t v[4];
-};
-__device__ __forceinline__ Piece split(u32x2 w) { return Piece{{w.x, w.x >> 8, w.y, w.y >> 8}}; }
-__device__ __forceinline__ Piece operator-(const Piece& a, const Piece& b) {
-  return Piece{{sub2(a.v[0], b.v[0]), sub2(a.v[1], b.v[1]), sub2(a.v[2], b.v[2]), sub2(a.v[3], b.v[3])}};
-}
-// The pixels one position to the left; `left` is the one before the piece.
-__device__ __forceinline__ Piece left_of(const Piece& p, uint32_t left) {
-  return Piece{{__builtin_amdgcn_alignbit(p.v[1], left << 16, 16), p.v[0], __builtin_amdgcn_alignbit(p.v[3], p.v[1], 16), p.v[2]}};
-}
-
-typedef uint32_t Histogram[256][kCopies];
-
-__device__ __forceinline__ void count8(Histogram& h, const Piece& p, uint32_t copy_bytes) {
-  typedef __attribute__((address_space(3))) uint32_t lds_u32;
-  typedef __attribute__((address_space(3))) char lds_char;
-  lds_char* base = (lds_char*)&h[0][0];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // byte 0 (and byte 2) times the bytes of a bin, plus the copy
-    const uint32_t lo = __builtin_amdgcn_udot4(p.v[i], (uint32_t)sizeof(h[0]), copy_bytes, false);
-    const uint32_t hi = __builtin_amdgcn_udot4(p.v[i], (uint32_t)sizeof(h[0]) << 16, copy_bytes, false);
-    __hip_atomic_fetch_add((lds_u32*)(base + lo), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __hip_atomic_fetch_add((lds_u32*)(base + hi), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-}
 
 // Counter by counter: the caller's array is 8-byte aligned, no more.
 __global__ void __launch_bounds__(kScoreThreads) clear_hist_kernel(uint64_t* hist, uint32_t n) {
@@ -196,39 +159,14 @@ __global__ void __launch_bounds__(kScoreThreads) residual_hist_kernel(const Scor
   }
 }
 
-// One workgroup per stream, one thread per bin: entropies of the five histograms, then the stream's cost in bits.
-// (On the host the logarithms of a candidate of 12 streams take about 100 us, longer than packing and counting it.)
+// One workgroup per stream, one thread per bin.  (On the host the logarithms of a candidate of 12 streams take about 100 us,
+// longer than packing and counting it.)
 __global__ void __launch_bounds__(256) proxy_cost_kernel(const uint64_t* hist, double* cost, double pixels, double later) {
-  __shared__ double part[2][KVC_N_RESIDUALS][4];
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint64_t* h = hist + (size_t)blockIdx.x * (KVC_N_RESIDUALS * 256) + tid;
+  const uint64_t* h = hist + (size_t)blockIdx.x * (KVC_N_RESIDUALS * 256) + threadIdx.x;
   double n[KVC_N_RESIDUALS];
 #pragma unroll
   for (int k = 0; k < KVC_N_RESIDUALS; ++k) n[k] = (double)h[k * 256];
-  // sum over the 256 threads; the barrier after the partial sums is also the one before the next use of the other half
-  const auto total = [&](double v, int half, int k) {
-    for (int m = 32; m; m >>= 1) v += __shfl_xor(v, m);
-    if (lane == 0) part[half][k][wave] = v;
-  };
-#pragma unroll
-  for (int k = 0; k < KVC_N_RESIDUALS; ++k) total(n[k], 0, k);
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < KVC_N_RESIDUALS; ++k) {
-    const double all = part[0][k][0] + part[0][k][1] + part[0][k][2] + part[0][k][3];
-    const double q = n[k] > 0.0 ? n[k] / all : 0.0;
-    total(q > 0.0 ? -q * log2(q) : 0.0, 1, k);
-  }
-  __syncthreads();
-  if (tid != 0) return;
-  double e[KVC_N_RESIDUALS];
-#pragma unroll
-  for (int k = 0; k < KVC_N_RESIDUALS; ++k) e[k] = part[1][k][0] + part[1][k][1] + part[1][k][2] + part[1][k][3];
-  const double first = e[KVC_RES_LEFT] < e[KVC_RES_UP] ? e[KVC_RES_LEFT] : e[KVC_RES_UP];
-  double inter = e[KVC_RES_TIME];
-  if (e[KVC_RES_TIME_LEFT] < inter) inter = e[KVC_RES_TIME_LEFT];
-  if (e[KVC_RES_TIME_UP] < inter) inter = e[KVC_RES_TIME_UP];
-  cost[blockIdx.x] = pixels * first + later * inter;
+  stream_cost(n, [](int, double counted) { return counted; }, pixels, later, &cost[blockIdx.x]);
 }
 
 }  // namespace

@@ -105,6 +105,9 @@ def load(path=None):
     ip = C.POINTER(i32)
     lib.kvc_tile_candidates.argtypes = [i32, i32, ip, ip, ip, i32]
     lib.kvc_tile_candidates.restype = i32
+    lib.kvc_tiling_costs_workspace.argtypes = [LP, i64, i32, ip, ip, ip, i32, i32]
+    lib.kvc_tiling_costs_workspace.restype = sz
+    lib.kvc_tiling_costs.argtypes = [LP, vp, Strides, i64, i32, ip, ip, ip, i32, i32, vp, sz, vp, vp]
     lib.kvc_probe_expand.argtypes = [vp, vp, sz, vp, sz, i32, i32, vp]
     if path is None:
         _lib = lib
@@ -212,6 +215,21 @@ def tile_candidates(num_kv_heads, head_dim):
     th, tw, seg = (C.c_int32 * n)(), (C.c_int32 * n)(), (C.c_int32 * n)()
     load().kvc_tile_candidates(num_kv_heads, head_dim, th, tw, seg, n)
     return [(th[i], tw[i], seg[i]) for i in range(n)]
+
+
+def tile_arrays(tiles):
+    """[(tile_h, tile_w, tile_seg)] as the arrays that the two calls below take."""
+    return tuple((C.c_int32 * len(tiles))(*column) for column in zip(*tiles))
+
+
+def tiling_costs_workspace(layout, n_tokens, tiles, width, height):
+    """Bytes, 0 if these tilings cannot be counted together; tiles as tile_arrays returns them."""
+    return load().kvc_tiling_costs_workspace(C.byref(layout), n_tokens, len(tiles[0]), *tiles, width, height)
+
+
+def kvc_tiling_costs(layout, kv_ptr, strides, n_tokens, tiles, width, height, workspace_ptr, workspace_bytes, cost_ptr, stream=0):
+    _check(load().kvc_tiling_costs(C.byref(layout), kv_ptr, Strides(*strides), n_tokens, len(tiles[0]), *tiles, width, height,
+                                   workspace_ptr, workspace_bytes, cost_ptr, stream), "kvc_tiling_costs")
 
 
 def kvc_fetch_pipeline(layout, chunks, staging_ptrs, staging_bytes, layer_cache_ptrs_dev, num_blocks, block_size,

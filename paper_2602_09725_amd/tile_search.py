@@ -8,6 +8,7 @@ byte of every candidate is produced and counted by the library's kernels.
 import threading
 
 import torch
+from torch import Tensor
 
 from . import kvc
 
@@ -76,6 +77,39 @@ class _Lane:
         return self.stream.cuda_stream
 
 
+def _ranked(rows, costs, elements):
+    for r, per_stream in zip(rows, costs.tolist()):
+        r["cost_bits"] = sum(per_stream)
+        r["bits_per_element"] = r["cost_bits"] / elements
+    rows.sort(key=lambda r: r["cost_bits"])
+    return rows
+
+
+def _count_together(kv, n_tokens, layout, candidates, frame_width, frame_height, stream):
+    """Rows and device costs [candidates][streams] of candidates whose planes are alike, counted from one packed copy
+    (kvc_tiling_costs), or None where the library does not take them so, or there is no memory for the copy."""
+    L, _, _, H, D = kv.shape
+    C, tiles = H * D, kvc.tile_arrays(candidates)
+    size = kvc.tiling_costs_workspace(layout, n_tokens, tiles, frame_width, frame_height)
+    if size == 0:
+        return None
+    n_streams = -(-n_tokens // layout.chunk_tokens) * 2 * L
+    try:
+        work = torch.empty(size, dtype=torch.uint8, device=kv.device)
+    except torch.OutOfMemoryError:
+        return None
+    costs = torch.empty((len(candidates), n_streams), dtype=torch.float64, device=kv.device)
+    kvc.kvc_tiling_costs(layout, kv.data_ptr(), (2 * n_tokens * C, n_tokens * C, C), n_tokens, tiles, frame_width, frame_height,
+                         work.data_ptr(), size, costs.data_ptr(), stream.cuda_stream)
+    th, tw, _ = candidates[0]
+    wide, high = max(1, frame_width // tw) * tw, max(1, frame_height // th) * th
+    frames = -(-layout.chunk_tokens * C // (wide * high))
+    chunk_bytes = 2 * (-(-L // 3)) * frames * 3 * wide * high
+    rows = [{"tile_h": th, "tile_w": tw, "tile_seg": seg, "tile_grid": [wide // tw, high // th], "frames_per_group": frames,
+             "frame_bytes_per_chunk": chunk_bytes} for th, tw, seg in candidates]
+    return rows, costs
+
+
 def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_mode=kvc.KVC_Q_PER_CHANNEL,
                v_mode=kvc.KVC_Q_PER_TOKEN, candidates=None, stream=None):
     """kv: contiguous CUDA tensor [L][2][n_tokens][H][D] (fp16 or bf16 bits); dtype: kvc.KVC_F16 | kvc.KVC_BF16.
@@ -92,6 +126,13 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
     stream = stream or torch.cuda.current_stream()
     if not isinstance(stream, torch.cuda.Stream):  # anything that carries a stream's handle
         stream = torch.cuda.ExternalStream(stream.cuda_stream, device=kv.device)
+    if len(candidates) > 1 and isinstance(kv, Tensor):  # what only looks like a tensor is scored candidate by candidate
+        with torch.cuda.stream(stream):
+            lo = kvc.Layout(L, H, D, dtype, chunk_tokens, 1, C, 1, chunk_tokens, k_mode, v_mode)
+            together = _count_together(kv, n_tokens, lo, candidates, frame_width, frame_height, stream)
+            if together is not None:
+                rows, costs = together
+                return _ranked(rows, costs.cpu(), L * 2 * n_tokens * C)
     with torch.cuda.stream(stream):
         costs = torch.empty((len(candidates), n_chunks * 2 * L), dtype=torch.float64, device=kv.device)
         kv_ptr, cost_ptr, cost_bytes = kv.data_ptr(), costs.data_ptr(), costs.stride(0) * 8
@@ -141,8 +182,4 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
                     stream.wait_stream(lane.stream)
         _own.searched = True
         host = costs[:len(rows)].cpu()   # synchronizes with the streams the work was enqueued on
-    for r, per_stream in zip(rows, host.tolist()):
-        r["cost_bits"] = sum(per_stream)
-        r["bits_per_element"] = r["cost_bits"] / (L * 2 * n_tokens * C)
-    rows.sort(key=lambda r: r["cost_bits"])
-    return rows
+    return _ranked(rows, host, L * 2 * n_tokens * C)
