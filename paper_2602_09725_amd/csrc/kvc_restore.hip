@@ -216,7 +216,11 @@ __device__ __forceinline__ uint32_t tile_elem(const Geo& g, uint32_t r, uint32_t
 // Unit `tg` is a group of rows_trw rows of tiles of one (chunk, kind, layer), in all F frames (chunk call) or in
 // frame ff alone (frame call: fsec is then that frame's plane and frame_stride 0).
 // LINE: rounds without a dead lane store in a straight line, as above; for a contiguous destination.
-template <int MODE, int DT, bool PAGED, int U, bool LINE>
+// EARLY: table entries are asked for with the codes.  One asked for between the stores is waited for by a counter that counts
+// stores as well, so each pass waited for the stores of the pass before it (tiles of (16,64), 80 layers x 2410 tokens, 13 tiles
+// a row 262 -> 246 us, of (8,64), 7158 tokens, 6 a row 375 -> 350).  Runs of frames of tiles 16 high do not gain by it (16 a
+// row, 30 frames 55 -> 56.5 us): the registers it takes leave one workgroup of 1024 threads on a CU.
+template <int MODE, int DT, bool PAGED, int U, bool LINE, bool EARLY>
 __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                   uint32_t tg, const uint8_t* fsec, uint32_t ff) {
   const Geo& g = p.g;
@@ -255,11 +259,13 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
   const uint32_t passes = (rows_left < (uint32_t)p.rows_trw ? rows_left : (uint32_t)p.rows_trw) * p.dpr.d;
   const uint32_t row_bytes = (uint32_t)g.th * (uint32_t)g.W;
   bool bad = false;
+  const auto entry = [&](uint32_t t) { return (int32_t)*((const KVC_GLOBAL int32_t*)p.table + fd_div(p.dbs, pos0 + t)); };
 
   for (uint32_t k0 = 0; k0 < passes; k0 += U) {
     u32x2 code[U];
     f32x2 sm[U];
     uint32_t tok[U];  // 2^32 - 1 for a lane past the end of the row of tiles
+    int32_t phys[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t k = k0 + u < passes ? k0 + u : passes - 1;
@@ -274,6 +280,7 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
         const uint32_t tp = tok[u] < n ? tok[u] : n - 1u;  // positions without a token: any pair in bounds
         sm[u] = *(const KVC_GLOBAL f32x2*)(mrow + (size_t)tp * ((uint32_t)g.H * 8u));
       }
+      if (PAGED && EARLY) phys[u] = entry(tok[u] < n ? tok[u] : n - 1u);
     }
     if (LINE) {
       uint16_t* dst[U];
@@ -301,14 +308,14 @@ __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32
       uint64_t off;
       bool ok = valid;
       if (PAGED) {
-        uint32_t b, slot;
-        fd_divmod(p.dbs, pos0 + t, b, slot);
-        const int32_t phys = as_const(p.table)[b];
-        const bool in_cache = (uint32_t)phys < (uint32_t)p.num_blocks;
+        if (!EARLY) phys[u] = entry(t);
+        const bool in_cache = (uint32_t)phys[u] < (uint32_t)p.num_blocks;
         // an id outside the cache: skip the block's writes and report it (Sec. 3.3.2 placement)
         bad = bad || (valid && !in_cache);
         ok = valid && in_cache;
-        off = ((uint64_t)(in_cache ? (uint32_t)phys : 0u) * p.dbs.d + slot) * ((uint32_t)g.C * 2u);
+        uint32_t b, slot;
+        fd_divmod(p.dbs, pos0 + t, b, slot);
+        off = ((uint64_t)(in_cache ? (uint32_t)phys[u] : 0u) * p.dbs.d + slot) * ((uint32_t)g.C * 2u);
       } else {
         off = (uint64_t)t * (uint64_t)p.ts * 2u;
       }
@@ -410,7 +417,7 @@ __device__ __forceinline__ void restore_body_lanes(const RestoreParams& p, uint3
 // when the blocks of the whole chunk were cut into eighths: 32 layers x 4096 channels 144 us, now 35 us.)
 //
 // Frame call: units are (frame of the run, plane, block of token slots), each XCD one contiguous range.
-constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2, kBodyRowsLine = 3;
+constexpr int kBodyLanes = 0, kBodyWaves = 1, kBodyRows = 2, kBodyRowsLine = 3, kBodyRowsLate = 4;
 
 template <int DT, bool PAGED, int BODY, int U>
 __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
@@ -452,15 +459,15 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
     fsec = p.frames + (int64_t)c * p.g.frame_bytes + (((int64_t)kind * p.g.LG + lg) * p.g.F * 3 + pl) * p.g.plane;
   }
   if (p.g.mode[kind] == KVC_Q_PER_CHANNEL) {
-    if (BODY == kBodyRows || BODY == kBodyRowsLine)
-      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine>(p, c, kind, l, tbi, fsec, ff);
+    if (BODY >= kBodyRows)
+      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
       restore_body_lanes<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
   } else {
-    if (BODY == kBodyRows || BODY == kBodyRowsLine)
-      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine>(p, c, kind, l, tbi, fsec, ff);
+    if (BODY >= kBodyRows)
+      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
@@ -472,9 +479,11 @@ template <int DT, bool PAGED>
 void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, unsigned lds, hipStream_t s) {
 #define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, lds, s, p)
   if (!PAGED && body == kBodyRowsLine) {
-    KVC_LAUNCH_RESTORE(kBodyRowsLine, 8);
+    if (u == 6) KVC_LAUNCH_RESTORE(kBodyRowsLine, 6); else KVC_LAUNCH_RESTORE(kBodyRowsLine, 8);
+  } else if (PAGED && body == kBodyRowsLate) {
+    KVC_LAUNCH_RESTORE(kBodyRowsLate, 8);
   } else if (body == kBodyRows) {
-    KVC_LAUNCH_RESTORE(kBodyRows, 8);
+    if (u == 6) KVC_LAUNCH_RESTORE(kBodyRows, 6); else KVC_LAUNCH_RESTORE(kBodyRows, 8);
   } else if (body == kBodyWaves) {
     if (u == 8) KVC_LAUNCH_RESTORE(kBodyWaves, 8); else if (u == 4) KVC_LAUNCH_RESTORE(kBodyWaves, 4); else KVC_LAUNCH_RESTORE(kBodyWaves, 2);
   } else {
@@ -544,20 +553,28 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     // From HBM where the other bodies would read half lines (tiles of 64 bytes: 6000 tokens x 80 layers x 1024 channels 643
     // -> 505 us, random table 520), unless runs are much longer than what is left for the last one: into a contiguous tensor
     // at least three quarters of a row's runs have to exist (17 tiles a row: 585 -> 727 us; 8192 tokens x 32 layers, 6 tiles
-    // 318 -> 294), under a table more (6 tiles a row 316 -> 331, 7 of them 324 -> 306), but for tokens of one wave (512
-    // channels, 6 tiles a row 172 -> 156), and the token has to be more than two heads of 128 (two: 39 -> 43 us, one: 137 ->
-    // 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole runs and one round of loads
+    // 318 -> 294), under a table more (6 tiles a row 316 -> 331, 17 of them 364 -> 387, 7 of them 324 -> 306), but for tokens of
+    // one wave (512 channels; with table entries that come with the codes: 6 tiles a row 374 -> 327, 17 of them 441 -> 416, 11
+    // 297 -> 274, 10 288 both, 9 290 -> 296; 600 tokens of 17 tiles a row, 1152 workgroups, 14.7 -> 15.8, 2304 of them 26.8 ->
+    // 26.2) and of half one (256 channels: 16 tiles a row 711 -> 652, 13 218 -> 200, 6 121 -> 111; 17 tiles 57 -> 58, 5 143 ->
+    // 150; 600 tokens, 1088 workgroups, 8.0 -> 8.7, 2720 of them 18.9 -> 17.2).  Of tokens of one head of 128 it loses (137 -> 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole runs and one round of loads
     // takes them (8192 tokens x 32 layers, 8 tiles a row, F = 4: 283 -> 275 us; 12 tiles 287 -> 310, 16 tiles 283 -> 294, F
     // = 16 148 -> 190 for 16 layers; under a random table 284 -> 287).  A launch that would not fill the chip is better cut
     // finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us, 644 tokens in groups of 10 frames 21.6 against
     // 24.8).
     const int tiles4 = 4 * g.TX, runs3 = 3 * q * runs;
-    const bool half_lines = g.tw < 128 && (paged ? g.apt > 32 && (tiles4 > runs3 || (tiles4 == runs3 && g.apt == 64))
-                                                 : g.apt >= 32 && tiles4 >= runs3);
+    const bool few_tiles = tiles4 < runs3;
+    bool half_lines = g.tw < 128 && (paged ? g.apt > 32 && (tiles4 > runs3 || (tiles4 == runs3 && g.apt == 64))
+                                           : g.apt >= 32 && !few_tiles);
+    int64_t fill = kFillWorkgroups;
+    if (paged && !p.frame_mode && g.tw < 128 && (g.apt == 32 ? !few_tiles : g.apt == 64 && few_tiles && 16 * g.TX >= 11 * q * runs)) {
+      half_lines = true;
+      fill = 2 * kFillWorkgroups;
+    }
     const bool linear = g.tw == 128 && !paged && g.TX % q == 0 && per_row <= kPasses && g.apt >= 64;
     const int64_t wgs = p.frame_mode ? (int64_t)p.fm_count * 3 * row_units(n_last)
                                      : 2 * (int64_t)g.L * ((p.n_chunks - 1) * (int64_t)row_units(g.T) + row_units(n_last));
-    rows = (half_lines || linear) && wgs >= kFillWorkgroups;
+    rows = (half_lines || linear) && wgs >= fill;
   }
   int body = rows ? kBodyRows : waves ? kBodyWaves : kBodyLanes;
   int u = kPasses, tpp = 1;
@@ -569,6 +586,10 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     p.dnf = make_fastdiv((uint32_t)nf);
     p.dpr = make_fastdiv((uint32_t)per_row);
     p.rows_trw = trw;
+    // Loads in flight: those of eight passes or of six, whichever leaves fewer of a unit's last round without one (twelve passes,
+    // the two calls above 246 -> 236 and 350 -> 327 us; six, 5000 tokens x 80 layers x 512 channels into a contiguous tensor,
+    // 13 tiles a row, 248 -> 241; but eight in two rounds of six 172 -> 182).
+    if (ceil_div(trw * per_row, 6) * 6 < ceil_div(trw * per_row, 8) * 8) u = 6;
     p.rows_tile_rows = (int32_t)ceil_div(ceil_div(g.T, g.F), g.TX);  // rows of tiles that hold tokens
     p.tbc = row_units(p.frame_mode ? n_last : g.T);  // units of one (chunk, kind, layer) or plane
     tbl = row_units(n_last);
@@ -623,6 +644,7 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     body = kBodyRowsLine;
     lds = kLdsForTwo;
   }
+  if (body == kBodyRows && paged && p.frame_mode && g.th > 8 && u == 8) body = kBodyRowsLate;
   if (g.dtype == KVC_F16) {
     if (paged)
       launch_variant<KVC_F16, true>(p, body, u, grid, block, lds, stream);
