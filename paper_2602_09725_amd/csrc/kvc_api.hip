@@ -291,7 +291,7 @@ kvc_status kvc_pack_form(const kvc_layout* layout, kvc_strides strides, int64_t 
   int th = 0;
   const kvc_status st = plan_of_pack(layout, strides, n_tokens, &p, &th);
   if (st != KVC_OK) return st;
-  if (form) *form = p.body;
+  if (form) *form = p.body == kPackTokens ? kPackStream : p.body;
   if (strip_channels) *strip_channels = p.n_kinds_ch > 0 ? 8 * p.strip_atoms : 0;
   if (threads) *threads = th;
   return KVC_OK;

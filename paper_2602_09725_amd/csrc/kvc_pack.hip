@@ -663,7 +663,12 @@ constexpr int kMediumGroup = 4;
 // alone take the light form up to kFewTokenRows rows, or as many bytes as that many rows of 1024 channels have, where its
 // smaller blocks fill the chip (two layers of 2048 tokens 15.8 -> 7.6 us; beyond, the larger workgroups of the streaming
 // form are faster: two layers of 20 000 tokens 58 against 65 us, six layers of 2048 tokens of 4096 channels 64 against
-// 76).
+// 76).  More rows of at most 512 channels, which leave those larger workgroups one batch of loads each, one workgroup a CU and
+// nothing that overlaps, go to a kernel of the per-token body alone: 50 registers and no LDS, two or four workgroups a CU (32 layers
+// x 9000 tokens of 256 channels 101 -> 82 us, 80 layers of 40 000 of 128 514 -> 392, floor 385; 32 layers of 3000 of 512 66 -> 60;
+// of 1024 and more channels it loses, 123 against 127 us).  Where most of the chunks is zero fill, few large workgroups fill faster:
+// up to six times the tokens for 256 channels (eight times, 80 layers of 20 000 tokens of 128: 653 against 718 us), 1.6 times for 512
+// (1.7 times 138 against 142 us, twice 253 against 262); and they are faster from 2^29 elements of 512 channels on (344 against 365).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
@@ -1034,7 +1039,7 @@ __device__ __forceinline__ void pack_zero_body(const PackParams& p, uint32_t z) 
 }
 
 template <int DT, bool UNIFORM, int BODY>
-__global__ void __launch_bounds__(BODY == kPackStream ? 1024 : kResidentThreads, BODY == kPackLight || BODY == kPackMedium ? 4 : 1)
+__global__ void __launch_bounds__(BODY == kPackStream ? 1024 : kResidentThreads, BODY == kPackLight || BODY == kPackMedium || BODY == kPackTokens ? 4 : 1)
 pack_kernel(const PackParams p) {
   fetch_params<PackParams>();
   // partial column extremes of the waves; the row after them carries the finished {mn} / {inv} of the strip
@@ -1052,7 +1057,7 @@ pack_kernel(const PackParams p) {
   const uint32_t xcd = blockIdx.x & 7u;
   uint32_t idx = blockIdx.x >> 3;
   const uint32_t n_ch = p.ch[0].per_xcd + p.ch[1].per_xcd, n_tok = p.tok[0].per_xcd + p.tok[1].per_xcd;
-  if (idx < n_ch) {
+  if (BODY != kPackTokens && idx < n_ch) {
     const bool last = idx >= p.ch[0].per_xcd;
     if (last) idx -= p.ch[0].per_xcd;
     const PackRange r = last ? p.ch[1] : p.ch[0];
@@ -1114,7 +1119,9 @@ hipError_t launch_variant(dim3 grid, dim3 block, hipStream_t stream, const PackP
   static std::atomic<uint64_t> raised{0};
   const auto fn = pack_kernel<DT, UNIFORM, BODY>;
   constexpr int slots = BODY == kPackResident ? kResidentLds : BODY == kPackMedium ? kMediumLds : BODY == kPackStream ? kStreamStashLoads : 0;
-  const size_t lds = (size_t)slots * block.x * sizeof(u32x4);
+  // Unused LDS keeps the workgroups of per-token kinds alone to two a CU where tokens have more than 128 channels (512: 32 layers
+  // of 9000 tokens 173 us with four, 165 with two, 80 layers of 128 95 against 104).
+  const size_t lds = BODY == kPackTokens ? (p.g.C > 128 ? 56u << 10 : 0u) : (size_t)slots * block.x * sizeof(u32x4);
   if (slots != 0) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -1162,7 +1169,10 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   p.strip_atoms = kResidentAtoms;
   if (p.n_kinds_ch == 0) {
     const int64_t rows = (int64_t)g.L * p.n_kinds_tok * p.n_tokens;
-    if (!wide && !many_chunks && rows < kFewTokenRows && rows * g.C < kFewTokenRows * 1024) p.body = kPackLight;
+    const bool few_rows = rows < kFewTokenRows && rows * g.C < kFewTokenRows * 1024;
+    const int64_t room = (int64_t)p.n_chunks * g.G * g.F;  // token positions of the chunks, with those that are zero fill
+    const bool narrow = g.C <= 256 ? room <= 6 * p.n_tokens : g.C <= 512 && 5 * room <= 8 * p.n_tokens && rows * g.C < 8 * kFewTokenRows * 1024;
+    if (!wide && !many_chunks) p.body = few_rows ? kPackLight : narrow ? kPackTokens : kPackStream;
   } else if (!wide) {
     const int64_t most = rows_of(kResidentLoads, kResidentAtoms);
     if (g.T <= most && fits(most)) p.body = most_tokens <= rows_of(kMediumLoads, kResidentAtoms) ? kPackMedium : kPackResident;
@@ -1232,17 +1242,36 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // threads, 256 positions: 12 000 tokens of 80 layers 270 -> 155 us)
   const int in_flight = p.tpp * (p.body == kPackResident ? kTokenLoadsResident : kTokenLoads);
   while (p.tb < in_flight) p.tb *= 2;
-  const auto token_blocks = [&](int64_t n) { return (int32_t)((n + p.tb - 1) / p.tb); };
   p.light_last = n_last <= rows_of(kLightLoads, p.strip_atoms) ? 1 : 0;
   p.n_whole = n_last == g.T ? p.n_chunks : p.n_chunks - 1;
   const int64_t short_chunks = p.n_chunks - p.n_whole;  // 0 or 1
+  const auto token_blocks = [&](int64_t n) { return (int32_t)((n + p.tb - 1) / p.tb); };
   const auto count_blocks = [&] { return (int64_t)p.n_whole * token_blocks(p.positions_full) + short_chunks * token_blocks(p.positions_last); };
+  // Longer ones for narrow tokens, which leave a workgroup of the forms that keep data on chip one batch of loads and
+  // nothing to overlap its wait and its stores with, and of which a CU holds one or two: 256 tokens of 512 channels, 256 of
+  // 256 and 512 of 128 (per token beside per channel, 32 layers of 9000 tokens of 256 channels 91 -> 85 us, of 30 000 293 ->
+  // 271, 80 layers of 9000 tokens of 128 112 -> 106, 32 layers of 3000 tokens of 512 62.5 -> 58.8; twice as long again 85 -> 86.4).
+  // As long as enough of them are left for the CUs: two for each place a workgroup has (80 layers of 1254 tokens of 256 channels,
+  // 400 units, 36.5 -> 37.3 us; 1024-token chunks, two places, 960 units, 34.1 -> 34.8), three in the streaming form
+  // (640 units 54.5 -> 55.7), one of 512 channels beside strips that wait on chip (256 units 41.7 -> 38.7; beside others
+  // 94.7 -> 95.4, not at all), eight of 512 channels without any (1536 units 113.8 -> 115.4, 2304 170 -> 165).
+  const auto units_tok = [&] { return count_blocks() * g.L * p.n_kinds_tok; };
+  const bool stream_body = p.body == kPackStream, beside = p.n_kinds_ch > 0;
+  const int32_t most_tb = p.body == kPackLight || p.body == kPackTokens || g.C > 512 || (g.C > 256 && stream_body && beside) ? 0 : g.C > 256 ? 4 * in_flight : 2 * in_flight;
+  const int64_t fewest = (g.C > 256 ? (beside ? 1 : 8) : stream_body ? 3 : 2) * kCus * (p.body == kPackMedium ? 2 : 1);
+  while (2 * p.tb <= most_tb) {
+    p.tb *= 2;
+    if (units_tok() < fewest) {
+      p.tb /= 2;
+      break;
+    }
+  }
   // Few blocks are made shorter until there are two for every CU; those of narrow tokens only as long as they are no more
   // than that, or the few of the second round cost a whole one (128 channels, 3 layers of 2048 tokens: 384 blocks of 32
   // tokens 5.3 us, 768 of 16 6.8; 256 channels 6.1 against 7.9), while wide tokens gain by the even spread (4096 channels, 3
   // layers of 2048 tokens: 38 against 34; 1024 channels, 3 layers of 6000 tokens: 31 against 28.8).
   const auto few = [&](int64_t blocks) { return g.C <= 256 ? 2 * blocks <= kFewTokenUnits : blocks < kFewTokenUnits; };
-  while (p.body == kPackLight && p.tb > 16 && few(count_blocks() * g.L * p.n_kinds_tok)) p.tb /= 2;
+  while ((p.body == kPackLight || p.body == kPackTokens) && p.tb > 16 && few(units_tok())) p.tb /= 2;
   p.tbc = token_blocks(p.positions_full);
   p.tbl = token_blocks(p.positions_last);
   // the blocks of the last chunk write the pairs of its tokens before this one, zero units the rest
@@ -1270,11 +1299,12 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // Token blocks in turn, in runs that hold about as many bytes as a block of 1024 channels.  Where blocks end inside a
   // row of tiles, neighbours stay on one XCD: in longer runs (rows of 36 positions, 8192 tokens of 32 layers x 1024
   // channels 307 -> 296 us; blocks of whole rows lose 1 % by it), or narrower ones in eighths (4096 x 32 x 256 54 -> 51 us).
-  // Per-token kinds alone, narrow and not so many, also stay in eighths (16 layers of 2048 tokens of 256 channels 17.5 -> 16.3 us,
-  // of 512 27.3 -> 25.3, 32 layers of 4096 tokens of 256 channels 50.2 -> 47.7; of 20 000 tokens of 512 358 against 354).
+  // Per-token kinds alone also stay in eighths where blocks were made shorter, or are those of the streaming form, of fewer than
+  // 1024 channels and not so many (16 layers of 2048 tokens of 512 channels 27.3 -> 25.3 us there; in the kernel of the per-token
+  // body 32 layers of 3000 tokens of 512 60 in turn, 62 in eighths; 64 rows of blocks of 64 tokens of 256 channels 9.7 and 9.5).
   const bool whole_rows = p.tb % (g.F * g.TX) == 0;
   p.tok_run = 0;
-  const bool few_narrow = p.n_kinds_ch == 0 && g.C < 1024 && rows_tok * p.n_tokens < 8 * kFewTokenRows;
+  const bool few_narrow = p.n_kinds_ch == 0 && (p.body == kPackLight ? p.tb < 128 : p.body == kPackStream) && g.C < 1024 && rows_tok * p.n_tokens < 8 * kFewTokenRows;
   if ((whole_rows && !few_narrow) || g.C >= 1024) {
     p.tok_run = whole_rows ? 1 : 4;
     while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
@@ -1311,6 +1341,7 @@ kvc_status launch_pack(PackParams p, hipStream_t stream) {
   err = p.body == kPackResident ? launch_variant<DT_, UNI_, kPackResident>(grid, block, stream, p)       \
         : p.body == kPackMedium ? launch_variant<DT_, UNI_, kPackMedium>(grid, block, stream, p)         \
         : p.body == kPackLight  ? launch_variant<DT_, UNI_, kPackLight>(grid, block, stream, p)          \
+        : p.body == kPackTokens ? launch_variant<DT_, UNI_, kPackTokens>(grid, block, stream, p)         \
                                 : launch_variant<DT_, UNI_, kPackStream>(grid, block, stream, p)
   if (g.dtype == KVC_F16) {
     if (uniform) KVC_LAUNCH_PACK(KVC_F16, true); else KVC_LAUNCH_PACK(KVC_F16, false);
