@@ -2,7 +2,8 @@
 
 For every tiling the three rules leave (kvc_tile_candidates) the same KV tensor is packed at one frame
 resolution (kvc_pack), its residual histograms are counted (kvc_residual_histograms) and turned into a cost in
-bits (kvc_proxy_costs); candidates are ranked by that cost.  This module only loops and marshals: every
+bits (kvc_proxy_costs); candidates are ranked by that cost.  Candidates whose planes are alike, which is all of them but for
+sizes that no grid fills alike, are counted from one packed copy instead (kvc_tiling_costs), with the same costs.  This module only loops and marshals: every
 byte of every candidate is produced and counted by the library's kernels.
 """
 import threading
