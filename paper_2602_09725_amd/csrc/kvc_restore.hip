@@ -54,6 +54,8 @@ constexpr int64_t kFillWorkgroups = 1024;
 // 656 tokens x 60 layers x 512 channels 28.3 -> 26.9 us).  The "lanes" body always takes 256: 12 345 tokens of 80
 // layers x 128 channels 141 -> 136 us, 52 172 tokens of 32 layers 230 -> 221 us.
 constexpr int64_t kManyWorkgroups = 4096;
+// Elements of a call from which "rows" of tiles 8 high under a table are better off with more waves than with early table entries.
+constexpr int64_t kLargeCall = 1ll << 28;
 // Four workgroups of 512 threads fit a CU.  Launches of full passes let in two (dynamic LDS that nobody uses keeps the others
 // out): fewer reads between the writes and fewer regions of the cache under way (2048 tokens x 32 layers x 4096 channels 289 us
 // with four, 285 with three, 272 with two; 32K tokens x 1024 channels in block order 1157 / 1130 / 1114; 5000 tokens into a
@@ -218,8 +220,13 @@ __device__ __forceinline__ uint32_t tile_elem(const Geo& g, uint32_t r, uint32_t
 // LINE: rounds without a dead lane store in a straight line, as above; for a contiguous destination.
 // EARLY: table entries are asked for with the codes.  One asked for between the stores is waited for by a counter that counts
 // stores as well, so each pass waited for the stores of the pass before it (tiles of (16,64), 80 layers x 2410 tokens, 13 tiles
-// a row 262 -> 246 us, of (8,64), 7158 tokens, 6 a row 375 -> 350).  Runs of frames of tiles 16 high do not gain by it (16 a
-// row, 30 frames 55 -> 56.5 us): the registers it takes leave one workgroup of 1024 threads on a CU.
+// a row 262 -> 246 us, of (8,64), 7158 tokens, 6 a row 375 -> 350).  In rounds of eight the registers it takes, 67 instead of 59,
+// leave one workgroup of 1024 threads on a CU (tiles 16 high) or three of 512.  Tiles 16 high gain by it where runs are cut short
+// (20 tiles a row 739 -> 702 us, 26 a row 0.93 of the time at the median) and lose where they are whole or nearly so (8 a row 172
+// -> 176, 24 of 24 670 -> 681, 32 of 32 608 -> 632, 22 of 24 203 -> 208, 30 of 32, 80 layers x 20 000 tokens, 1836 -> 1873), and
+// in runs of frames (16 a row, 30 frames 55 -> 56.5).  Tiles 8 high of 512 channels gain 4 to 14 % in calls of 2048 tokens x 80 layers
+// and less, whatever the runs, and lose in large ones of whole runs (15 of 16, 32 layers x 30 000 tokens, 541 -> 561, 14 of 16 546
+// -> 556, 24 of 24 354 -> 362).  Over the host link a wave has reads to wait for either way (11 a row, F = 4, of 256 channels 336 -> 340).
 template <int MODE, int DT, bool PAGED, int U, bool LINE, bool EARLY>
 __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                   uint32_t tg, const uint8_t* fsec, uint32_t ff) {
@@ -538,6 +545,15 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
   const int per_row = nf * runs;                                         // passes one row of tiles takes
   const int trw = per_row >= kPasses ? 1 : kPasses / per_row;            // about one round of loads per wave
   const auto row_units = [&](int32_t n) { return (int32_t)ceil_div(ceil_div(ceil_div(n, g.F), g.TX), trw); };
+  // Loads in flight: those of eight passes or of six, whichever leaves fewer of a unit's last round without one (under a table
+  // twelve passes, tiles of (16,64) and (8,64), 246 -> 236 and 350 -> 327 us; six, 5000 tokens x 80 layers x 512 channels into a
+  // contiguous tensor, 13 tiles a row, 248 -> 241; but eight in two rounds of six 172 -> 182).  More than three rounds of six only
+  // under a table and where runs are cut short (of tiles 16 high, thirty passes into a contiguous tensor 594 -> 611 us,
+  // twenty-nine of whole runs 210 -> 218), and none over the host link, which wants the reads (fetched in place, tiles of
+  // (8,64), 13 a row, F = 4: 634 -> 663 us).
+  const int row_passes = trw * per_row;
+  const bool six = q != 0 && !p.host_frames && (row_passes <= 18 || (paged && g.TX % q != 0)) && ceil_div(row_passes, 6) * 6 < ceil_div(row_passes, 8) * 8;
+  const int rows_u = six ? 6 : kPasses;
   bool rows = q >= 2 && g.th <= 16;
   if (p.host_frames) {
     // Over the host link what counts is the length of a read (below: GB/s of codes, 2048 tokens, the others' against that of
@@ -554,22 +570,26 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     // -> 505 us, random table 520), unless runs are much longer than what is left for the last one: into a contiguous tensor
     // at least three quarters of a row's runs have to exist (17 tiles a row: 585 -> 727 us; 8192 tokens x 32 layers, 6 tiles
     // 318 -> 294), under a table more (6 tiles a row 316 -> 331, 17 of them 364 -> 387, 7 of them 324 -> 306), but for tokens of
-    // one wave (512 channels; with table entries that come with the codes: 6 tiles a row 374 -> 327, 17 of them 441 -> 416, 11
-    // 297 -> 274, 10 288 both, 9 290 -> 296; 600 tokens of 17 tiles a row, 1152 workgroups, 14.7 -> 15.8, 2304 of them 26.8 ->
-    // 26.2) and of half one (256 channels: 16 tiles a row 711 -> 652, 13 218 -> 200, 6 121 -> 111; 17 tiles 57 -> 58, 5 143 ->
-    // 150; 600 tokens, 1088 workgroups, 8.0 -> 8.7, 2720 of them 18.9 -> 17.2).  Of tokens of one head of 128 it loses (137 -> 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole runs and one round of loads
-    // takes them (8192 tokens x 32 layers, 8 tiles a row, F = 4: 283 -> 275 us; 12 tiles 287 -> 310, 16 tiles 283 -> 294, F
-    // = 16 148 -> 190 for 16 layers; under a random table 284 -> 287).  A launch that would not fill the chip is better cut
-    // finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us, 644 tokens in groups of 10 frames 21.6 against
-    // 24.8).
+    // one wave.  Of those, 512 channels, eleven sixteenths do where one round of loads takes a row of tiles (17 a row, F = 2, 60
+    // layers x 10 000 tokens 358 -> 343 us; more rounds lose: F = 6 114 -> 128, F = 3, 2048 tokens of 80 layers 106 -> 112), from
+    // 4096 workgroups on (700 tokens of 11 a row, F = 3, 3520 workgroups, 36.4 -> 37.4).  Half a wave, 256 channels: three quarters,
+    // one round, and several frames (16 a row, F = 2, 21 533 tokens of 80 layers 497 -> 466, 13 a row 218 -> 200, 6 a row 121 -> 111;
+    // one frame 44.6 -> 46.1, two rounds of 13 a row, F = 5, 493 -> 502, of 8 a row, F = 16, 50.6 -> 60.5, eight of 23 475 -> 535),
+    // from 2048 workgroups on (600 tokens, 1088 workgroups, 8.0 -> 8.7, 2720 of them 18.9 -> 17.2).  Of tokens of one head of 128
+    // it loses (137 -> 148).  And for tiles of 128 bytes into a contiguous tensor, where rows of tiles are whole
+    // runs and one round of loads takes them (8192 tokens x 32 layers, 8 tiles a row, F = 4: 283 -> 275 us; 12 tiles 287 -> 310,
+    // 16 tiles 283 -> 294, F = 16 148 -> 190 for 16 layers; under a random table 284 -> 287).  A launch that would not fill the
+    // chip is better cut finer by the other bodies (100 tokens x 80 layers 15.0 against 16.9 us, 644 tokens in groups of 10
+    // frames 21.6 against 24.8).
     const int tiles4 = 4 * g.TX, runs3 = 3 * q * runs;
     const bool few_tiles = tiles4 < runs3;
     bool half_lines = g.tw < 128 && (paged ? g.apt > 32 && (tiles4 > runs3 || (tiles4 == runs3 && g.apt == 64))
                                            : g.apt >= 32 && !few_tiles);
     int64_t fill = kFillWorkgroups;
-    if (paged && !p.frame_mode && g.tw < 128 && (g.apt == 32 ? !few_tiles : g.apt == 64 && few_tiles && 16 * g.TX >= 11 * q * runs)) {
+    if (paged && !p.frame_mode && g.tw < 128 && row_passes <= rows_u &&
+        (g.apt == 32 ? g.F > 1 && !few_tiles : g.apt == 64 && few_tiles && 16 * g.TX >= 11 * q * runs)) {
       half_lines = true;
-      fill = 2 * kFillWorkgroups;
+      fill = (g.apt == 32 ? 2 : 4) * kFillWorkgroups;
     }
     const bool linear = g.tw == 128 && !paged && g.TX % q == 0 && per_row <= kPasses && g.apt >= 64;
     const int64_t wgs = p.frame_mode ? (int64_t)p.fm_count * 3 * row_units(n_last)
@@ -586,10 +606,7 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     p.dnf = make_fastdiv((uint32_t)nf);
     p.dpr = make_fastdiv((uint32_t)per_row);
     p.rows_trw = trw;
-    // Loads in flight: those of eight passes or of six, whichever leaves fewer of a unit's last round without one (twelve passes,
-    // the two calls above 246 -> 236 and 350 -> 327 us; six, 5000 tokens x 80 layers x 512 channels into a contiguous tensor,
-    // 13 tiles a row, 248 -> 241; but eight in two rounds of six 172 -> 182).
-    if (ceil_div(trw * per_row, 6) * 6 < ceil_div(trw * per_row, 8) * 8) u = 6;
+    u = rows_u;
     p.rows_tile_rows = (int32_t)ceil_div(ceil_div(g.T, g.F), g.TX);  // rows of tiles that hold tokens
     p.tbc = row_units(p.frame_mode ? n_last : g.T);  // units of one (chunk, kind, layer) or plane
     tbl = row_units(n_last);
@@ -644,7 +661,12 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     body = kBodyRowsLine;
     lds = kLdsForTwo;
   }
-  if (body == kBodyRows && paged && p.frame_mode && g.th > 8 && u == 8) body = kBodyRowsLate;
+  // Table entries late in rounds of eight: over the host link, for runs of frames of tiles 16 high, and where no more than a
+  // twelfth of the runs is missing of tiles 16 high, or an eighth of lower ones in a large call.
+  const bool large = (int64_t)g.L * p.n_tokens * g.C >= kLargeCall;
+  if (body == kBodyRows && paged && u == kPasses &&
+      (p.host_frames || (p.frame_mode ? g.th > 8 : g.th > 8 ? 12 * g.TX >= 11 * q * runs : large && 8 * g.TX >= 7 * q * runs)))
+    body = kBodyRowsLate;
   if (g.dtype == KVC_F16) {
     if (paged)
       launch_variant<KVC_F16, true>(p, body, u, grid, block, lds, stream);

@@ -2,6 +2,7 @@
 binding and the CPU oracle on the same seeded inputs.  Holds no arithmetic of
 the method: it only allocates, calls and compares."""
 import ctypes
+import re
 import sys
 
 import numpy as np
@@ -28,6 +29,47 @@ def layouts(L, H, D, dtype, T, th, tw, TX, TY, k_mode=0, v_mode=1, seg=0):
 
 def workload_layouts(w, L=None):
     return layouts(w.L if L is None else L, w.H, w.D, w.dtype, w.T, w.th, w.tw, w.TX, w.TY)
+
+
+class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint32 * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def kernels_of(call):
+    """[(kernel, template arguments, threads, workgroups)] of what call() launches of the library's on the current stream, in
+    order: which variant the rule of a dispatch has chosen.  They are captured into a graph that is never run."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    hip.hipKernelNameRefByPtr.argtypes = [ctypes.c_void_p, ctypes.c_void_p]
+    handle, count = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(count)) == 0
+    launched = []
+    for node in nodes:
+        k = _KernelNode()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(k)) == 0, "not a kernel"
+        name = hip.hipKernelNameRefByPtr(k.func, None).decode()
+        m = re.search(r"\d([a-z_]+_kernel)(?:I((?:L[a-z]\d+E)+)E)?", name)
+        assert m, name
+        args = tuple(int(a) for a in re.findall(r"L[a-z](\d+)E", m[2] or ""))
+        launched.append((m[1], args, k.block[0], k.grid[0]))
+    return launched
+
+
+RESTORE_BODIES = ["lanes", "waves", "rows", "rows line", "rows late"]
+
+
+def restore_body(call):
+    """(body, passes in flight) of the one kernel that a restore launches."""
+    ((name, args, _, _),) = kernels_of(call)
+    assert name == "restore_kernel"
+    return RESTORE_BODIES[args[2]], args[3]
 
 
 def stream_handle():
