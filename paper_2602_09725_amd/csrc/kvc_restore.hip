@@ -467,14 +467,14 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
   }
   if (p.g.mode[kind] == KVC_Q_PER_CHANNEL) {
     if (BODY >= kBodyRows)
-      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_rows<KVC_Q_PER_CHANNEL, DT, PAGED, U, BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
       restore_body_lanes<KVC_Q_PER_CHANNEL, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
   } else {
     if (BODY >= kBodyRows)
-      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U, !PAGED && BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
+      restore_body_rows<KVC_Q_PER_TOKEN, DT, PAGED, U, BODY == kBodyRowsLine, BODY != kBodyRowsLate>(p, c, kind, l, tbi, fsec, ff);
     else if (BODY == kBodyWaves)
       restore_body_waves<KVC_Q_PER_TOKEN, DT, PAGED, U>(p, c, kind, l, tbi, fsec, ff);
     else
@@ -485,11 +485,17 @@ __global__ void __launch_bounds__(1024) restore_kernel(const RestoreParams p) {
 template <int DT, bool PAGED>
 void launch_variant(const RestoreParams& p, int body, int u, dim3 grid, dim3 block, unsigned lds, hipStream_t s) {
 #define KVC_LAUNCH_RESTORE(BODY_, U_) hipLaunchKernelGGL((restore_kernel<DT, PAGED, BODY_, U_>), grid, block, lds, s, p)
-  if (!PAGED && body == kBodyRowsLine) {
+  // (table entries exist under a table alone, straight lines into a contiguous tensor: the other kernels are not built)
+  if constexpr (PAGED) {
+    if (body == kBodyRowsLate) {
+      KVC_LAUNCH_RESTORE(kBodyRowsLate, 8);
+      return;
+    }
+  } else if (body == kBodyRowsLine) {
     if (u == 6) KVC_LAUNCH_RESTORE(kBodyRowsLine, 6); else KVC_LAUNCH_RESTORE(kBodyRowsLine, 8);
-  } else if (PAGED && body == kBodyRowsLate) {
-    KVC_LAUNCH_RESTORE(kBodyRowsLate, 8);
-  } else if (body == kBodyRows) {
+    return;
+  }
+  if (body == kBodyRows) {
     if (u == 6) KVC_LAUNCH_RESTORE(kBodyRows, 6); else KVC_LAUNCH_RESTORE(kBodyRows, 8);
   } else if (body == kBodyWaves) {
     if (u == 8) KVC_LAUNCH_RESTORE(kBodyWaves, 8); else if (u == 4) KVC_LAUNCH_RESTORE(kBodyWaves, 4); else KVC_LAUNCH_RESTORE(kBodyWaves, 2);

@@ -454,3 +454,12 @@ def test_shared_strips_of_the_parity_test(kvc_lib):
     for (L, H, D, T, th, tw, TX, TY, n, modes, seg) in parity.SHARED_STRIPS:
         lo, C = kvc.Layout(L, H, D, 0, T, th, tw, TX, TY, *modes, seg), H * D
         assert kvc.pack_form(lo, (2 * n * C, n * C, C), n)[:2] == (TWO_PASS, 64 if tw < 128 else 128), (L, H, T, n)
+
+
+def test_no_restore_kernel_is_built_that_no_call_launches(kvc_lib):
+    """A straight line of stores is for a contiguous destination, late table entries are for a paged one."""
+    with open(kvc.lib_path(), "rb") as f:
+        built = set(re.findall(rb"restore_kernelILi(\d)ELb(\d)ELi(\d)ELi(\d)E", f.read()))
+    assert {dtype for dtype, _, _, _ in built} == {b"0", b"1"}
+    assert {body for _, paged, body, _ in built if paged == b"0"} == {b"0", b"1", b"2", b"3"}
+    assert {body for _, paged, body, _ in built if paged == b"1"} == {b"0", b"1", b"2", b"4"}
