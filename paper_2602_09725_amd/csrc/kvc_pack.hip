@@ -1299,12 +1299,12 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // Token blocks in turn, in runs that hold about as many bytes as a block of 1024 channels.  Where blocks end inside a
   // row of tiles, neighbours stay on one XCD: in longer runs (rows of 36 positions, 8192 tokens of 32 layers x 1024
   // channels 307 -> 296 us; blocks of whole rows lose 1 % by it), or narrower ones in eighths (4096 x 32 x 256 54 -> 51 us).
-  // Per-token kinds alone also stay in eighths where blocks were made shorter, or are those of the streaming form, of fewer than
-  // 1024 channels and not so many (16 layers of 2048 tokens of 512 channels 27.3 -> 25.3 us there; in the kernel of the per-token
-  // body 32 layers of 3000 tokens of 512 60 in turn, 62 in eighths; 64 rows of blocks of 64 tokens of 256 channels 9.7 and 9.5).
+  // Per-token kinds alone, of fewer than 1024 channels and not so many, also stay in eighths (16 layers of 2048 tokens of 512
+  // channels 27.3 -> 25.3 us, 2 layers of 8625 tokens of 256 10.5 -> 10.0, of 128 7.2 -> 6.7), but for the kernel of the per-token
+  // body (32 layers of 3000 tokens of 512 60 in turn, 62 in eighths).
   const bool whole_rows = p.tb % (g.F * g.TX) == 0;
   p.tok_run = 0;
-  const bool few_narrow = p.n_kinds_ch == 0 && (p.body == kPackLight ? p.tb < 128 : p.body == kPackStream) && g.C < 1024 && rows_tok * p.n_tokens < 8 * kFewTokenRows;
+  const bool few_narrow = p.n_kinds_ch == 0 && p.body != kPackTokens && g.C < 1024 && rows_tok * p.n_tokens < 8 * kFewTokenRows;
   if ((whole_rows && !few_narrow) || g.C >= 1024) {
     p.tok_run = whole_rows ? 1 : 4;
     while (p.tok_run * 2 * (uint32_t)g.C <= 1024u) p.tok_run *= 2;
