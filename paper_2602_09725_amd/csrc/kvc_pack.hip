@@ -668,7 +668,11 @@ constexpr int kMediumGroup = 4;
 // x 9000 tokens of 256 channels 101 -> 82 us, 80 layers of 40 000 of 128 514 -> 392, floor 385; 32 layers of 3000 of 512 66 -> 60;
 // of 1024 and more channels it loses, 123 against 127 us).  Where most of the chunks is zero fill, few large workgroups fill faster:
 // up to six times the tokens for 256 channels (eight times, 80 layers of 20 000 tokens of 128: 653 against 718 us), 1.6 times for 512
-// (1.7 times 138 against 142 us, twice 253 against 262); and they are faster from 2^29 elements of 512 channels on (344 against 365).
+// (1.7 times 138 against 142 us, twice 253 against 262).  Of 512 channels they are faster from 2^29 elements on (344 against 365) and
+// below 98 304 rows, where the last round of the smaller ones is short (24 layers of 1577 tokens 27.9 against 30.0, 11 of 3213 29.1
+// against 31.0; of 3950 31.4 against 29.5).  And whatever the channels on tiles of more than four rows, whose codes are cut into
+// shorter pieces (of 512 channels in 64 bytes, 80 layers of 2892 tokens, 178 against 189, of 256 in 32 bytes, 60 layers of 7630, 216
+// against 263, of 128 in 32 bytes 62 against 71).
 constexpr int kLightLoads = 16;
 constexpr int kRegGroup = 8;
 constexpr int kFewestAtoms = 2;
@@ -1171,7 +1175,9 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
     const int64_t rows = (int64_t)g.L * p.n_kinds_tok * p.n_tokens;
     const bool few_rows = rows < kFewTokenRows && rows * g.C < kFewTokenRows * 1024;
     const int64_t room = (int64_t)p.n_chunks * g.G * g.F;  // token positions of the chunks, with those that are zero fill
-    const bool narrow = g.C <= 256 ? room <= 6 * p.n_tokens : g.C <= 512 && 5 * room <= 8 * p.n_tokens && rows * g.C < 8 * kFewTokenRows * 1024;
+    const bool narrow = g.C <= 256 ? g.tw >= 64 && room <= 6 * p.n_tokens
+                                   : g.C <= 512 && g.tw >= 128 && 5 * room <= 8 * p.n_tokens && 2 * rows >= 3 * kFewTokenRows &&
+                                         rows * g.C < 8 * kFewTokenRows * 1024;
     if (!wide && !many_chunks) p.body = few_rows ? kPackLight : narrow ? kPackTokens : kPackStream;
   } else if (!wide) {
     const int64_t most = rows_of(kResidentLoads, kResidentAtoms);

@@ -463,3 +463,24 @@ def test_no_restore_kernel_is_built_that_no_call_launches(kvc_lib):
     assert {dtype for dtype, _, _, _ in built} == {b"0", b"1"}
     assert {body for _, paged, body, _ in built if paged == b"0"} == {b"0", b"1", b"2", b"3"}
     assert {body for _, paged, body, _ in built if paged == b"1"} == {b"0", b"1", b"2", b"4"}
+
+
+TOKENS, STREAM = 512, 1024  # threads of the kernel of the per-token body alone and of the streaming one
+
+
+@pytest.mark.parametrize("L,H,D,T,th,tw,TX,TY,n,want", [
+    (80, 1, 128, 2048, 1, 128, 8, 64, 500, TOKENS), (80, 1, 128, 2048, 2, 64, 16, 76, 410, TOKENS),    # room 4.1 and 5.93 times the tokens
+    (80, 1, 128, 2048, 2, 64, 16, 77, 410, STREAM),                                                    # 6.01
+    (60, 2, 128, 2048, 4, 64, 16, 64, 3000, TOKENS), (60, 2, 128, 2048, 8, 32, 32, 32, 3000, STREAM),  # 256 channels in 64 bytes, 32
+    (32, 1, 128, 1024, 4, 32, 32, 8, 8022, STREAM), (32, 1, 128, 1024, 2, 64, 16, 16, 8022, TOKENS),   # 128 channels
+    (80, 4, 128, 2048, 4, 128, 8, 64, 2892, TOKENS), (80, 4, 128, 2048, 8, 64, 16, 64, 2892, STREAM),  # 512 in 128 bytes, 64
+    (40, 4, 128, 1100, 4, 128, 4, 96, 1440, TOKENS), (40, 4, 128, 1100, 4, 128, 4, 97, 1440, STREAM),  # room 1.6 times the tokens, 1.62
+    (24, 4, 128, 2048, 4, 128, 8, 64, 2048, TOKENS), (24, 4, 128, 2048, 4, 128, 8, 64, 2047, STREAM),  # 98 304 rows
+    (32, 4, 128, 2048, 4, 128, 8, 64, 16383, TOKENS), (32, 4, 128, 2048, 4, 128, 8, 64, 16384, STREAM),  # 2^29 elements
+    (40, 9, 64, 2048, 9, 64, 16, 32, 4096, STREAM),                                                    # 576 channels
+])
+def test_which_packs_of_narrow_tokens_take_the_kernel_of_the_per_token_body(kvc_lib, L, H, D, T, th, tw, TX, TY, n, want):
+    lo, C = kvc.Layout(L, H, D, 0, T, th, tw, TX, TY, 1, 1), H * D
+    form, strip, threads = kvc.pack_form(lo, (2 * n * C, n * C, C), n)
+    assert (form, strip) == (TWO_PASS, 0)
+    assert threads == want if want == TOKENS else threads > TOKENS
