@@ -1257,17 +1257,24 @@ kvc_status plan_pack(PackParams& p, int* threads_out, bool many_chunks) {
   // nothing to overlap its wait and its stores with, and of which a CU holds one or two: 256 tokens of 512 channels, 256 of
   // 256 and 512 of 128 (per token beside per channel, 32 layers of 9000 tokens of 256 channels 91 -> 85 us, of 30 000 293 ->
   // 271, 80 layers of 9000 tokens of 128 112 -> 106, 32 layers of 3000 tokens of 512 62.5 -> 58.8; twice as long again 85 -> 86.4).
-  // As long as enough of them are left for the CUs: two for each place a workgroup has (80 layers of 1254 tokens of 256 channels,
-  // 400 units, 36.5 -> 37.3 us; 1024-token chunks, two places, 960 units, 34.1 -> 34.8), three in the streaming form
-  // (640 units 54.5 -> 55.7), one of 512 channels beside strips that wait on chip (256 units 41.7 -> 38.7; beside others
-  // 94.7 -> 95.4, not at all), eight of 512 channels without any (1536 units 113.8 -> 115.4, 2304 170 -> 165).
+  // On tiles of at most four rows, of 64 bytes and more (32 bytes: 48 layers of 3754 tokens of 256 channels 70.8 -> 76.7; 512 channels in
+  // 64 bytes: 80 layers of 1297 tokens 82 -> 89.6, of 36 818 1927 -> 1959).  And as long as enough of them are left for the CUs, or
+  // the last round is half empty: two for each place a workgroup has (80 layers of 1254 tokens of 256 channels, 400 units, 36.5 ->
+  // 37.3; 1024-token chunks, two places, 960 units, 34.1 -> 34.8; from 512 units on single sizes lose up to 2 %, 80 layers of 1592
+  // tokens 42.6 -> 43.4, their neighbours gain 3 to 7), three in the streaming form (640 units 54.5 -> 55.7).  512 channels beside
+  // strips that wait on chip: three (288 units 55.3 -> 58.3, 480 71.4 -> 77.3, 660 107 -> 110, 720 123 -> 120.5, 736 114 -> 109.6), or as many for
+  // each CU (256 units 41.7 -> 38.8, 512 76.0 -> 73.6); beside others not at all (94.7 -> 95.4); without any eight, and several
+  // frames (1536 units 113.8 -> 115.4, 2304 170 -> 165; one frame 485 -> 505).
   const auto units_tok = [&] { return count_blocks() * g.L * p.n_kinds_tok; };
-  const bool stream_body = p.body == kPackStream, beside = p.n_kinds_ch > 0;
-  const int32_t most_tb = p.body == kPackLight || p.body == kPackTokens || g.C > 512 || (g.C > 256 && stream_body && beside) ? 0 : g.C > 256 ? 4 * in_flight : 2 * in_flight;
-  const int64_t fewest = (g.C > 256 ? (beside ? 1 : 8) : stream_body ? 3 : 2) * kCus * (p.body == kPackMedium ? 2 : 1);
+  const bool stream_body = p.body == kPackStream, beside = p.n_kinds_ch > 0, half_wide = g.C > 256;
+  const bool longer = p.body != kPackLight && p.body != kPackTokens && g.C <= 512 && g.tw >= (half_wide ? 128 : 64) &&
+                      !(half_wide && stream_body && (beside || g.F == 1));
+  const int32_t most_tb = !longer ? 0 : half_wide ? 4 * in_flight : 2 * in_flight;
+  const int64_t fewest = (half_wide && !beside ? 8 : half_wide || stream_body ? 3 : 2) * kCus * (p.body == kPackMedium ? 2 : 1);
+  const auto even = [&] { return half_wide && p.body == kPackResident && units_tok() % kCus == 0; };
   while (2 * p.tb <= most_tb) {
     p.tb *= 2;
-    if (units_tok() < fewest) {
+    if (units_tok() < fewest && !even()) {
       p.tb /= 2;
       break;
     }

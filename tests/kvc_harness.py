@@ -72,6 +72,21 @@ def restore_body(call):
     return RESTORE_BODIES[args[2]], args[3]
 
 
+PACK_BODIES = ["resident", "streaming", "light", "medium", "tokens"]
+
+
+def pack_kernels(glo, n_tokens):
+    """[(body, threads, workgroups)] of what a pack of n_tokens tokens launches, but for the clearing of shared strips' words."""
+    fb, mb, _ = kvc.chunk_sizes(glo)
+    nc, C = -(-n_tokens // glo.chunk_tokens), glo.num_kv_heads * glo.head_dim
+    kv = torch.empty(glo.num_layers * 2 * n_tokens * C, dtype=torch.int16, device="cuda")
+    frames = torch.empty(nc * fb, dtype=torch.uint8, device="cuda")
+    meta = torch.empty(nc * mb, dtype=torch.uint8, device="cuda")
+    launched = kernels_of(lambda: kvc.kvc_pack(glo, kv.data_ptr(), (2 * n_tokens * C, n_tokens * C, C), n_tokens, frames.data_ptr(),
+                                               nc * fb, meta.data_ptr(), nc * mb, stream_handle()))
+    return [(PACK_BODIES[args[2]], threads, wgs) for name, args, threads, wgs in launched if name == "pack_kernel"]
+
+
 def stream_handle():
     return torch.cuda.current_stream().cuda_stream
 
