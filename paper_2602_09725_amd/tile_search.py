@@ -2,14 +2,15 @@
 
 For every tiling the three rules leave (kvc_tile_candidates) the same KV tensor is packed at one frame
 resolution (kvc_pack), its residual histograms are counted (kvc_residual_histograms) and turned into a cost in
-bits (kvc_proxy_costs); candidates are ranked by that cost.  Candidates whose planes are alike, which is all of them but for
-sizes that no grid fills alike, are counted from one packed copy instead (kvc_tiling_costs), with the same costs.  This module only loops and marshals: every
-byte of every candidate is produced and counted by the library's kernels.
+bits (kvc_proxy_costs); candidates are ranked by that cost.  A list of candidates whose planes are all alike is counted from
+one packed copy instead (kvc_tiling_costs), with the same costs.  Planes are alike where whole tiles of every candidate fill
+the same part of the frame, as those of 8 heads of 128 elements do in 1024 x 512 pixels, but not in 426 x 240, 854 x 480, 1138 x 640
+or 1920 x 1080; one candidate whose plane differs leaves the whole list to the first way.  This module only loops and marshals:
+every byte of every candidate is produced and counted by the library's kernels.
 """
 import threading
 
 import torch
-from torch import Tensor
 
 from . import kvc
 
@@ -86,6 +87,23 @@ def _ranked(rows, costs, elements):
     return rows
 
 
+def _may_be_alike(candidates, head_dim, frame_width, frame_height):
+    """False where the library would refuse to count these together: heads of no power of two, or a plane that differs among
+    the first, the middle and the last candidate (which has the widest and the narrowest tile of the default list).  A list that
+    the library itself refuses has cost 10 to 20 us by then, and two candidates take 120."""
+    if head_dim & (head_dim - 1):
+        return False
+    plane = None
+    for th, tw, _ in (candidates[0], candidates[-1], candidates[len(candidates) // 2]):
+        if th < 1 or tw < 1:
+            return False
+        p = max(1, frame_width // tw) * tw, max(1, frame_height // th) * th
+        if plane is not None and p != plane:
+            return False
+        plane = p
+    return True
+
+
 def _count_together(kv, n_tokens, layout, candidates, frame_width, frame_height, stream):
     """Rows and device costs [candidates][streams] of candidates whose planes are alike, counted from one packed copy
     (kvc_tiling_costs), or None where the library does not take them so, or there is no memory for the copy."""
@@ -127,14 +145,13 @@ def rank_tiles(kv, n_tokens, dtype, chunk_tokens, frame_width, frame_height, k_m
     stream = stream or torch.cuda.current_stream()
     if not isinstance(stream, torch.cuda.Stream):  # anything that carries a stream's handle
         stream = torch.cuda.ExternalStream(stream.cuda_stream, device=kv.device)
-    if len(candidates) > 1 and isinstance(kv, Tensor):  # what only looks like a tensor is scored candidate by candidate
-        with torch.cuda.stream(stream):
+    with torch.cuda.stream(stream):
+        if len(candidates) > 1 and _may_be_alike(candidates, D, frame_width, frame_height):
             lo = kvc.Layout(L, H, D, dtype, chunk_tokens, 1, C, 1, chunk_tokens, k_mode, v_mode)
             together = _count_together(kv, n_tokens, lo, candidates, frame_width, frame_height, stream)
             if together is not None:
                 rows, costs = together
                 return _ranked(rows, costs.cpu(), L * 2 * n_tokens * C)
-    with torch.cuda.stream(stream):
         costs = torch.empty((len(candidates), n_chunks * 2 * L), dtype=torch.float64, device=kv.device)
         kv_ptr, cost_ptr, cost_bytes = kv.data_ptr(), costs.data_ptr(), costs.stride(0) * 8
         lanes, used = [], []

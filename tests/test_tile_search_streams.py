@@ -76,6 +76,7 @@ class Tensor:
         n = item
         for k in self.shape:
             n *= k
+        self.rows = self.shape[0]
         self.at, self.n = model.allocate(n)
 
     def data_ptr(self):
@@ -106,9 +107,9 @@ class Tensor:
 
 
 def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, candidates=None, meanwhile=None, refuse_above=None,
-           model=None, stream=None, searched=True):
+           model=None, stream=None, searched=True, workspace=0):
     """rank_tiles on the model, by a thread that has searched before; `meanwhile(model)` runs after the first candidate is
-    enqueued."""
+    enqueued.  The library is said to want `workspace` bytes to count candidates together, and not to take them so if that is 0."""
     m = model or Model()
     tile_search._own.searched = searched
     m.refuse_above = refuse_above
@@ -149,6 +150,18 @@ def search(monkeypatch, layers, heads, head_dim, tokens, chunk, width, height, c
         m.access(by(handle), hist, kvc.residual_histograms_size(lo, n_chunks), False, f"{count[0]} cost: counters")
         m.access(by(handle), cost, n_chunks * 2 * layers * 8, True, f"{count[0]} cost")
 
+    def together(lo, kv, strides, n, tiles, width, height, work, work_bytes, cost, handle):
+        count[0] += 1
+        assert work_bytes == workspace and len(tiles[0]) == len(tiles[1]) == len(tiles[2])
+        m.access(by(handle), work, work_bytes, True, "workspace")
+        m.access(by(handle), cost, len(tiles[0]) * -(-n // lo.chunk_tokens) * 2 * layers * 8, True, "costs")
+        m.together = len(tiles[0])
+        if meanwhile:
+            meanwhile(m)
+
+    m.together = 0
+    monkeypatch.setattr(tile_search.kvc, "tiling_costs_workspace", lambda *a: workspace)
+    monkeypatch.setattr(tile_search.kvc, "kvc_tiling_costs", together)
     monkeypatch.setattr(tile_search.kvc, "kvc_pack", pack)
     monkeypatch.setattr(tile_search.kvc, "kvc_residual_histograms", histograms)
     monkeypatch.setattr(tile_search.kvc, "kvc_proxy_costs", costs)
@@ -234,3 +247,56 @@ def test_streams_are_made_once(kvc_lib, monkeypatch):
     thread.start()
     thread.join()
     assert not m.races and len(m.streams) == 2 + 2 * (tile_search.LANES - 1)
+
+
+ALIKE = SHAPES[4]
+
+
+def test_candidates_counted_together(kvc_lib, monkeypatch):
+    """Planes alike: one call on the caller's stream, in an order with what others do there; memory given back after it."""
+    def another_thread(m):
+        for n in (1 << 20, 40 << 20):
+            t = Tensor(m, (n,), 1)
+            m.access(m.caller, t.at, t.n, True, "another thread's work")
+            del t
+
+    m, rows = search(monkeypatch, *ALIKE, workspace=30 << 20, meanwhile=another_thread)
+    assert m.together == len(rows) == 20 and not m.races and len(m.streams) == 1 and m.live <= 64 * 1024
+    m = Model()
+    other = Stream(m)
+    for stream in (other, m.caller, other):
+        m, rows = search(monkeypatch, *ALIKE, workspace=30 << 20, model=m, stream=stream)
+        assert m.together == 20 and not m.races and len(m.streams) == 2
+    # one alone is scored by itself, and so are all where a plane differs, without a question to the library
+    m, rows = search(monkeypatch, *ALIKE, workspace=30 << 20, candidates=kvc.tile_candidates(8, 128)[:1])
+    assert m.together == 0 and len(rows) == 1
+    m, rows = search(monkeypatch, *SHAPES[1], workspace=30 << 20)
+    assert m.together == 0 and len(rows) == 20 and not m.races
+
+
+def test_no_memory_to_count_candidates_together(kvc_lib, monkeypatch):
+    """They are scored one by one then, with the same rows in the same form."""
+    most = max(sets_of(*ALIKE))
+    want = search(monkeypatch, *ALIKE)[1]
+    m, rows = search(monkeypatch, *ALIKE, workspace=5 * most, refuse_above=2 * most + (1 << 20))
+    assert m.together == 0 and not m.races and rows == want
+    shared = search(monkeypatch, *ALIKE, workspace=most)[1]
+    facts = ("tile_h", "tile_w", "tile_seg", "tile_grid", "frames_per_group", "frame_bytes_per_chunk")
+    assert [[r[k] for k in facts] for r in shared] == [[r[k] for k in facts] for r in want]
+
+
+@pytest.mark.parametrize("heads,head_dim", [(8, 128), (32, 128), (2, 96), (1, 64)])
+def test_what_is_asked_before_the_library(kvc_lib, heads, head_dim):
+    """Candidates that the library counts together are never held back, and pairs that it does not for their planes are."""
+    tiles = kvc.tile_candidates(heads, head_dim)
+    lo = kvc.Layout(3, heads, head_dim, kvc.KVC_F16, 64, 1, heads * head_dim, 1, 64, 0, 0)
+
+    def counted(some, width, height):
+        return kvc.tiling_costs_workspace(lo, 64, kvc.tile_arrays(some), width, height) > 0
+
+    lists = [tiles, tiles[::-1], tiles[1:], tiles[:-1]] + [[a, b] for a in tiles for b in tiles]
+    for width, height in ((1024, 512), (2048, 1024), (4096, 64), (426, 240), (854, 480), (1138, 640), (1920, 1080), (64, 4), (1, 1)):
+        for some in lists:
+            asked = tile_search._may_be_alike(some, head_dim, width, height)
+            assert asked if counted(some, width, height) else (len(some) > 2 or not asked), (some, width, height)
+    assert not tile_search._may_be_alike([(0, 128, 0), (8, 128, 0)], 128, 1024, 512)
