@@ -39,7 +39,11 @@ CASES = [
     (2, 2, 64, 21, 20, 128, 8, "f16", (0, 1), [(1, 128, 0), (4, 32, 0), (2, 64, 0), (8, 16, 8)]),       # row-major tiles; F = 3
     (1, 1, 8, 7, 7, 8, 3, "f16", (0, 1), [(1, 8, 8), (1, 8, 0)]),      # one atom a token, F = 3
     (200, 1, 16, 5, 13, 16, 2, "f16", (0, 1), None),                   # 1200 streams, one slice each
+    (13, 8, 128, 2048, 2048, 1024, 512, "f16", (0, 1), None),          # 26 streams of 2 MB in groups of 9, 9 and 8
+    (7, 8, 128, 2048, 2048 + 300, 1024, 512, "bf16", (0, 1), None),    # 28 streams of two chunks in groups of 10, 10 and 8
+    (1, 16, 128, 12300, 12300, 2048, 1024, "f16", (0, 1), [(1, 2048, 128), (16, 128, 128), (8, 256, 64), (128, 16, 16)]),  # a group of each stream
 ]
+GAPS = {0: (1024, 24), 2: (8, 0), 7: (64, 128), 11: (8, 8)}  # case -> more elements from token to token and from kind to kind
 
 
 @pytest.mark.gpu
@@ -52,14 +56,19 @@ def test_costs_equal_those_of_the_candidates_one_by_one(kvc_lib, case):
     hz.say(f"[case] tiling costs L={L} H={H} D={D} T={T} n={n} {width}x{height} {dtype} modes {km}{vm}, {len(tiles)} tiles")
     kv = kv_synth.make_kv_correlated(L, H, D, n, TD[dtype], seed=300 + L + n, device="cuda")
     want = one_by_one(kv, n, dt, T, width, height, km, vm, tiles)
+    gap, kind_gap = GAPS.get(CASES.index(case), (0, 0))
+    kind = n * (H * D + gap) + kind_gap
+    wide = torch.full((L, 2, kind), float("inf"), dtype=TD[dtype], device="cuda")  # nothing between the tokens may be looked at
+    wide[:, :, :n * (H * D + gap)].unflatten(2, (n, H * D + gap))[..., :H * D] = kv.view(L, 2, n, H * D)
     lo, arrays = kvc.Layout(L, H, D, dt, T, 1, H * D, 1, T, km, vm), kvc.tile_arrays(tiles)
     size = kvc.tiling_costs_workspace(lo, n, arrays, width, height)
     assert size > 0
     guard, C = 256, H * D
+    hz.say(f"[case] from token to token {C + gap}, from K to V {kind}")
     work = torch.full((guard + size + guard,), 0xA5, dtype=torch.uint8, device="cuda")
     cost = torch.full((want.numel() + 2,), -1.0, dtype=torch.float64, device="cuda")
     for _ in range(2):  # the second time on what the first has left there
-        kvc.kvc_tiling_costs(lo, kv.data_ptr(), (2 * n * C, n * C, C), n, arrays, width, height, work[guard:].data_ptr(), size,
+        kvc.kvc_tiling_costs(lo, wide.data_ptr(), (2 * kind, kind, C + gap), n, arrays, width, height, work[guard:].data_ptr(), size,
                              cost[1:].data_ptr(), hz.stream_handle())
         torch.cuda.synchronize()
         assert bool((work[:guard] == 0xA5).all()) and bool((work[guard + size:] == 0xA5).all()), "wrote outside its workspace"
