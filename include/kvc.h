@@ -194,7 +194,8 @@ typedef enum kvc_pack_launch_form {
   KVC_PACK_RESIDENT = 0, /* a strip of up to 2048 tokens waits on chip, its workgroup has a CU to itself    */
   KVC_PACK_TWO_PASS = 1, /* long chunks: several workgroups share a strip, each of which holds a part of its
                             tokens, or (few or unshareable strips) all but its last tokens are read twice;
-                            also per-token kinds alone                                                  */
+                            also per-token kinds alone, with 512 threads where narrow tokens have a kernel
+                            of their own and more in the streaming one                                  */
   KVC_PACK_LIGHT = 2,    /* few loads a thread: few tokens, or few strips, which are then made narrower      */
   KVC_PACK_MEDIUM = 3    /* up to 1024 tokens of a strip wait on chip, two workgroups to a CU                */
 } kvc_pack_launch_form;

@@ -70,7 +70,9 @@ struct PairRows {
 kvc_status launch_copy_pairs(const PairRows& k, const PairRows& v, uint32_t layers, hipStream_t stream);
 
 constexpr int kPackResident = KVC_PACK_RESIDENT, kPackStream = KVC_PACK_TWO_PASS, kPackLight = KVC_PACK_LIGHT, kPackMedium = KVC_PACK_MEDIUM;
-constexpr int kPackTokens = 4;  // per-token kinds alone, many narrow tokens; told as the form that per-token kinds alone take
+// Per-token kinds alone, many narrow tokens.  No form of the interface: kvc_pack_form tells the one of per-token kinds alone, and
+// by the number of threads which of its two kernels a call takes.
+constexpr int kPackTokens = 100;
 
 // How often the members of a shared strip look for each other's extremes before they read what is missing: about a
 // microsecond each.  On an idle chip up to 27 members need between 64 and 128 looks (three chunks of 10 240 tokens 1225 us with 64,

@@ -1123,8 +1123,9 @@ hipError_t launch_variant(dim3 grid, dim3 block, hipStream_t stream, const PackP
   static std::atomic<uint64_t> raised{0};
   const auto fn = pack_kernel<DT, UNIFORM, BODY>;
   constexpr int slots = BODY == kPackResident ? kResidentLds : BODY == kPackMedium ? kMediumLds : BODY == kPackStream ? kStreamStashLoads : 0;
-  // Unused LDS keeps the workgroups of per-token kinds alone to two a CU where tokens have more than 128 channels (512: 32 layers
-  // of 9000 tokens 173 us with four, 165 with two, 80 layers of 128 95 against 104).
+  // Unused LDS keeps the workgroups of per-token kinds alone to two a CU where tokens have more than 128 channels (32 layers of
+  // 9000 tokens with four and with two: 512 channels 173 and 165 us, 256 94.7 and 92.5, 384 128 and 130.5, 192 74.0 and 81.8; 80
+  // layers of 128 95 and 104).
   const size_t lds = BODY == kPackTokens ? (p.g.C > 128 ? 56u << 10 : 0u) : (size_t)slots * block.x * sizeof(u32x4);
   if (slots != 0) {
     int dev = 0;

@@ -72,7 +72,7 @@ def restore_body(call):
     return RESTORE_BODIES[args[2]], args[3]
 
 
-PACK_BODIES = ["resident", "streaming", "light", "medium", "tokens"]
+PACK_BODIES = {0: "resident", 1: "streaming", 2: "light", 3: "medium", 100: "tokens"}
 
 
 def pack_kernels(glo, n_tokens):
