@@ -226,7 +226,9 @@ __device__ __forceinline__ uint32_t tile_elem(const Geo& g, uint32_t r, uint32_t
 // -> 176, 24 of 24 670 -> 681, 32 of 32 608 -> 632, 22 of 24 203 -> 208, 30 of 32, 80 layers x 20 000 tokens, 1836 -> 1873), and
 // in runs of frames (16 a row, 30 frames 55 -> 56.5).  Tiles 8 high of 512 channels gain 4 to 14 % in calls of 2048 tokens x 80 layers
 // and less, whatever the runs, and lose in large ones of whole runs (15 of 16, 32 layers x 30 000 tokens, 541 -> 561, 14 of 16 546
-// -> 556, 24 of 24 354 -> 362).  Over the host link a wave has reads to wait for either way (11 a row, F = 4, of 256 channels 336 -> 340).
+// -> 556, 24 of 24 354 -> 362).  Over the host link the frames of a layer group gain by it (fetched by layer, 80 layers of 240 tokens of 128 channels 280 -> 245
+// us, of (8,128) tiles 0.99), and whole chunks, at once or as a run of frames, lose where tokens have more than 256 channels (13 a
+// row of (16,64), F = 4, 1276 -> 1337, 11 a row of (8,128) 1247 -> 1301, 17 a row of (8,64) 673 -> 692; of 128 channels 0.99).
 template <int MODE, int DT, bool PAGED, int U, bool LINE, bool EARLY>
 __device__ __forceinline__ void restore_body_rows(const RestoreParams& p, uint32_t c, uint32_t kind, uint32_t l,
                                                   uint32_t tg, const uint8_t* fsec, uint32_t ff) {
@@ -667,11 +669,14 @@ kvc_status launch_restore(RestoreParams p, bool paged, hipStream_t stream) {
     body = kBodyRowsLine;
     lds = kLdsForTwo;
   }
-  // Table entries late in rounds of eight: over the host link, for runs of frames of tiles 16 high, and where no more than a
-  // twelfth of the runs is missing of tiles 16 high, or an eighth of lower ones in a large call.
+  // Table entries late in rounds of eight: for runs of frames of tiles 16 high; over the host link for tokens of more than 256
+  // channels, but for runs of frames that are a small launch; and else for chunks of which no more than a twelfth of the runs is
+  // missing in tiles 16 high, or an eighth in lower ones of a large call.
   const bool large = (int64_t)g.L * p.n_tokens * g.C >= kLargeCall;
+  const bool small = p.frame_mode && p.n_units < kFillWorkgroups;
   if (body == kBodyRows && paged && u == kPasses &&
-      (p.host_frames || (p.frame_mode ? g.th > 8 : g.th > 8 ? 12 * g.TX >= 11 * q * runs : large && 8 * g.TX >= 7 * q * runs)))
+      ((p.frame_mode && g.th > 8) || (p.host_frames ? g.C > 256 && !small
+                                                    : !p.frame_mode && (g.th > 8 ? 12 * g.TX >= 11 * q * runs : large && 8 * g.TX >= 7 * q * runs))))
     body = kBodyRowsLate;
   if (g.dtype == KVC_F16) {
     if (paged)

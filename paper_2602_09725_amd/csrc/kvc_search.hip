@@ -21,9 +21,10 @@
 // A search is four launches: the pack, search_turn_kernel, which lays the codes out so that any pair is two runs of
 // neighbouring words, search_hist_kernel, a workgroup for a part of a stream (chunk, kind, layer) and a task -- the insides of
 // atoms, a level of seams, a d2, a tiling --, and the costs.  (Six layers of 2048 tokens: 20 packs, clears, counts and costs on
-// four streams 855 us, so 183, of which the kernels are 19, 12, 90 and 6 and the host the rest; 32 layers 6060 and 600.)
+// four streams 855 us, so 183, of which the kernels are 19, 12, 97 (90 in a loop of their own) and 6 and the host the rest; 32
+// layers 6060 and 600.)
 //
-// What bounds the counting is what bounds residual_hist_kernel: LDS atomics, 64 lanes in 4 cycles at best, 64 us of the 90.
+// What bounds the counting is what bounds residual_hist_kernel: LDS atomics, 64 lanes in 4 cycles at best, 64 us of the 90 to 97.
 #include <hip/hip_runtime.h>
 
 #include "kvc_count.h"

@@ -83,7 +83,8 @@ def test_rows_of_narrow_tiles(kvc_lib, case, modes):
 
 @pytest.mark.parametrize("case", [CASES[i] for i in (2, 5, 6, 7, 9)], ids=["512 channels", "256 channels", "c6", "c7", "c9"])
 def test_rows_from_host_memory(kvc_lib, case):
-    """Frames read in place: rounds of eight, whatever a row of tiles takes, and table entries with the stores."""
+    """Frames read in place: rounds of eight, whatever a row of tiles takes; table entries with the stores in whole chunks of
+    more than 256 channels and in runs of frames of tiles 16 high, but not in the frames of a layer group of lower ones."""
     L, H, D, T, th, TX, TY, n, bs, _, _, _, _ = case
     C, nb = H * D, -(-n // bs)
     glo, olo = hz.layouts(L, H, D, "f16", T, th, 64, TX, TY)
@@ -99,7 +100,25 @@ def test_rows_from_host_memory(kvc_lib, case):
     for l, (a, b) in enumerate(zip(cache.numpy_layers(), want)):
         hz.assert_same_bytes(f"paged layer {l}", a, b)
     assert hz.restore_body(lambda: hz.kvc.kvc_restore_paged(glo, frames.data_ptr(), meta.data_ptr(), 0, n, cache.ptrs.data_ptr(), nb, bs,
-                                                            on_gpu.data_ptr(), nb, cache.err.data_ptr(), hz.stream_handle())) == LATE8
+                                                            on_gpu.data_ptr(), nb, cache.err.data_ptr(),
+                                                            hz.stream_handle())) == (LATE8 if C > 256 else ROWS8)
+    F, part = oracle.frames_per_group(olo), hz.PagedCache(L, nb, bs, C)
+
+    def run_of_frames(k=2 * ((L + 2) // 3) * F):
+        hz.kvc.kvc_restore_paged_frames(glo, frames.data_ptr(), meta.data_ptr(), 0, k, 0, n, part.ptrs.data_ptr(), nb, bs,
+                                        on_gpu.data_ptr(), nb, part.err.data_ptr(), hz.stream_handle())
+
+    assert hz.restore_body(run_of_frames) == (LATE8 if C > 256 else ROWS8)
+    assert hz.restore_body(lambda: run_of_frames(F)) == (LATE8 if th > 8 else ROWS8)
+    run_of_frames()
+    torch.cuda.synchronize()
+    for l, (a, b) in enumerate(zip(part.numpy_layers(), want)):
+        hz.assert_same_bytes(f"frames, layer {l}", a, b)
+    part = hz.PagedCache(L, nb, bs, C)
+    run_of_frames(F)   # K of the first three layers
+    torch.cuda.synchronize()
+    for l, (a, b) in enumerate(zip(part.numpy_layers()[:3], want)):
+        hz.assert_same_bytes(f"first frames, layer {l}", a.reshape(2, -1)[0], b.reshape(2, -1)[0])
     out = torch.empty((L, 2, n, H, D), dtype=torch.float16, device="cuda")
     assert hz.restore_body(lambda: hz.kvc.kvc_restore(glo, frames.data_ptr(), meta.data_ptr(), n, out.data_ptr(),
                                                       (2 * n * C, n * C, C), hz.stream_handle())) == ROWS8
