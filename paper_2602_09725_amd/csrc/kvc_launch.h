@@ -200,6 +200,7 @@ struct SearchParams {
   FastDiv dround, dparts, dstreams;  // dround: workgroups of an XCD in a group of streams
   SearchTask tasks[kMostSearchTasks];
 };
+static_assert(sizeof(SearchParams) <= 4096, "parameters of a launch");
 
 struct SearchTiling {
   uint32_t upper, edge, inner, seams;  // slots (inner 0: none) and levels of seams
